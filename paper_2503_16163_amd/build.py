@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspecache.so")
 STAMP = os.path.join(HERE, "libspecache.srchash")   # hash of the sources the library was built from
-SOURCES = ["specache.hip", "quant.hip", "score.hip", "score_mfma.hip", "score_i8.hip", "select.hip", "topk.hip", "gather.hip", "attend.hip", "attend_i8.hip", "fourbit.hip", "measure.hip"]
+SOURCES = ["specache.hip", "quant.hip", "score.hip", "score_i8.hip", "select.hip", "topk.hip", "gather.hip", "attend.hip", "attend_i8.hip", "rows_mfma.hip", "rows_b1.hip", "rows_b2.hip", "fourbit.hip", "measure.hip"]
 # -ffp-contract=off: the quantiser's binary32 operation order is part of its definition and
 # fused multiply-adds are written out where they are wanted.  Packed FP32 code generation is
 # switched off for the device pass.
@@ -29,7 +29,7 @@ def _compile(src):
 
 def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=6) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         results = list(ex.map(_compile, SOURCES))
     if verbose:
         for _, err in results:
@@ -57,13 +57,11 @@ def source_hash():
 
 
 def kernel_sources(kernel):
-    """The .hip file that defines __global__ `kernel` and every header it includes, directly or not
-    (base names, sorted); None if no source defines it."""
+    """The .hip file that defines __global__ `kernel` (or the header that does, for a kernel built in several files) and
+    every header it includes, directly or not (base names, sorted); None if no source defines it."""
     import re
     pat = re.compile(r"__global__[^;{]*?\b" + re.escape(kernel) + r"\s*\(", re.S)
     for f in sorted(os.listdir(CSRC)):
-        if not f.endswith(".hip"):
-            continue
         with open(os.path.join(CSRC, f)) as fh:
             if not pat.search(fh.read()):
                 continue

@@ -14,12 +14,9 @@
 //
 // Values are quantised per token over g channels, so for the main chunks
 //   sum_i p_i V'[i][c] = sum_i (p_i s[i][m]) code[i][c] + sum_i p_i z[i][m],  m = c / g.
-// With up to four query rows per KV head the first sum runs on the vector ALUs: a lane owns
-// 8/BITS channels and reads 16 tokens of them as one 16-byte load; p_i s[i][m] comes from
-// LDS (computed once per token by the softmax phase).  With 8 or 16 rows it is a dense
-// enough contraction for the matrix cores (v_mfma_f32_16x16x32_f16, fp32 accumulation):
-// the codes enter as f16 subnormals straight from the packed bytes, p_i s[i][m] as a
-// hi + lo pair of f16.
+// The first sum runs on the vector ALUs: a lane owns 8/BITS channels and reads 16 tokens of them as one 16-byte load;
+// p_i s[i][m] comes from LDS (computed once per token by the softmax phase).  With 8 or 16 query rows per KV head the
+// matrix cores take the contraction (rows_mfma.h).
 #include "attend_common.h"
 
 namespace specache {
@@ -36,18 +33,13 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     constexpr int LPB = 32 * BITS;           // lanes per 32-token block
     constexpr uint32_t MASK = ((1u << BITS) - 1u) * 0x01010101u;
     constexpr int TPT = (CH + kThreads - 1) / kThreads;   // chunk tokens per thread
-    // With up to four query rows the value side runs on the vector ALUs, with more on the matrix
-    // cores (kSplit).  One LDS region serves, in turn: for main chunks ps[M][CH][NR] (vector
-    // path) or the planes p[CH][NR+1], z[CH][M], s[CH][M] (matrix path); for extra chunks
-    // the areas of attend_extra_chunk; at the end o_lds[kWaves][NR][128] (vector path).
+    // One LDS region serves, in turn: for main chunks ps[M][CH][NR]; for extra chunks the areas of
+    // attend_extra_chunk; at the end o_lds[kWaves][NR][128].
     // ps is stored in cells [16-token half block][value group m] of 16*NR floats plus one
     // 16-byte pad: the lanes of one LDS read differ only in (half block, m), i.e. in
     // consecutive cells, and the pad spreads those over distinct banks.
-    constexpr bool kSplit = NR > 4;
     constexpr int kCell = 16 * NR + 4;
-    constexpr int kPl = NR + 1;              // row pitch of the p plane: lanes of one read in distinct banks
-    constexpr int kPlanes = CH * kPl + 2 * CH * M;
-    constexpr int kPs = kSplit ? kPlanes : (CH / 16) * M * kCell, kOl = kWaves * NR * kD;
+    constexpr int kPs = (CH / 16) * M * kCell, kOl = kWaves * NR * kD;
     // a workgroup is either a main or an extra chunk (16-bit candidates, attend_extra_chunk): both use
     // the one region, and LDS per workgroup decides how many chunks are resident per compute unit
     constexpr int kExtra = extra_chunk_floats(NR);
@@ -58,7 +50,6 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     __shared__ float red[kWaves * NR * (1 + M)];
     __shared__ float red_sum[kWaves * NR];
     __shared__ float red_z[kWaves * NR * M];
-    __shared__ float red_scale[kWaves];
     __shared__ uint32_t maskbits[CH / 32];
 
     float* ps = smem;                        // [CH/16][M] cells
@@ -168,16 +159,8 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
         }
 
         // p = exp(l - m); p * s per (token, value group); the zero-point term sum_i p_i z[i][m] and
-        // the row sums sum_i p_i.  With up to four query rows every thread adds up its own tokens
-        // and the waves reduce those sums.  With more rows a thread has one token and NR * (M + 1)
-        // sums, too many wave reductions: p and z go to LDS instead (in the area the merged
-        // outputs use later) and the lanes re-read them as (row, slice of this wave's tokens), so
-        // that only the slices of a row are left to add up.
-        float* pl = smem;                        // [CH][kPl]
-        float* zl = pl + CH * kPl;               // [CH][M]
-        float* sl = zl + CH * M;                 // [CH][M]
+        // the row sums sum_i p_i: every thread adds up its own tokens and the waves reduce those sums
         float zacc[NR][M], sloc[NR];
-        float sc_max = 0.0f;     // largest value scale of this thread's tokens (MFMA path: operand scaling)
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             sloc[r] = 0.0f;
@@ -193,87 +176,28 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
                 for (int r = 0; r < NR; ++r) {
                     const float ms = m_row[r] == -INFINITY ? 0.0f : m_row[r];
                     p[r] = __expf(lgr[tt][r] - ms);
-                    if constexpr (kSplit) pl[i * kPl + r] = p[r];
-                    else sloc[r] += p[r];
+                    sloc[r] += p[r];
                 }
-                float scv[M], zv[M];
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
                     float sc, z;
                     derive_scale_zero<BITS>(widen16<BF16>(meta[tt][m] & 0xFFFFu), widen16<BF16>(meta[tt][m] >> 16), L.one_bit_plain, sc, z);
-                    scv[m] = sc;
-                    zv[m] = z;
-                    if constexpr (kSplit) {
-                        sc_max = fmaxf(sc_max, sc);
-                    } else {
 #pragma unroll
-                        for (int r = 0; r < NR; ++r) {
-                            ps[((i >> 4) * M + m) * kCell + (i & 15) * NR + r] = p[r] * sc;
-                            zacc[r][m] = __builtin_fmaf(p[r], z, zacc[r][m]);
-                        }
-                    }
-                }
-                if constexpr (kSplit) {   // one vector store per plane and token
-                    if constexpr (M == 4) {
-                        *reinterpret_cast<float4*>(&zl[i * M]) = make_float4(zv[0], zv[1], zv[2], zv[3]);
-                        *reinterpret_cast<float4*>(&sl[i * M]) = make_float4(scv[0], scv[1], scv[2], scv[3]);
-                    } else if constexpr (M == 2) {
-                        *reinterpret_cast<float2*>(&zl[i * M]) = make_float2(zv[0], zv[1]);
-                        *reinterpret_cast<float2*>(&sl[i * M]) = make_float2(scv[0], scv[1]);
-                    } else {
-                        zl[i] = zv[0];
-                        sl[i] = scv[0];
+                    for (int r = 0; r < NR; ++r) {
+                        ps[((i >> 4) * M + m) * kCell + (i & 15) * NR + r] = p[r] * sc;
+                        zacc[r][m] = __builtin_fmaf(p[r], z, zacc[r][m]);
                     }
                 }
             }
         }
-        if constexpr (kSplit) {
-            {
-                const float v = wave_max(sc_max);
-                if (lane == 0) red_scale[wave] = v;
-            }
-            __syncthreads();
-            constexpr int S = 64 / NR;                    // slices per row inside a wave
-            constexpr int T = (CH / kWaves) / S;          // tokens per lane
-            static_assert(S == 8 || S == 4, "slice reduction below covers 4 or 8 adjacent lanes");
-            const int r = lane / S, slice = lane % S;
-            float sa = 0.0f, za[M];
 #pragma unroll
-            for (int m = 0; m < M; ++m) za[m] = 0.0f;
-#pragma unroll
-            for (int j = 0; j < T; ++j) {
-                const int i = wave * (CH / kWaves) + j * S + slice;   // slices interleaved: one read's lanes in distinct banks
-                if (i < n) {
-                    const float pr = pl[i * kPl + r];
-                    sa += pr;
-#pragma unroll
-                    for (int m = 0; m < M; ++m) za[m] = __builtin_fmaf(pr, zl[i * M + m], za[m]);
-                }
-            }
-            sa += dpp_move<kDppXor1>(sa);
-            sa += dpp_move<kDppXor2>(sa);
-            if constexpr (S == 8) sa += dpp_move<kDppHalfMirror>(sa);
+        for (int r = 0; r < NR; ++r) {
+            const float v = wave_sum(sloc[r]);
+            if (lane == 0) red_sum[wave * NR + r] = v;
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                za[m] += dpp_move<kDppXor1>(za[m]);
-                za[m] += dpp_move<kDppXor2>(za[m]);
-                if constexpr (S == 8) za[m] += dpp_move<kDppHalfMirror>(za[m]);
-            }
-            if (slice == 0) {
-                red_sum[wave * NR + r] = sa;
-#pragma unroll
-                for (int m = 0; m < M; ++m) red_z[(wave * NR + r) * M + m] = za[m];
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const float v = wave_sum(sloc[r]);
-                if (lane == 0) red_sum[wave * NR + r] = v;
-#pragma unroll
-                for (int m = 0; m < M; ++m) {
-                    const float zv = wave_sum(zacc[r][m]);
-                    if (lane == 0) red_z[(wave * NR + r) * M + m] = zv;
-                }
+                const float zv = wave_sum(zacc[r][m]);
+                if (lane == 0) red_z[(wave * NR + r) * M + m] = zv;
             }
         }
         __syncthreads();
@@ -285,115 +209,7 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
             l_row[r] = v;
         }
 
-        if constexpr (kSplit) {
-            // ---- value side on the matrix cores (8 or 16 query rows per KV head) ----
-            // o[r][c] = sum_i code[i][c] * ps[i][m(c)][r] per 32-token block is a 16 x 32 x 16 product:
-            // A = codes (rows: 16 channels of one value group, columns: 32 tokens), read from the
-            // packed bytes as f16 subnormals (code << (8 - BITS), i.e. code * 2^(8 - BITS - 24), exact);
-            // B = ps = p * s (from the planes), scaled by a power of two near the top of the f16
-            // range and split into hi + lo f16 (columns: (row r, hi | lo)), C accumulates in fp32.  Wave w owns the 32
-            // channels 32 w .. 32 w + 31 (two tiles, one value group), so no sums cross waves.
-            constexpr int NT = NR / 8;                      // column tiles of 8 query rows x (hi, lo)
-            constexpr int JT = CPB / 2;                     // codes of one byte that go to one tile
-            constexpr int LW = 32 / CPB;                    // code lanes (bytes per token) of this wave's channels
-            const int ic = lane & 15, kq = lane >> 4;
-            const int Lrow = wave * LW + ic % LW;           // code lane of this A row; row's bit = BITS * (JT t + ic / LW)
-            const int mw = (32 * wave) / GROUP;             // value group of this wave's channels
-            float smax = red_scale[0];
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) smax = fmaxf(smax, red_scale[w]);
-            // 2^(14 - exponent(smax)): the largest p * s (p <= 1) lands in [2^14, 2^15)
-            uint32_t eb = (__float_as_uint(smax) >> 23) & 0xFFu;
-            eb = eb < 15u ? 15u : (eb > 240u ? 240u : eb);
-            const float bscale = __uint_as_float((268u - eb) << 23);
-            float4v acc[2][NT];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[t][nt] = float4v{0.f, 0.f, 0.f, 0.f};
-            // every code is lifted to the top bits of its byte before it is widened: the matrix
-            // cores do not normalise subnormal inputs before they align the products of a dot
-            // product, so a code left in the low bits (two significant bits under eight leading
-            // zeros) loses the low end of its small products (measured: 3e-5 of the sum for codes
-            // at bit 0, 2e-7 at bit 6)
-            uint32_t amask[2], ashift[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int j = JT * t + ic / LW;
-                amask[t] = MASK << (BITS * j);
-                ashift[t] = (8 - BITS) - BITS * j;
-            }
-            const int nblk = n / kBlockTokens;
-            // 8 tokens of code lane Lrow: half block kq / 2, bytes 8 (kq % 2) .. + 7
-            const uint8_t* a_lane = vc_row + ((size_t)(kq >> 1) * (16 * BITS) + Lrow) * 16 + 8 * (kq & 1);
-            uint2 aw = make_uint2(0, 0);
-            if (nblk > 0) aw = *reinterpret_cast<const uint2*>(a_lane);
-            for (int b = 0; b < nblk; ++b) {
-                uint2 awn = make_uint2(0, 0);
-                if (b + 1 < nblk) awn = *reinterpret_cast<const uint2*>(a_lane + (size_t)(b + 1) * code_block_bytes(BITS));
-                // B: column (r, hi | lo) = lane % 16, tokens 32 b + 8 kq .. + 7
-                const int i0 = b * kBlockTokens + 8 * kq;
-                // the two lanes of a column share the work: the hi lane splits tokens 0..3, the lo
-                // lane tokens 4..7, then each hands the other the halves of the other's kind
-                const int hl = ic & 1, ih = i0 + 4 * hl;
-                float sv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sv[e] = sl[(ih + e) * M + mw] * bscale;
-                uint4v bop[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int r = 8 * nt + (ic >> 1);
-                    float x[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) x[e] = pl[(ih + e) * kPl + r] * sv[e];
-                    uint32_t keep[2], send[2];
-#pragma unroll
-                    for (int e2 = 0; e2 < 2; ++e2) {
-                        // hi by truncation, lo = x - hi rounded: hi + lo is x to 2^-21
-                        const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x[2 * e2], x[2 * e2 + 1]));
-                        const float h0 = widen16<false>(hi & 0xFFFFu), h1 = widen16<false>(hi >> 16);
-                        const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x[2 * e2] - h0, x[2 * e2 + 1] - h1));
-                        keep[e2] = hl ? lo : hi;
-                        send[e2] = hl ? hi : lo;
-                    }
-                    const uint32_t r0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send[0], kDppXor1, 0xf, 0xf, true);
-                    const uint32_t r1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send[1], kDppXor1, 0xf, 0xf, true);
-                    bop[nt] = hl ? uint4v{r0, r1, keep[0], keep[1]} : uint4v{keep[0], keep[1], r0, r1};
-                }
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint32_t m0 = (aw.x & amask[t]) << ashift[t], m1 = (aw.y & amask[t]) << ashift[t];
-                    const uint4v aop{bytes_to_halves<0>(m0), bytes_to_halves<1>(m0), bytes_to_halves<0>(m1), bytes_to_halves<1>(m1)};
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, aop), __builtin_bit_cast(half8, bop[nt]),
-                                                                             acc[t][nt], 0, 0, 0);
-                }
-                aw = awn;
-            }
-            // C rows 4 kq + v of tile t are A rows (channels), C column = (r, hi | lo): add the lo
-            // column to its hi neighbour, undo the two scalings, add the zero-point term, store
-            const float unscale = __uint_as_float((127u + 24u + eb - 141u) << 23);   // 2^24 / bscale
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int r = 8 * nt + (ic >> 1);
-                    float zsum = 0.0f;
-#pragma unroll
-                    for (int w = 0; w < kWaves; ++w) zsum += red_z[(w * NR + r) * M + mw];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        float val = acc[t][nt][v];
-                        val += dpp_move<kDppXor1>(val);
-                        const int row16 = 4 * kq + v;                    // A row inside the tile
-                        const int j = JT * t + row16 / LW;               // code index inside its byte
-                        const int c = (wave * LW + row16 % LW) * CPB + j;
-                        val = val * (unscale * __uint_as_float((uint32_t)(127 - (8 - BITS)) << 23)) + zsum;
-                        if ((ic & 1) == 0) po[r * kD + c] = val;
-                    }
-                }
-        } else {
+        {
             // sum_i (p_i s_i) code[i][c] for this lane's CPB channels, all (at most four) query rows
             for (int r0 = 0; r0 < NR; r0 += RH) {
                 float acc[CPB][RH];
@@ -598,8 +414,7 @@ hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, floa
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
         return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, stream); \
     }
-    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1) SPC_CASE(4, 2) SPC_CASE(8, 1)
-    SPC_CASE(8, 2)
+    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1)
 #undef SPC_CASE
     return hipErrorInvalidValue;
 }
@@ -650,6 +465,18 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
             SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, scratch.part_o, scratch.part_ml,
                        scratch.max_chunks, n_chunks, NR, out);
         }
+        return hipGetLastError();
+    }
+    // 8 or 16 query rows per KV head: a partial pass of their own (rows_mfma.h), with its own chunking
+    if (rows_uses_matrix_cores(L, n_rows)) {
+        if (phases & kAttendPartial) {
+            RowsArgs R{A, nullptr, 0, n_rows, 0};
+            hipError_t e = launch_rows(L, R, kRowsAttend, stream);
+            if (e != hipSuccess) return e;
+        }
+        if (phases & kAttendCombine)
+            SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * L.G * n_rows), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
+                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex), L.G * n_rows, out);
         return hipGetLastError();
     }
     // one query head per KV head, two rows, 2-bit values: the partial pass with the value side on the

@@ -4,6 +4,7 @@
 #pragma once
 #include "kernels.h"
 #include "layout.h"
+#include "rows_args.h"
 #include "wave_ops.h"
 
 namespace specache {
@@ -55,21 +56,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     v += dpp_move<kDppMirror>(v);
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
-
-struct AttendArgs {
-    const uint16_t* q;         // [rows*NR][128]
-    const float* logits;       // [rows*NR][logit_stride]
-    float* logits_out;         // only the kernel that scores and attends in one pass: where to leave the logits, or null
-    size_t logit_stride;
-    const uint16_t* slot;      // [rows][k][256] or null
-    const int32_t* slot_idx;   // [rows][k] or null
-    const uint16_t* k_spec;    // [rows][128] or null
-    const uint16_t* v_spec;
-    float* part_o;             // [rows][max_chunks][NR][128]
-    float* part_ml;            // [rows][max_chunks][NR][2]
-    int max_chunks, n_main, n_chunks, N, Nq;
-    float sm_scale;
-};
 
 // Softmax numerators of one chunk held in lg[NR][CH]: on return lg holds
 // p = exp(l - m); m_out/l_out hold the chunk max and sum of every row.

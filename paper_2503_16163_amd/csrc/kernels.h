@@ -64,7 +64,6 @@ LaunchEvents& pending_launch_events();
 hipError_t launch_score(const LayerView& L, const void* q, int n_rows, int Nq, float sm_scale, float* logits,
                         size_t logit_stride, uint32_t* keys, size_t key_stride, hipStream_t stream);
 
-// the same for 8 or 16 query rows per KV head, on the matrix cores
 // selection keys from the heads' log-probabilities (after launch_score); scratch of
 // select_logprob_scratch_floats(rows, G, max_seq) floats
 size_t select_logprob_scratch_floats(int rows, int G, int max_seq);
@@ -74,13 +73,10 @@ hipError_t launch_select_logprob(const LayerView& L, int n_rows, int Nq, const f
 hipError_t launch_patch_staged(const LayerView& L, const void* q, int n_rows, int Nq, float sm_scale, const uint16_t* slot,
                                const int32_t* slot_idx, float* logits, size_t logit_stride, uint32_t* keys,
                                size_t key_stride, hipStream_t stream);
-bool score_uses_matrix_cores(int G, int n_rows);
 // one query head per KV head, two rows: integer matrix cores (q must be 16-byte aligned)
 bool score_uses_int8_matrix_cores(int G, int n_rows);
 hipError_t launch_score_i8(const LayerView& L, const void* q, int Nq, float sm_scale, float* logits,
                            size_t logit_stride, uint32_t* keys, size_t key_stride, hipStream_t stream);
-hipError_t launch_score_mfma(const LayerView& L, const void* q, int n_rows, int Nq, float sm_scale, float* logits,
-                             size_t logit_stride, uint32_t* keys, size_t key_stride, hipStream_t stream);
 
 // top-k over keys[row][0..Nq): idx_out [rows][k], ascending, -1 padded.  Rows too long for one
 // workgroup's registers are selected in two launches through the candidate buffers.

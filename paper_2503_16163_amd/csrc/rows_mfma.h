@@ -1,0 +1,828 @@
+// Scoring and mixed attention for several query rows per KV head (grouped-query attention: 4, 8 or 16 rows)
+// on the f16 matrix cores: the low-bit scoring of Appendix A "Decoding" (A = Q K^T on C'), the mixed attention of
+// Eq. 1, or both in one pass over the packed cache (the logits then never leave the chip).
+//
+// Both contractions have the packed codes as their A operand, read as f16 subnormals straight from the packed
+// bytes: a dword is two 16-bit halves of 2-bit (1-, 4-bit) fields, and a shift and a mask leave one field of either
+// half at bits 6 to 9, where a subnormal keeps its precision (the matrix cores do not normalise subnormal operands
+// before they align products: a field at bit 0 loses the low end of small products, 3e-5 of the sum, one at bit 6
+// does not, 2e-7).  0.75 vector instructions per 2-bit code.
+//   scoring  logit[r][i] = sum_c code[i][c] (sm q[r][c] s[j][c]) + sm sum_c q[r][c] z[j][c],  j = i / g
+//            B = the multipliers of (row, token group) as hi + lo f16 (24 bits);
+//   values   o[r][c] = sum_i code[i][c] (p[r][i] s[i][m]) + sum_i p[r][i] z[i][m],  m = c / g
+//            B = p s as hi + lo f16.
+// Building the operands is what bounds these shapes (vector-instruction issue: at 8 rows, g = 64 about 380 vector
+// instructions per 32 tokens, a wave's vector ALU busy 9 cycles in 10), so no lane does it twice: the 16 columns are
+// (row r, sub-group s) with 16 / NR sub-groups of 32 tokens in flight.  For 8 rows the two lanes of a row then exchange
+// halves, so that the columns of a product are (r, hi | lo) and every column of it is used (the matrix cores are not
+// free: 17 clocks each, 10 of which no vector instruction of the SIMD fills); with 8 rows and two token groups per unit
+// the scoring keeps (r, s) columns, drops the other sub-group's and runs hi and lo as two products; with 16 rows the
+// columns are the rows.
+// A lane (column (r, s), quarter kq) ends the scoring with the logits of row r for 8 consecutive tokens, which is the
+// order in which the value side wants its B operand: no logit is exchanged between lanes.
+//
+// A wave walks units of 32 * 16 / NR tokens with a running softmax maximum per row (moved only when a logit exceeds it
+// by 4, so that the accumulators are rescaled rarely); the loads of the next unit travel while the other half of the
+// current one is worked on.  The four waves of a workgroup merge once, at the end.  The 16-bit candidates are a wave
+// each per 32: the keys times the queries on the matrix cores in their own type, the values on the vector ALUs.
+//
+// Measured alone on MI355X (scoring + attention as two launches of the earlier kernels -> as one launch): 32 KV rows x 32768
+// tokens, 8 query rows, 2 bits, g = 64: 27.5 + 37.9 -> 37.7 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 45.0 us;
+// 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.4 us; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 16.5 us (the earlier
+// kernels' 16-bit chunk was a chain of 40 us there).  168 registers, three workgroups per compute unit; held to four it
+// spills.
+#pragma once
+#include "attend_common.h"
+#include "rows_args.h"
+
+namespace specache {
+namespace {
+
+typedef __bf16 bfloat8 __attribute__((ext_vector_type(8)));
+
+constexpr int kRowsOStride = kD + 4;           // floats between the columns of a wave's merged outputs
+constexpr float kLazyMax = 4.0f;               // a column's maximum moves when a logit exceeds it by more than this
+constexpr float kLog2e = 1.44269504088896340736f;
+
+// lane exchange across the 16-lane rows of a wave: result pairs of lanes 16 (32) apart
+__device__ __forceinline__ float xor16_max(float v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ float xor32_max(float v) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ float xor16_sum(float v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float xor32_sum(float v) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ uint32_t ror8(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppRowRor8, 0xf, 0xf, true); }
+__device__ __forceinline__ float quarters_max(float v) { return xor32_max(xor16_max(v)); }
+__device__ __forceinline__ float quarters_sum(float v) { return xor32_sum(xor16_sum(v)); }
+
+// Key codes.  Dword W of a token holds 32 / BITS channels, channel 4 h + b of it at bit 8 b + BITS h.  A lane quarter kq
+// reads the dwords W = kq + 4 i; step kc of the contraction takes two fields h, i.e. 8 consecutive channels from
+// key_channel(kc, kq) on, in the pair order (0, 2) (1, 3) (4, 6) (5, 7) that the halves of a dword have.
+template <int BITS>
+__device__ __forceinline__ constexpr int key_channel(int kc, int kq) {
+    return BITS == 2 ? 16 * (kq + 4 * (kc >> 1)) + 8 * (kc & 1) : BITS == 1 ? 32 * kq + 8 * kc : 32 * kc + 8 * kq;
+}
+template <int BITS>
+__device__ __forceinline__ constexpr int key_load(int kc) { return BITS == 2 ? kc >> 1 : BITS == 1 ? 0 : kc; }
+template <int BITS>
+__device__ __forceinline__ uint4v key_operand(uint32_t w, int kc) {
+    if constexpr (BITS == 2) {
+        return (kc & 1) == 0 ? uint4v{(w << 8) & 0x03000300u, w & 0x03000300u, (w << 4) & 0x00C000C0u, (w >> 4) & 0x00C000C0u}
+                             : uint4v{(w << 4) & 0x03000300u, (w >> 4) & 0x03000300u, w & 0x00C000C0u, (w >> 8) & 0x00C000C0u};
+    } else if constexpr (BITS == 1) {
+        switch (kc) {
+            case 0: return uint4v{(w << 8) & 0x01000100u, w & 0x01000100u, (w << 8) & 0x02000200u, w & 0x02000200u};
+            case 1: return uint4v{(w << 4) & 0x00400040u, (w >> 4) & 0x00400040u, (w << 4) & 0x00800080u, (w >> 4) & 0x00800080u};
+            case 2: return uint4v{(w << 4) & 0x01000100u, (w >> 4) & 0x01000100u, (w << 4) & 0x02000200u, (w >> 4) & 0x02000200u};
+            default: return uint4v{w & 0x00400040u, (w >> 8) & 0x00400040u, w & 0x00800080u, (w >> 8) & 0x00800080u};
+        }
+    } else {
+        return uint4v{(w << 4) & 0x00F000F0u, (w >> 4) & 0x00F000F0u, w & 0x00F000F0u, (w >> 8) & 0x00F000F0u};
+    }
+}
+// the fields arrive at different bits: the multiplier of channel c carries the factor that makes every product
+// code * 2^kKeyPos * 2^-24
+template <int BITS>
+__device__ __forceinline__ float key_factor(int c) {
+    if constexpr (BITS == 2) return ((c >> 2) & 1) ? 4.0f : 1.0f;
+    if constexpr (BITS == 1) return (c >> 2) & 1 ? ((c >> 3) & 1 ? 4.0f : 1.0f) : ((c >> 3) & 1 ? 8.0f : 2.0f);
+    return 1.0f;
+}
+constexpr int key_pos(int bits) { return bits == 2 ? 8 : bits == 1 ? 9 : 4; }
+constexpr int key_q_bits(int bits) { return bits == 2 ? 5 : bits == 1 ? 4 : 7; }   // |q'| < 2^this: q' factor s' < 2^15 with s' < 2^8
+
+// Value codes.  Byte t of a 16-byte piece is a token, its fields are channels.  A channel tile (mb, jj) is 16 channels of
+// the 32-channel block mb, so that it lies in one value group whatever g is: A row i is channel value_channel(mb, jj, i).
+// Even tokens of a dword sit in the low byte of its halves, odd ones in the high byte; a lane's shift brings the two
+// fields its row may want to bits 6 to 9 (8 and 9 with 1-bit codes, 4 to 7 with 4-bit codes).
+template <int BITS>
+__device__ __forceinline__ int value_lane(int mb, int ic) { return BITS == 2 ? 8 * mb + (ic & 7) : BITS == 1 ? 4 * mb + (ic & 3) : 16 * mb + ic; }
+template <int BITS>
+__device__ __forceinline__ int value_channel(int mb, int jj, int i) {
+    return BITS == 2 ? 4 * (8 * mb + (i & 7)) + 2 * (i >> 3) + jj : BITS == 1 ? 8 * (4 * mb + (i & 3)) + 2 * (i >> 2) + jj : 2 * (16 * mb + i) + jj;
+}
+constexpr int value_pos(int bits, int jj) { return bits == 2 ? (jj ? 8 : 6) : bits == 1 ? 8 + jj : 4; }
+struct ValueShift { uint32_t left, right; };   // of the lane's A row (2- and 1-bit codes)
+template <int BITS>
+__device__ __forceinline__ ValueShift value_shift(int ic) {
+    if constexpr (BITS == 2) return {6u - 4u * (ic >> 3), 2u + 4u * (ic >> 3)};
+    return {8u - 2u * (ic >> 2), 2u * (ic >> 2)};
+}
+// both channel tiles of a block from the 8 tokens of a lane
+template <int BITS>
+__device__ __forceinline__ void value_operands(uint2 w, ValueShift sh, uint4v a[2]) {
+    if constexpr (BITS == 4) {
+        a[0] = uint4v{(w.x << 4) & 0x00F000F0u, (w.x >> 4) & 0x00F000F0u, (w.y << 4) & 0x00F000F0u, (w.y >> 4) & 0x00F000F0u};
+        a[1] = uint4v{w.x & 0x00F000F0u, (w.x >> 8) & 0x00F000F0u, w.y & 0x00F000F0u, (w.y >> 8) & 0x00F000F0u};
+    } else {
+        constexpr uint32_t m0 = BITS == 2 ? 0x00C000C0u : 0x01000100u, m1 = BITS == 2 ? 0x03000300u : 0x02000200u;
+        const uint32_t e0 = w.x << sh.left, o0 = w.x >> sh.right, e1 = w.y << sh.left, o1 = w.y >> sh.right;
+        a[0] = uint4v{e0 & m0, o0 & m0, e1 & m0, o1 & m0};
+        a[1] = uint4v{e0 & m1, o0 & m1, e1 & m1, o1 & m1};
+    }
+}
+
+// x as hi + lo f16, both rounded to nearest (24 bits), packed in the pair order of the A operands
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split8(const float x[8], uint4v& hi, uint4v& lo) {
+    constexpr int kFirst[4] = {0, 1, 4, 5};
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const float2v a = {x[kFirst[d]], x[kFirst[d] + 2]};
+        const half2v h = __builtin_convertvector(a, half2v);
+        const float2v rest = {a.x - (float)h.x, a.y - (float)h.y};
+        hi[d] = __builtin_bit_cast(uint32_t, h);
+        lo[d] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, half2v));
+    }
+}
+
+__device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+}
+// the product of 16-bit inputs of the cache's own type: exact products, fp32 accumulation
+template <bool BF16>
+__device__ __forceinline__ float4v mfma_native(uint4v a, uint4v b, float4v c) {
+    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfloat8, a), __builtin_bit_cast(bfloat8, b), c, 0, 0, 0);
+    else return mfma16(a, b, c);
+}
+
+__device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2f(x); }
+
+template <int BITS, int GROUP, int NR>
+struct RowsShape {
+    static constexpr int SUBS = 16 / NR;                                     // sub-groups of 32 tokens in flight
+    static constexpr int UNIT = 32 * SUBS;                                   // tokens of a unit
+    static constexpr int SG = UNIT > GROUP ? UNIT / GROUP : 1;               // token groups of a unit
+    static constexpr int M = kD / GROUP;
+    static constexpr int kSStride = kD + 4;                                  // floats between the token groups' scale rows
+    static constexpr int kZStride = kD + 8;                                  // halves between the token groups' (min), (max) rows
+    static constexpr int kQStride = kD + 4;
+    static constexpr int kKeyStride = UNIT + 4;
+    // LDS: query rows scaled (floats) and as they are (halves), then per wave the tables; later the waves' outputs
+    static constexpr int kQBytes = NR * kQStride * 4 + NR * kZStride * 2 + NR * 8;
+    static constexpr int kKeyTab = SG * kSStride * 4 + SG * kZStride * 2 * (BITS == 1 ? 2 : 1);
+    static constexpr int kValTab = 2 * M * UNIT * 4;
+    static constexpr int kLogitTab = NR * kKeyStride * 4;
+    static constexpr int kWaveBytes = (kKeyTab + kValTab + kLogitTab + 15) / 16 * 16;
+    static constexpr int kMainBytes = (kQBytes + 15) / 16 * 16 + kWaves * kWaveBytes;
+    // a workgroup of 16-bit candidates: per wave its weights [32][NR]
+    static constexpr int kExtraBytes = (kQBytes + 15) / 16 * 16 + kWaves * 32 * NR * 4;
+    static constexpr int kMergeBytes = kWaves * 16 * kRowsOStride * 4;
+    static constexpr int kBytes = kMainBytes > kMergeBytes ? (kMainBytes > kExtraBytes ? kMainBytes : kExtraBytes)
+                                                           : (kMergeBytes > kExtraBytes ? kMergeBytes : kExtraBytes);
+};
+
+// what the waves hand to the merge, per column (r, s): softmax maximum and sum; the merge turns the maximum into the weight
+struct RowsOut {
+    float m[kWaves][16], l[kWaves][16], w[kWaves][16];
+};
+
+// ---- one wave's 32 candidates in 16 bits: staged pairs, residual, the speculative pair ---------------------------
+template <int NR, bool BF16>
+__device__ __forceinline__ void rows_extra_wave(const LayerView& L, const AttendArgs& A, int n_rows, int row, int x0, int lane, int wave,
+                                                const uint16_t* qraw, int q_stride, float* weights, float* o_lds, RowsOut& out) {
+    const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
+    const int ks = A.slot_idx ? L.topk : 0, n_res = A.N - A.Nq, n_ex = ks + n_res + (A.k_spec ? 1 : 0);
+    // A rows: tile mt, row ic is candidate x0 + 2 ic + mt
+    const uint16_t* kp[2];
+    const uint16_t* vp[2];
+    bool spec[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        const int x = x0 + 2 * ic + mt;
+        kp[mt] = nullptr;
+        spec[mt] = false;
+        if (x < ks) {
+            const int t = A.slot_idx[(size_t)row * L.topk + x];
+            if (t >= 0 && t < A.Nq) kp[mt] = A.slot + ((size_t)row * L.topk + x) * 256;
+        } else if (x < ks + n_res) {
+            const int t = A.Nq + (x - ks);
+            kp[mt] = L.ring + ((size_t)row * L.R + (t % L.R)) * 256;
+        } else {
+            spec[mt] = x < n_ex;
+        }
+        vp[mt] = kp[mt] ? kp[mt] + kD : nullptr;
+        // a token that this very launch appends (its copy into the ring may not have landed yet) is read from the
+        // caller's buffers, and so is the speculative pair
+        if (L.tail_k != nullptr && x >= ks && x < ks + n_res && A.Nq + (x - ks) == L.tail_N0) {
+            kp[mt] = L.tail_k + (size_t)row * kD;
+            vp[mt] = L.tail_v + (size_t)row * kD;
+        }
+        if (spec[mt]) {
+            kp[mt] = A.k_spec + (size_t)row * kD;
+            vp[mt] = A.v_spec + (size_t)row * kD;
+        }
+    }
+    uint4v kb[2][4];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+            kb[mt][kc] = kp[mt] ? *reinterpret_cast<const uint4v*>(kp[mt] + 32 * kc + 8 * kq) : uint4v{0u, 0u, 0u, 0u};
+    // value rows: lane = channel pair, one 256-byte row per candidate (lane 2 ic + mt / 2 of the wave knows where)
+    uint32_t vw[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const uint64_t p = (uint64_t)(uintptr_t)vp[i & 1];
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)p, i >> 1), hi = __builtin_amdgcn_readlane((uint32_t)(p >> 32), i >> 1);
+        const uint16_t* v = reinterpret_cast<const uint16_t*>((uintptr_t)(((uint64_t)hi << 32) | lo));
+        vw[i] = v ? *reinterpret_cast<const uint32_t*>(v + 2 * lane) : 0u;
+    }
+    float4v acc[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) {
+        const uint4v b = *reinterpret_cast<const uint4v*>(qraw + r * q_stride + 32 * kc + 8 * kq);
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) acc[mt] = mfma_native<BF16>(kb[mt][kc], b, acc[mt]);
+    }
+    // C row 4 kq + v of tile mt is candidate x0 + 8 kq + 2 v + mt.  Which of them exist, and which is the speculative
+    // pair: one bit per candidate, from the lanes of the first quarter
+    const unsigned long long have0 = __ballot(kp[0] != nullptr) & 0xFFFFull, have1 = __ballot(kp[1] != nullptr) & 0xFFFFull;
+    const unsigned long long spec0 = __ballot(spec[0]) & 0xFFFFull, spec1 = __ballot(spec[1]) & 0xFFFFull;
+    const bool last = r % n_rows == n_rows - 1;
+    float l[8], m = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int i = 4 * kq + v;
+            const bool sees = s == 0 && (((mt ? have1 : have0) >> i) & 1) && (last || !(((mt ? spec1 : spec0) >> i) & 1));
+            l[2 * v + mt] = sees ? acc[mt][v] * A.sm_scale : -INFINITY;
+            m = fmaxf(m, l[2 * v + mt]);
+        }
+    m = quarters_max(m);
+    const float ms = m == -INFINITY ? 0.0f : m;
+    float sum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const float p = exp2_of((l[t] - ms) * kLog2e);
+        sum += p;
+        if (s == 0) weights[(8 * kq + t) * NR + r] = p;
+    }
+    sum = quarters_sum(sum);
+    if (kq == 0) {
+        out.m[wave][ic] = m;
+        out.l[wave][ic] = sum;
+    }
+    wave_sync();
+    float o[NR][2];
+#pragma unroll
+    for (int rr = 0; rr < NR; ++rr) o[rr][0] = o[rr][1] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const float v0 = widen16<BF16>(vw[i] & 0xFFFFu), v1 = widen16<BF16>(vw[i] >> 16);
+#pragma unroll
+        for (int r4 = 0; r4 < NR / 4; ++r4) {
+            const float4 p = *reinterpret_cast<const float4*>(weights + i * NR + 4 * r4);
+            const float pv[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                o[4 * r4 + e][0] = __builtin_fmaf(pv[e], v0, o[4 * r4 + e][0]);
+                o[4 * r4 + e][1] = __builtin_fmaf(pv[e], v1, o[4 * r4 + e][1]);
+            }
+        }
+    }
+    __syncthreads();   // every wave is done with its weights and with the query rows: the outputs take their place
+#pragma unroll
+    for (int rr = 0; rr < NR; ++rr)
+        *reinterpret_cast<float2*>(o_lds + ((size_t)wave * 16 + rr) * kRowsOStride + 2 * lane) = make_float2(o[rr][0], o[rr][1]);
+}
+
+template <int BITS, int GROUP, int NR, bool BF16, int MODE>
+__global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs R) {
+    using S = RowsShape<BITS, GROUP, NR>;
+    constexpr int SUBS = S::SUBS, UNIT = S::UNIT, SG = S::SG, M = S::M;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[S::kBytes];
+    __shared__ uint32_t maskbits[MODE == kRowsScore ? 1 : kRowsMaxChunk / 32];
+    __shared__ RowsOut out;
+    const AttendArgs& A = R.at;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
+
+    // ---- which (row, chunk): workgroups that append the step's token first, then the 16-bit chunks, then the rest
+    const int n_tail = L.tail_k ? L.rows : 0;
+    if ((int)blockIdx.x < n_tail) {
+        const int rw = blockIdx.x;
+        if (tid < 32) {
+            const uint4 v = reinterpret_cast<const uint4*>(tid < 16 ? L.tail_k : L.tail_v)[(size_t)rw * 16 + (tid & 15)];
+            reinterpret_cast<uint4*>(L.host)[((size_t)rw * L.max_seq + L.tail_N0) * 32 + tid] = v;
+            reinterpret_cast<uint4*>(L.ring)[((size_t)rw * L.R + (L.tail_N0 % L.R)) * 32 + tid] = v;
+        }
+        return;
+    }
+    int row, chunk;
+    {
+        const int bid = (int)blockIdx.x - n_tail, n_extra = A.n_chunks - A.n_main;
+        if (bid < L.rows * n_extra) {
+            row = bid / n_extra;
+            chunk = A.n_main + bid % n_extra;
+        } else {
+            const int id = bid - L.rows * n_extra;
+            row = id / A.n_main;
+            chunk = id % A.n_main;
+        }
+    }
+
+    // ---- the query rows: scaled by a power of two and by the channels' factors, and as they are
+    float* qs = reinterpret_cast<float*>(smem);                                    // [NR][kQStride]
+    uint16_t* qraw = reinterpret_cast<uint16_t*>(smem + NR * S::kQStride * 4);      // [NR][kZStride]
+    float* q_unscale = reinterpret_cast<float*>(smem + NR * S::kQStride * 4 + NR * S::kZStride * 2);   // [NR]
+    for (int rr = wave; rr < NR; rr += kWaves) {
+        const uint32_t w = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + rr) * kD)[lane];
+        reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
+        if constexpr (MODE != kRowsAttend) {
+            const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
+            const float top = wave_max(fmaxf(fabsf(a), fabsf(b)));
+            int f = 253 + key_q_bits(BITS) - (int)((__float_as_uint(top) >> 23) & 0xFFu);   // top < 2^(E - 126): field of 2^(kbits - E + 126)
+            f = f < 100 ? 100 : (f > 224 ? 224 : f);
+            const float sc = __uint_as_float((uint32_t)f << 23);
+            const int c = 2 * lane;
+            *reinterpret_cast<float2*>(qs + rr * S::kQStride + c) = make_float2(a * sc * key_factor<BITS>(c), b * sc * key_factor<BITS>(c + 1));
+            if (lane == 0) q_unscale[rr] = __uint_as_float((uint32_t)(254 - f) << 23);
+        }
+    }
+
+    float* o_lds = reinterpret_cast<float*>(smem);                                  // [kWaves][16][kRowsOStride], at the end
+    if (MODE != kRowsScore && chunk >= A.n_main) {
+        __syncthreads();
+        float* weights = reinterpret_cast<float*>(smem + (S::kQBytes + 15) / 16 * 16) + wave * 32 * NR;
+        rows_extra_wave<NR, BF16>(L, A, R.n_rows, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, S::kZStride, weights,
+                                  o_lds, out);
+    } else {
+        const int chunk_tokens = kWaves * R.wave_units * UNIT, c0 = chunk * chunk_tokens;
+        const int w0 = c0 + wave * R.wave_units * UNIT;                             // the wave's first token
+        const int n_sub = A.Nq / kBlockTokens;
+        const uint8_t* kc_row = L.kc + (size_t)row * L.kc_stride;
+        const uint8_t* vc_row = L.vc + (size_t)row * L.vc_stride;
+        const uint32_t* km_row = L.km + (size_t)row * L.km_stride;
+        const uint32_t* vm_row = L.vm + (size_t)row * L.vm_stride;
+        uint8_t* area = smem + (S::kQBytes + 15) / 16 * 16 + wave * S::kWaveBytes;
+        float* s_tab = reinterpret_cast<float*>(area);                              // [SG][kSStride]
+        uint16_t* z_tab = reinterpret_cast<uint16_t*>(area + SG * S::kSStride * 4);  // [1 or 2][SG][kZStride]
+        float* vs_tab = reinterpret_cast<float*>(area + S::kKeyTab);                 // [M][UNIT]
+        float* vz_tab = vs_tab + M * UNIT;
+        float* l_tab = vz_tab + M * UNIT;                                            // [heads][kKeyStride]
+
+        // ---- loads of one unit
+        constexpr int kVm = UNIT * M / 64 > 0 ? UNIT * M / 64 : 1;                   // value metadata words per lane
+        uint2 kcw[SUBS][BITS], kmw[SG], vcw[SUBS][4];
+        uint32_t vmw[kVm];
+        auto sub_of = [&](int t0, int x) {
+            const int sub = t0 / kBlockTokens + x;
+            return sub < n_sub ? sub : n_sub - 1;                                    // past the end: a valid sub-group again
+        };
+        auto load_keys = [&](int t0) {
+            if constexpr (MODE != kRowsAttend) {
+#pragma unroll
+                for (int gi = 0; gi < SG; ++gi) {
+                    int grp = t0 / GROUP + gi;
+                    const int n_grp = A.Nq / GROUP;
+                    grp = grp < n_grp ? grp : n_grp - 1;
+                    kmw[gi] = *reinterpret_cast<const uint2*>(km_row + (size_t)grp * kD + 2 * lane);
+                }
+#pragma unroll
+                for (int x = 0; x < SUBS; ++x) {
+                    const int sub = sub_of(t0, x);
+                    // row ic is tokens 2 ic and 2 ic + 1: half (ic % 4) / 2 of layout lane 4 (sub % 16) + ic / 4
+                    const uint8_t* base = kc_row + (size_t)(sub / 16) * k_tile_bytes(BITS) + (size_t)((ic % 4) / 2) * 1024 +
+                                          (size_t)(4 * (sub % 16) + ic / 4) * 16 + 8 * (ic % 2);
+#pragma unroll
+                    for (int i = 0; i < BITS; ++i) kcw[x][i] = *reinterpret_cast<const uint2*>(base + (size_t)(kq + 4 * i) * 2048);
+                }
+            }
+        };
+        auto load_values = [&](int t0) {
+            if constexpr (MODE != kRowsScore) {
+                // metadata words of the unit in memory order: word lane * kVm + e
+                const int word = lane * kVm;
+                const int last = A.Nq * M - kVm;
+                int at = t0 * M + word;
+                at = at < last ? at : last;
+                if constexpr (kVm % 4 == 0) {
+#pragma unroll
+                    for (int e = 0; e < kVm; e += 4) {
+                        const uint4 v = *reinterpret_cast<const uint4*>(vm_row + at + e);
+                        vmw[e] = v.x; vmw[e + 1] = v.y; vmw[e + 2] = v.z; vmw[e + 3] = v.w;
+                    }
+                } else if constexpr (kVm == 2) {
+                    const uint2 v = *reinterpret_cast<const uint2*>(vm_row + at);
+                    vmw[0] = v.x; vmw[1] = v.y;
+                } else {
+                    vmw[0] = vm_row[at];
+                }
+#pragma unroll
+                for (int x = 0; x < SUBS; ++x) {
+                    const uint8_t* base = vc_row + (size_t)sub_of(t0, x) * code_block_bytes(BITS) + (size_t)(kq >> 1) * (256 * BITS) + 8 * (kq & 1);
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb) vcw[x][mb] = *reinterpret_cast<const uint2*>(base + value_lane<BITS>(mb, ic) * 16);
+                }
+            }
+        };
+        load_keys(w0 < A.Nq ? w0 : 0);
+        load_values(w0 < A.Nq ? w0 : 0);
+
+        // ---- bitmap of the chunk's staged positions (they enter through the 16-bit chunks)
+        if constexpr (MODE != kRowsScore) {
+            const int words = chunk_tokens / 32;
+            for (int i = tid; i < words; i += kThreads) maskbits[i] = 0u;
+            __syncthreads();
+            if (A.slot_idx)
+                for (int j = tid; j < L.topk; j += kThreads) {
+                    const int t = A.slot_idx[(size_t)row * L.topk + j] - c0;
+                    if (t >= 0 && t < chunk_tokens) atomicOr(&maskbits[t >> 5], 1u << (t & 31));
+                }
+        }
+        __syncthreads();
+
+        const ValueShift vsh = value_shift<BITS>(ic);
+        const int my_group = SG > 1 ? s * kBlockTokens / GROUP : 0;                   // the column's token group inside the unit
+        float4v acc[4][2];
+        float m_used = -INFINITY, lsum = 0.0f, zacc[M], vscale = 0.0f;
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) acc[mb][jj] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < M; ++m) zacc[m] = 0.0f;
+        constexpr bool kKeepB = MODE != kRowsAttend && UNIT < GROUP;                  // a token group's multipliers serve several units
+        // Two sub-groups of one token group: columns (r, hi | lo).  The two lanes of a row work out half of the
+        // multipliers each and exchange them.
+        constexpr bool kHiLo = SUBS == 2 && SG == 1;
+        constexpr int kSteps = kHiLo ? 2 : 4;
+        uint4v bhi[kKeepB || kHiLo ? 4 : 1], blo[kKeepB && !kHiLo ? 4 : 1];
+        auto multipliers = [&](int kc, uint4v& hi, uint4v& lo) {
+            const int c = key_channel<BITS>(kc, kq);
+            float x[8];
+#pragma unroll
+            for (int e4 = 0; e4 < 2; ++e4) {
+                const float4 qv = *reinterpret_cast<const float4*>(qs + r * S::kQStride + c + 4 * e4);
+                const float4 sv4 = *reinterpret_cast<const float4*>(s_tab + my_group * S::kSStride + c + 4 * e4);
+                x[4 * e4] = qv.x * sv4.x;
+                x[4 * e4 + 1] = qv.y * sv4.y;
+                x[4 * e4 + 2] = qv.z * sv4.z;
+                x[4 * e4 + 3] = qv.w * sv4.w;
+            }
+            split8(x, hi, lo);
+        };
+        float unscale = 0.0f, qz = 0.0f;
+        int group_done = -1;
+
+        for (int u = 0; u < R.wave_units; ++u) {
+            const int t0 = w0 + u * UNIT;
+            if (t0 >= A.Nq) break;                                                    // uniform over the wave
+            const bool active = t0 / kBlockTokens + s < n_sub;
+            float l[8];
+            if constexpr (MODE != kRowsAttend) {
+                // ---- multipliers of the unit's token groups (a group longer than a unit is worked out once)
+                const int grp0 = t0 / GROUP;
+                if (grp0 != group_done) {
+                    group_done = grp0;
+                    float sv[SG][2], top = 0.0f;
+                    wave_sync();
+#pragma unroll
+                    for (int gi = 0; gi < SG; ++gi) {
+                        const uint32_t wd[2] = {kmw[gi].x, kmw[gi].y};
+                        // words 2 lane, 2 lane + 1 are channels c and c + 4
+                        const int c = 4 * ((2 * lane) & 31) + (lane >> 4);
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            float z;
+                            derive_scale_zero<BITS>(widen16<BF16>(wd[e] & 0xFFFFu), widen16<BF16>(wd[e] >> 16), L.one_bit_plain, sv[gi][e], z);
+                            top = fmaxf(top, sv[gi][e]);
+                            z_tab[gi * S::kZStride + c + 4 * e] = (uint16_t)wd[e];
+                            if constexpr (BITS == 1) z_tab[(SG + gi) * S::kZStride + c + 4 * e] = (uint16_t)(wd[e] >> 16);
+                        }
+                    }
+                    top = wave_max(top);
+                    // s < 2^(E - 126): scaled to below 2^8
+                    int f = 261 - (int)((__float_as_uint(top) >> 23) & 0xFFu);
+                    f = f < 100 ? 100 : (f > 224 ? 224 : f);
+                    const float sc = __uint_as_float((uint32_t)f << 23);
+#pragma unroll
+                    for (int gi = 0; gi < SG; ++gi) {
+                        const int c = 4 * ((2 * lane) & 31) + (lane >> 4);
+                        s_tab[gi * S::kSStride + c] = sv[gi][0] * sc;
+                        s_tab[gi * S::kSStride + c + 4] = sv[gi][1] * sc;
+                    }
+                    wave_sync();
+                    unscale = q_unscale[r] * (__uint_as_float((uint32_t)(254 - f) << 23) * (float)(1 << (24 - key_pos(BITS))));
+                    // zero-point term: z is the stored 16-bit minimum (Eq. 3: a quarter of three minima and a maximum),
+                    // q the 16-bit query, so the products are exact.  A row i is token group i & 3.
+                    const int zg = SG > 1 ? (ic & (SG - 1)) : 0;
+                    float4v zc = {0.f, 0.f, 0.f, 0.f}, xc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kc = 0; kc < 4; ++kc) {
+                        const uint4v b = *reinterpret_cast<const uint4v*>(qraw + r * S::kZStride + 32 * kc + 8 * kq);
+                        const uint4v a = *reinterpret_cast<const uint4v*>(z_tab + zg * S::kZStride + 32 * kc + 8 * kq);
+                        zc = mfma_native<BF16>(a, b, zc);
+                        if constexpr (BITS == 1) {
+                            const uint4v a2 = *reinterpret_cast<const uint4v*>(z_tab + (SG + zg) * S::kZStride + 32 * kc + 8 * kq);
+                            xc = mfma_native<BF16>(a2, b, xc);
+                        }
+                    }
+                    float zq = zc[0], xq = xc[0];
+#pragma unroll
+                    for (int gi = 1; gi < SG; ++gi) {
+                        zq = my_group == gi ? zc[gi] : zq;
+                        xq = my_group == gi ? xc[gi] : xq;
+                    }
+                    if constexpr (BITS == 1) zq = L.one_bit_plain ? zq : __builtin_fmaf(zq, 3.0f, xq) * 0.25f;
+                    qz = zq * A.sm_scale;
+                    if constexpr (kHiLo) {
+#pragma unroll
+                        for (int i = 0; i < kSteps; ++i) {
+                            uint4v hi, lo;
+                            multipliers(i + 2 * s, hi, lo);
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) {
+                                const uint32_t got = ror8(s ? hi[d] : lo[d]);
+                                bhi[i][d] = s ? got : hi[d];
+                                bhi[i + 2][d] = s ? lo[d] : got;
+                            }
+                        }
+                    } else if constexpr (kKeepB) {
+#pragma unroll
+                        for (int kc = 0; kc < 4; ++kc) multipliers(kc, bhi[kc], blo[kc]);
+                    }
+                }
+                // ---- products: four channel steps x sub-groups x two tiles (even and odd tokens) x (hi, lo)
+                float4v c[SUBS][2];
+#pragma unroll
+                for (int x = 0; x < SUBS; ++x) c[x][0] = c[x][1] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kc = 0; kc < 4; ++kc) {
+                    uint4v bh, bl;
+                    if constexpr (kHiLo) bh = bhi[kc];
+                    else if constexpr (kKeepB) { bh = bhi[kc]; bl = blo[kc]; }
+                    else multipliers(kc, bh, bl);
+#pragma unroll
+                    for (int x = 0; x < SUBS; ++x)
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) {
+                            const uint2 w = kcw[x][key_load<BITS>(kc)];
+                            const uint4v a = key_operand<BITS>(mt == 0 ? w.x : w.y, kc);
+                            c[x][mt] = mfma16(a, bh, c[x][mt]);
+                            if constexpr (!kHiLo) c[x][mt] = mfma16(a, bl, c[x][mt]);
+                        }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                float o[8];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt) {
+                        if constexpr (kHiLo) {     // the lane's sub-group: its own column plus the other one's
+                            const float other = s ? c[0][mt][v] : c[SUBS - 1][mt][v];
+                            o[2 * v + mt] = (s ? c[SUBS - 1][mt][v] : c[0][mt][v]) + dpp_move<kDppRowRor8>(other);
+                        } else {
+                            o[2 * v + mt] = c[0][mt][v];
+#pragma unroll
+                            for (int x = 1; x < SUBS; ++x) o[2 * v + mt] = s == x ? c[x][mt][v] : o[2 * v + mt];
+                        }
+                    }
+                if (u + 1 < R.wave_units) load_keys(t0 + UNIT < A.Nq ? t0 + UNIT : t0);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) l[t] = __builtin_fmaf(o[t], unscale, qz);
+                // ---- selection keys: the largest logit of the heads' last rows
+                {
+                    const int G = NR / R.n_rows;
+                    if (r % R.n_rows == R.n_rows - 1) {
+                        float4* d = reinterpret_cast<float4*>(l_tab + (r / R.n_rows) * S::kKeyStride + 32 * s + 8 * kq);
+                        d[0] = make_float4(l[0], l[1], l[2], l[3]);
+                        d[1] = make_float4(l[4], l[5], l[6], l[7]);
+                    }
+                    wave_sync();
+#pragma unroll
+                    for (int i = 0; i < (UNIT + 63) / 64; ++i) {
+                        const int t = UNIT >= 64 ? 64 * i + lane : lane & (UNIT - 1);
+                        float b = -INFINITY;
+                        if constexpr (UNIT >= 64) {
+                            for (int h = 0; h < G; ++h) b = fmaxf(b, l_tab[h * S::kKeyStride + t]);
+                        } else {       // two lanes per token, half of the heads each
+                            for (int h = 0; h < G / 2; ++h) b = fmaxf(b, l_tab[((lane >> 5) * (G / 2) + h) * S::kKeyStride + t]);
+                            b = xor32_max(b);
+                        }
+                        if (t0 + t < A.Nq && (UNIT >= 64 || lane < 32)) R.keys[(size_t)row * R.key_stride + t0 + t] = float_to_key(b);
+                    }
+                    wave_sync();
+                }
+                if (A.logits_out && active) {
+                    float4* d = reinterpret_cast<float4*>(A.logits_out + ((size_t)row * NR + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    d[0] = make_float4(l[0], l[1], l[2], l[3]);
+                    d[1] = make_float4(l[4], l[5], l[6], l[7]);
+                }
+            } else {
+                float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+                if (active) {
+                    const float4* d = reinterpret_cast<const float4*>(A.logits + ((size_t)row * NR + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    a = d[0];
+                    b = d[1];
+                }
+                l[0] = a.x; l[1] = a.y; l[2] = a.z; l[3] = a.w; l[4] = b.x; l[5] = b.y; l[6] = b.z; l[7] = b.w;
+            }
+
+            if constexpr (MODE != kRowsScore) {
+                // ---- scales and zero-points of the unit's tokens
+                float vtop = 0.0f;
+                wave_sync();
+#pragma unroll
+                for (int e = 0; e < kVm; ++e) {
+                    const int word = lane * kVm + e, tok = word / M, m = word % M;
+                    float sc, z;
+                    derive_scale_zero<BITS>(widen16<BF16>(vmw[e] & 0xFFFFu), widen16<BF16>(vmw[e] >> 16), L.one_bit_plain, sc, z);
+                    if (UNIT * M >= 64 || word < UNIT * M) {
+                        vs_tab[m * UNIT + tok] = sc;
+                        vz_tab[m * UNIT + tok] = z;
+                    }
+                    vtop = fmaxf(vtop, sc);
+                }
+                vtop = wave_max(vtop);
+                wave_sync();
+                // ---- softmax numerators
+                const uint32_t mask = (maskbits[(t0 - c0) / 32 + s] >> (8 * kq)) & 0xFFu;
+                float mx = -INFINITY;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    l[t] = active && !((mask >> t) & 1u) ? l[t] : -INFINITY;
+                    mx = fmaxf(mx, l[t]);
+                }
+                mx = quarters_max(mx);
+                if constexpr (SUBS == 2) mx = fmaxf(mx, dpp_move<kDppRowRor8>(mx));   // both columns of a row share the maximum
+                if (__any(mx > m_used + kLazyMax) || vtop * vscale > 512.0f || vscale == 0.0f) {
+                    // the maxima, or the fixed scale of the value side (p s vscale < 2^15 with p < 2^6), move
+                    const float m_new = fmaxf(m_used, mx);
+                    const float a = m_new == -INFINITY ? 1.0f : exp2_of((m_used - m_new) * kLog2e);
+                    float ns = vscale;
+                    if (vtop * vscale > 512.0f || vscale == 0.0f) {
+                        // vtop < 2^(E - 126): vtop * scale < 2^5, four binary orders of room
+                        int f = 258 - (int)((__float_as_uint(vtop) >> 23) & 0xFFu);
+                        f = f > 224 ? 224 : f;
+                        ns = __uint_as_float((uint32_t)f << 23);
+                    }
+                    const float b = vscale == 0.0f ? 0.0f : a * (ns / vscale);
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[mb][jj][e] *= b;
+#pragma unroll
+                    for (int m = 0; m < M; ++m) zacc[m] *= a;
+                    lsum *= a;
+                    m_used = m_new;
+                    vscale = ns;
+                }
+                const float ms = m_used == -INFINITY ? 0.0f : m_used;
+                float p[8], pv[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    p[t] = exp2_of((l[t] - ms) * kLog2e);
+                    lsum += p[t];
+                    pv[t] = p[t] * vscale;
+                }
+                // ---- per value group: B operand and zero-point sums; per sub-group and 32-channel block of the
+                // ---- group two channel tiles x (hi, lo)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    uint4v phi, plo;
+                    {
+                        const float4* sp = reinterpret_cast<const float4*>(vs_tab + m * UNIT + 32 * s + 8 * kq);
+                        const float4* zp = reinterpret_cast<const float4*>(vz_tab + m * UNIT + 32 * s + 8 * kq);
+                        const float4 s0 = sp[0], s1 = sp[1], z0 = zp[0], z1 = zp[1];
+                        const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+                        const float zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+                        float x[8];
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) {
+                            x[t] = pv[t] * sv[t];
+                            zacc[m] = __builtin_fmaf(p[t], zv[t], zacc[m]);
+                        }
+                        split8(x, phi, plo);
+                    }
+                    if constexpr (SUBS == 2) {
+                        // columns (r, hi | lo): the lane of sub-group 0 sends its lo halves and receives hi halves of sub-group 1
+                        uint4v b[2];
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            const uint32_t got = ror8(s ? phi[d] : plo[d]);
+                            b[0][d] = s ? got : phi[d];
+                            b[1][d] = s ? plo[d] : got;
+                        }
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+#pragma unroll
+                            for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb) {
+                                uint4v a[2];
+                                value_operands<BITS>(vcw[x][mb], vsh, a);
+#pragma unroll
+                                for (int jj = 0; jj < 2; ++jj) acc[mb][jj] = mfma16(a[jj], b[x], acc[mb][jj]);
+                            }
+                    } else {
+#pragma unroll
+                        for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb) {
+                            uint4v a[2];
+                            value_operands<BITS>(vcw[0][mb], vsh, a);
+#pragma unroll
+                            for (int jj = 0; jj < 2; ++jj) {
+                                acc[mb][jj] = mfma16(a[jj], phi, acc[mb][jj]);
+                                acc[mb][jj] = mfma16(a[jj], plo, acc[mb][jj]);
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (u + 1 < R.wave_units) load_values(t0 + UNIT < A.Nq ? t0 + UNIT : t0);
+            }
+        }
+        if constexpr (MODE == kRowsScore) return;
+        // ---- the wave's outputs per column, for the merge
+        lsum = quarters_sum(lsum);
+#pragma unroll
+        for (int m = 0; m < M; ++m) zacc[m] = quarters_sum(zacc[m]);
+        if (kq == 0) {
+            out.m[wave][ic] = m_used;
+            out.l[wave][ic] = lsum;
+        }
+        __syncthreads();   // every wave is done with its tables: the outputs take their place
+        const float inv = vscale == 0.0f ? 0.0f : 16777216.0f / vscale;
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // C row 4 kq + e of the tile
+                    const int c = value_channel<BITS>(mb, jj, 4 * kq + e);
+                    o_lds[((size_t)wave * 16 + ic) * kRowsOStride + c] =
+                        __builtin_fmaf(acc[mb][jj][e], inv * (1.0f / (float)(1 << value_pos(BITS, jj))), zacc[mb * 32 / GROUP]);
+                }
+    }
+    if constexpr (MODE == kRowsScore) return;
+    __syncthreads();
+    // ---- merge: the columns of a row over the waves and sub-groups
+    if (tid < kWaves * 16) {
+        const int w = tid >> 4, col = tid & 15, rr = col % NR;
+        float mx = -INFINITY;
+        for (int ww = 0; ww < kWaves; ++ww)
+#pragma unroll
+            for (int ss = 0; ss < SUBS; ++ss) mx = fmaxf(mx, out.m[ww][ss * NR + rr]);
+        const float mv = out.m[w][col];
+        out.w[w][col] = mv == -INFINITY ? 0.0f : exp2_of((mv - mx) * kLog2e);
+    }
+    __syncthreads();
+    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
+    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2;
+    for (int e = tid; e < NR * kD; e += kThreads) {
+        const int rr = e / kD, c = e % kD;
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+            for (int ss = 0; ss < SUBS; ++ss) {
+                const float wt = out.w[w][ss * NR + rr];
+                if (wt != 0.0f) v = __builtin_fmaf(wt, o_lds[((size_t)w * 16 + ss * NR + rr) * kRowsOStride + c], v);
+            }
+        po[e] = v;
+    }
+    if (tid < NR) {
+        float mx = -INFINITY, sum = 0.0f;
+        for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+            for (int ss = 0; ss < SUBS; ++ss) {
+                mx = fmaxf(mx, out.m[w][ss * NR + tid]);
+                sum = __builtin_fmaf(out.w[w][ss * NR + tid], out.l[w][ss * NR + tid], sum);
+            }
+        pml[2 * tid] = mx;
+        pml[2 * tid + 1] = sum;
+    }
+}
+
+// launch of one mode for codes of BITS bits; at: everything but the chunking
+template <int BITS, int MODE>
+hipError_t launch_rows_mode(const LayerView& L, const RowsArgs& R, int NR, hipStream_t stream) {
+    const dim3 grid(R.at.n_chunks * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
+#define SPC_ROWS(G_, N_)                                                                            \
+    if (L.group == G_ && NR == N_) {                                                                \
+        if (L.bf16) SPC_LAUNCH((rows_kernel<BITS, G_, N_, true, MODE>), grid, block, stream, L, R); \
+        else SPC_LAUNCH((rows_kernel<BITS, G_, N_, false, MODE>), grid, block, stream, L, R);       \
+        return hipGetLastError();                                                                   \
+    }
+    SPC_ROWS(32, 8) SPC_ROWS(64, 8) SPC_ROWS(128, 8)
+    SPC_ROWS(32, 16) SPC_ROWS(64, 16) SPC_ROWS(128, 16)
+#undef SPC_ROWS
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+}  // namespace specache

@@ -12,9 +12,7 @@
 // metadata, quad lane k those of the channels with channel % 4 == k, and exchange them
 // through a wave-private LDS area (one vector write and up to four 16-byte reads per mask)
 // so that they reach the multiply-accumulates as plain register operands.  Codes become
-// floats with v_cvt_f32_ubyte{0..3} after one mask per four codes.  Query rows are taken in
-// passes of at most four (a pass converts the codes again, but 32 accumulators instead of up
-// to 128 keep four waves per SIMD resident); after a pass the waves swap partial sums through
+// floats with v_cvt_f32_ubyte{0..3} after one mask per four codes.  The waves then swap partial sums through
 // the same LDS area and each finishes, stores and ranks two of the lane's eight tokens.
 // Measured on MI355X, with every load of the kernel served from cache: the kernel takes as
 // long as with the loads from HBM less about a tenth, and its time follows the count of
@@ -23,6 +21,7 @@
 // multipliers travel through LDS.
 #include "kernels.h"
 #include "layout.h"
+#include "rows_args.h"
 
 namespace specache {
 namespace {
@@ -54,7 +53,8 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
                                                                  size_t logit_stride, uint32_t* __restrict__ keys,
                                                                  size_t key_stride) {
     constexpr int NR = G * NROWS;              // query rows sharing this KV head
-    constexpr int RH = NR < 4 ? NR : 4;        // query rows per pass
+    constexpr int RH = NR;
+    static_assert(NR <= 4, "8 and 16 rows: rows_mfma.h");
     constexpr int HPD = (32 / BITS) / 4;       // masks (= multiplier registers) per code dword
     constexpr int NW = 4 * BITS;               // code dwords per token
     constexpr int WPW = NW / kScoreWaves;      // code dwords per wave
@@ -105,22 +105,8 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
 #pragma unroll
     for (int t = 0; t < TPW; ++t) best[t] = -INFINITY;
 
-#pragma unroll 1
-    for (int r0 = 0; r0 < NR; r0 += RH) {
-        if constexpr (NR > RH) {
-            // Everything derived from the loaded dwords is the same in every pass; hoisting it out of
-            // the loop would cost the registers the passes are there to save, so the loads are
-            // made to look pass-dependent.
-#pragma unroll
-            for (int i = 0; i < WPW; ++i) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    asm volatile("" : "+v"(cw[i][j].x), "+v"(cw[i][j].y), "+v"(cw[i][j].z), "+v"(cw[i][j].w));
-#pragma unroll
-                for (int j = 0; j < HPD / 4; ++j)
-                    asm volatile("" : "+v"(mt[i][j].x), "+v"(mt[i][j].y), "+v"(mt[i][j].z), "+v"(mt[i][j].w));
-            }
-        }
+    constexpr int r0 = 0;
+    {
         // Every lane folds the multipliers of its channel class for all masks of this wave and
         // leaves them in LDS, from where the four lanes of the quad read all four classes back:
         // the lanes of a wave run in lockstep and LDS serves one wave's accesses in order, so
@@ -246,7 +232,6 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
                     *reinterpret_cast<float2*>(logits + ((size_t)row * NR + r0 + r) * logit_stride + i0) = make_float2(o[0], o[1]);
             }
         }
-        if (r0 + RH < NR) __syncthreads();   // partial sums consumed before the next pass reuses the area
     }
     if constexpr (!kRowSplit) {
         if (active)
@@ -273,8 +258,7 @@ hipError_t launch2(const LayerView& L, const void* q, int n_rows, int Nq, float 
 #define SPC_CASE(g_, n_)                                                                                    \
     if (L.G == g_ && n_rows == n_)                                                                          \
         return launch3<BITS, g_, n_>(L, q, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
-    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1) SPC_CASE(4, 2) SPC_CASE(8, 1)
-    SPC_CASE(8, 2)
+    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1)
 #undef SPC_CASE
     return hipErrorInvalidValue;
 }
@@ -290,8 +274,18 @@ hipError_t launch_score(const LayerView& L, const void* q, int n_rows, int Nq, f
     // time; the C ABI rejects a q that is not 16-byte aligned)
     if (score_uses_int8_matrix_cores(L.G, n_rows) && !(kernel_choice() & kChoiceScoreValu))
         return launch_score_i8(L, q, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
-    if (score_uses_matrix_cores(L.G, n_rows))
-        return launch_score_mfma(L, q, n_rows, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
+    if (rows_uses_matrix_cores(L, n_rows)) {
+        RowsArgs R{};
+        R.at.q = (const uint16_t*)q;
+        R.at.logits_out = logits;
+        R.at.logit_stride = logit_stride;
+        R.at.N = R.at.Nq = Nq;
+        R.at.sm_scale = sm_scale;
+        R.keys = keys;
+        R.key_stride = key_stride;
+        R.n_rows = n_rows;
+        return launch_rows(L, R, kRowsScore, stream);
+    }
     if (L.bits == 2) return launch2<2>(L, q, n_rows, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
     if (L.bits == 1) return launch2<1>(L, q, n_rows, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
     return hipErrorInvalidValue;

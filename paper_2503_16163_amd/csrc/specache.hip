@@ -13,6 +13,7 @@
 
 #include "kernels.h"
 #include "layout.h"
+#include "rows_args.h"
 #include <cstdlib>
 
 using namespace specache;
@@ -468,6 +469,7 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         const int m = (int)((cap + ch - 1) / ch);
         max_main = m > max_main ? m : max_main;
     }
+    if (rows_max_main_chunks(rows, (int)cap) > max_main) max_main = rows_max_main_chunks(rows, (int)cap);
     const int ec = attend_extra_chunk_tokens();
     ctx->scratch.max_chunks = max_main + (c.topk + c.residual + 1 + ec - 1) / ec;
     SPC_ALLOC(hipMalloc((void**)&ctx->scratch.part_o, (size_t)rows * ctx->scratch.max_chunks * G * 2 * kD * 4));
@@ -754,7 +756,10 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
     if (static_scratch) {
         // partial outputs [rows][chunks][NR][128] floats, then the (max, sum) pairs [rows][chunks][NR][2]
         const int NR = L.view.G * n_rows;
-        const int chunks = attend_chunks(NR, L.Nq, (slot >= 0 ? ctx->cfg.topk : 0) + (L.N - L.Nq) + (k_spec ? 1 : 0));
+        const int n_16bit = (slot >= 0 ? ctx->cfg.topk : 0) + (L.N - L.Nq) + (k_spec ? 1 : 0);
+        int chunks = attend_chunks(NR, L.Nq, n_16bit);
+        if (rows_uses_matrix_cores(L.view, n_rows) && rows_chunks(L.view, n_rows, L.Nq, n_16bit) > chunks)
+            chunks = rows_chunks(L.view, n_rows, L.Nq, n_16bit);
         const size_t o_floats = (size_t)L.view.rows * chunks * NR * kD, ml_floats = (size_t)L.view.rows * chunks * NR * 2;
         if ((o_floats + ml_floats) * sizeof(float) > kStaticScratchBytes)
             return fail(ctx, SPECACHE_ECAPACITY, "specache_attend_static: the partial results of this call (rows x chunks x query rows "
@@ -795,9 +800,11 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
         if (specache_plan_append(ctx->cfg.residual, ctx->cfg.group, L.N, L.Nq, 1, &n_flush) != SPECACHE_OK)
             return fail(ctx, SPECACHE_ESTATE, "inconsistent token counts");
     }
-    const bool one_pass = L.view.G == 1 && n_rows == 2 && attend_uses_int8_matrix_cores(L.view, n_rows) && L.Nq > 0 &&
-                          ctx->cfg.select_cache == SPECACHE_SELECT_LOWBIT && q && out && !((uintptr_t)q & 15) &&
-                          !(kernel_choice() & (kChoiceScoreValu | kChoiceAttendValu));
+    const bool rows_pass = (n_rows == 1 || n_rows == 2) && rows_uses_matrix_cores(L.view, n_rows) &&
+                           ctx->cfg.select_form == SPECACHE_SELECT_MAX_LOGIT;
+    const bool one_pass = (rows_pass || (L.view.G == 1 && n_rows == 2 && attend_uses_int8_matrix_cores(L.view, n_rows) &&
+                                         !(kernel_choice() & (kChoiceScoreValu | kChoiceAttendValu)))) &&
+                          L.Nq > 0 && ctx->cfg.select_cache == SPECACHE_SELECT_LOWBIT && q && out && !((uintptr_t)q & 15);
     const bool carry = k_new && one_pass && n_flush == 0;
     if (k_new && !carry)
         if (int rc = specache_quantize_append(ctx, layer, k_new, v_new, 1, stream)) return rc;
@@ -825,9 +832,30 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
         CarriedEvent scored(ctx, L.idx_ready);
-        SPC_HIP(ctx, launch_attend_i8_partial(view, q, N1, L.Nq, ctx->sm_scale, nullptr, ctx->logit_stride,
-                                              slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
-                                              v_spec, ctx->scratch, L.keys, ctx->logit_stride, keep ? ctx->logits : nullptr, st));
+        if (rows_pass) {
+            RowsArgs R{};
+            R.at.q = (const uint16_t*)q;
+            R.at.logits_out = keep ? ctx->logits : nullptr;
+            R.at.logit_stride = ctx->logit_stride;
+            R.at.slot = slot >= 0 ? L.slot[slot] : nullptr;
+            R.at.slot_idx = slot >= 0 ? L.slot_idx[slot] : nullptr;
+            R.at.k_spec = (const uint16_t*)k_spec;
+            R.at.v_spec = (const uint16_t*)v_spec;
+            R.at.part_o = ctx->scratch.part_o;
+            R.at.part_ml = ctx->scratch.part_ml;
+            R.at.max_chunks = ctx->scratch.max_chunks;
+            R.at.N = N1;
+            R.at.Nq = L.Nq;
+            R.at.sm_scale = ctx->sm_scale;
+            R.keys = L.keys;
+            R.key_stride = ctx->logit_stride;
+            R.n_rows = n_rows;
+            SPC_HIP(ctx, launch_rows(view, R, kRowsBoth, st));
+        } else {
+            SPC_HIP(ctx, launch_attend_i8_partial(view, q, N1, L.Nq, ctx->sm_scale, nullptr, ctx->logit_stride,
+                                                  slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
+                                                  v_spec, ctx->scratch, L.keys, ctx->logit_stride, keep ? ctx->logits : nullptr, st));
+        }
         scored_carried = scored.landed();
     }
     L.N = N1;   // only once the launch that copies the token is enqueued
