@@ -300,7 +300,11 @@ constexpr int kCombineThreads = 1024, kCombineSlices = kCombineThreads / 64;
 __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(const float* __restrict__ part_o,
                                                                          const float* __restrict__ part_ml,
                                                                          int max_chunks, int n_chunks, int NR,
-                                                                         float* __restrict__ out) {
+                                                                         float* __restrict__ out, Announce announce) {
+    // The kernel boundary in front of this kernel has made everything the earlier launch wrote visible, so a plain store is
+    // all another stream's wait needs.
+    if (announce.word && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(announce.word, announce.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __shared__ float wgt[kCombineMaxChunks];
     __shared__ float red[2 * kCombineSlices];
     __shared__ float2 osum[kCombineSlices][64];
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(const f
 }
 
 template <int BITS, int GROUP, int G, int NROWS>
-hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* out, int phases, hipStream_t stream) {
+hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* out, int phases, Announce announce, hipStream_t stream) {
     constexpr int NR = G * NROWS;
     if (A.n_main + n_extra > kCombineMaxChunks) return hipErrorInvalidValue;
     if (phases & kAttendPartial) {
@@ -400,19 +404,19 @@ hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* 
     }
     if (phases & kAttendCombine)
         SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                   A.max_chunks, A.n_main + n_extra, NR, out);
+                   A.max_chunks, A.n_main + n_extra, NR, out, announce);
     return hipGetLastError();
 }
 
 template <int BITS, int GROUP>
-hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, float* out, int phases, hipStream_t stream) {
+hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, float* out, int phases, Announce announce, hipStream_t stream) {
 #define SPC_CASE(g_, n_)                                                        \
     if (L.G == g_ && n_rows == n_) {                                            \
         A.n_main = (A.Nq + main_chunk(g_ * n_) - 1) / main_chunk(g_ * n_);      \
         const int n_extra = (n_ex + kExtraChunk - 1) / kExtraChunk;             \
         A.n_chunks = A.n_main + n_extra;                                        \
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
-        return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, stream); \
+        return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, announce, stream); \
     }
     SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1)
 #undef SPC_CASE
@@ -431,7 +435,7 @@ int attend_max_chunks() { return kCombineMaxChunks; }
 hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, int Nq, float sm_scale,
                          const float* logits, size_t logit_stride, const uint16_t* slot, const int32_t* slot_idx,
                          const void* k_spec, const void* v_spec, const AttendScratch& scratch, float* out,
-                         int phases, hipStream_t stream) {
+                         int phases, hipStream_t stream, Announce announce) {
     AttendArgs A;
     A.q = (const uint16_t*)q;
     A.logits = logits;
@@ -463,7 +467,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
             const int n_chunks = attend_chunks(NR, Nq, n_ex);
             if (n_chunks > kCombineMaxChunks || n_chunks > scratch.max_chunks) return hipErrorInvalidValue;
             SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, scratch.part_o, scratch.part_ml,
-                       scratch.max_chunks, n_chunks, NR, out);
+                       scratch.max_chunks, n_chunks, NR, out, announce);
         }
         return hipGetLastError();
     }
@@ -476,7 +480,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
         }
         if (phases & kAttendCombine)
             SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * L.G * n_rows), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex), L.G * n_rows, out);
+                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex), L.G * n_rows, out, announce);
         return hipGetLastError();
     }
     // one query head per KV head, two rows, 2-bit values: the partial pass with the value side on the
@@ -488,12 +492,12 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
         phases &= ~kAttendPartial;
         if (!phases) return hipSuccess;
     }
-    if (L.bits == 2 && L.group == 32) return launch2<2, 32>(L, A, n_rows, n_ex, out, phases, stream);
-    if (L.bits == 2 && L.group == 64) return launch2<2, 64>(L, A, n_rows, n_ex, out, phases, stream);
-    if (L.bits == 1 && L.group == 32) return launch2<1, 32>(L, A, n_rows, n_ex, out, phases, stream);
-    if (L.bits == 1 && L.group == 64) return launch2<1, 64>(L, A, n_rows, n_ex, out, phases, stream);
-    if (L.bits == 2 && L.group == 128) return launch2<2, 128>(L, A, n_rows, n_ex, out, phases, stream);
-    if (L.bits == 1 && L.group == 128) return launch2<1, 128>(L, A, n_rows, n_ex, out, phases, stream);
+    if (L.bits == 2 && L.group == 32) return launch2<2, 32>(L, A, n_rows, n_ex, out, phases, announce, stream);
+    if (L.bits == 2 && L.group == 64) return launch2<2, 64>(L, A, n_rows, n_ex, out, phases, announce, stream);
+    if (L.bits == 1 && L.group == 32) return launch2<1, 32>(L, A, n_rows, n_ex, out, phases, announce, stream);
+    if (L.bits == 1 && L.group == 64) return launch2<1, 64>(L, A, n_rows, n_ex, out, phases, announce, stream);
+    if (L.bits == 2 && L.group == 128) return launch2<2, 128>(L, A, n_rows, n_ex, out, phases, announce, stream);
+    if (L.bits == 1 && L.group == 128) return launch2<1, 128>(L, A, n_rows, n_ex, out, phases, announce, stream);
     return hipErrorInvalidValue;
 }
 

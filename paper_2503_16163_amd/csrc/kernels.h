@@ -101,6 +101,12 @@ struct AttendScratch {
     int max_chunks;
 };
 enum { kAttendPartial = 1, kAttendCombine = 2 };   // which of the two launches launch_attend issues
+// A 64-bit word that other streams wait on (hipStreamWaitValue64): the merge kernel stores value there as it starts, i.e.
+// when the launch in front of it on its stream has completed.  word == null: nothing to announce.
+struct Announce {
+    uint64_t* word = nullptr;
+    uint64_t value = 0;
+};
 int attend_main_chunk_tokens(int NR);
 // chunks the partial pass writes for NR query rows per KV head, Nq quantised and n_16bit 16-bit candidates
 int attend_chunks(int NR, int Nq, int n_16bit);
@@ -109,7 +115,7 @@ int attend_max_chunks();   // chunks per row the merge kernel handles
 hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, int Nq, float sm_scale,
                          const float* logits, size_t logit_stride, const uint16_t* slot,
                          const int32_t* slot_idx, const void* k_spec, const void* v_spec,
-                         const AttendScratch& scratch, float* out, int phases, hipStream_t stream);
+                         const AttendScratch& scratch, float* out, int phases, hipStream_t stream, Announce announce = Announce());
 
 // the same partial pass for one query head per KV head, two rows, 2-bit values: value side on the integer matrix cores
 bool attend_uses_int8_matrix_cores(const LayerView& L, int n_rows);
