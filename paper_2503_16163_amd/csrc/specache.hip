@@ -107,6 +107,7 @@ struct specache_ctx {
     // selections on the gather's stream: those of two side streams may overlap, so the candidate
     // arrays of the two-launch ArgTopK exist twice, each remembering its last user
     bool select_on_gather = false;
+    bool scores_by_word = true;    // see Layer::scored_word
     struct SelectScratch { TopkScratch s{}; bool used = false; hipStream_t stream = nullptr; hipEvent_t done = nullptr; };
     SelectScratch select_scratch[2];
     int select_scratch_next = 0;
@@ -448,6 +449,9 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
     }
     ctx->async_select = c.async_select == SPECACHE_SELECT_STREAM_OWN;
     ctx->select_on_gather = c.async_select == SPECACHE_SELECT_STREAM_GATHER;
+    // A profiler that collects counters (rocprofv3 --pmc, which sets this variable) runs the kernels of all queues one at a
+    // time.  The wait for a word is itself a kernel, and the one that stores the word would not start before it ended.
+    ctx->scores_by_word = std::getenv("ROCPROF_COUNTERS") == nullptr;
     if (ctx->select_on_gather) {
         for (Layer& L : ctx->layers) {
             SPC_ALLOC(hipMalloc((void**)&L.keys, (size_t)rows * cap * 4));
@@ -848,6 +852,10 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
         view.tail_N0 = L.N;
     }
     const int N1 = L.N + (carry ? 1 : 0);
+    // Under capture the word is no order: a replayed merge stores the value of its capture again, and the selection's
+    // stream, if it is not part of the capture, would wait at once for a value that only a replay stores.  An event it is.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool by_word = ctx->scores_by_word && hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
         if (rows_pass) {
@@ -882,10 +890,10 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
         TimedLaunch t(ctx, st, SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
                                    slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec, v_spec,
-                                   ctx->scratch, out, kAttendCombine, st, Announce{L.scored_word, L.scored_value + 1}));
+                                   ctx->scratch, out, kAttendCombine, st, by_word ? Announce{L.scored_word, L.scored_value + 1} : Announce{}));
     }
-    ++L.scored_value;
-    if (int rc = record_scored(ctx, L, layer, n_rows, st, false, /*by_word=*/true)) return rc;
+    if (by_word) ++L.scored_value;
+    if (int rc = record_scored(ctx, L, layer, n_rows, st, false, by_word)) return rc;
     return record_attended(ctx, L, slot, st);
 }
 
