@@ -533,12 +533,12 @@ def main():
     pairs = rows * ((k if not args.no_gather else 0) + (N - Nq) + 1) * 512   # staged, residual and transient 16-bit pairs
     us_layer = ms_per_step * 1e3 / layers
     n_q_rows = G * (2 if spec else 1)
-    score_name = ("score4_kernel" if bits == 4 else
-                  "score_i8_kernel" if (G == 1 and spec and args.vector_alu not in ("score", "both"))
-                  else "rows_kernel" if n_q_rows % 8 == 0 else "score_kernel")
-    attend_name = ("attend4_partial_kernel" if bits == 4 else
+    on_rows_kernel = n_q_rows % 8 == 0 or bits == 4
+    score_name = ("rows_kernel" if on_rows_kernel else
+                  "score_i8_kernel" if (G == 1 and spec and args.vector_alu not in ("score", "both")) else "score_kernel")
+    attend_name = ("rows_kernel<attention>" if on_rows_kernel else
                    "attend_i8_kernel" if (G == 1 and spec and bits in (1, 2) and args.vector_alu not in ("attend", "both"))
-                   else "rows_kernel<attention>" if n_q_rows % 8 == 0 else "attend_partial_kernel")
+                   else "attend_partial_kernel")
     one_pass_name = ("attend_i8_kernel" if G == 1 else "rows_kernel") + "<scoring pass in front>"
     stream_peak = peaks["hbm_stream_peak_gbs"]
     link_peak = peaks["link_peak_gbs"]

@@ -454,24 +454,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
     A.Nq = Nq;
     A.sm_scale = sm_scale;
     const int n_ex = (slot_idx ? L.topk : 0) + (N - Nq) + (k_spec ? 1 : 0);
-    if (L.bits == 4) {
-        // 4-bit codes: a plain partial pass of their own, the merge kernel of the other widths
-        const int NR = L.G * n_rows;
-        if (phases & kAttendPartial) {
-            const AttendArgs4 a4{q, logits, logit_stride, slot, slot_idx, k_spec, v_spec, scratch.part_o, scratch.part_ml,
-                                 scratch.max_chunks, N, Nq, sm_scale};
-            hipError_t e = launch_attend4_partial(L, a4, n_rows, stream);
-            if (e != hipSuccess) return e;
-        }
-        if (phases & kAttendCombine) {
-            const int n_chunks = attend_chunks(NR, Nq, n_ex);
-            if (n_chunks > kCombineMaxChunks || n_chunks > scratch.max_chunks) return hipErrorInvalidValue;
-            SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, scratch.part_o, scratch.part_ml,
-                       scratch.max_chunks, n_chunks, NR, out, announce);
-        }
-        return hipGetLastError();
-    }
-    // 8 or 16 query rows per KV head: a partial pass of their own (rows_mfma.h), with its own chunking
+    // 8 or 16 query rows per KV head, and 4-bit codes: a partial pass of their own (rows_mfma.h), with its own chunking
     if (rows_uses_matrix_cores(L, n_rows)) {
         if (phases & kAttendPartial) {
             RowsArgs R{A, nullptr, 0, n_rows, 0};
@@ -480,7 +463,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
         }
         if (phases & kAttendCombine)
             SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * L.G * n_rows), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex), L.G * n_rows, out, announce);
+                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex, A.max_chunks), L.G * n_rows, out, announce);
         return hipGetLastError();
     }
     // one query head per KV head, two rows, 2-bit values: the partial pass with the value side on the

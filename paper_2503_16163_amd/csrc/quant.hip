@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
     constexpr int M = kD / G;        // value groups per token
     constexpr int NT = G / 8;        // tokens per thread
     constexpr int NW = 4 * BITS;     // K code dwords per token
-    constexpr int KL = 32 / BITS / 4;  // lanes that share one K code dword
+    constexpr int KL = 32 / BITS / 4;  // lanes that share one K code dword: 8, 4, 2
     constexpr int VL = G / 4;        // lanes of one value group
     constexpr int kExactUnroll = NT > 8 ? NT : 1;   // see the exact-division path of the keys
     __shared__ float kmn[8][kD];
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
             // channel 4j+b is code w' = 4 (j % KL) + b of dword j / KL: bit 8 b + BITS (j % KL)
             w <<= BITS * (j % KL);
             w |= dpp_u32<kDppXor1>(w);
-            w |= dpp_u32<kDppXor2>(w);
+            if constexpr (KL >= 4) w |= dpp_u32<kDppXor2>(w);
             if constexpr (KL == 8) w |= dpp_u32<kDppHalfMirror>(w);
             if (j % KL == 0) kd[j / KL][(i * 4 + wave) * 2 + hf] = w;
         }
@@ -226,6 +226,10 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
             byte <<= 4 * (j % 2);
             byte |= dpp_u32<kDppXor1>(byte);
             if (j % 2 == 0) vb[j / 2][e] = (uint8_t)byte;
+        } else if constexpr (BITS == 4) {
+            // a byte holds 2 channels: the lane's 4 are two bytes
+            vb[2 * j][e] = (uint8_t)byte;
+            vb[2 * j + 1][e] = (uint8_t)(byte >> 8);
         } else {
             vb[j][e] = (uint8_t)byte;
         }
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
     __syncthreads();
 
     // ---- 16-byte pieces of the device layout ----
-    constexpr int kPieces = G * BITS;  // per operand; <= 256
+    constexpr int kPieces = G * BITS;  // per operand
     auto k_piece = [&](int id) {
         // K: [32-token sub-block][dword W][half of the lane's 8 tokens][quad lane]
         const int kl = id % 4, h2 = (id / 4) % 2, W = (id / 8) % NW, sb = id / (8 * NW);
@@ -252,9 +256,12 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
         if (tid < kPieces) k_piece(tid);
         else if (tid >= 128 && tid < 128 + kPieces) v_piece(tid - 128);
     } else {
-        static_assert(kPieces == kFlushThreads, "one K piece and one V piece per thread");
-        k_piece(tid);
-        v_piece(tid);
+        static_assert(kPieces % kFlushThreads == 0, "whole passes over the pieces");
+#pragma unroll
+        for (int id = tid; id < kPieces; id += kFlushThreads) {
+            k_piece(id);
+            v_piece(id);
+        }
     }
 }
 
@@ -348,13 +355,15 @@ hipError_t export_dispatch(const LayerView& L, int Nq, uint8_t* k_codes, uint16_
 hipError_t launch_flush(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0, int Nq0,
                         int n_flush, hipStream_t stream) {
     if (n_flush <= 0) return hipSuccess;
-    if (L.bits == 4) return launch_flush4(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 2 && L.group == 32) return flush_dispatch<2, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 2 && L.group == 64) return flush_dispatch<2, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 1 && L.group == 32) return flush_dispatch<1, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 2 && L.group == 128) return flush_dispatch<2, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 1 && L.group == 128) return flush_dispatch<1, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     if (L.bits == 1 && L.group == 64) return flush_dispatch<1, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
+    if (L.bits == 4 && L.group == 32) return flush_dispatch<4, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
+    if (L.bits == 4 && L.group == 64) return flush_dispatch<4, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
+    if (L.bits == 4 && L.group == 128) return flush_dispatch<4, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
     return hipErrorInvalidValue;
 }
 
@@ -370,13 +379,15 @@ hipError_t launch_append_copy(const LayerView& L, const void* k_new, const void*
 hipError_t launch_export(const LayerView& L, int Nq, uint8_t* k_codes, uint16_t* k_mnmx, float* k_sz,
                          uint8_t* v_codes, uint16_t* v_mnmx, float* v_sz, hipStream_t stream) {
     if (Nq <= 0) return hipSuccess;
-    if (L.bits == 4) return launch_export4(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 2 && L.group == 32) return export_dispatch<2, 32>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 2 && L.group == 64) return export_dispatch<2, 64>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 1 && L.group == 32) return export_dispatch<1, 32>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 2 && L.group == 128) return export_dispatch<2, 128>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 1 && L.group == 128) return export_dispatch<1, 128>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     if (L.bits == 1 && L.group == 64) return export_dispatch<1, 64>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
+    if (L.bits == 4 && L.group == 32) return export_dispatch<4, 32>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
+    if (L.bits == 4 && L.group == 64) return export_dispatch<4, 64>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
+    if (L.bits == 4 && L.group == 128) return export_dispatch<4, 128>(L, Nq, k_codes, k_mnmx, k_sz, v_codes, v_mnmx, v_sz, stream);
     return hipErrorInvalidValue;
 }
 

@@ -19,7 +19,7 @@ struct AttendArgs {
     float sm_scale;
 };
 
-// rows_kernel (rows_mfma.h): scoring and attention of 4, 8 or 16 query rows per KV head
+// rows_kernel (rows_mfma.h): scoring and attention of 8 or 16 query rows per KV head, and of up to 16 on 4-bit codes
 enum { kRowsBoth = 0, kRowsScore = 1, kRowsAttend = 2 };
 struct RowsArgs {
     AttendArgs at;       // n_main, n_chunks: filled in by launch_rows
@@ -31,8 +31,10 @@ struct RowsArgs {
 constexpr int kRowsMaxChunk = 16384;   // tokens of a workgroup's chunk, at most (its bitmap of staged positions)
 
 bool rows_uses_matrix_cores(const LayerView& L, int n_rows);
+bool rows_in_one_launch(const LayerView& L, int n_rows);                       // scoring and attention together (kRowsBoth)
 int rows_max_main_chunks(int rows, int max_seq);                               // most chunks of quantised positions per row
-int rows_chunks(const LayerView& L, int n_rows, int Nq, int n_16bit);          // chunks launch_rows splits a row into
+// chunks launch_rows splits a row into: at most max_chunks, where chunks of kRowsMaxChunk tokens allow that
+int rows_chunks(const LayerView& L, int n_rows, int Nq, int n_16bit, int max_chunks);
 hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, hipStream_t stream);
 
 }  // namespace specache

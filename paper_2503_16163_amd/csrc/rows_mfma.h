@@ -1,4 +1,4 @@
-// Scoring and mixed attention for several query rows per KV head (grouped-query attention: 4, 8 or 16 rows)
+// Scoring and mixed attention for several query rows per KV head (grouped-query attention: 8 or 16 rows; 1 to 16 on 4-bit codes)
 // on the f16 matrix cores: the low-bit scoring of Appendix A "Decoding" (A = Q K^T on C'), the mixed attention of
 // Eq. 1, or both in one pass over the packed cache (the logits then never leave the chip).
 //
@@ -29,7 +29,9 @@
 // Measured alone on MI355X (scoring + attention as two launches of the earlier kernels -> as one launch): 32 KV rows x 32768
 // tokens, 8 query rows, 2 bits, g = 64: 27.5 + 37.9 -> 37.7 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 45.0 us;
 // 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.4 us; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 16.5 us (the earlier
-// kernels' 16-bit chunk was a chain of 40 us there).  168 registers, three workgroups per compute unit; held to four it
+// kernels' 16-bit chunk was a chain of 40 us there).  4-bit codes, two launches: 32 x 16384, 2 query rows as 8 columns'
+// worth, g = 32: a decode step of a layer 70.7 -> 52.8 us against vector-ALU kernels (scoring 13.0, attention 15.4 us
+// alone, 20.6 beside the gathers; the 84 MB they read need 14 us at the rate of a plain read).  168 registers, three workgroups per compute unit; held to four it
 // spills.
 #pragma once
 #include "attend_common.h"
@@ -87,7 +89,7 @@ __device__ __forceinline__ uint4v key_operand(uint32_t w, int kc) {
             default: return uint4v{w & 0x00400040u, (w >> 8) & 0x00400040u, w & 0x00800080u, (w >> 8) & 0x00800080u};
         }
     } else {
-        return uint4v{(w << 4) & 0x00F000F0u, (w >> 4) & 0x00F000F0u, w & 0x00F000F0u, (w >> 8) & 0x00F000F0u};
+        return uint4v{(w << 6) & 0x03C003C0u, (w >> 2) & 0x03C003C0u, (w << 2) & 0x03C003C0u, (w >> 6) & 0x03C003C0u};
     }
 }
 // the fields arrive at different bits: the multiplier of channel c carries the factor that makes every product
@@ -98,20 +100,20 @@ __device__ __forceinline__ float key_factor(int c) {
     if constexpr (BITS == 1) return (c >> 2) & 1 ? ((c >> 3) & 1 ? 4.0f : 1.0f) : ((c >> 3) & 1 ? 8.0f : 2.0f);
     return 1.0f;
 }
-constexpr int key_pos(int bits) { return bits == 2 ? 8 : bits == 1 ? 9 : 4; }
+constexpr int key_pos(int bits) { return bits == 2 ? 8 : bits == 1 ? 9 : 6; }
 constexpr int key_q_bits(int bits) { return bits == 2 ? 5 : bits == 1 ? 4 : 7; }   // |q'| < 2^this: q' factor s' < 2^15 with s' < 2^8
 
 // Value codes.  Byte t of a 16-byte piece is a token, its fields are channels.  A channel tile (mb, jj) is 16 channels of
 // the 32-channel block mb, so that it lies in one value group whatever g is: A row i is channel value_channel(mb, jj, i).
 // Even tokens of a dword sit in the low byte of its halves, odd ones in the high byte; a lane's shift brings the two
-// fields its row may want to bits 6 to 9 (8 and 9 with 1-bit codes, 4 to 7 with 4-bit codes).
+// fields its row may want to bits 6 to 9 (8 and 9 with 1-bit codes).
 template <int BITS>
 __device__ __forceinline__ int value_lane(int mb, int ic) { return BITS == 2 ? 8 * mb + (ic & 7) : BITS == 1 ? 4 * mb + (ic & 3) : 16 * mb + ic; }
 template <int BITS>
 __device__ __forceinline__ int value_channel(int mb, int jj, int i) {
     return BITS == 2 ? 4 * (8 * mb + (i & 7)) + 2 * (i >> 3) + jj : BITS == 1 ? 8 * (4 * mb + (i & 3)) + 2 * (i >> 2) + jj : 2 * (16 * mb + i) + jj;
 }
-constexpr int value_pos(int bits, int jj) { return bits == 2 ? (jj ? 8 : 6) : bits == 1 ? 8 + jj : 4; }
+constexpr int value_pos(int bits, int jj) { return bits == 2 ? (jj ? 8 : 6) : bits == 1 ? 8 + jj : 6; }
 struct ValueShift { uint32_t left, right; };   // of the lane's A row (2- and 1-bit codes)
 template <int BITS>
 __device__ __forceinline__ ValueShift value_shift(int ic) {
@@ -122,8 +124,8 @@ __device__ __forceinline__ ValueShift value_shift(int ic) {
 template <int BITS>
 __device__ __forceinline__ void value_operands(uint2 w, ValueShift sh, uint4v a[2]) {
     if constexpr (BITS == 4) {
-        a[0] = uint4v{(w.x << 4) & 0x00F000F0u, (w.x >> 4) & 0x00F000F0u, (w.y << 4) & 0x00F000F0u, (w.y >> 4) & 0x00F000F0u};
-        a[1] = uint4v{w.x & 0x00F000F0u, (w.x >> 8) & 0x00F000F0u, w.y & 0x00F000F0u, (w.y >> 8) & 0x00F000F0u};
+        a[0] = uint4v{(w.x << 6) & 0x03C003C0u, (w.x >> 2) & 0x03C003C0u, (w.y << 6) & 0x03C003C0u, (w.y >> 2) & 0x03C003C0u};
+        a[1] = uint4v{(w.x << 2) & 0x03C003C0u, (w.x >> 6) & 0x03C003C0u, (w.y << 2) & 0x03C003C0u, (w.y >> 6) & 0x03C003C0u};
     } else {
         constexpr uint32_t m0 = BITS == 2 ? 0x00C000C0u : 0x01000100u, m1 = BITS == 2 ? 0x03000300u : 0x02000200u;
         const uint32_t e0 = w.x << sh.left, o0 = w.x >> sh.right, e1 = w.y << sh.left, o1 = w.y >> sh.right;
@@ -309,6 +311,10 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     const AttendArgs& A = R.at;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
+    // 4-bit codes bring 1, 2 and 4 rows too: the columns of rows that do not exist carry zero queries and nothing of them
+    // is written
+    constexpr bool kPadded = BITS == 4 && NR == 8;
+    const int nq = kPadded ? L.G * R.n_rows : NR;
 
     // ---- which (row, chunk): workgroups that append the step's token first, then the 16-bit chunks, then the rest
     const int n_tail = L.tail_k ? L.rows : 0;
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     uint16_t* qraw = reinterpret_cast<uint16_t*>(smem + NR * S::kQStride * 4);      // [NR][kZStride]
     float* q_unscale = reinterpret_cast<float*>(smem + NR * S::kQStride * 4 + NR * S::kZStride * 2);   // [NR]
     for (int rr = wave; rr < NR; rr += kWaves) {
-        const uint32_t w = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + rr) * kD)[lane];
+        const uint32_t w = rr < nq ? reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * nq + rr) * kD)[lane] : 0u;
         reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
         if constexpr (MODE != kRowsAttend) {
             const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
@@ -481,7 +487,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         for (int u = 0; u < R.wave_units; ++u) {
             const int t0 = w0 + u * UNIT;
             if (t0 >= A.Nq) break;                                                    // uniform over the wave
-            const bool active = t0 / kBlockTokens + s < n_sub;
+            const bool active = t0 / kBlockTokens + s < n_sub && (!kPadded || r < nq);
             float l[8];
             if constexpr (MODE != kRowsAttend) {
                 // ---- multipliers of the unit's token groups (a group longer than a unit is worked out once)
@@ -596,8 +602,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 for (int t = 0; t < 8; ++t) l[t] = __builtin_fmaf(o[t], unscale, qz);
                 // ---- selection keys: the largest logit of the heads' last rows
                 {
-                    const int G = NR / R.n_rows;
-                    if (r % R.n_rows == R.n_rows - 1) {
+                    const int G = nq / R.n_rows;
+                    if (r % R.n_rows == R.n_rows - 1 && (!kPadded || r < nq)) {
                         float4* d = reinterpret_cast<float4*>(l_tab + (r / R.n_rows) * S::kKeyStride + 32 * s + 8 * kq);
                         d[0] = make_float4(l[0], l[1], l[2], l[3]);
                         d[1] = make_float4(l[4], l[5], l[6], l[7]);
@@ -618,14 +624,14 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                     wave_sync();
                 }
                 if (A.logits_out && active) {
-                    float4* d = reinterpret_cast<float4*>(A.logits_out + ((size_t)row * NR + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    float4* d = reinterpret_cast<float4*>(A.logits_out + ((size_t)row * nq + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
                     d[0] = make_float4(l[0], l[1], l[2], l[3]);
                     d[1] = make_float4(l[4], l[5], l[6], l[7]);
                 }
             } else {
                 float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
                 if (active) {
-                    const float4* d = reinterpret_cast<const float4*>(A.logits + ((size_t)row * NR + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    const float4* d = reinterpret_cast<const float4*>(A.logits + ((size_t)row * nq + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
                     a = d[0];
                     b = d[1];
                 }
@@ -781,9 +787,9 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         out.w[w][col] = mv == -INFINITY ? 0.0f : exp2_of((mv - mx) * kLog2e);
     }
     __syncthreads();
-    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
-    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2;
-    for (int e = tid; e < NR * kD; e += kThreads) {
+    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * nq) * kD;
+    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * nq) * 2;
+    for (int e = tid; e < nq * kD; e += kThreads) {
         const int rr = e / kD, c = e % kD;
         float v = 0.0f;
 #pragma unroll
@@ -795,7 +801,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
             }
         po[e] = v;
     }
-    if (tid < NR) {
+    if (tid < nq) {
         float mx = -INFINITY, sum = 0.0f;
         for (int w = 0; w < kWaves; ++w)
 #pragma unroll

@@ -485,6 +485,8 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
     if (rows_max_main_chunks(rows, (int)cap) > max_main) max_main = rows_max_main_chunks(rows, (int)cap);
     const int ec = attend_extra_chunk_tokens();
     ctx->scratch.max_chunks = max_main + (c.topk + c.residual + 1 + ec - 1) / ec;
+    // no more than the merge kernel takes: with that many candidates rows_kernel splits a row less finely
+    if (ctx->scratch.max_chunks > attend_max_chunks()) ctx->scratch.max_chunks = attend_max_chunks();
     SPC_ALLOC(hipMalloc((void**)&ctx->scratch.part_o, (size_t)rows * ctx->scratch.max_chunks * G * 2 * kD * 4));
     SPC_ALLOC(hipMalloc((void**)&ctx->scratch.part_ml, (size_t)rows * ctx->scratch.max_chunks * G * 2 * 2 * 4));
     ctx->topk_scratch.max_parts = topk_parts((int)cap, c.topk);
@@ -674,8 +676,7 @@ int specache_append_score(specache_ctx* ctx, int32_t layer, const void* k_new, c
     if (specache_plan_append(ctx->cfg.residual, ctx->cfg.group, L.N, L.Nq, 1, &n_flush) != SPECACHE_OK)
         return fail(ctx, SPECACHE_ESTATE, "inconsistent token counts");
     // a group leaves the residual with this token, or nothing is quantised yet (no scoring launch): two steps
-    // (the 4-bit scoring kernel carries no append)
-    if (n_flush > 0 || L.Nq == 0 || ctx->cfg.bits == 4) {
+    if (n_flush > 0 || L.Nq == 0) {
         if (int rc = specache_quantize_append(ctx, layer, k_new, v_new, 1, stream)) return rc;
         return score_impl(ctx, layer, q, n_rows, stream, nullptr, nullptr);
     }
@@ -773,7 +774,10 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
     Layer& L = ctx->layers[layer];
     if (ctx->scored_layer != layer || ctx->scored_rows != n_rows || ctx->scored_N != L.N || ctx->scored_Nq != L.Nq)
         return fail(ctx, SPECACHE_ESTATE, "attend must follow score_topk of the same layer, n_rows and cache state");
-    if (!ctx->logits_kept) return fail(ctx, SPECACHE_ESTATE, "the last scoring pass of this layer was specache_score_attend, which keeps no logits");
+    // several query heads per KV head: the one-launch scoring and attention keeps no logits, an attend behind it scores again
+    const bool rescore = !ctx->logits_kept && rows_uses_matrix_cores(L.view, n_rows) && L.Nq > 0;
+    if (!ctx->logits_kept && !rescore)
+        return fail(ctx, SPECACHE_ESTATE, "the last scoring pass of this layer was specache_score_attend, which keeps no logits");
     if (slot >= 0 && !L.slot_filled[slot]) return fail(ctx, SPECACHE_ESTATE, "slot was never gathered");
     if (L.N == 0 && !k_spec) return fail(ctx, SPECACHE_ESTATE, "no attention candidate");
     AttendScratch scratch = ctx->scratch;
@@ -782,12 +786,16 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
         const int NR = L.view.G * n_rows;
         const int n_16bit = (slot >= 0 ? ctx->cfg.topk : 0) + (L.N - L.Nq) + (k_spec ? 1 : 0);
         int chunks = attend_chunks(NR, L.Nq, n_16bit);
-        if (rows_uses_matrix_cores(L.view, n_rows) && rows_chunks(L.view, n_rows, L.Nq, n_16bit) > chunks)
-            chunks = rows_chunks(L.view, n_rows, L.Nq, n_16bit);
-        const size_t o_floats = (size_t)L.view.rows * chunks * NR * kD, ml_floats = (size_t)L.view.rows * chunks * NR * 2;
-        if ((o_floats + ml_floats) * sizeof(float) > kStaticScratchBytes)
+        const size_t chunk_floats = (size_t)L.view.rows * NR * (kD + 2);
+        if (chunks * chunk_floats * sizeof(float) > kStaticScratchBytes)
             return fail(ctx, SPECACHE_ECAPACITY, "specache_attend_static: the partial results of this call (rows x chunks x query rows "
                                                  "x 130 floats) exceed the 16 MiB static scratch array; use specache_attend");
+        if (rows_uses_matrix_cores(L.view, n_rows)) {
+            // that kernel splits a row as finely as the array and the merge kernel have room for
+            const int room = (int)(kStaticScratchBytes / (chunk_floats * sizeof(float)));
+            chunks = rows_chunks(L.view, n_rows, L.Nq, n_16bit, room < attend_max_chunks() ? room : attend_max_chunks());
+        }
+        const size_t o_floats = (size_t)L.view.rows * chunks * NR * kD;
         scratch.part_o = static_scratch->part_o;
         scratch.part_ml = static_scratch->part_o + o_floats;
         scratch.max_chunks = chunks;
@@ -795,6 +803,11 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
     hipStream_t st = (hipStream_t)stream;
     if (slot >= 0 && L.gather_stream[slot] != st && !(L.gathered_waited_set[slot] && L.gathered_waited[slot] == st))
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
+    if (rescore) {
+        // (into ctx->keys: a selection on another stream may be reading the layer's own)
+        SPC_HIP(ctx, launch_score(L.view, q, n_rows, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride, ctx->keys, ctx->logit_stride, st));
+        ctx->logits_kept = true;
+    }
     for (int phase : {kAttendPartial, kAttendCombine}) {
         TimedLaunch t(ctx, st, phase == kAttendPartial ? SPECACHE_K_ATTEND : SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
@@ -824,7 +837,7 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
         if (specache_plan_append(ctx->cfg.residual, ctx->cfg.group, L.N, L.Nq, 1, &n_flush) != SPECACHE_OK)
             return fail(ctx, SPECACHE_ESTATE, "inconsistent token counts");
     }
-    const bool rows_pass = (n_rows == 1 || n_rows == 2) && rows_uses_matrix_cores(L.view, n_rows) &&
+    const bool rows_pass = (n_rows == 1 || n_rows == 2) && rows_in_one_launch(L.view, n_rows) &&
                            ctx->cfg.select_form == SPECACHE_SELECT_MAX_LOGIT;
     const bool one_pass = (rows_pass || (L.view.G == 1 && n_rows == 2 && attend_uses_int8_matrix_cores(L.view, n_rows) &&
                                          !(kernel_choice() & (kChoiceScoreValu | kChoiceAttendValu)))) &&

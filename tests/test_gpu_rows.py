@@ -60,3 +60,48 @@ def test_rows_kernel_with_several_units_per_wave(S):
     finally:
         c.close()
         binding.debug_kernel_choice(0)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,dtype,g,R,k,n_rows", [
+    (1, 2, 2, 100, synth.FP16, 32, 64, 16, 1),      # one row per KV head, 64 quantised positions: one unit
+    (2, 3, 3, 1500, synth.FP16, 32, 128, 300, 2),   # two rows, three chunks of 16-bit pairs
+    (1, 4, 2, 90, synth.BF16, 32, 64, 40, 2),       # four rows, half a unit
+    (1, 4, 1, 1300, synth.BF16, 64, 64, 48, 1),     # four rows, one of each head
+    (2, 8, 2, 2100, synth.FP16, 128, 128, 64, 2),   # eight rows, a token group is two units
+    (1, 16, 2, 1300, synth.BF16, 32, 96, 40, 2),    # sixteen rows
+    (1, 8, 1, 900, synth.FP16, 128, 256, 40, 2),
+])
+@pytest.mark.parametrize("calls", ["split", "fused append"])
+def test_rows_kernel_on_four_bit_codes(B, Hq, Hkv, S, dtype, g, R, k, n_rows, calls):
+    """4-bit codes take the kernel with any number of rows: with fewer than 8 some of its columns have no row."""
+    from tests.harness import Case
+    c = Case(B, Hq, Hkv, S, dtype, 4, g, k, R=R, seed=5300 + Hq + g + S, n_rows=n_rows, async_select=2, fused_append=calls != "split")
+    try:
+        c.load()
+        c.check_quantized()
+        c.decode_step(use_spec=n_rows == 2)
+        for t in range(36):
+            c.append_token(t)
+            c.decode_step(use_spec=n_rows == 2, check_logits=(t % 6 == 0))
+        c.check_quantized()
+        print(c.stats)
+        assert c.stats["max_logit_err"] < LOGITS and c.stats["max_out_err"] < OUTPUTS
+    finally:
+        c.close()
+
+
+def test_attend_after_the_one_launch_call():
+    """The one launch of grouped-query heads leaves no logits; an attend of the same cache state behind it still works
+    (it scores again) and gives the same output up to the rounding of other partial sums."""
+    import torch
+    from tests.harness import Case, to_dev
+    c = Case(1, 8, 2, 1700, synth.BF16, 2, 64, 48, seed=5400, async_select=2, one_pass=True)
+    try:
+        c.load()
+        _, out = c.decode_step(use_spec=False, check_logits=False, do_gather=False)
+        again = torch.empty((1, 8, 2, 128), dtype=torch.float32, device="cuda")
+        c.sc.attend(0, to_dev(c.last_q_bits, c.dtype), 2, None, None, -1, again, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert abs(again.cpu().numpy() - out).max() <= OUTPUTS * abs(out).max()
+    finally:
+        c.close()
