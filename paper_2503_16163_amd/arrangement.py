@@ -26,12 +26,12 @@ The rule compares two times that follow from the shape:
                            tokens, k = 384: 118 us per layer against 147 to 169).
 
 One query head per KV head without the one-launch kernel (4-bit codes, selection on the mixed cache):
-the same ladder with score + select_gather + attend in place of the one-launch call.  4 or 8 query heads per KV
-head: main_us is 14 us + 40 (8 heads: 55) us per million pairs; below 0.9 of it the one-launch call on two side streams
+the same ladder with score + select_gather + attend in place of the one-launch call.  2 to 8 query heads per
+KV head: main_us is 14 us + 40 (8 heads: 55) us per million pairs; below 0.9 of it the one-launch call on two side streams
 (131k tokens, k = 256: 60.6 us per layer against 70 as two launches), else score + select_gather + attend with ArgTopK on
 the gather's stream and two side streams (131k tokens, k = 1024: 86.7 against 94 to 109 for one-launch variants; batch
-of 4 at 32k, k = 512: 149 to 155, the link).  2 query heads per KV head: always the latter.  One layer, or the
-non-speculative variant: everything on the caller's stream.
+of 4 at 32k, k = 512: 149 to 155, the link).  One layer, or the non-speculative variant: everything on the caller's
+stream.
 
 Evidence, us per layer at 32 rows (rule's pick against the best of five arrangements tried), shapes that are
 not the benchmark's own: 8k tokens k = 32: 31.8 / 31.8; 8k k = 96: 33.5 / 33.5; 16k k = 192: 57.8 / 57.8;
@@ -50,7 +50,7 @@ def link_us(rows, k):
 
 def main_us(rows, S, G=1):
     if G > 1:
-        return max(33.0, 14.0 + (40.0 if G == 4 else 55.0) * rows * S / 1e6)
+        return max(33.0, 14.0 + (55.0 if G == 8 else 40.0) * rows * S / 1e6)
     return max(33.0, 22.0 + 19.8 * rows * S / 1e6)
 
 
@@ -62,7 +62,7 @@ def plan(B, Hkv, G, S, k, layers, bits=2, speculative=True, select_lowbit=True):
     if layers == 1 or not speculative:
         return dict(calls="four", async_select=SELECT_ON_CALLER, side_streams=1, carry_append=False)
     # the shapes specache_score_attend has a one-launch kernel for
-    one_pass = bits in (1, 2) and select_lowbit and G in (1, 4, 8)
+    one_pass = bits in (1, 2) and select_lowbit
     if link_us(rows, k) <= 0.9 * main_us(rows, S, G):
         return dict(calls="one-pass" if one_pass else "split", async_select=SELECT_ON_GATHER_STREAM, side_streams=2,
                     carry_append=one_pass)

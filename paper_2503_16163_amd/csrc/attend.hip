@@ -15,7 +15,7 @@
 // Values are quantised per token over g channels, so for the main chunks
 //   sum_i p_i V'[i][c] = sum_i (p_i s[i][m]) code[i][c] + sum_i p_i z[i][m],  m = c / g.
 // The first sum runs on the vector ALUs: a lane owns 8/BITS channels and reads 16 tokens of them as one 16-byte load;
-// p_i s[i][m] comes from LDS (computed once per token by the softmax phase).  With 8 or 16 query rows per KV head the
+// p_i s[i][m] comes from LDS (computed once per token by the softmax phase).  With 4, 8 or 16 query rows per KV head the
 // matrix cores take the contraction (rows_mfma.h).
 #include "attend_common.h"
 
@@ -418,7 +418,7 @@ hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, floa
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
         return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, announce, stream); \
     }
-    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1)
+    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1)
 #undef SPC_CASE
     return hipErrorInvalidValue;
 }
@@ -454,7 +454,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
     A.Nq = Nq;
     A.sm_scale = sm_scale;
     const int n_ex = (slot_idx ? L.topk : 0) + (N - Nq) + (k_spec ? 1 : 0);
-    // 8 or 16 query rows per KV head, and 4-bit codes: a partial pass of their own (rows_mfma.h), with its own chunking
+    // 4, 8 or 16 query rows per KV head, and 4-bit codes: a partial pass of their own (rows_mfma.h), with its own chunking
     if (rows_uses_matrix_cores(L, n_rows)) {
         if (phases & kAttendPartial) {
             RowsArgs R{A, nullptr, 0, n_rows, 0};

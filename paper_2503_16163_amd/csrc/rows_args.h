@@ -19,7 +19,7 @@ struct AttendArgs {
     float sm_scale;
 };
 
-// rows_kernel (rows_mfma.h): scoring and attention of 8 or 16 query rows per KV head, and of up to 16 on 4-bit codes
+// rows_kernel (rows_mfma.h): scoring and attention of 4, 8 or 16 query rows per KV head, and of any number on 4-bit codes
 enum { kRowsBoth = 0, kRowsScore = 1, kRowsAttend = 2 };
 struct RowsArgs {
     AttendArgs at;       // n_main, n_chunks: filled in by launch_rows

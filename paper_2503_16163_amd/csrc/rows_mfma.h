@@ -1,4 +1,4 @@
-// Scoring and mixed attention for several query rows per KV head (grouped-query attention: 8 or 16 rows; 1 to 16 on 4-bit codes)
+// Scoring and mixed attention for several query rows per KV head (grouped-query attention: 4, 8 or 16 rows; 1 to 16 on 4-bit codes)
 // on the f16 matrix cores: the low-bit scoring of Appendix A "Decoding" (A = Q K^T on C'), the mixed attention of
 // Eq. 1, or both in one pass over the packed cache (the logits then never leave the chip).
 //
@@ -301,7 +301,7 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
         *reinterpret_cast<float2*>(o_lds + ((size_t)wave * 16 + rr) * kRowsOStride + 2 * lane) = make_float2(o[rr][0], o[rr][1]);
 }
 
-template <int BITS, int GROUP, int NR, bool BF16, int MODE>
+template <int BITS, int GROUP, int NR, bool PADDED, bool BF16, int MODE>
 __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs R) {
     using S = RowsShape<BITS, GROUP, NR>;
     constexpr int SUBS = S::SUBS, UNIT = S::UNIT, SG = S::SG, M = S::M;
@@ -311,10 +311,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     const AttendArgs& A = R.at;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
-    // 4-bit codes bring 1, 2 and 4 rows too: the columns of rows that do not exist carry zero queries and nothing of them
-    // is written
-    constexpr bool kPadded = BITS == 4 && NR == 8;
-    const int nq = kPadded ? L.G * R.n_rows : NR;
+    // fewer than 8 rows: the columns of rows that do not exist carry zero queries and nothing of them is written
+    const int nq = PADDED ? L.G * R.n_rows : NR;
 
     // ---- which (row, chunk): workgroups that append the step's token first, then the 16-bit chunks, then the rest
     const int n_tail = L.tail_k ? L.rows : 0;
@@ -487,7 +485,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         for (int u = 0; u < R.wave_units; ++u) {
             const int t0 = w0 + u * UNIT;
             if (t0 >= A.Nq) break;                                                    // uniform over the wave
-            const bool active = t0 / kBlockTokens + s < n_sub && (!kPadded || r < nq);
+            const bool active = t0 / kBlockTokens + s < n_sub && (!PADDED || r < nq);
             float l[8];
             if constexpr (MODE != kRowsAttend) {
                 // ---- multipliers of the unit's token groups (a group longer than a unit is worked out once)
@@ -603,7 +601,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 // ---- selection keys: the largest logit of the heads' last rows
                 {
                     const int G = nq / R.n_rows;
-                    if (r % R.n_rows == R.n_rows - 1 && (!kPadded || r < nq)) {
+                    if (r % R.n_rows == R.n_rows - 1 && (!PADDED || r < nq)) {
                         float4* d = reinterpret_cast<float4*>(l_tab + (r / R.n_rows) * S::kKeyStride + 32 * s + 8 * kq);
                         d[0] = make_float4(l[0], l[1], l[2], l[3]);
                         d[1] = make_float4(l[4], l[5], l[6], l[7]);
@@ -818,14 +816,16 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
 template <int BITS, int MODE>
 hipError_t launch_rows_mode(const LayerView& L, const RowsArgs& R, int NR, hipStream_t stream) {
     const dim3 grid(R.at.n_chunks * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
-#define SPC_ROWS(G_, N_)                                                                            \
-    if (L.group == G_ && NR == N_) {                                                                \
-        if (L.bf16) SPC_LAUNCH((rows_kernel<BITS, G_, N_, true, MODE>), grid, block, stream, L, R); \
-        else SPC_LAUNCH((rows_kernel<BITS, G_, N_, false, MODE>), grid, block, stream, L, R);       \
-        return hipGetLastError();                                                                   \
+    const bool padded = L.G * R.n_rows < NR;
+#define SPC_ROWS(G_, N_, P_)                                                                            \
+    if (L.group == G_ && NR == N_ && padded == P_) {                                                    \
+        if (L.bf16) SPC_LAUNCH((rows_kernel<BITS, G_, N_, P_, true, MODE>), grid, block, stream, L, R); \
+        else SPC_LAUNCH((rows_kernel<BITS, G_, N_, P_, false, MODE>), grid, block, stream, L, R);       \
+        return hipGetLastError();                                                                       \
     }
-    SPC_ROWS(32, 8) SPC_ROWS(64, 8) SPC_ROWS(128, 8)
-    SPC_ROWS(32, 16) SPC_ROWS(64, 16) SPC_ROWS(128, 16)
+    SPC_ROWS(32, 8, false) SPC_ROWS(64, 8, false) SPC_ROWS(128, 8, false)
+    SPC_ROWS(32, 8, true) SPC_ROWS(64, 8, true) SPC_ROWS(128, 8, true)
+    SPC_ROWS(32, 16, false) SPC_ROWS(64, 16, false) SPC_ROWS(128, 16, false)
 #undef SPC_ROWS
     return hipErrorInvalidValue;
 }

@@ -15,7 +15,7 @@ namespace {
 // equal length the launch has no second, emptier round.
 constexpr int kRowsTarget = 768;
 
-// rows of the kernel's columns: 4-bit codes with fewer than 8 rows run as 8, of which some do not exist
+// rows of the kernel's columns: fewer than 8 run as 8, of which some do not exist
 int padded_rows(const LayerView& L, int n_rows) { return L.G * n_rows < 8 ? 8 : L.G * n_rows; }
 
 // units of 32 * 16 / NR tokens that each of a workgroup's four waves takes, and the chunks of a row
@@ -33,11 +33,14 @@ void rows_split(int rows, int NR, int Nq, int max_main, int& wave_units, int& n_
 }  // namespace
 
 bool rows_uses_matrix_cores(const LayerView& L, int n_rows) {
-    // Fewer rows leave columns empty.  1- and 2-bit codes have kernels made for them (two rows: scoring and attention in one
+    // Four rows leave half of the columns empty and are still faster than a conversion and four multiply-accumulates per code
+    // on the vector ALUs in two launches: a decode step of a layer, 16 x 16384, 2 bits 45.5 -> 27.7 us, 32 x 32768 85.3 -> 61.6,
+    // 8 x 131072, 1 bit 79.5 -> 53.7; one row of each of four heads, 8 x 32768, 62.7 -> 54.1.
+    // Fewer rows leave more of them empty.  1- and 2-bit codes have kernels made for them (two rows: scoring and attention in one
     // launch on the int8 matrix cores, 17.8 us for 32 x 16384 positions); with 4-bit codes the alternative was a conversion and
     // a multiply-accumulate per code on the vector ALUs: 45 + 54 us for 32 x 32768, two rows, against 13.0 + 15.4 for half of it.
     const int NR = L.G * n_rows;
-    return NR == 8 || NR == 16 || L.bits == 4;
+    return NR >= 4 || L.bits == 4;
 }
 
 // 4-bit codes keep two launches: a step's arrangement scores and attends in two calls there, and the one launch would not

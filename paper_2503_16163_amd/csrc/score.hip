@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
                                                                  size_t key_stride) {
     constexpr int NR = G * NROWS;              // query rows sharing this KV head
     constexpr int RH = NR;
-    static_assert(NR <= 4, "8 and 16 rows: rows_mfma.h");
+    static_assert(NR <= 2, "4, 8 and 16 rows: rows_mfma.h");
     constexpr int HPD = (32 / BITS) / 4;       // masks (= multiplier registers) per code dword
     constexpr int NW = 4 * BITS;               // code dwords per token
     constexpr int WPW = NW / kScoreWaves;      // code dwords per wave
@@ -132,8 +132,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
                     qz[r] = __builtin_fmaf(qv, z, qz[r]);
                 }
                 float* dst = mq + ((i * HPD + h) * 4 + k) * RH;
-                if constexpr (RH == 4) *reinterpret_cast<float4*>(dst) = make_float4(qs[0], qs[1], qs[2], qs[3]);
-                else if constexpr (RH == 2) *reinterpret_cast<float2*>(dst) = make_float2(qs[0], qs[1]);
+                if constexpr (RH == 2) *reinterpret_cast<float2*>(dst) = make_float2(qs[0], qs[1]);
                 else dst[0] = qs[0];
             }
         }
@@ -258,7 +257,7 @@ hipError_t launch2(const LayerView& L, const void* q, int n_rows, int Nq, float 
 #define SPC_CASE(g_, n_)                                                                                    \
     if (L.G == g_ && n_rows == n_)                                                                          \
         return launch3<BITS, g_, n_>(L, q, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
-    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1) SPC_CASE(2, 2) SPC_CASE(4, 1)
+    SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1)
 #undef SPC_CASE
     return hipErrorInvalidValue;
 }

@@ -90,6 +90,35 @@ def test_rows_kernel_on_four_bit_codes(B, Hq, Hkv, S, dtype, g, R, k, n_rows, ca
         c.close()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,dtype,bits,g,R,k,n_rows", [
+    (1, 2, 1, 90, synth.FP16, 2, 32, 64, 16, 2),       # 32 quantised positions: half a unit, three empty waves
+    (1, 4, 2, 130, synth.BF16, 1, 32, 64, 300, 2),     # one unit and a half; more pairs asked for than there are
+    (1, 4, 2, 1700, synth.BF16, 2, 64, 64, 48, 2),     # a token group is a unit
+    (2, 6, 3, 2100, synth.FP16, 2, 128, 128, 300, 2),  # a token group is two units, three chunks of 16-bit pairs
+    (1, 4, 2, 1500, synth.FP16, 1, 128, 256, 40, 2),
+    (1, 8, 2, 1300, synth.BF16, 2, 32, 64, 40, 1),     # one row of each of four heads
+    (1, 4, 1, 1500, synth.FP16, 1, 64, 64, 130, 1),
+])
+@pytest.mark.parametrize("calls", ["one-pass", "carry", "split"])
+def test_rows_kernel_with_four_rows(B, Hq, Hkv, S, dtype, bits, g, R, k, n_rows, calls):
+    """Four rows of 1- and 2-bit codes run as eight, of which four do not exist."""
+    from tests.harness import Case
+    binding.debug_kernel_choice(binding.KEEP_ONE_PASS_LOGITS)
+    c = Case(B, Hq, Hkv, S, dtype, bits, g, k, R=R, seed=5500 + Hq + g + bits + S, n_rows=n_rows, async_select=2,
+             one_pass=calls != "split", fused_append=calls == "carry")
+    try:
+        c.load()
+        c.decode_step(use_spec=n_rows == 2)
+        for t in range(36):                  # across a flush
+            c.append_token(t)
+            c.decode_step(use_spec=n_rows == 2, check_logits=(t % 6 == 0))
+        print(c.stats)
+        assert c.stats["max_logit_err"] < LOGITS and c.stats["max_out_err"] < OUTPUTS
+    finally:
+        c.close()
+        binding.debug_kernel_choice(0)
+
+
 def test_attend_after_the_one_launch_call():
     """The one launch of grouped-query heads leaves no logits; an attend of the same cache state behind it still works
     (it scores again) and gives the same output up to the rounding of other partial sums."""
