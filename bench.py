@@ -618,7 +618,7 @@ def main():
         "scaling": "weak", "vs_baseline": None,
         "dtype": "f32",
         "dtype_note": "accumulation and outputs are binary32; the contractions run on the matrix cores with int8 operands (packed "
-                      "codes, fixed-point multipliers, exact int32 sums) or, with 8 and 16 query rows per KV head, f16 operands",
+                      "codes, fixed-point multipliers, exact int32 sums) or, with 4 or more query rows per KV head, f16 operands",
         "data": "synthetic" if not args.filler_mb else f"synthetic; EMULATED rest of the layer: {args.filler_mb} MB streamed per layer",
         "config": {"workload": DESCR[args.workload] + (f" [code width overridden: {bits} bits]" if args.bits else "") +
                                (f" [context overridden: S = {S}]" if args.seq else ""), "layers": layers, "tokens_cached": N, "tokens_quantized": Nq,
