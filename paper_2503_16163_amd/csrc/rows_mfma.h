@@ -4,20 +4,18 @@
 //
 // Both contractions have the packed codes as their A operand, read as f16 subnormals straight from the packed
 // bytes: a dword is two 16-bit halves of 2-bit (1-, 4-bit) fields, and a shift and a mask leave one field of either
-// half at bits 6 to 9, where a subnormal keeps its precision (the matrix cores do not normalise subnormal operands
-// before they align products: a field at bit 0 loses the low end of small products, 3e-5 of the sum, one at bit 6
-// does not, 2e-7).  0.75 vector instructions per 2-bit code.
+// half at bits 8 and 9 (4-bit codes: 6 to 9), as high as a subnormal goes (see rows_normal_operands).  0.94 vector
+// instructions per 2-bit code.
 //   scoring  logit[r][i] = sum_c code[i][c] (sm q[r][c] s[j][c]) + sm sum_c q[r][c] z[j][c],  j = i / g
-//            B = the multipliers of (row, token group) as hi + lo f16 (24 bits);
+//            B = the multipliers of (row, token group) as hi + lo f16: to 2^-23 of a multiplier down to 2^-3, to 2^-25 below;
 //   values   o[r][c] = sum_i code[i][c] (p[r][i] s[i][m]) + sum_i p[r][i] z[i][m],  m = c / g
-//            B = p s as hi + lo f16.
+//            B = p s as hi + lo f16, the scale factor of each value group following the scales of the unit's tokens.
 // Building the operands is what bounds these shapes (vector-instruction issue: at 8 rows, g = 64 about 380 vector
 // instructions per 32 tokens, a wave's vector ALU busy 9 cycles in 10), so no lane does it twice: the 16 columns are
 // (row r, sub-group s) with 16 / NR sub-groups of 32 tokens in flight.  For 8 rows the two lanes of a row then exchange
 // halves, so that the columns of a product are (r, hi | lo) and every column of it is used (the matrix cores are not
-// free: 17 clocks each, 10 of which no vector instruction of the SIMD fills); with 8 rows and two token groups per unit
-// the scoring keeps (r, s) columns, drops the other sub-group's and runs hi and lo as two products; with 16 rows the
-// columns are the rows.
+// free: 17 clocks each, 10 of which no vector instruction of the SIMD fills), and hi and lo add up in sums of their own;
+// with 16 rows the columns are the rows.
 // A lane (column (r, s), quarter kq) ends the scoring with the logits of row r for 8 consecutive tokens, which is the
 // order in which the value side wants its B operand: no logit is exchanged between lanes.
 //
@@ -44,6 +42,11 @@ typedef __bf16 bfloat8 __attribute__((ext_vector_type(8)));
 
 constexpr int kRowsOStride = kD + 4;           // floats between the columns of a wave's merged outputs
 constexpr float kLazyMax = 4.0f;               // a column's maximum moves when a logit exceeds it by more than this
+// The f16 operands are hi + lo (23 bits of a product's multiplier as long as hi is at least 2^-3, an absolute 2^-25 below
+// that), so the scales that go into them are kept near the top of the range: times a power of two, 2^3 to 2^9 for the value
+// scales (p < 2^6), 2^4 to 2^8 for the key scales (|q'| < 2^7), moved where a unit's largest one leaves these bounds.
+constexpr float kValueScaleMost = 512.0f, kValueScaleLeast = 8.0f, kKeyScaleMost = 256.0f, kKeyScaleLeast = 16.0f;
+constexpr int kScaleSet = 7;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 // lane exchange across the 16-lane rows of a wave: result pairs of lanes 16 (32) apart
@@ -63,9 +66,37 @@ __device__ __forceinline__ float xor32_sum(float v) {
     const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
-__device__ __forceinline__ uint32_t ror8(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppRowRor8, 0xf, 0xf, true); }
+// hi halves of the lanes of sub-group 0 beside lo halves of sub-group 1's lanes, or the other way round: with the two lanes of a
+// row (8 apart) holding (hi, lo) of sub-groups 0 and 1, columns (r, hi | lo) of sub-group 0 and of sub-group 1
+__device__ __forceinline__ void hi_lo_columns(const uint4v& hi, const uint4v& lo, uint4v& sub0, uint4v& sub1) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        sub0[d] = (uint32_t)__builtin_amdgcn_update_dpp((int)hi[d], (int)lo[d], kDppRowRor8, 0xf, 0xc, false);
+        sub1[d] = (uint32_t)__builtin_amdgcn_update_dpp((int)lo[d], (int)hi[d], kDppRowRor8, 0xf, 0x3, false);
+    }
+}
+// largest value of a wave; floats that are not negative order as their bits do
+__device__ __forceinline__ uint32_t wave_max_bits(uint32_t v) {
+    auto step = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor1, 0xf, 0xf, true));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor2, 0xf, 0xf, true));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppHalfMirror, 0xf, 0xf, true));
+    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppMirror, 0xf, 0xf, true));
+    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    return step(step(a, b), step(c, d));
+}
+__device__ __forceinline__ float times_pow2(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 __device__ __forceinline__ float quarters_max(float v) { return xor32_max(xor16_max(v)); }
 __device__ __forceinline__ float quarters_sum(float v) { return xor32_sum(xor16_sum(v)); }
+
+// Codes as normal numbers instead of subnormals, at half a vector instruction more per code.  The matrix cores align products
+// by their operands' exponents, so that a subnormal code gives up the low end of the other products of a step by as many bits as
+// it has leading zeros.  Outputs' distance from 64 bits (rms; value scales even | 4096 apart from token to token), in units of
+// 1e-7: 4-bit codes at bits 6 to 9 9.8 | 17, normal 6.4 | 7.9, in binary32 on the vector ALUs 6.9 | 7.6; 2-bit codes at bits 8
+// and 9 7.0 | 13, binary32 8.5 | 7.3.  With 8 and 16 rows the f16 operands took the place of kernels with 47 | 80.
+constexpr bool rows_normal_operands(int bits, bool padded) { return bits == 4 || padded; }
+constexpr int kNormalBits = 14;
 
 // Key codes.  Dword W of a token holds 32 / BITS channels, channel 4 h + b of it at bit 8 b + BITS h.  A lane quarter kq
 // reads the dwords W = kq + 4 i; step kc of the contraction takes two fields h, i.e. 8 consecutive channels from
@@ -77,31 +108,36 @@ __device__ __forceinline__ constexpr int key_channel(int kc, int kq) {
 template <int BITS>
 __device__ __forceinline__ constexpr int key_load(int kc) { return BITS == 2 ? kc >> 1 : BITS == 1 ? 0 : kc; }
 template <int BITS>
-__device__ __forceinline__ uint4v key_operand(uint32_t w, int kc) {
+__device__ __forceinline__ uint4v key_fields(uint32_t w, int kc) {
     if constexpr (BITS == 2) {
-        return (kc & 1) == 0 ? uint4v{(w << 8) & 0x03000300u, w & 0x03000300u, (w << 4) & 0x00C000C0u, (w >> 4) & 0x00C000C0u}
-                             : uint4v{(w << 4) & 0x03000300u, (w >> 4) & 0x03000300u, w & 0x00C000C0u, (w >> 8) & 0x00C000C0u};
+        constexpr uint32_t m = 0x03000300u;
+        return (kc & 1) == 0 ? uint4v{(w << 8) & m, w & m, (w << 6) & m, (w >> 2) & m} : uint4v{(w << 4) & m, (w >> 4) & m, (w << 2) & m, (w >> 6) & m};
     } else if constexpr (BITS == 1) {
         switch (kc) {
             case 0: return uint4v{(w << 8) & 0x01000100u, w & 0x01000100u, (w << 8) & 0x02000200u, w & 0x02000200u};
-            case 1: return uint4v{(w << 4) & 0x00400040u, (w >> 4) & 0x00400040u, (w << 4) & 0x00800080u, (w >> 4) & 0x00800080u};
+            case 1: return uint4v{(w << 6) & 0x01000100u, (w >> 2) & 0x01000100u, (w << 6) & 0x02000200u, (w >> 2) & 0x02000200u};
             case 2: return uint4v{(w << 4) & 0x01000100u, (w >> 4) & 0x01000100u, (w << 4) & 0x02000200u, (w >> 4) & 0x02000200u};
-            default: return uint4v{w & 0x00400040u, (w >> 8) & 0x00400040u, w & 0x00800080u, (w >> 8) & 0x00800080u};
+            default: return uint4v{(w << 2) & 0x01000100u, (w >> 6) & 0x01000100u, (w << 2) & 0x02000200u, (w >> 6) & 0x02000200u};
         }
     } else {
         return uint4v{(w << 6) & 0x03C003C0u, (w >> 2) & 0x03C003C0u, (w << 2) & 0x03C003C0u, (w >> 6) & 0x03C003C0u};
     }
 }
+template <bool NORMAL>
+__device__ __forceinline__ uint4v normal(uint4v a) {
+    return NORMAL ? __builtin_bit_cast(uint4v, __builtin_bit_cast(half8, a) * (_Float16)(1 << kNormalBits)) : a;
+}
+template <int BITS, bool NORMAL>
+__device__ __forceinline__ uint4v key_operand(uint32_t w, int kc) { return normal<NORMAL>(key_fields<BITS>(w, kc)); }
 // the fields arrive at different bits: the multiplier of channel c carries the factor that makes every product
 // code * 2^kKeyPos * 2^-24
 template <int BITS>
 __device__ __forceinline__ float key_factor(int c) {
-    if constexpr (BITS == 2) return ((c >> 2) & 1) ? 4.0f : 1.0f;
-    if constexpr (BITS == 1) return (c >> 2) & 1 ? ((c >> 3) & 1 ? 4.0f : 1.0f) : ((c >> 3) & 1 ? 8.0f : 2.0f);
-    return 1.0f;
+    return BITS == 1 && !((c >> 2) & 1) ? 2.0f : 1.0f;
 }
-constexpr int key_pos(int bits) { return bits == 2 ? 8 : bits == 1 ? 9 : 6; }
-constexpr int key_q_bits(int bits) { return bits == 2 ? 5 : bits == 1 ? 4 : 7; }   // |q'| < 2^this: q' factor s' < 2^15 with s' < 2^8
+template <int BITS, bool NORMAL>
+__device__ __forceinline__ constexpr int key_pos() { return (BITS == 2 ? 8 : BITS == 1 ? 9 : 6) + (NORMAL ? kNormalBits : 0); }
+constexpr int key_q_bits(int bits) { return bits == 1 ? 6 : 7; }   // |q'| < 2^this: q' factor s' < 2^15 with s' < 2^8
 
 // Value codes.  Byte t of a 16-byte piece is a token, its fields are channels.  A channel tile (mb, jj) is 16 channels of
 // the 32-channel block mb, so that it lies in one value group whatever g is: A row i is channel value_channel(mb, jj, i).
@@ -113,7 +149,8 @@ template <int BITS>
 __device__ __forceinline__ int value_channel(int mb, int jj, int i) {
     return BITS == 2 ? 4 * (8 * mb + (i & 7)) + 2 * (i >> 3) + jj : BITS == 1 ? 8 * (4 * mb + (i & 3)) + 2 * (i >> 2) + jj : 2 * (16 * mb + i) + jj;
 }
-constexpr int value_pos(int bits, int jj) { return bits == 2 ? (jj ? 8 : 6) : bits == 1 ? 8 + jj : 6; }
+template <int BITS, bool NORMAL>
+__device__ __forceinline__ constexpr int value_pos(int jj) { return (BITS == 2 ? 8 : BITS == 1 ? 8 + jj : 6) + (NORMAL ? kNormalBits : 0); }
 struct ValueShift { uint32_t left, right; };   // of the lane's A row (2- and 1-bit codes)
 template <int BITS>
 __device__ __forceinline__ ValueShift value_shift(int ic) {
@@ -121,20 +158,23 @@ __device__ __forceinline__ ValueShift value_shift(int ic) {
     return {8u - 2u * (ic >> 2), 2u * (ic >> 2)};
 }
 // both channel tiles of a block from the 8 tokens of a lane
-template <int BITS>
+template <int BITS, bool NORMAL>
 __device__ __forceinline__ void value_operands(uint2 w, ValueShift sh, uint4v a[2]) {
     if constexpr (BITS == 4) {
         a[0] = uint4v{(w.x << 6) & 0x03C003C0u, (w.x >> 2) & 0x03C003C0u, (w.y << 6) & 0x03C003C0u, (w.y >> 2) & 0x03C003C0u};
         a[1] = uint4v{(w.x << 2) & 0x03C003C0u, (w.x >> 6) & 0x03C003C0u, (w.y << 2) & 0x03C003C0u, (w.y >> 6) & 0x03C003C0u};
     } else {
-        constexpr uint32_t m0 = BITS == 2 ? 0x00C000C0u : 0x01000100u, m1 = BITS == 2 ? 0x03000300u : 0x02000200u;
+        constexpr uint32_t m0 = BITS == 2 ? 0x03000300u : 0x01000100u, m1 = BITS == 2 ? 0x03000300u : 0x02000200u;
+        constexpr int up = BITS == 2 ? 2 : 0;
         const uint32_t e0 = w.x << sh.left, o0 = w.x >> sh.right, e1 = w.y << sh.left, o1 = w.y >> sh.right;
-        a[0] = uint4v{e0 & m0, o0 & m0, e1 & m0, o1 & m0};
+        a[0] = uint4v{(e0 << up) & m0, (o0 << up) & m0, (e1 << up) & m0, (o1 << up) & m0};
         a[1] = uint4v{e0 & m1, o0 & m1, e1 & m1, o1 & m1};
     }
+    a[0] = normal<NORMAL>(a[0]);
+    a[1] = normal<NORMAL>(a[1]);
 }
 
-// x as hi + lo f16, both rounded to nearest (24 bits), packed in the pair order of the A operands
+// x as hi + lo f16, both rounded to nearest (to 2^-23 of x), packed in the pair order of the A operands
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split8(const float x[8], uint4v& hi, uint4v& lo) {
@@ -301,10 +341,31 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
         *reinterpret_cast<float2*>(o_lds + ((size_t)wave * 16 + rr) * kRowsOStride + 2 * lane) = make_float2(o[rr][0], o[rr][1]);
 }
 
+// sum_c code[i][c] q'[c] s'[c] of the eight tokens of a lane in binary32
+template <int BITS>
+__device__ __forceinline__ void scaled_logits(const uint8_t* kc_row, int sub, int kq, const float* q, const float* s, float o[8]) {
+    const uint8_t* base = kc_row + (size_t)(sub / 16) * k_tile_bytes(BITS) + (size_t)(4 * (sub % 16) + kq) * 16;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) o[t] = 0.0f;
+#pragma unroll 1
+    for (int W = 0; W < 4 * BITS; ++W) {
+        const uint4 a = *reinterpret_cast<const uint4*>(base + (size_t)W * 2048), b = *reinterpret_cast<const uint4*>(base + (size_t)W * 2048 + 1024);
+        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll 1
+        for (int j = 0; j < 32 / BITS; ++j) {
+            const int c = W * (32 / BITS) + j, bit = 8 * (j & 3) + BITS * (j >> 2);
+            const float x = q[c] / key_factor<BITS>(c) * s[c];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) o[t] = __builtin_fmaf((float)((w[t] >> bit) & ((1u << BITS) - 1u)), x, o[t]);
+        }
+    }
+}
+
 template <int BITS, int GROUP, int NR, bool PADDED, bool BF16, int MODE>
 __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs R) {
     using S = RowsShape<BITS, GROUP, NR>;
     constexpr int SUBS = S::SUBS, UNIT = S::UNIT, SG = S::SG, M = S::M;
+    constexpr bool NORMAL = rows_normal_operands(BITS, PADDED);
     __shared__ __attribute__((aligned(16))) uint8_t smem[S::kBytes];
     __shared__ uint32_t maskbits[MODE == kRowsScore ? 1 : kRowsMaxChunk / 32];
     __shared__ RowsOut out;
@@ -341,7 +402,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     // ---- the query rows: scaled by a power of two and by the channels' factors, and as they are
     float* qs = reinterpret_cast<float*>(smem);                                    // [NR][kQStride]
     uint16_t* qraw = reinterpret_cast<uint16_t*>(smem + NR * S::kQStride * 4);      // [NR][kZStride]
-    float* q_unscale = reinterpret_cast<float*>(smem + NR * S::kQStride * 4 + NR * S::kZStride * 2);   // [NR]
+    int* q_unscale = reinterpret_cast<int*>(smem + NR * S::kQStride * 4 + NR * S::kZStride * 2);   // [NR], exponents
     for (int rr = wave; rr < NR; rr += kWaves) {
         const uint32_t w = rr < nq ? reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * nq + rr) * kD)[lane] : 0u;
         reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
@@ -349,11 +410,11 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
             const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
             const float top = wave_max(fmaxf(fabsf(a), fabsf(b)));
             int f = 253 + key_q_bits(BITS) - (int)((__float_as_uint(top) >> 23) & 0xFFu);   // top < 2^(E - 126): field of 2^(kbits - E + 126)
-            f = f < 100 ? 100 : (f > 224 ? 224 : f);
+            f = f > 254 ? 254 : f;
             const float sc = __uint_as_float((uint32_t)f << 23);
             const int c = 2 * lane;
             *reinterpret_cast<float2*>(qs + rr * S::kQStride + c) = make_float2(a * sc * key_factor<BITS>(c), b * sc * key_factor<BITS>(c + 1));
-            if (lane == 0) q_unscale[rr] = __uint_as_float((uint32_t)(254 - f) << 23);
+            if (lane == 0) q_unscale[rr] = 127 - f;
         }
     }
 
@@ -382,32 +443,52 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         constexpr int kVm = UNIT * M / 64 > 0 ? UNIT * M / 64 : 1;                   // value metadata words per lane
         uint2 kcw[SUBS][BITS], kmw[SG], vcw[SUBS][4];
         uint32_t vmw[kVm];
+        int vexp[M], kexp[SG];    // the same for the whole wave: acc of value group m is scaled by 2^vexp[m]
+        // the lanes whose word e is of value group m
+        auto group_lanes = [](int m, int e) constexpr {
+            unsigned long long lanes = 0;
+            for (int i = 0; i < 64; ++i) lanes |= (unsigned long long)((i * kVm + e) % M == m && i * kVm + e < UNIT * M) << i;
+            return lanes;
+        };
+        auto group_exp = [&](int m) {
+            int x = vexp[0];
+#pragma unroll
+            for (int mm = 1; mm < M; ++mm) x += m == mm ? vexp[mm] - vexp[0] : 0;     // (no choice between array elements: it stays in registers)
+            return x;
+        };
         auto sub_of = [&](int t0, int x) {
             const int sub = t0 / kBlockTokens + x;
             return sub < n_sub ? sub : n_sub - 1;                                    // past the end: a valid sub-group again
         };
-        auto load_keys = [&](int t0) {
+        // a wave's position is the same for its lanes: addresses are a scalar base plus a lane's offset
+        const uint32_t km_lane = 8u * lane, kc_lane = (uint32_t)(((ic % 4) / 2) * 1024 + (ic / 4) * 16 + 8 * (ic % 2) + kq * 2048);
+        const uint32_t vc_lane = (uint32_t)((kq >> 1) * (256 * BITS) + 8 * (kq & 1) + value_lane<BITS>(0, ic) * 16);
+        uint32_t* keys_row = R.keys + (size_t)row * R.key_stride;
+        const size_t row_logits = (size_t)row * nq * A.logit_stride;
+        const uint32_t logit_lane = (uint32_t)(r * A.logit_stride + 32 * s + 8 * kq);
+        auto load_keys = [&](int t_wave) {
             if constexpr (MODE != kRowsAttend) {
+                const int t0 = __builtin_amdgcn_readfirstlane(t_wave);
 #pragma unroll
                 for (int gi = 0; gi < SG; ++gi) {
                     int grp = t0 / GROUP + gi;
                     const int n_grp = A.Nq / GROUP;
                     grp = grp < n_grp ? grp : n_grp - 1;
-                    kmw[gi] = *reinterpret_cast<const uint2*>(km_row + (size_t)grp * kD + 2 * lane);
+                    kmw[gi] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(km_row + (size_t)grp * kD) + km_lane);
                 }
 #pragma unroll
                 for (int x = 0; x < SUBS; ++x) {
                     const int sub = sub_of(t0, x);
                     // row ic is tokens 2 ic and 2 ic + 1: half (ic % 4) / 2 of layout lane 4 (sub % 16) + ic / 4
-                    const uint8_t* base = kc_row + (size_t)(sub / 16) * k_tile_bytes(BITS) + (size_t)((ic % 4) / 2) * 1024 +
-                                          (size_t)(4 * (sub % 16) + ic / 4) * 16 + 8 * (ic % 2);
+                    const uint8_t* base = kc_row + (size_t)(sub / 16) * k_tile_bytes(BITS) + (size_t)(sub % 16) * 64;
 #pragma unroll
-                    for (int i = 0; i < BITS; ++i) kcw[x][i] = *reinterpret_cast<const uint2*>(base + (size_t)(kq + 4 * i) * 2048);
+                    for (int i = 0; i < BITS; ++i) kcw[x][i] = *reinterpret_cast<const uint2*>(base + 4 * i * 2048 + kc_lane);
                 }
             }
         };
-        auto load_values = [&](int t0) {
+        auto load_values = [&](int t_wave) {
             if constexpr (MODE != kRowsScore) {
+                const int t0 = __builtin_amdgcn_readfirstlane(t_wave);
                 // metadata words of the unit in memory order: word lane * kVm + e
                 const int word = lane * kVm;
                 const int last = A.Nq * M - kVm;
@@ -416,20 +497,20 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 if constexpr (kVm % 4 == 0) {
 #pragma unroll
                     for (int e = 0; e < kVm; e += 4) {
-                        const uint4 v = *reinterpret_cast<const uint4*>(vm_row + at + e);
+                        const uint4 v = *reinterpret_cast<const uint4*>(vm_row + (uint32_t)(at + e));
                         vmw[e] = v.x; vmw[e + 1] = v.y; vmw[e + 2] = v.z; vmw[e + 3] = v.w;
                     }
                 } else if constexpr (kVm == 2) {
-                    const uint2 v = *reinterpret_cast<const uint2*>(vm_row + at);
+                    const uint2 v = *reinterpret_cast<const uint2*>(vm_row + (uint32_t)at);
                     vmw[0] = v.x; vmw[1] = v.y;
                 } else {
-                    vmw[0] = vm_row[at];
+                    vmw[0] = vm_row[(uint32_t)at];
                 }
 #pragma unroll
                 for (int x = 0; x < SUBS; ++x) {
-                    const uint8_t* base = vc_row + (size_t)sub_of(t0, x) * code_block_bytes(BITS) + (size_t)(kq >> 1) * (256 * BITS) + 8 * (kq & 1);
+                    const uint8_t* base = vc_row + (size_t)sub_of(t0, x) * code_block_bytes(BITS);
 #pragma unroll
-                    for (int mb = 0; mb < 4; ++mb) vcw[x][mb] = *reinterpret_cast<const uint2*>(base + value_lane<BITS>(mb, ic) * 16);
+                    for (int mb = 0; mb < 4; ++mb) vcw[x][mb] = *reinterpret_cast<const uint2*>(base + value_lane<BITS>(mb, 0) * 16 + vc_lane);
                 }
             }
         };
@@ -452,19 +533,23 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         const ValueShift vsh = value_shift<BITS>(ic);
         const int my_group = SG > 1 ? s * kBlockTokens / GROUP : 0;                   // the column's token group inside the unit
         float4v acc[4][2];
-        float m_used = -INFINITY, lsum = 0.0f, zacc[M], vscale = 0.0f;
+        float m_used = -INFINITY, lsum = 0.0f, zacc[M];
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) acc[mb][jj] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int m = 0; m < M; ++m) zacc[m] = 0.0f;
+        for (int m = 0; m < M; ++m) {
+            zacc[m] = 0.0f;
+            vexp[m] = 0;
+        }
+#pragma unroll
+        for (int gi = 0; gi < SG; ++gi) kexp[gi] = 0;
+        // Two sub-groups in flight: columns (r, hi | lo).  Where they are one token group the two lanes of a row work out
+        // half of its multipliers each, for all the units it has; else each those of its own group, step by step.
+        constexpr bool kHiLo = SUBS == 2, kHalves = kHiLo && SG == 1;
         constexpr bool kKeepB = MODE != kRowsAttend && UNIT < GROUP;                  // a token group's multipliers serve several units
-        // Two sub-groups of one token group: columns (r, hi | lo).  The two lanes of a row work out half of the
-        // multipliers each and exchange them.
-        constexpr bool kHiLo = SUBS == 2 && SG == 1;
-        constexpr int kSteps = kHiLo ? 2 : 4;
-        uint4v bhi[kKeepB || kHiLo ? 4 : 1], blo[kKeepB && !kHiLo ? 4 : 1];
+        uint4v bhi[kKeepB || kHalves ? 4 : 1], blo[kKeepB && !kHiLo ? 4 : 1];
         auto multipliers = [&](int kc, uint4v& hi, uint4v& lo) {
             const int c = key_channel<BITS>(kc, kq);
             float x[8];
@@ -479,8 +564,10 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
             }
             split8(x, hi, lo);
         };
-        float unscale = 0.0f, qz = 0.0f;
-        int group_done = -1;
+        float unscale = 0.0f;
+        int unscale_more = 0, group_done = -1;
+        const bool q_some = MODE != kRowsAttend && q_unscale[r] > -127;             // a query that is not zero
+        float qz = 0.0f;
 
         for (int u = 0; u < R.wave_units; ++u) {
             const int t0 = w0 + u * UNIT;
@@ -492,37 +579,41 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 const int grp0 = t0 / GROUP;
                 if (grp0 != group_done) {
                     group_done = grp0;
-                    float sv[SG][2], top = 0.0f;
                     wave_sync();
+                    int es = 0;
 #pragma unroll
                     for (int gi = 0; gi < SG; ++gi) {
                         const uint32_t wd[2] = {kmw[gi].x, kmw[gi].y};
                         // words 2 lane, 2 lane + 1 are channels c and c + 4
                         const int c = 4 * ((2 * lane) & 31) + (lane >> 4);
+                        float sv[2];
 #pragma unroll
                         for (int e = 0; e < 2; ++e) {
                             float z;
-                            derive_scale_zero<BITS>(widen16<BF16>(wd[e] & 0xFFFFu), widen16<BF16>(wd[e] >> 16), L.one_bit_plain, sv[gi][e], z);
-                            top = fmaxf(top, sv[gi][e]);
+                            derive_scale_zero<BITS>(widen16<BF16>(wd[e] & 0xFFFFu), widen16<BF16>(wd[e] >> 16), L.one_bit_plain, sv[e], z);
                             z_tab[gi * S::kZStride + c + 4 * e] = (uint16_t)wd[e];
                             if constexpr (BITS == 1) z_tab[(SG + gi) * S::kZStride + c + 4 * e] = (uint16_t)(wd[e] >> 16);
                         }
-                    }
-                    top = wave_max(top);
-                    // s < 2^(E - 126): scaled to below 2^8
-                    int f = 261 - (int)((__float_as_uint(top) >> 23) & 0xFFu);
-                    f = f < 100 ? 100 : (f > 224 ? 224 : f);
-                    const float sc = __uint_as_float((uint32_t)f << 23);
-#pragma unroll
-                    for (int gi = 0; gi < SG; ++gi) {
-                        const int c = 4 * ((2 * lane) & 31) + (lane >> 4);
-                        s_tab[gi * S::kSStride + c] = sv[gi][0] * sc;
-                        s_tab[gi * S::kSStride + c + 4] = sv[gi][1] * sc;
+                        float sc[2] = {times_pow2(sv[0], kexp[gi]), times_pow2(sv[1], kexp[gi])};
+                        const float top = fmaxf(sc[0], sc[1]);
+                        if (__builtin_expect(__any(top > kKeyScaleMost) || !__any(top > kKeyScaleLeast), 0)) {
+                            const uint32_t E = wave_max_bits(__float_as_uint(fmaxf(sv[0], sv[1]))) >> 23;      // s < 2^(E - 126)
+                            kexp[gi] = 126 + kScaleSet - (int)(E & 0xFFu);
+                            sc[0] = times_pow2(sv[0], kexp[gi]);
+                            sc[1] = times_pow2(sv[1], kexp[gi]);
+                        }
+                        s_tab[gi * S::kSStride + c] = sc[0];
+                        s_tab[gi * S::kSStride + c + 4] = sc[1];
+                        es = my_group == gi ? kexp[gi] : es;
                     }
                     wave_sync();
-                    unscale = q_unscale[r] * (__uint_as_float((uint32_t)(254 - f) << 23) * (float)(1 << (24 - key_pos(BITS))));
+                    {
+                        const int e = q_unscale[r] - es + 24 - key_pos<BITS, NORMAL>(), u = e > 127 ? 127 : e < -126 ? -126 : e;
+                        unscale = __uint_as_float((uint32_t)(127 + u) << 23);
+                        unscale_more = e - u;                                          // beyond binary32's powers of two
+                    }
                     // zero-point term: z is the stored 16-bit minimum (Eq. 3: a quarter of three minima and a maximum),
-                    // q the 16-bit query, so the products are exact.  A row i is token group i & 3.
+                    // q the 16-bit query, so the products are exact.  A row i is token group i & (SG - 1).
                     const int zg = SG > 1 ? (ic & (SG - 1)) : 0;
                     float4v zc = {0.f, 0.f, 0.f, 0.f}, xc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -543,58 +634,82 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                     }
                     if constexpr (BITS == 1) zq = L.one_bit_plain ? zq : __builtin_fmaf(zq, 3.0f, xq) * 0.25f;
                     qz = zq * A.sm_scale;
-                    if constexpr (kHiLo) {
+                    if constexpr (kHalves) {
 #pragma unroll
-                        for (int i = 0; i < kSteps; ++i) {
+                        for (int i = 0; i < 2; ++i) {
                             uint4v hi, lo;
                             multipliers(i + 2 * s, hi, lo);
-#pragma unroll
-                            for (int d = 0; d < 4; ++d) {
-                                const uint32_t got = ror8(s ? hi[d] : lo[d]);
-                                bhi[i][d] = s ? got : hi[d];
-                                bhi[i + 2][d] = s ? lo[d] : got;
-                            }
+                            hi_lo_columns(hi, lo, bhi[i], bhi[i + 2]);
                         }
                     } else if constexpr (kKeepB) {
 #pragma unroll
                         for (int kc = 0; kc < 4; ++kc) multipliers(kc, bhi[kc], blo[kc]);
                     }
                 }
-                // ---- products: four channel steps x sub-groups x two tiles (even and odd tokens) x (hi, lo)
-                float4v c[SUBS][2];
+                float o[8];
+                {
+                    // ---- products: four channel steps x sub-groups x two tiles (even and odd tokens), hi and lo in sums of their
+                    // own: added to the larger one step by step the small sum would lose its low end each time
+                    float4v c[2][2];
 #pragma unroll
-                for (int x = 0; x < SUBS; ++x) c[x][0] = c[x][1] = float4v{0.f, 0.f, 0.f, 0.f};
+                    for (int x = 0; x < 2; ++x) c[x][0] = c[x][1] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kc = 0; kc < 4; ++kc) {
-                    uint4v bh, bl;
-                    if constexpr (kHiLo) bh = bhi[kc];
-                    else if constexpr (kKeepB) { bh = bhi[kc]; bl = blo[kc]; }
-                    else multipliers(kc, bh, bl);
-#pragma unroll
-                    for (int x = 0; x < SUBS; ++x)
+                    for (int kc = 0; kc < 4; ++kc) {
+                        uint4v b[2];     // kHiLo: of either sub-group; else hi and lo
+                        if constexpr (kHalves) {
+                            b[0] = b[1] = bhi[kc];
+                        } else if constexpr (kKeepB) {
+                            b[0] = bhi[kc];
+                            b[1] = blo[kc];
+                        } else {
+                            uint4v hi, lo;
+                            multipliers(kc, hi, lo);
+                            if constexpr (kHiLo) {
+                                hi_lo_columns(hi, lo, b[0], b[1]);
+                            } else {
+                                b[0] = hi;
+                                b[1] = lo;
+                            }
+                        }
 #pragma unroll
                         for (int mt = 0; mt < 2; ++mt) {
-                            const uint2 w = kcw[x][key_load<BITS>(kc)];
-                            const uint4v a = key_operand<BITS>(mt == 0 ? w.x : w.y, kc);
-                            c[x][mt] = mfma16(a, bh, c[x][mt]);
-                            if constexpr (!kHiLo) c[x][mt] = mfma16(a, bl, c[x][mt]);
+                            uint4v a;
+#pragma unroll
+                            for (int x = 0; x < 2; ++x) {
+                                if (x < SUBS) {
+                                    const uint2 w = kcw[x][key_load<BITS>(kc)];
+                                    a = key_operand<BITS, NORMAL>(mt == 0 ? w.x : w.y, kc);
+                                }
+                                c[x][mt] = mfma16(a, b[x], c[x][mt]);
+                            }
                         }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                float o[8];
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt) {
-                        if constexpr (kHiLo) {     // the lane's sub-group: its own column plus the other one's
-                            const float other = s ? c[0][mt][v] : c[SUBS - 1][mt][v];
-                            o[2 * v + mt] = (s ? c[SUBS - 1][mt][v] : c[0][mt][v]) + dpp_move<kDppRowRor8>(other);
-                        } else {
-                            o[2 * v + mt] = c[0][mt][v];
-#pragma unroll
-                            for (int x = 1; x < SUBS; ++x) o[2 * v + mt] = s == x ? c[x][mt][v] : o[2 * v + mt];
-                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) {
+                            if constexpr (kHiLo) {     // the lane's sub-group: its own column plus the other one's
+                                const float other = s ? c[0][mt][v] : c[1][mt][v];
+                                o[2 * v + mt] = (s ? c[1][mt][v] : c[0][mt][v]) + dpp_move<kDppRowRor8>(other);
+                            } else {
+                                o[2 * v + mt] = c[0][mt][v] + c[1][mt][v];
+                            }
+                        }
+                }
+                // Tokens of a row all next to nothing: its query is small where the channels' scales are large.  What is
+                // left of the multipliers then lies in the f16 subnormals, and the lanes work in binary32 instead.
+                const float most = fmaxf(fmaxf(fabsf(o[0]), fabsf(o[2])), fmaxf(fabsf(o[5]), fabsf(o[7])));
+                const bool faint = most < times_pow2(4.0f, key_pos<BITS, NORMAL>() - 24) && q_some && (!PADDED || r < nq);
+                if (__builtin_expect(__any(faint || unscale_more != 0), 0)) {
+                    if (__any(faint)) {
+                        scaled_logits<BITS>(kc_row, sub_of(t0, s), kq, qs + r * S::kQStride, s_tab + my_group * S::kSStride, o);
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) o[t] = times_pow2(o[t], key_pos<BITS, NORMAL>() - 24);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) o[t] = times_pow2(o[t], unscale_more);
+                }
                 if (u + 1 < R.wave_units) load_keys(t0 + UNIT < A.Nq ? t0 + UNIT : t0);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) l[t] = __builtin_fmaf(o[t], unscale, qz);
@@ -617,19 +732,19 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                             for (int h = 0; h < G / 2; ++h) b = fmaxf(b, l_tab[((lane >> 5) * (G / 2) + h) * S::kKeyStride + t]);
                             b = xor32_max(b);
                         }
-                        if (t0 + t < A.Nq && (UNIT >= 64 || lane < 32)) R.keys[(size_t)row * R.key_stride + t0 + t] = float_to_key(b);
+                        if (t0 + t < A.Nq && (UNIT >= 64 || lane < 32)) keys_row[(uint32_t)(t0 + t)] = float_to_key(b);
                     }
                     wave_sync();
                 }
                 if (A.logits_out && active) {
-                    float4* d = reinterpret_cast<float4*>(A.logits_out + ((size_t)row * nq + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    float4* d = reinterpret_cast<float4*>(A.logits_out + row_logits + (logit_lane + (uint32_t)t0));
                     d[0] = make_float4(l[0], l[1], l[2], l[3]);
                     d[1] = make_float4(l[4], l[5], l[6], l[7]);
                 }
             } else {
                 float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
                 if (active) {
-                    const float4* d = reinterpret_cast<const float4*>(A.logits + ((size_t)row * nq + r) * A.logit_stride + t0 + 32 * s + 8 * kq);
+                    const float4* d = reinterpret_cast<const float4*>(A.logits + row_logits + (logit_lane + (uint32_t)t0));
                     a = d[0];
                     b = d[1];
                 }
@@ -638,20 +753,68 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
 
             if constexpr (MODE != kRowsScore) {
                 // ---- scales and zero-points of the unit's tokens
-                float vtop = 0.0f;
                 wave_sync();
+                float vs[kVm], vsc[kVm];
 #pragma unroll
                 for (int e = 0; e < kVm; ++e) {
                     const int word = lane * kVm + e, tok = word / M, m = word % M;
-                    float sc, z;
-                    derive_scale_zero<BITS>(widen16<BF16>(vmw[e] & 0xFFFFu), widen16<BF16>(vmw[e] >> 16), L.one_bit_plain, sc, z);
-                    if (UNIT * M >= 64 || word < UNIT * M) {
-                        vs_tab[m * UNIT + tok] = sc;
-                        vz_tab[m * UNIT + tok] = z;
-                    }
-                    vtop = fmaxf(vtop, sc);
+                    float z;
+                    derive_scale_zero<BITS>(widen16<BF16>(vmw[e] & 0xFFFFu), widen16<BF16>(vmw[e] >> 16), L.one_bit_plain, vs[e], z);
+                    if (UNIT * M >= 64 || word < UNIT * M) vz_tab[m * UNIT + tok] = z;
+                    vsc[e] = times_pow2(vs[e], group_exp(m));
                 }
-                vtop = wave_max(vtop);
+                // does every group's largest scale lie within the bounds?  (which lanes hold a group's words is fixed)
+                bool moved = false;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    unsigned long long over = 0, some = 0;
+#pragma unroll
+                    for (int e = 0; e < kVm; ++e) {
+                        const unsigned long long lanes = group_lanes(m, e);
+                        if (lanes == 0) continue;
+                        over |= __ballot(vsc[e] > kValueScaleMost) & lanes;
+                        some |= __ballot(vsc[e] > kValueScaleLeast) & lanes;
+                    }
+                    moved = moved || over != 0 || some == 0;
+                }
+                if (__builtin_expect(moved, 0)) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        uint32_t top = 0;
+#pragma unroll
+                        for (int e = 0; e < kVm; ++e) {
+                            const int word = lane * kVm + e;
+                            const uint32_t b = word % M == m && word < UNIT * M ? __float_as_uint(vs[e]) : 0u;
+                            top = top > b ? top : b;
+                        }
+                        top = wave_max_bits(top);
+                        float sum = 0.0f;
+#pragma unroll
+                        for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb)
+#pragma unroll
+                            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) sum = fmaxf(sum, fabsf(acc[mb][jj][i]));
+                        // s < 2^(E - 126): to below 2^kScaleSet, but no sum so far beyond 2^100
+                        const int room = 226 - (int)(wave_max_bits(__float_as_uint(sum)) >> 23);
+                        int e = 126 + kScaleSet - (int)((top >> 23) & 0xFFu);
+                        e = top == 0 ? vexp[m] : e < vexp[m] + room ? e : vexp[m] + room;
+#pragma unroll
+                        for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb)
+#pragma unroll
+                            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) acc[mb][jj][i] = times_pow2(acc[mb][jj][i], e - vexp[m]);
+                        vexp[m] = e;
+                    }
+#pragma unroll
+                    for (int e = 0; e < kVm; ++e) vsc[e] = times_pow2(vs[e], group_exp((lane * kVm + e) % M));
+                }
+#pragma unroll
+                for (int e = 0; e < kVm; ++e) {
+                    const int word = lane * kVm + e, tok = word / M, m = word % M;
+                    if (UNIT * M >= 64 || word < UNIT * M) vs_tab[m * UNIT + tok] = vsc[e];
+                }
                 wave_sync();
                 // ---- softmax numerators
                 const uint32_t mask = (maskbits[(t0 - c0) / 32 + s] >> (8 * kq)) & 0xFFu;
@@ -663,37 +826,26 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 }
                 mx = quarters_max(mx);
                 if constexpr (SUBS == 2) mx = fmaxf(mx, dpp_move<kDppRowRor8>(mx));   // both columns of a row share the maximum
-                if (__any(mx > m_used + kLazyMax) || vtop * vscale > 512.0f || vscale == 0.0f) {
-                    // the maxima, or the fixed scale of the value side (p s vscale < 2^15 with p < 2^6), move
+                if (__any(mx > m_used + kLazyMax)) {
                     const float m_new = fmaxf(m_used, mx);
                     const float a = m_new == -INFINITY ? 1.0f : exp2_of((m_used - m_new) * kLog2e);
-                    float ns = vscale;
-                    if (vtop * vscale > 512.0f || vscale == 0.0f) {
-                        // vtop < 2^(E - 126): vtop * scale < 2^5, four binary orders of room
-                        int f = 258 - (int)((__float_as_uint(vtop) >> 23) & 0xFFu);
-                        f = f > 224 ? 224 : f;
-                        ns = __uint_as_float((uint32_t)f << 23);
-                    }
-                    const float b = vscale == 0.0f ? 0.0f : a * (ns / vscale);
 #pragma unroll
                     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
                         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[mb][jj][e] *= b;
+                            for (int e = 0; e < 4; ++e) acc[mb][jj][e] *= a;
 #pragma unroll
                     for (int m = 0; m < M; ++m) zacc[m] *= a;
                     lsum *= a;
                     m_used = m_new;
-                    vscale = ns;
                 }
                 const float ms = m_used == -INFINITY ? 0.0f : m_used;
-                float p[8], pv[8];
+                float p[8];
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     p[t] = exp2_of((l[t] - ms) * kLog2e);
                     lsum += p[t];
-                    pv[t] = p[t] * vscale;
                 }
                 // ---- per value group: B operand and zero-point sums; per sub-group and 32-channel block of the
                 // ---- group two channel tiles x (hi, lo)
@@ -709,26 +861,20 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                         float x[8];
 #pragma unroll
                         for (int t = 0; t < 8; ++t) {
-                            x[t] = pv[t] * sv[t];
+                            x[t] = p[t] * sv[t];
                             zacc[m] = __builtin_fmaf(p[t], zv[t], zacc[m]);
                         }
                         split8(x, phi, plo);
                     }
                     if constexpr (SUBS == 2) {
-                        // columns (r, hi | lo): the lane of sub-group 0 sends its lo halves and receives hi halves of sub-group 1
-                        uint4v b[2];
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            const uint32_t got = ror8(s ? phi[d] : plo[d]);
-                            b[0][d] = s ? got : phi[d];
-                            b[1][d] = s ? plo[d] : got;
-                        }
+                        uint4v b[2];     // columns (r, hi | lo) of either sub-group
+                        hi_lo_columns(phi, plo, b[0], b[1]);
 #pragma unroll
                         for (int x = 0; x < 2; ++x)
 #pragma unroll
                             for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb) {
                                 uint4v a[2];
-                                value_operands<BITS>(vcw[x][mb], vsh, a);
+                                value_operands<BITS, NORMAL>(vcw[x][mb], vsh, a);
 #pragma unroll
                                 for (int jj = 0; jj < 2; ++jj) acc[mb][jj] = mfma16(a[jj], b[x], acc[mb][jj]);
                             }
@@ -736,7 +882,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
 #pragma unroll
                         for (int mb = m * (GROUP / 32); mb < (m + 1) * (GROUP / 32); ++mb) {
                             uint4v a[2];
-                            value_operands<BITS>(vcw[0][mb], vsh, a);
+                            value_operands<BITS, NORMAL>(vcw[0][mb], vsh, a);
 #pragma unroll
                             for (int jj = 0; jj < 2; ++jj) {
                                 acc[mb][jj] = mfma16(a[jj], phi, acc[mb][jj]);
@@ -759,7 +905,6 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
             out.l[wave][ic] = lsum;
         }
         __syncthreads();   // every wave is done with its tables: the outputs take their place
-        const float inv = vscale == 0.0f ? 0.0f : 16777216.0f / vscale;
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -768,8 +913,9 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 for (int e = 0; e < 4; ++e) {
                     // C row 4 kq + e of the tile
                     const int c = value_channel<BITS>(mb, jj, 4 * kq + e);
+                    const int m = mb * 32 / GROUP;
                     o_lds[((size_t)wave * 16 + ic) * kRowsOStride + c] =
-                        __builtin_fmaf(acc[mb][jj][e], inv * (1.0f / (float)(1 << value_pos(BITS, jj))), zacc[mb * 32 / GROUP]);
+                        times_pow2(acc[mb][jj][e], 24 - value_pos<BITS, NORMAL>(jj) - vexp[m]) + zacc[m];
                 }
     }
     if constexpr (MODE == kRowsScore) return;

@@ -1,14 +1,16 @@
 """Several query rows per KV head on the f16 matrix cores (rows_kernel): scoring and attention in one launch and as two,
 at the sizes where units of tokens, waves and chunks end."""
+import numpy as np
 import pytest
 
 from paper_2503_16163_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
-# Multipliers and p s are hi + lo f16, each truncated: 2^-21 of a product.  The products of a logit add up to at most
-# about ten times the largest logit of a row (128 channels, outlier channels included), so 5e-6 of it; an output is a
-# convex combination of such errors in numerator and softmax: four times that.
+# Multipliers and p s are hi + lo f16, each rounded to nearest: 2^-23 of a product, and sums of 128 in binary32 are good for about
+# the same.  The products of a logit add up to at most about ten times the largest logit of a row (128 channels, outlier
+# channels included), so 3e-6 of it, 5e-6 with the zero-point term; an output is a convex combination of such errors in numerator
+# and softmax: four times that.
 LOGITS, OUTPUTS = 5e-6, 2e-5
 
 
@@ -134,3 +136,78 @@ def test_attend_after_the_one_launch_call():
         assert abs(again.cpu().numpy() - out).max() <= OUTPUTS * abs(out).max()
     finally:
         c.close()
+
+
+def _spread(c, kind, rng):
+    """Keys and values of the case with scales far apart, in place."""
+    M = 128 // c.g
+    for b, h in c.sample:
+        k, v = synth.from_bits(c.k_bits[b, h], c.dtype).copy(), synth.from_bits(c.v_bits[b, h], c.dtype).copy()
+        S = v.shape[0]
+        if kind in ("value groups", "large token"):
+            v *= np.where(np.arange(128) // c.g < M // 2, 2.0 ** -12, 1.0).astype(np.float32)[None] if M > 1 else 1.0
+        if kind == "large token":             # the first tokens of a wave's walk, and one in the middle
+            v[[3, 40, S // 2]] *= 256.0
+        if kind == "tokens":
+            v *= np.exp2(rng.integers(-6, 7, size=S)).astype(np.float32)[:, None]
+        if kind == "key channels":
+            k *= np.exp2(rng.permutation(np.linspace(-6, 6, 128).round())).astype(np.float32)[None]
+        if kind == "key groups":
+            k *= np.exp2(rng.integers(-10, 1, size=-(-S // 32))).astype(np.float32).repeat(32)[:S, None]
+        if kind == "huge key":                # (its query is as small, below)
+            k[3::97, 5] = 2.0 ** 40
+        if kind == "nothing":
+            k[:, 7] = 0.0
+            v[:, :32] = 0.5
+        c.k_bits[b, h], c.v_bits[b, h] = synth.to_bits(k, c.dtype), synth.to_bits(v, c.dtype)
+
+
+@pytest.mark.parametrize("kind,dtype", [("value groups", synth.FP16), ("large token", synth.BF16), ("tokens", synth.FP16), ("key channels", synth.BF16),
+                                        ("key groups", synth.FP16), ("huge key", synth.BF16), ("nothing", synth.FP16)])
+@pytest.mark.parametrize("B,Hq,Hkv,S,bits,g,n_rows", [
+    (1, 4, 2, 2500, 2, 32, 2),         # four rows
+    (1, 8, 2, 2500, 2, 64, 2),
+    (1, 8, 2, 2500, 1, 32, 2),
+    (1, 16, 2, 2500, 2, 32, 2),        # sixteen rows: a value group's scales lie in every other or every fourth lane
+    (1, 16, 2, 2500, 1, 64, 2),
+    (1, 3, 3, 2500, 4, 32, 2),
+    (2, 64, 16, 40000, 2, 64, 2),      # waves of several units
+])
+def test_rows_kernel_with_scales_far_apart(kind, dtype, B, Hq, Hkv, S, bits, g, n_rows):
+    """Value groups of a token, tokens, key channels and token groups up to 4096 apart, single tokens far above the rest, a key channel
+    2^40 above the others that the query all but ignores, a zero query and constant channels: the f16 operands keep what binary32
+    kept.  Outputs are compared per value group, so that small channels count as much as large ones."""
+    import torch
+    from tests.harness import Case, to_dev
+    binding.debug_kernel_choice(binding.KEEP_ONE_PASS_LOGITS)
+    c = Case(B, Hq, Hkv, S, dtype, bits, g, 16, R=max(64, g), seed=5600 + Hq + bits, n_rows=n_rows, async_select=2,
+             sample=[(0, 0)] if S > 10000 else None)
+    try:
+        _spread(c, kind, np.random.default_rng(17))
+        c.load()
+        q_bits = synth.make_queries(c.seed, B, Hq, 128, dtype, n_rows=n_rows)
+        if kind in ("huge key", "nothing"):
+            q = synth.from_bits(q_bits, dtype).copy()
+            if kind == "huge key":
+                q[..., 5] *= 2.0 ** -44
+            else:
+                q[:, ::2] = 0.0
+            q_bits = synth.to_bits(q, dtype).reshape(q_bits.shape)
+        q, stream = to_dev(q_bits, dtype), torch.cuda.current_stream()
+        out = torch.empty((B, Hq, n_rows, 128), dtype=torch.float32, device="cuda")
+        c.sc.score_attend(0, q, n_rows, None, None, -1, out, stream)
+        torch.cuda.synchronize()
+        logits, got = c.sc.debug_logits(0, n_rows), out.cpu().numpy().astype(np.float64)
+        for b, h in c.sample:
+            heads = slice(h * c.G, (h + 1) * c.G)
+            want_logits, _ = c.oc[(b, h)].scores(q_bits[b, heads], c.sm_scale)
+            err = np.abs(logits[b, heads] - want_logits).max(-1) / np.maximum(np.abs(want_logits).max(-1), 1e-30)
+            assert err.max() < LOGITS, (b, h, err.max())
+            want = c.oc[(b, h)].attend(q_bits[b, heads], c.sm_scale).reshape(c.G, n_rows, 128 // g, g)
+            diff = got[b, heads].reshape(want.shape) - want
+            err = np.sqrt((diff ** 2).sum(-1) / (want ** 2).sum(-1))
+            print(kind, (b, h), "outputs", err.max())
+            assert err.max() < OUTPUTS, (b, h, err.max())
+    finally:
+        c.close()
+        binding.debug_kernel_choice(0)
