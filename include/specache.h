@@ -258,6 +258,21 @@ int specache_score_attend(specache_ctx* ctx, int32_t layer, const void* q, int32
                           const void* v_spec, int32_t slot, float* out, void* stream);
 
 /*
+ * How the selection on the side stream is ordered behind the scores of the one-launch form of specache_score_attend (and of the
+ * calls built on it).  By default the merge kernel stores a word that the side stream waits for (hipStreamWaitValue64), which
+ * costs the issuing thread 8 to 18 us less per layer than an event that is still pending.  That wait is a kernel which ends when
+ * the merge kernel, on another queue, has started: where something makes the kernels of different queues run one at a time (a
+ * profiler that collects counters or traces threads), it would block them for good.  The library therefore goes by an event
+ *   - when the environment names a profiling tool at specache_create (ROCPROF*, ROCP_*, HSA_TOOLS_LIB), or AMD_DIRECT_DISPATCH=0,
+ *   - from the call on by which a rocprofiler library has been loaded into the process,
+ *   - while the scoring stream is being captured, and where the device cannot wait for a word,
+ *   - after specache_order_by_events(ctx, 1): for a program that expects kernels to be serialised in any other way.
+ * enable = 0 returns to the default.  Takes effect with the context's next scoring call.  Results are the same.
+ * Errors: EINVAL (null ctx).
+ */
+int specache_order_by_events(specache_ctx* ctx, int32_t enable);
+
+/*
  * specache_quantize_append of ONE token followed by specache_score_attend, as one call: a whole layer-step on
  * the caller's stream but for the selection and the prefetch (Appendix A "Decoding": C' = [C', Quant(K_t, V_t)],
  * C = [C, Offload(C_t)], A, O).  k_new, v_new: device, 16-bit, [B, Hkv, 1, 128].  Where specache_score_attend
@@ -339,6 +354,12 @@ int specache_debug_poison_slot(specache_ctx* ctx, int32_t layer, int32_t slot, v
  * 0 switches it off; the setting is consumed by that one create.  Errors: EINVAL (nth < 0).
  */
 int specache_debug_fail_alloc(int32_t nth);
+
+/*
+ * Test hook: whether the layer's last scoring is announced by a word (1) or by an event (0), see specache_order_by_events.
+ * Errors: EINVAL.
+ */
+int specache_debug_scored_by_word(specache_ctx* ctx, int32_t layer, int32_t* by_word);
 
 /*
  * Measurement hook, process-wide: which formulation of the two streaming kernels runs for one

@@ -18,7 +18,7 @@ _NAMES = {EINVAL: "EINVAL", ECAPACITY: "ECAPACITY", ENOMEM: "ENOMEM", EHIP: "EHI
 EXPORTS = ["specache_create", "specache_destroy", "specache_last_error", "specache_counts",
            "specache_plan_append", "specache_quantize_append", "specache_score_topk", "specache_gather",
            "specache_score", "specache_select_gather", "specache_append_score",
-           "specache_attend", "specache_score_attend", "specache_append_score_attend", "specache_decode_step", "specache_attend_static", "specache_debug_poison_slot", "specache_debug_fail_alloc", "specache_debug_kernel_choice", "specache_export_quantized", "specache_export_rows", "specache_debug_logits",
+           "specache_attend", "specache_score_attend", "specache_append_score_attend", "specache_decode_step", "specache_attend_static", "specache_debug_poison_slot", "specache_debug_fail_alloc", "specache_debug_scored_by_word", "specache_order_by_events", "specache_debug_kernel_choice", "specache_export_quantized", "specache_export_rows", "specache_debug_logits",
            "specache_timing", "specache_measure_hbm_read", "specache_measure_link"]
 
 
@@ -71,6 +71,8 @@ def lib():
         L.specache_debug_poison_slot.argtypes = [vp, i32, i32, vp]
         L.specache_debug_kernel_choice.argtypes = [i32]
         L.specache_debug_fail_alloc.argtypes = [i32]
+        L.specache_debug_scored_by_word.argtypes = [vp, i32, C.POINTER(i32)]
+        L.specache_order_by_events.argtypes = [vp, i32]
         L.specache_export_quantized.argtypes = [vp, i32] + [vp] * 6
         L.specache_export_rows.argtypes = [vp, i32, i32, i32, vp]
         L.specache_debug_logits.argtypes = [vp, vp]
@@ -216,6 +218,14 @@ class SpeCache:
 
     def debug_poison_slot(self, layer, slot, stream=None):
         self._check(lib().specache_debug_poison_slot(self._ctx, layer, slot, _stream(stream)))
+
+    def order_by_events(self, enable):
+        self._check(lib().specache_order_by_events(self._ctx, int(bool(enable))))
+
+    def debug_scored_by_word(self, layer):
+        out = C.c_int32()
+        self._check(lib().specache_debug_scored_by_word(self._ctx, layer, C.byref(out)))
+        return bool(out.value)
 
     KERNELS = ("flush", "append_copy", "score", "topk", "gather", "attend", "attend_combine", "score_attend")
 

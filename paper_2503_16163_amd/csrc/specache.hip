@@ -16,6 +16,9 @@
 #include "rows_args.h"
 #include <cstdlib>
 
+#include <link.h>
+#include <unistd.h>
+
 using namespace specache;
 
 namespace specache {
@@ -107,7 +110,10 @@ struct specache_ctx {
     // selections on the gather's stream: those of two side streams may overlap, so the candidate
     // arrays of the two-launch ArgTopK exist twice, each remembering its last user
     bool select_on_gather = false;
-    bool scores_by_word = true;    // see Layer::scored_word
+    // Whether a word may order the selection (see Layer::scored_word, words_may_order).  No: the device cannot wait for one,
+    // the caller wants events, or kernels of different queues may run one at a time.
+    bool scores_by_word = false, events_wanted = false, one_at_a_time = false;
+    unsigned long long objects_seen = 0;   // how many objects had been loaded into the process when they were looked at last
     struct SelectScratch { TopkScratch s{}; bool used = false; hipStream_t stream = nullptr; hipEvent_t done = nullptr; };
     SelectScratch select_scratch[2];
     int select_scratch_next = 0;
@@ -198,6 +204,42 @@ struct CarriedEvent {
     }
     ~CarriedEvent() { if (armed) pending_launch_events() = LaunchEvents{}; }
 };
+
+// The wait for a word is a kernel without a bound, which ends only if the merge kernel on another queue runs beside it or before
+// it.  Submission order sees to that (the merge is enqueued first) unless something between the streams and the queues holds
+// kernels back: a tool that collects counters or traces threads runs the kernels of all queues one at a time, and without direct
+// dispatch a thread per stream submits them in an order of its own.  No call reports such a tool, so every sign of one
+// counts: its variables in the environment, and its libraries among the process's objects, however late they are loaded.
+bool environment_names_a_tool() {
+    for (char** e = environ; e && *e; ++e)
+        for (const char* name : {"ROCPROF", "ROCP_", "HSA_TOOLS_LIB="})
+            if (std::strncmp(*e, name, std::strlen(name)) == 0) return true;
+    const char* direct = std::getenv("AMD_DIRECT_DISPATCH");
+    return direct && std::strcmp(direct, "0") == 0;
+}
+
+int look_at_object(dl_phdr_info* info, size_t, void* data) {
+    specache_ctx* ctx = (specache_ctx*)data;
+    const char* name = info->dlpi_name;
+    // (every HIP process has the library that tools register with, and markers alone hold nothing back)
+    if (name && std::strstr(name, "rocprofiler") && !std::strstr(name, "rocprofiler-register") && !std::strstr(name, "roctx"))
+        ctx->one_at_a_time = true;
+    ctx->objects_seen = info->dlpi_adds;
+    return 0;
+}
+
+int objects_loaded(dl_phdr_info* info, size_t, void* data) {
+    *(unsigned long long*)data = info->dlpi_adds;
+    return 1;   // the count comes with every object: one is enough
+}
+
+bool words_may_order(specache_ctx* ctx) {
+    if (!ctx->scores_by_word || ctx->events_wanted || ctx->one_at_a_time) return false;
+    unsigned long long loaded = 0;
+    dl_iterate_phdr(objects_loaded, &loaded);
+    if (loaded != ctx->objects_seen) dl_iterate_phdr(look_at_object, ctx);
+    return !ctx->one_at_a_time;
+}
 
 int check_ctx_layer(specache_ctx* ctx, int32_t layer) {
     if (!ctx) return SPECACHE_EINVAL;
@@ -449,15 +491,18 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
     }
     ctx->async_select = c.async_select == SPECACHE_SELECT_STREAM_OWN;
     ctx->select_on_gather = c.async_select == SPECACHE_SELECT_STREAM_GATHER;
-    // A profiler that collects counters (rocprofv3 --pmc, which sets this variable) runs the kernels of all queues one at a
-    // time.  The wait for a word is itself a kernel, and the one that stores the word would not start before it ended.
-    ctx->scores_by_word = std::getenv("ROCPROF_COUNTERS") == nullptr;
     if (ctx->select_on_gather) {
+        int waits = 0;
+        (void)hipDeviceGetAttribute(&waits, hipDeviceAttributeCanUseStreamWaitValue, ctx->device);
+        ctx->scores_by_word = waits != 0;
+        ctx->one_at_a_time = environment_names_a_tool();
         for (Layer& L : ctx->layers) {
             SPC_ALLOC(hipMalloc((void**)&L.keys, (size_t)rows * cap * 4));
             SPC_ALLOC(hipEventCreateWithFlags(&L.selected, kOrderEventFlags));
-            SPC_ALLOC(hipExtMallocWithFlags((void**)&L.scored_word, 8, hipMallocSignalMemory));
-            *L.scored_word = 0;
+            if (ctx->scores_by_word) {
+                SPC_ALLOC(hipExtMallocWithFlags((void**)&L.scored_word, 8, hipMallocSignalMemory));
+                *L.scored_word = 0;
+            }
         }
         const int parts = topk_parts((int)cap, c.topk);
         for (auto& ss : ctx->select_scratch) {
@@ -610,8 +655,11 @@ static int wait_for_keys_readers(specache_ctx* ctx, Layer& L, hipStream_t st) {
 // st waits for the layer's last scoring
 static int wait_for_scored(specache_ctx* ctx, Layer& L, hipStream_t st) {
     if (st == L.idx_ready_stream) return SPECACHE_OK;
-    if (L.scored_by_word) SPC_HIP(ctx, hipStreamWaitValue64(st, L.scored_word, L.scored_value, hipStreamWaitValueGte));
-    else SPC_HIP(ctx, hipStreamWaitEvent(st, L.idx_ready, 0));
+    if (!L.scored_by_word) {
+        SPC_HIP(ctx, hipStreamWaitEvent(st, L.idx_ready, 0));
+        return SPECACHE_OK;
+    }
+    SPC_HIP(ctx, hipStreamWaitValue64(st, L.scored_word, L.scored_value, hipStreamWaitValueGte));
     return SPECACHE_OK;
 }
 
@@ -868,7 +916,8 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     // Under capture the word is no order: a replayed merge stores the value of its capture again, and the selection's
     // stream, if it is not part of the capture, would wait at once for a value that only a replay stores.  An event it is.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool by_word = ctx->scores_by_word && hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+    const bool by_word = !captured && words_may_order(ctx);
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
         if (rows_pass) {
@@ -936,6 +985,19 @@ int specache_attend_static(specache_ctx* ctx, int32_t layer, const void* q, int3
     if (int rc = static_scratch_of_current_device(ctx, &base)) return rc;
     const AttendScratch st{base, nullptr, 0};
     return attend_impl(ctx, layer, q, n_rows, k_spec, v_spec, slot, out, stream, &st);
+}
+
+int specache_order_by_events(specache_ctx* ctx, int32_t enable) {
+    if (!ctx) return SPECACHE_EINVAL;
+    ctx->events_wanted = enable != 0;
+    return SPECACHE_OK;
+}
+
+int specache_debug_scored_by_word(specache_ctx* ctx, int32_t layer, int32_t* by_word) {
+    if (int rc = check_ctx_layer(ctx, layer)) return rc;
+    if (!by_word) return fail(ctx, SPECACHE_EINVAL, "null by_word");
+    *by_word = ctx->layers[layer].scored_by_word;
+    return SPECACHE_OK;
 }
 
 int specache_debug_fail_alloc(int32_t nth) {
