@@ -659,6 +659,11 @@ static int wait_for_scored(specache_ctx* ctx, Layer& L, hipStream_t st) {
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.idx_ready, 0));
         return SPECACHE_OK;
     }
+    // recorded into a graph the wait would be for a value long passed (waiting for an event from outside is an error there, too)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    SPC_HIP(ctx, hipStreamIsCapturing(st, &capture));
+    if (capture != hipStreamCaptureStatusNone)
+        return fail(ctx, SPECACHE_ESTATE, "the side stream is being captured and the layer was scored outside the capture");
     SPC_HIP(ctx, hipStreamWaitValue64(st, L.scored_word, L.scored_value, hipStreamWaitValueGte));
     return SPECACHE_OK;
 }

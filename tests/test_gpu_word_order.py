@@ -74,6 +74,30 @@ def test_replayed_step_leaves_later_selections_alone(steps, Hq, Hkv):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+def test_selection_in_a_capture_behind_scores_outside_it_is_refused(steps):
+    """As waiting for an event from outside a capture is: a recorded wait would be for a value long passed."""
+    import ctypes
+    import torch
+    s = steps()
+    want = s.eager()
+    hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    s.score()
+    torch.cuda.synchronize()
+    assert s.sc.debug_scored_by_word(0)
+    side, graph = ctypes.c_void_p(s.side.cuda_stream), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(side, 2) == 0         # relaxed
+    try:
+        with pytest.raises(binding.SpeCacheError) as e:
+            s.sc.select_gather(0, s.idx, -1, s.side)
+        assert e.value.code == binding.ESTATE
+    finally:
+        hip.hipStreamEndCapture(side, ctypes.byref(graph))
+        if graph.value:
+            hip.hipGraphDestroy(graph)
+    got = s.eager()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("variable,value", [("ROCPROF_COUNTERS", "pmc: SQ_WAVES"), ("ROCPROF_ADVANCED_THREAD_TRACE", "1"), ("ROCP_TOOL_LIBRARIES", "/x.so"),
                                             ("HSA_TOOLS_LIB", "/x.so"), ("AMD_DIRECT_DISPATCH", "0")])
 def test_steps_beside_a_tool_named_in_the_environment(monkeypatch, steps, variable, value):
