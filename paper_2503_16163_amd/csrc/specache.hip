@@ -923,8 +923,10 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
     const bool by_word = !captured && words_may_order(ctx);
+    bool scored_carried = false;
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
+        CarriedEvent scored(ctx, by_word || captured ? nullptr : L.idx_ready);
         if (rows_pass) {
             RowsArgs R{};
             R.at.q = (const uint16_t*)q;
@@ -949,18 +951,24 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
                                                   slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
                                                   v_spec, ctx->scratch, L.keys, ctx->logit_stride, keep ? ctx->logits : nullptr, st));
         }
+        scored_carried = scored.landed();
     }
     L.N = N1;   // only once the launch that copies the token is enqueued
     ctx->logits_kept = keep;
+    // the keys are complete here, in front of the merge: the event says so, or else the merge as it starts, and the selection on
+    // the side stream runs beside it
+    if (!by_word)
+        if (int rc = record_scored(ctx, L, layer, n_rows, st, scored_carried)) return rc;
     {
-        // the keys are complete when the merge starts: it says so, and the selection on the side stream runs beside it
         TimedLaunch t(ctx, st, SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
                                    slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec, v_spec,
                                    ctx->scratch, out, kAttendCombine, st, by_word ? Announce{L.scored_word, L.scored_value + 1} : Announce{}));
     }
-    if (by_word) ++L.scored_value;
-    if (int rc = record_scored(ctx, L, layer, n_rows, st, false, by_word)) return rc;
+    if (by_word) {
+        ++L.scored_value;
+        if (int rc = record_scored(ctx, L, layer, n_rows, st, false, true)) return rc;
+    }
     return record_attended(ctx, L, slot, st);
 }
 
