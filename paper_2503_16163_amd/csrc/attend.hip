@@ -440,6 +440,7 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
     A.q = (const uint16_t*)q;
     A.logits = logits;
     A.logits_out = nullptr;
+    A.q_out = nullptr;
     A.logit_stride = logit_stride;
     A.slot = slot;
     A.slot_idx = slot_idx;

@@ -8,6 +8,7 @@ struct AttendArgs {
     const uint16_t* q;         // [rows*NR][128]
     const float* logits;       // [rows*NR][logit_stride]
     float* logits_out;         // only the kernel that scores and attends in one pass: where to leave the logits, or null
+    uint16_t* q_out;           // that kernel, for several rows per KV head: where to leave a copy of q instead, or null
     size_t logit_stride;
     const uint16_t* slot;      // [rows][k][256] or null
     const int32_t* slot_idx;   // [rows][k] or null

@@ -406,6 +406,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     for (int rr = wave; rr < NR; rr += kWaves) {
         const uint32_t w = rr < nq ? reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * nq + rr) * kD)[lane] : 0u;
         reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
+        if constexpr (MODE == kRowsBoth)
+            if (A.q_out && chunk == 0 && rr < nq) reinterpret_cast<uint32_t*>(A.q_out + ((size_t)row * nq + rr) * kD)[lane] = w;
         if constexpr (MODE != kRowsAttend) {
             const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
             const float top = wave_max(fmaxf(fabsf(a), fabsf(b)));

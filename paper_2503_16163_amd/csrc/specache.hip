@@ -98,6 +98,7 @@ struct specache_ctx {
     TopkScratch topk_scratch{};
     int scored_layer = -1, scored_rows = 0, scored_N = 0, scored_Nq = 0;
     bool logits_kept = false;    // the last scoring pass left its logits in `logits` (the one-pass score + attend need not)
+    bool q_kept = false;         // it left a copy of its queries in `lse` instead (that buffer serves the other selection form)
     uint64_t seq = 0;            // counts the calls that order streams (see Layer)
     hipStream_t last_gather_stream = nullptr;   // stream of the previous specache_gather, of any layer
     bool last_gather_stream_set = false;
@@ -520,7 +521,10 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
     ctx->logit_stride = cap;
     SPC_ALLOC(hipMalloc((void**)&ctx->logits, (size_t)rows * G * 2 * cap * 4));
     SPC_ALLOC(hipMalloc((void**)&ctx->keys, (size_t)rows * cap * 4));
-    SPC_ALLOC(hipMalloc((void**)&ctx->lse, select_logprob_scratch_floats(rows, G, cap) * 4));
+    {
+        const size_t floats = select_logprob_scratch_floats(rows, G, cap), queries = (size_t)rows * G * 2 * kD / 2;
+        SPC_ALLOC(hipMalloc((void**)&ctx->lse, (floats > queries ? floats : queries) * 4));
+    }
     int max_main = 0;
     for (int n = 1; n <= 2; ++n) {
         const int ch = attend_main_chunk_tokens(G * n);
@@ -816,6 +820,15 @@ static int record_attended(specache_ctx* ctx, Layer& L, int slot, hipStream_t st
     return SPECACHE_OK;
 }
 
+// The logits of the last scoring pass from the copy of its queries that it left.
+static int score_again(specache_ctx* ctx, Layer& L, hipStream_t st) {
+    // (into ctx->keys: a selection on another stream may be reading the layer's own)
+    SPC_HIP(ctx, launch_score(L.view, ctx->lse, ctx->scored_rows, ctx->scored_Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride, ctx->keys,
+                              ctx->logit_stride, st));
+    ctx->logits_kept = true;
+    return SPECACHE_OK;
+}
+
 // specache_attend with the partial results in `scratch`: the context's own, or the static array
 static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t n_rows, const void* k_spec,
                        const void* v_spec, int32_t slot, float* out, void* stream, const AttendScratch* static_scratch) {
@@ -827,8 +840,8 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
     Layer& L = ctx->layers[layer];
     if (ctx->scored_layer != layer || ctx->scored_rows != n_rows || ctx->scored_N != L.N || ctx->scored_Nq != L.Nq)
         return fail(ctx, SPECACHE_ESTATE, "attend must follow score_topk of the same layer, n_rows and cache state");
-    // several query heads per KV head: the one-launch scoring and attention keeps no logits, an attend behind it scores again
-    const bool rescore = !ctx->logits_kept && rows_uses_matrix_cores(L.view, n_rows) && L.Nq > 0;
+    // several query heads per KV head: the one-launch scoring and attention keeps its queries, and an attend behind it scores again
+    const bool rescore = !ctx->logits_kept && ctx->q_kept;
     if (!ctx->logits_kept && !rescore)
         return fail(ctx, SPECACHE_ESTATE, "the last scoring pass of this layer was specache_score_attend, which keeps no logits");
     if (slot >= 0 && !L.slot_filled[slot]) return fail(ctx, SPECACHE_ESTATE, "slot was never gathered");
@@ -856,11 +869,8 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
     hipStream_t st = (hipStream_t)stream;
     if (slot >= 0 && L.gather_stream[slot] != st && !(L.gathered_waited_set[slot] && L.gathered_waited[slot] == st))
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
-    if (rescore) {
-        // (into ctx->keys: a selection on another stream may be reading the layer's own)
-        SPC_HIP(ctx, launch_score(L.view, q, n_rows, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride, ctx->keys, ctx->logit_stride, st));
-        ctx->logits_kept = true;
-    }
+    if (rescore)
+        if (int rc = score_again(ctx, L, st)) return rc;
     for (int phase : {kAttendPartial, kAttendCombine}) {
         TimedLaunch t(ctx, st, phase == kAttendPartial ? SPECACHE_K_ATTEND : SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
@@ -931,6 +941,7 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
             RowsArgs R{};
             R.at.q = (const uint16_t*)q;
             R.at.logits_out = keep ? ctx->logits : nullptr;
+            R.at.q_out = keep ? nullptr : (uint16_t*)ctx->lse;
             R.at.logit_stride = ctx->logit_stride;
             R.at.slot = slot >= 0 ? L.slot[slot] : nullptr;
             R.at.slot_idx = slot >= 0 ? L.slot_idx[slot] : nullptr;
@@ -955,6 +966,7 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     }
     L.N = N1;   // only once the launch that copies the token is enqueued
     ctx->logits_kept = keep;
+    ctx->q_kept = rows_pass && !keep;
     // the keys are complete here, in front of the merge: the event says so, or else the merge as it starts, and the selection on
     // the side stream runs beside it
     if (!by_word)
@@ -1100,8 +1112,13 @@ int specache_timing(specache_ctx* ctx, int32_t enable, double* total_us, int64_t
 int specache_debug_logits(specache_ctx* ctx, float* out) {
     if (!ctx || !out) return SPECACHE_EINVAL;
     if (ctx->scored_layer < 0) return fail(ctx, SPECACHE_ESTATE, "nothing scored yet");
-    if (!ctx->logits_kept) return fail(ctx, SPECACHE_ESTATE, "specache_score_attend kept no logits (see specache_debug_kernel_choice)");
+    if (!ctx->logits_kept && !ctx->q_kept)
+        return fail(ctx, SPECACHE_ESTATE, "specache_score_attend kept no logits (see specache_debug_kernel_choice)");
     SPC_HIP(ctx, hipDeviceSynchronize());
+    if (!ctx->logits_kept) {
+        if (int rc = score_again(ctx, ctx->layers[ctx->scored_layer], nullptr)) return rc;
+        SPC_HIP(ctx, hipDeviceSynchronize());
+    }
     const size_t n = (size_t)ctx->layers[ctx->scored_layer].view.rows * ctx->layers[ctx->scored_layer].view.G * ctx->scored_rows;
     const size_t Nq = ctx->scored_Nq;
     if (Nq == 0) return SPECACHE_OK;

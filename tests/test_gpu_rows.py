@@ -211,3 +211,27 @@ def test_rows_kernel_with_scales_far_apart(kind, dtype, B, Hq, Hkv, S, bits, g, 
     finally:
         c.close()
         binding.debug_kernel_choice(0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,bits,n_rows", [(8, 2, 2, 2), (4, 2, 1, 2), (8, 1, 2, 2), (8, 2, 1, 1)])
+def test_logits_after_the_one_launch_call(Hq, Hkv, bits, n_rows):
+    """The one launch of grouped-query heads keeps its queries in place of the logits: specache_debug_logits works them out from those,
+    also when the caller's buffer holds something else by then and the cache has grown."""
+    import torch
+    from tests.harness import Case, to_dev
+    c = Case(1, Hq, Hkv, 1700, synth.BF16, bits, 32, 48, seed=5700 + Hq, n_rows=n_rows, async_select=2, one_pass=True)
+    try:
+        c.load()
+        q_bits = synth.make_queries(c.seed, 1, Hq, 128, c.dtype, n_rows=n_rows)
+        q = to_dev(q_bits, c.dtype)
+        out = torch.empty((1, Hq, n_rows, 128), dtype=torch.float32, device="cuda")
+        want = [c.oc[0, h].scores(q_bits[0, h * c.G:(h + 1) * c.G], c.sm_scale)[0] for h in range(Hkv)]
+        c.sc.score_attend(0, q, n_rows, None, None, -1, out, torch.cuda.current_stream())
+        q.zero_()
+        c.append_token(0)
+        got = c.sc.debug_logits(0, n_rows)
+        for h in range(Hkv):
+            err = np.abs(got[0, h * c.G:(h + 1) * c.G] - want[h]).max(-1) / np.abs(want[h]).max(-1)
+            assert err.max() < LOGITS
+    finally:
+        c.close()
