@@ -221,9 +221,10 @@ bool environment_names_a_tool() {
 
 int look_at_object(dl_phdr_info* info, size_t, void* data) {
     specache_ctx* ctx = (specache_ctx*)data;
-    const char* name = info->dlpi_name;
+    const char* slash = info->dlpi_name ? std::strrchr(info->dlpi_name, '/') : nullptr;
+    const char* name = slash ? slash + 1 : info->dlpi_name ? info->dlpi_name : "";
     // (every HIP process has the library that tools register with, and markers alone hold nothing back)
-    if (name && std::strstr(name, "rocprofiler") && !std::strstr(name, "rocprofiler-register") && !std::strstr(name, "roctx"))
+    if (std::strncmp(name, "librocprofiler", 14) == 0 && !std::strstr(name, "-register") && !std::strstr(name, "roctx"))
         ctx->one_at_a_time = true;
     ctx->objects_seen = info->dlpi_adds;
     return 0;
@@ -497,6 +498,7 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         (void)hipDeviceGetAttribute(&waits, hipDeviceAttributeCanUseStreamWaitValue, ctx->device);
         ctx->scores_by_word = waits != 0;
         ctx->one_at_a_time = environment_names_a_tool();
+        dl_iterate_phdr(look_at_object, ctx);
         for (Layer& L : ctx->layers) {
             SPC_ALLOC(hipMalloc((void**)&L.keys, (size_t)rows * cap * 4));
             SPC_ALLOC(hipEventCreateWithFlags(&L.selected, kOrderEventFlags));
