@@ -358,7 +358,7 @@ def profile_figures(workload_key, kernel_names):
     """HBM traffic and vector-instruction counts per launch from the committed rocprofv3 --pmc summaries
     (written by paper_2503_16163_amd.profile_summary).  A figure is quoted only for a kernel whose sources still
     hash to what the file recorded for it."""
-    from paper_2503_16163_amd import build as hip_build
+    from paper_2503_16163_amd import profile_summary
     res = {}
     for key, fname in (("traffic", "traffic.json"), ("valu", "valu.json")):
         path = os.path.join(ROOT, "profiles", fname)
@@ -372,7 +372,7 @@ def profile_figures(workload_key, kernel_names):
         for n in kernel_names:
             if w.get(n) is None:
                 continue
-            if hashes.get(n) == hip_build.kernel_source_hash(n.split("+")[0]):
+            if hashes.get(n) == profile_summary.hash_of(n):
                 tbl[n] = w[n]
             else:
                 stale.append(n)
@@ -460,7 +460,7 @@ def main():
         sys.exit(2)
 
     import torch
-    from paper_2503_16163_amd import binding, synth
+    from paper_2503_16163_amd import arrangement, binding, synth
 
     assert torch.cuda.is_available(), "bench.py needs an MI355X"
     torch.cuda.set_device(0)
@@ -477,10 +477,12 @@ def main():
     bits = args.bits or bits
     G, D = Hq // Hkv, 128
     spec = args.variant == "speculative"
-    one_pass_kernel = G == 1 and bits in (1, 2) and spec and args.select_cache == "lowbit" and not args.vector_alu
+    valu = {"both": ("score", "attend")}.get(args.vector_alu, (args.vector_alu,) if args.vector_alu else ())
+    score_name, attend_name, one_pass_key = arrangement.step_kernels(G, 2 if spec else 1, bits, valu)
+    one_pass_kernel = (one_pass_key is not None and spec and args.select_cache == "lowbit" and not args.vector_alu and
+                       (G == 1 or args.select != "logprob"))
     calls = args.calls
     if calls == "auto":
-        from paper_2503_16163_amd import arrangement
         calls = arrangement.plan(B, Hkv, G, S, k, layers, bits, spec, args.select_cache == "lowbit")["calls"]
         # options that name another arrangement than the rule's
         if calls == "one-pass" and (not one_pass_kernel or args.serial_gather or args.fused_append or
@@ -533,13 +535,7 @@ def main():
     pairs = rows * ((k if not args.no_gather else 0) + (N - Nq) + 1) * 512   # staged, residual and transient 16-bit pairs
     us_layer = ms_per_step * 1e3 / layers
     n_q_rows = G * (2 if spec else 1)
-    on_rows_kernel = n_q_rows % 8 == 0 or bits == 4
-    score_name = ("rows_kernel" if on_rows_kernel else
-                  "score_i8_kernel" if (G == 1 and spec and args.vector_alu not in ("score", "both")) else "score_kernel")
-    attend_name = ("rows_kernel<attention>" if on_rows_kernel else
-                   "attend_i8_kernel" if (G == 1 and spec and bits in (1, 2) and args.vector_alu not in ("attend", "both"))
-                   else "attend_partial_kernel")
-    one_pass_name = ("attend_i8_kernel" if G == 1 else "rows_kernel") + "<scoring pass in front>"
+    one_pass_name = one_pass_key.split("+")[0] + "<scoring pass in front>" if one_pass_key else None
     stream_peak = peaks["hbm_stream_peak_gbs"]
     link_peak = peaks["link_peak_gbs"]
 
@@ -575,12 +571,12 @@ def main():
     # the dominant streaming kernel of the main stream
     cands = [e for e in kern if e["kernel"] in (one_pass_name, score_name, attend_name)]
     dom = max(cands, key=lambda e: e["avg_us"])
-    dom_base = dom["kernel"].split("<")[0] + ("+score" if dom["kernel"] == one_pass_name else "")
+    dom_base = one_pass_key if dom["kernel"] == one_pass_name else dom["kernel"]
     workload_key = f"{args.workload}:k{k}:g{g}:b{bits}" + (f":S{S}" if args.seq else "")
     prof = profile_figures(workload_key, [dom_base, score_name, attend_name, "topk_kernel", "gather_kernel", "attend_combine_kernel"])
     traffic_tbl, traffic_src = prof["traffic"]
     for e in kern:   # measured HBM bytes per launch beside the algorithmic ones, where the profile covers the kernel
-        base = e["kernel"].split("<")[0] + ("+score" if e["kernel"] == one_pass_name else "")
+        base = one_pass_key if e["kernel"] == one_pass_name else e["kernel"]
         if traffic_tbl.get(base) is not None:
             e["traffic"] = traffic_tbl[base]
     roofline = {"bound": "hbm", "kernel": dom["kernel"], "achieved": dom["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",

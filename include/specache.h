@@ -107,7 +107,8 @@ typedef struct specache_config {
                            key array of its own (4 bytes per cached position and KV head)
                            and a layer-step needs two event records and two event waits
                            between the streams, against three and four with 1; each
-                           costs the issuing thread several microseconds                */
+                           costs the issuing thread several microseconds (one of the two
+                           is a word in memory where specache_order_by_events allows)   */
 } specache_config;
 
 enum { SPECACHE_SELECT_STREAM_CALLER = 0, SPECACHE_SELECT_STREAM_OWN = 1, SPECACHE_SELECT_STREAM_GATHER = 2 };
@@ -245,13 +246,20 @@ int specache_attend(specache_ctx* ctx, int32_t layer, const void* q, int32_t n_r
  * A = Softmax(Q K^T) on the mixed cache and O = A V, with the low-bit logits of both rows computed
  * on the way and the speculative row's selection keys left for the following
  * specache_select_gather (which may be enqueued right after this call: the slot it fills is the
- * other one).  With one query head per KV head, two query rows, 1- or 2-bit codes and selection on the
- * low-bit logits, one pass over a chunk of 512 positions reads its packed keys, keeps the logits
- * on the chip, and reads its packed values: the logits never travel to memory and back, and the
- * layer-step has one launch less.  Every other shape or option runs the two calls one after the
- * other.  Results are those of the two calls (the attention output to the 2e-3 bar: the softmax
- * partials are formed per 128 positions instead of per 512); specache_debug_logits afterwards
- * needs SPECACHE_KEEP_ONE_PASS_LOGITS.  Arguments as in specache_score and specache_attend.
+ * other one).  One launch reads the packed keys and values of a chunk of positions once and keeps the logits on the
+ * chip, so that they never travel to memory and back and the layer-step has one launch less:
+ *   - 1- or 2-bit codes and selection on the low-bit logits, with one query head per KV head and two query rows, or
+ *     with 4, 8 or 16 query rows per KV head (2 to 8 heads; of those with SPECACHE_SELECT_MAX_LOGIT only).
+ * Every other shape or option, and a layer with nothing quantised yet, runs the two calls one after the other.  Results
+ * are those of the two calls (the attention output to the 2e-3 bar: the softmax partials are formed over other ranges
+ * of positions, 128 with one query head, as many as fill the chip with several).
+ * After the one launch: with several heads a copy of the queries stays in the context, from which specache_debug_logits
+ * and a specache_attend of the same layer, n_rows and cache state work the logits out once more (the low-bit part of that
+ * attend is then of the queries given here, the 16-bit part of its own q); with one head both need
+ * SPECACHE_KEEP_ONE_PASS_LOGITS (ESTATE otherwise).
+ * How the selection is ordered behind the scores: see specache_order_by_events.  A select_gather or gather whose stream is
+ * being captured while the layer was scored outside the capture is an error (EHIP or ESTATE).
+ * Arguments as in specache_score and specache_attend.
  * Errors: those of the two calls.
  */
 int specache_score_attend(specache_ctx* ctx, int32_t layer, const void* q, int32_t n_rows, const void* k_spec,
@@ -328,7 +336,7 @@ int specache_attend_static(specache_ctx* ctx, int32_t layer, const void* q, int3
  *   v_codes u8 [B,Hkv,Nq,128], v_minmax u16 [B,Hkv,Nq,128/g,2], v_scale_zero f32 [...,2]
  * specache_export_rows: 16-bit rows [first, first+count) of the host store C,
  *   out u16 [B,Hkv,count,2,128] (K row then V row per token).
- * specache_debug_logits: the logits kept by the last specache_score_topk,
+ * specache_debug_logits: the logits of the last scoring call (see specache_score_attend for those of the one launch),
  *   out f32 [B,Hq,n_rows,Nq].
  */
 int specache_export_quantized(specache_ctx* ctx, int32_t layer, uint8_t* k_codes, uint16_t* k_minmax,

@@ -54,6 +54,18 @@ def main_us(rows, S, G=1):
     return max(33.0, 22.0 + 19.8 * rows * S / 1e6)
 
 
+def step_kernels(G, n_rows, bits, valu=()):
+    """Names of the kernels that score, attend and do both in one launch (None: no such launch) for G query heads per KV head and
+    n_rows query rows each, as profile_summary.short_name gives them: the library's own dispatch (rows_uses_matrix_cores in
+    csrc/rows_mfma.hip, then the int8 kernels).  valu: those of "score" and "attend" that are held to the vector ALUs."""
+    if G * n_rows >= 4 or bits == 4:
+        return "rows_kernel", "rows_kernel<attention>", "rows_kernel+score" if bits != 4 else None
+    i8 = G == 1 and n_rows == 2
+    return ("score_i8_kernel" if i8 and "score" not in valu else "score_kernel",
+            "attend_i8_kernel" if i8 and "attend" not in valu else "attend_partial_kernel",
+            "attend_i8_kernel+score" if i8 and not valu else None)
+
+
 def plan(B, Hkv, G, S, k, layers, bits=2, speculative=True, select_lowbit=True):
     """-> dict(calls, async_select, side_streams, carry_append).  calls: "one-pass" ([quantize_append,]
     score_attend or append_score_attend, select_gather), "split" (quantize_append, score, select_gather, attend)

@@ -22,12 +22,12 @@
 namespace specache {
 namespace {
 
-__host__ __device__ constexpr int main_chunk(int NR) { return NR <= 8 ? 512 : 256; }
+constexpr int kMainChunk = 512;   // quantised positions per workgroup
 
 template <int BITS, int GROUP, int G, int NROWS, bool BF16>
 __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, AttendArgs A) {
     constexpr int NR = G * NROWS;
-    constexpr int CH = main_chunk(NR);
+    constexpr int CH = kMainChunk;
     constexpr int M = kD / GROUP;            // value groups per token
     constexpr int CPB = 8 / BITS;            // channels per code byte (per lane)
     constexpr int LPB = 32 * BITS;           // lanes per 32-token block
@@ -44,7 +44,6 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     // the one region, and LDS per workgroup decides how many chunks are resident per compute unit
     constexpr int kExtra = extra_chunk_floats(NR);
     constexpr int kMax1 = kExtra > kPs ? kExtra : kPs;
-    constexpr int RH = NR;
     constexpr int kRegion = kMax1 > kOl ? kMax1 : kOl;
     __shared__ __attribute__((aligned(16))) float smem[kRegion];
     __shared__ float red[kWaves * NR * (1 + M)];
@@ -209,72 +208,67 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
             l_row[r] = v;
         }
 
-        {
-            // sum_i (p_i s_i) code[i][c] for this lane's CPB channels, all (at most four) query rows
-            for (int r0 = 0; r0 < NR; r0 += RH) {
-                float acc[CPB][RH];
-    #pragma unroll
-                for (int j = 0; j < CPB; ++j)
-    #pragma unroll
-                    for (int r = 0; r < RH; ++r) acc[j][r] = 0.0f;
-                uint4 w4 = w4_first;
-                if (r0 > 0 && tid < units) w4 = *reinterpret_cast<const uint4*>(vc_lane + (size_t)(tid / LPB) * code_block_bytes(BITS));
-                for (int u = tid; u < units; u += kThreads) {
-                    const int blk = u / LPB;
-                    uint4 w4n = make_uint4(0, 0, 0, 0);   // next iteration's codes, in flight during this one's arithmetic
-                    if (u + kThreads < units)
-                        w4n = *reinterpret_cast<const uint4*>(vc_lane + (size_t)((u + kThreads) / LPB) * code_block_bytes(BITS));
-                    const int hb = blk * 2 + within / (16 * BITS);   // 16-token half block inside the chunk
-                    const float* psb = ps + (hb * M + mgrp) * kCell + r0;
-    #pragma unroll
-                    for (int dq = 0; dq < 4; ++dq) {
-                        const uint32_t w = comp(w4, dq);
-                        float pv[4][RH];
-    #pragma unroll
-                        for (int b = 0; b < 4; ++b)
-    #pragma unroll
-                            for (int r = 0; r < RH; ++r) pv[b][r] = psb[(dq * 4 + b) * NR + r];
-    #pragma unroll
-                        for (int j = 0; j < CPB; ++j) {
-                            const uint32_t mk = w & (MASK << (BITS * j));
-                            const float f0 = cvt_ubyte<0>(mk), f1 = cvt_ubyte<1>(mk), f2 = cvt_ubyte<2>(mk), f3 = cvt_ubyte<3>(mk);
-    #pragma unroll
-                            for (int r = 0; r < RH; ++r) {
-                                acc[j][r] = __builtin_fmaf(f0, pv[0][r], acc[j][r]);
-                                acc[j][r] = __builtin_fmaf(f1, pv[1][r], acc[j][r]);
-                                acc[j][r] = __builtin_fmaf(f2, pv[2][r], acc[j][r]);
-                                acc[j][r] = __builtin_fmaf(f3, pv[3][r], acc[j][r]);
-                            }
-                        }
+        // sum_i (p_i s_i) code[i][c] for this lane's CPB channels
+        float acc[CPB][NR];
+#pragma unroll
+        for (int j = 0; j < CPB; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[j][r] = 0.0f;
+        uint4 w4 = w4_first;
+        for (int u = tid; u < units; u += kThreads) {
+            const int blk = u / LPB;
+            uint4 w4n = make_uint4(0, 0, 0, 0);   // next iteration's codes, in flight during this one's arithmetic
+            if (u + kThreads < units)
+                w4n = *reinterpret_cast<const uint4*>(vc_lane + (size_t)((u + kThreads) / LPB) * code_block_bytes(BITS));
+            const int hb = blk * 2 + within / (16 * BITS);   // 16-token half block inside the chunk
+            const float* psb = ps + (hb * M + mgrp) * kCell;
+#pragma unroll
+            for (int dq = 0; dq < 4; ++dq) {
+                const uint32_t w = comp(w4, dq);
+                float pv[4][NR];
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) pv[b][r] = psb[(dq * 4 + b) * NR + r];
+#pragma unroll
+                for (int j = 0; j < CPB; ++j) {
+                    const uint32_t mk = w & (MASK << (BITS * j));
+                    const float f0 = cvt_ubyte<0>(mk), f1 = cvt_ubyte<1>(mk), f2 = cvt_ubyte<2>(mk), f3 = cvt_ubyte<3>(mk);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        acc[j][r] = __builtin_fmaf(f0, pv[0][r], acc[j][r]);
+                        acc[j][r] = __builtin_fmaf(f1, pv[1][r], acc[j][r]);
+                        acc[j][r] = __builtin_fmaf(f2, pv[2][r], acc[j][r]);
+                        acc[j][r] = __builtin_fmaf(f3, pv[3][r], acc[j][r]);
                     }
-                    w4 = w4n;
-                }
-                // codes arrived scaled by 2^(BITS*j); lanes with equal Lc hold the same channels
-    #pragma unroll
-                for (int j = 0; j < CPB; ++j)
-    #pragma unroll
-                    for (int r = 0; r < RH; ++r) {
-                        float v = acc[j][r] * __uint_as_float((uint32_t)(127 - BITS * j) << 23);
-    #pragma unroll
-                        for (int mask = 32; mask >= 16 * BITS; mask >>= 1) v += __shfl_xor(v, mask, 64);
-                        acc[j][r] = v;
-                    }
-                __syncthreads();   // o_lds shares the region with ps: everyone is done with ps
-                if (lane < 16 * BITS) {
-    #pragma unroll
-                    for (int j = 0; j < CPB; ++j)
-    #pragma unroll
-                        for (int r = 0; r < RH; ++r) o_lds[((size_t)wave * NR + r0 + r) * kD + Lc * CPB + j] = acc[j][r];
                 }
             }
-            __syncthreads();
-            for (int e = tid; e < NR * kD; e += kThreads) {
-                const int r = e / kD, c = e % kD;
-                float v = 0.0f;
-    #pragma unroll
-                for (int w = 0; w < kWaves; ++w) v += o_lds[((size_t)w * NR + r) * kD + c] + red_z[(w * NR + r) * M + c / GROUP];
-                po[e] = v;
+            w4 = w4n;
+        }
+        // codes arrived scaled by 2^(BITS*j); lanes with equal Lc hold the same channels
+#pragma unroll
+        for (int j = 0; j < CPB; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                float v = acc[j][r] * __uint_as_float((uint32_t)(127 - BITS * j) << 23);
+#pragma unroll
+                for (int mask = 32; mask >= 16 * BITS; mask >>= 1) v += __shfl_xor(v, mask, 64);
+                acc[j][r] = v;
             }
+        __syncthreads();   // o_lds shares the region with ps: everyone is done with ps
+        if (lane < 16 * BITS) {
+#pragma unroll
+            for (int j = 0; j < CPB; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) o_lds[((size_t)wave * NR + r) * kD + Lc * CPB + j] = acc[j][r];
+        }
+        __syncthreads();
+        for (int e = tid; e < NR * kD; e += kThreads) {
+            const int r = e / kD, c = e % kD;
+            float v = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) v += o_lds[((size_t)w * NR + r) * kD + c] + red_z[(w * NR + r) * M + c / GROUP];
+            po[e] = v;
         }
     } else {
         attend_extra_chunk<NR, NROWS, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
@@ -412,7 +406,7 @@ template <int BITS, int GROUP>
 hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, float* out, int phases, Announce announce, hipStream_t stream) {
 #define SPC_CASE(g_, n_)                                                        \
     if (L.G == g_ && n_rows == n_) {                                            \
-        A.n_main = (A.Nq + main_chunk(g_ * n_) - 1) / main_chunk(g_ * n_);      \
+        A.n_main = (A.Nq + kMainChunk - 1) / kMainChunk;                        \
         const int n_extra = (n_ex + kExtraChunk - 1) / kExtraChunk;             \
         A.n_chunks = A.n_main + n_extra;                                        \
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
@@ -425,9 +419,12 @@ hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, floa
 
 }  // namespace
 
-int attend_main_chunk_tokens(int NR) { return main_chunk(NR); }
+// What the limits of specache_create and specache_attend_static are stated in: the chunks above, half as long with 16 rows
+// (rows_kernel splits a row as the room allows).
+int attend_main_chunk_tokens(int NR) { return NR <= 8 ? kMainChunk : kMainChunk / 2; }
 int attend_chunks(int NR, int Nq, int n_16bit) {
-    return (Nq + main_chunk(NR) - 1) / main_chunk(NR) + (n_16bit + kExtraChunk - 1) / kExtraChunk;
+    const int chunk = attend_main_chunk_tokens(NR);
+    return (Nq + chunk - 1) / chunk + (n_16bit + kExtraChunk - 1) / kExtraChunk;
 }
 int attend_extra_chunk_tokens() { return kExtraChunk; }
 int attend_max_chunks() { return kCombineMaxChunks; }

@@ -14,7 +14,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kExtraChunk = 128;
 
-
 template <int B>
 __device__ __forceinline__ float cvt_ubyte(uint32_t w) {
     float f;
@@ -32,12 +31,6 @@ __device__ __forceinline__ uint32_t comp(const uint4& v, int i) { return i == 0 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-
-// two bytes of w, each widened to 16 bits: a small integer n read as f16 is the subnormal n * 2^-24
-template <int HI>
-__device__ __forceinline__ uint32_t bytes_to_halves(uint32_t w) {
-    return __builtin_amdgcn_perm(0u, w, HI ? 0x0c030c02u : 0x0c010c00u);
-}
 
 // Wave-wide reductions on the VALU: four DPP steps leave every lane with its 16-lane row's
 // result, the four row results are then read as scalars.  (A butterfly of ds_bpermute

@@ -107,8 +107,8 @@ struct Announce {
     uint64_t* word = nullptr;
     uint64_t value = 0;
 };
-int attend_main_chunk_tokens(int NR);
-// chunks the partial pass writes for NR query rows per KV head, Nq quantised and n_16bit 16-bit candidates
+int attend_main_chunk_tokens(int NR);   // for the limits of specache_create and specache_attend_static
+// the chunks that such a limit allows for NR query rows per KV head, Nq quantised and n_16bit 16-bit candidates
 int attend_chunks(int NR, int Nq, int n_16bit);
 int attend_extra_chunk_tokens();
 int attend_max_chunks();   // chunks per row the merge kernel handles

@@ -53,7 +53,6 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
                                                                  size_t logit_stride, uint32_t* __restrict__ keys,
                                                                  size_t key_stride) {
     constexpr int NR = G * NROWS;              // query rows sharing this KV head
-    constexpr int RH = NR;
     static_assert(NR <= 2, "4, 8 and 16 rows: rows_mfma.h");
     constexpr int HPD = (32 / BITS) / 4;       // masks (= multiplier registers) per code dword
     constexpr int NW = 4 * BITS;               // code dwords per token
@@ -64,10 +63,10 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
     // query rows in quad layout [row][channel % 4][channel / 4], rows of 32 padded to 36 floats so
     // that the four quad lanes read different banks
     __shared__ __attribute__((aligned(16))) float qfq[NR][4][36];
-    // Per wave: first the multipliers of a pass, [sub-group][mask][channel % 4][row] with the
+    // Per wave: first the multipliers, [sub-group][mask][channel % 4][row] with the
     // sub-groups 8 floats apart in bank space; once it has scored its share, its partial sums.
-    constexpr int kMultQuad = WPW * HPD * 4 * RH + 8;
-    constexpr int kWaveFloats = 16 * kMultQuad > kTok * RH * 64 ? 16 * kMultQuad : kTok * RH * 64;
+    constexpr int kMultQuad = WPW * HPD * 4 * NR + 8;
+    constexpr int kWaveFloats = 16 * kMultQuad > kTok * NR * 64 ? 16 * kMultQuad : kTok * NR * 64;
     __shared__ __attribute__((aligned(16))) float wsm[kScoreWaves][kWaveFloats];
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, k = lane & 3;
@@ -105,131 +104,128 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_kernel(LayerView L, co
 #pragma unroll
     for (int t = 0; t < TPW; ++t) best[t] = -INFINITY;
 
-    constexpr int r0 = 0;
-    {
-        // Every lane folds the multipliers of its channel class for all masks of this wave and
-        // leaves them in LDS, from where the four lanes of the quad read all four classes back:
-        // the lanes of a wave run in lockstep and LDS serves one wave's accesses in order, so
-        // no workgroup barrier is involved.
-        float qz[RH];
+    // Every lane folds the multipliers of its channel class for all masks of this wave and
+    // leaves them in LDS, from where the four lanes of the quad read all four classes back:
+    // the lanes of a wave run in lockstep and LDS serves one wave's accesses in order, so
+    // no workgroup barrier is involved.
+    float qz[NR];
 #pragma unroll
-        for (int r = 0; r < RH; ++r) qz[r] = 0.0f;
+    for (int r = 0; r < NR; ++r) qz[r] = 0.0f;
 #pragma unroll
-        for (int i = 0; i < WPW; ++i) {
-            const int W = wave * WPW + i;
+    for (int i = 0; i < WPW; ++i) {
+        const int W = wave * WPW + i;
 #pragma unroll
-            for (int h = 0; h < HPD; ++h) {
-                const uint32_t m = comp(mt[i][h / 4], h % 4);
-                float sc, z;
-                derive_scale_zero<BITS>(widen16<BF16>(m & 0xFFFFu), widen16<BF16>(m >> 16), L.one_bit_plain, sc, z);
-                // the codes of mask h arrive scaled by 2^(BITS*h)
-                const float sf = sc * __uint_as_float((uint32_t)(127 - BITS * h) << 23);
-                float qs[RH];
+        for (int h = 0; h < HPD; ++h) {
+            const uint32_t m = comp(mt[i][h / 4], h % 4);
+            float sc, z;
+            derive_scale_zero<BITS>(widen16<BF16>(m & 0xFFFFu), widen16<BF16>(m >> 16), L.one_bit_plain, sc, z);
+            // the codes of mask h arrive scaled by 2^(BITS*h)
+            const float sf = sc * __uint_as_float((uint32_t)(127 - BITS * h) << 23);
+            float qs[NR];
 #pragma unroll
-                for (int r = 0; r < RH; ++r) {
-                    const float qv = qfq[r0 + r][k][HPD * W + h];
-                    qs[r] = qv * sf;
-                    qz[r] = __builtin_fmaf(qv, z, qz[r]);
-                }
-                float* dst = mq + ((i * HPD + h) * 4 + k) * RH;
-                if constexpr (RH == 2) *reinterpret_cast<float2*>(dst) = make_float2(qs[0], qs[1]);
-                else dst[0] = qs[0];
+            for (int r = 0; r < NR; ++r) {
+                const float qv = qfq[r][k][HPD * W + h];
+                qs[r] = qv * sf;
+                qz[r] = __builtin_fmaf(qv, z, qz[r]);
             }
+            float* dst = mq + ((i * HPD + h) * 4 + k) * NR;
+            if constexpr (NR == 2) *reinterpret_cast<float2*>(dst) = make_float2(qs[0], qs[1]);
+            else dst[0] = qs[0];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        float acc[kTok][RH];
+    float acc[kTok][NR];
 #pragma unroll
-        for (int s = 0; s < kTok; ++s)
+    for (int s = 0; s < kTok; ++s)
 #pragma unroll
-            for (int r = 0; r < RH; ++r) acc[s][r] = 0.0f;
+        for (int r = 0; r < NR; ++r) acc[s][r] = 0.0f;
 #pragma unroll
-        for (int i = 0; i < WPW; ++i) {
+    for (int i = 0; i < WPW; ++i) {
 #pragma unroll
-            for (int h = 0; h < HPD; ++h) {
-                float b[4][RH];
-                const float* src = mq + (i * HPD + h) * 4 * RH;
+        for (int h = 0; h < HPD; ++h) {
+            float b[4][NR];
+            const float* src = mq + (i * HPD + h) * 4 * NR;
 #pragma unroll
-                for (int v = 0; v < RH; ++v) {   // RH 16-byte reads cover [4 channel classes][RH rows]
-                    const float4 t = *reinterpret_cast<const float4*>(src + 4 * v);
-                    const float tv[4] = {t.x, t.y, t.z, t.w};
+            for (int v = 0; v < NR; ++v) {   // NR 16-byte reads cover [4 channel classes][NR rows]
+                const float4 t = *reinterpret_cast<const float4*>(src + 4 * v);
+                const float tv[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) b[(4 * v + e) / RH][(4 * v + e) % RH] = tv[e];
-                }
-                float f[kTok][4];
+                for (int e = 0; e < 4; ++e) b[(4 * v + e) / NR][(4 * v + e) % NR] = tv[e];
+            }
+            float f[kTok][4];
+#pragma unroll
+            for (int s = 0; s < kTok; ++s) {
+                const uint32_t mk = comp(cw[i][s / 4], s % 4) & (MASK << (BITS * h));
+                f[s][0] = cvt_ubyte<0>(mk);
+                f[s][1] = cvt_ubyte<1>(mk);
+                f[s][2] = cvt_ubyte<2>(mk);
+                f[s][3] = cvt_ubyte<3>(mk);
+            }
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
 #pragma unroll
                 for (int s = 0; s < kTok; ++s) {
-                    const uint32_t mk = comp(cw[i][s / 4], s % 4) & (MASK << (BITS * h));
-                    f[s][0] = cvt_ubyte<0>(mk);
-                    f[s][1] = cvt_ubyte<1>(mk);
-                    f[s][2] = cvt_ubyte<2>(mk);
-                    f[s][3] = cvt_ubyte<3>(mk);
+                    acc[s][r] = __builtin_fmaf(f[s][0], b[0][r], acc[s][r]);
+                    acc[s][r] = __builtin_fmaf(f[s][1], b[1][r], acc[s][r]);
+                    acc[s][r] = __builtin_fmaf(f[s][2], b[2][r], acc[s][r]);
+                    acc[s][r] = __builtin_fmaf(f[s][3], b[3][r], acc[s][r]);
                 }
-#pragma unroll
-                for (int r = 0; r < RH; ++r)
-#pragma unroll
-                    for (int s = 0; s < kTok; ++s) {
-                        acc[s][r] = __builtin_fmaf(f[s][0], b[0][r], acc[s][r]);
-                        acc[s][r] = __builtin_fmaf(f[s][1], b[1][r], acc[s][r]);
-                        acc[s][r] = __builtin_fmaf(f[s][2], b[2][r], acc[s][r]);
-                        acc[s][r] = __builtin_fmaf(f[s][3], b[3][r], acc[s][r]);
-                    }
-            }
         }
-        // the zero-point term of this wave's channels: sum over the quad's four channel classes
+    }
+    // the zero-point term of this wave's channels: sum over the quad's four channel classes
 #pragma unroll
-        for (int r = 0; r < RH; ++r) {
-            float v = qz[r];
-            v += dpp_move<0xB1>(v);   // quad lanes 1 apart
-            v += dpp_move<0x4E>(v);   // quad lanes 2 apart
+    for (int r = 0; r < NR; ++r) {
+        float v = qz[r];
+        v += dpp_move<0xB1>(v);   // quad lanes 1 apart
+        v += dpp_move<0x4E>(v);   // quad lanes 2 apart
 #pragma unroll
-            for (int s = 0; s < kTok; ++s) acc[s][r] += v;
+        for (int s = 0; s < kTok; ++s) acc[s][r] += v;
+    }
+    // swap partial sums (the area is this wave's own: its multiplier reads are behind it)
+#pragma unroll
+    for (int s = 0; s < kTok; ++s)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) wsm[wave][(s * NR + r) * 64 + lane] = acc[s][r];
+    __syncthreads();
+    if constexpr (kRowSplit) {
+        // one KV head per query head, two rows: wave = (row, half of the lane's tokens), so that
+        // logits and keys leave as 16-byte stores; the keys are the speculative row's alone
+        const int r = wave & 1, hf = wave >> 1;
+        float o[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int s = 4 * hf + t;
+            float v = wsm[0][(s * NR + r) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < kScoreWaves; ++w) v += wsm[w][(s * NR + r) * 64 + lane];
+            o[t] = v;
         }
-        // swap partial sums (the area is this wave's own: its multiplier reads are behind it)
+        if (active) {
+            const int i4 = sub * kBlockTokens + kTok * k + 4 * hf;
+            *reinterpret_cast<float4*>(logits + ((size_t)row * NR + r) * logit_stride + i4) = make_float4(o[0], o[1], o[2], o[3]);
+            if (r == NROWS - 1)
+                *reinterpret_cast<uint4*>(keys + (size_t)row * key_stride + i4) =
+                    make_uint4(float_to_key(o[0]), float_to_key(o[1]), float_to_key(o[2]), float_to_key(o[3]));
+        }
+    } else {
 #pragma unroll
-        for (int s = 0; s < kTok; ++s)
+        for (int r = 0; r < NR; ++r) {
+            float o[TPW];
 #pragma unroll
-            for (int r = 0; r < RH; ++r) wsm[wave][(s * RH + r) * 64 + lane] = acc[s][r];
-        __syncthreads();
-        if constexpr (kRowSplit) {
-            // one KV head per query head, two rows: wave = (row, half of the lane's tokens), so that
-            // logits and keys leave as 16-byte stores; the keys are the speculative row's alone
-            const int r = wave & 1, hf = wave >> 1;
-            float o[4];
+            for (int t = 0; t < TPW; ++t) {
+                const int s = TPW * wave + t;
+                float v = wsm[0][(s * NR + r) * 64 + lane];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int s = 4 * hf + t;
-                float v = wsm[0][(s * RH + r) * 64 + lane];
-#pragma unroll
-                for (int w = 1; w < kScoreWaves; ++w) v += wsm[w][(s * RH + r) * 64 + lane];
+                for (int w = 1; w < kScoreWaves; ++w) v += wsm[w][(s * NR + r) * 64 + lane];
                 o[t] = v;
+                if (r % NROWS == NROWS - 1) best[t] = fmaxf(best[t], v);
             }
-            if (active) {
-                const int i4 = sub * kBlockTokens + kTok * k + 4 * hf;
-                *reinterpret_cast<float4*>(logits + ((size_t)row * NR + r) * logit_stride + i4) = make_float4(o[0], o[1], o[2], o[3]);
-                if (r == NROWS - 1)
-                    *reinterpret_cast<uint4*>(keys + (size_t)row * key_stride + i4) =
-                        make_uint4(float_to_key(o[0]), float_to_key(o[1]), float_to_key(o[2]), float_to_key(o[3]));
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < RH; ++r) {
-                float o[TPW];
-#pragma unroll
-                for (int t = 0; t < TPW; ++t) {
-                    const int s = TPW * wave + t;
-                    float v = wsm[0][(s * RH + r) * 64 + lane];
-#pragma unroll
-                    for (int w = 1; w < kScoreWaves; ++w) v += wsm[w][(s * RH + r) * 64 + lane];
-                    o[t] = v;
-                    if ((r0 + r) % NROWS == NROWS - 1) best[t] = fmaxf(best[t], v);
-                }
-                static_assert(TPW == 2, "one 8-byte store per lane and row");
-                if (active)
-                    *reinterpret_cast<float2*>(logits + ((size_t)row * NR + r0 + r) * logit_stride + i0) = make_float2(o[0], o[1]);
-            }
+            static_assert(TPW == 2, "one 8-byte store per lane and row");
+            if (active)
+                *reinterpret_cast<float2*>(logits + ((size_t)row * NR + r) * logit_stride + i0) = make_float2(o[0], o[1]);
         }
     }
     if constexpr (!kRowSplit) {

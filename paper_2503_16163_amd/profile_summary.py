@@ -81,7 +81,7 @@ def medians(dir_, counter):
 
 
 def hash_of(short):
-    return build.kernel_source_hash(short.split("+")[0])
+    return build.kernel_source_hash(re.split(r"[+<]", short)[0])
 
 
 def update_json(fname, workload, table, extra):

@@ -79,6 +79,39 @@ def test_arrangement_plan_on_the_benchmarks_shapes():
     assert abs(a.link_us(32, 256) - 72.9) < 0.1 and abs(a.main_us(32, 32768) - 42.8) < 0.1 and a.main_us(32, 4096) == 33.0
 
 
+def test_step_kernel_names_follow_the_librarys_dispatch():
+    """bench.py attributes its times to these names: the rule of the C++ dispatch, read from its source, over every shape."""
+    from paper_2503_16163_amd import arrangement as a, profile_summary
+    src = open(os.path.join(ROOT, "paper_2503_16163_amd", "csrc", "rows_mfma.hip")).read()
+    body = src[src.index("bool rows_uses_matrix_cores"):]
+    rule = re.search(r"return (.*?);", body[:body.index("\n}")]).group(1)
+    assert rule == "NR >= 4 || L.bits == 4"
+    for G in (1, 2, 4, 8):
+        for n_rows in (1, 2):
+            for bits in (1, 2, 4):
+                score, attend, both = a.step_kernels(G, n_rows, bits)
+                rows = G * n_rows >= 4 or bits == 4
+                assert (score == "rows_kernel") == (attend == "rows_kernel<attention>") == rows
+                assert (both is not None) == (bits != 4 and (rows or (G, n_rows) == (1, 2)))
+                for name in (score, attend, both):
+                    assert name is None or profile_summary.hash_of(name), name
+    assert a.step_kernels(1, 2, 2, ("attend",)) == ("score_i8_kernel", "attend_partial_kernel", None)
+
+
+def test_arrangement_plan_of_grouped_heads():
+    """2 to 8 query heads per KV head take the one call where the link leaves the main stream most of the step."""
+    from paper_2503_16163_amd import arrangement as a
+    one_call = ("one-pass", 2, 2, True)
+    for G, Hkv, S, k, bits in ((4, 8, 131072, 256, 1), (4, 8, 32768, 64, 2), (8, 8, 8192, 64, 2), (2, 16, 16384, 64, 2)):
+        p = a.plan(1, Hkv, G, S, k, 8, bits)
+        assert (p["calls"], p["async_select"], p["side_streams"], p["carry_append"]) == one_call, (G, p)
+        rows, S_most = Hkv, int((a.link_us(Hkv, k) / 0.9 - 14.0) / (55.0 if G == 8 else 40.0) * 1e6 / Hkv)   # where main_us no longer hides the link
+        if S_most > 1024 and a.link_us(rows, k) > 0.9 * 33.0:
+            assert a.plan(1, Hkv, G, S_most - 1024, k, 8, bits)["calls"] == "split"
+    assert a.plan(1, 8, 4, 131072, 1024, 8, 1)["calls"] == "split"      # the link
+    assert a.plan(1, 8, 4, 32768, 64, 8, 4)["calls"] == "split"         # 4-bit codes have no one launch
+
+
 def test_kernel_source_hash_follows_the_kernels_own_sources():
     """Figures in profiles/*.json are tied to the sources of the kernel they were measured on: the .hip file that
     defines it and the headers it includes, nothing else."""
