@@ -33,6 +33,11 @@ the gather's stream and two side streams (131k tokens, k = 1024: 86.7 against 94
 of 4 at 32k, k = 512: 149 to 155, the link).  One layer, or the non-speculative variant: everything on the caller's
 stream.
 
+Evidence for grouped heads (four layers, us per layer; KV rows x tokens): the one-launch step with a prefetch of half of main_us
+against main_us, 2 heads 16 x 16k 31.8 / 33.0, 32 x 32k 62.7 / 55.9, 8 x 131k with 1 bit 68.4 / 55.9; 4 heads 32 x 32k 53.6 / 55.9, 8 x
+131k with 1 bit 67.0 / 55.9; 8 heads 16 x 8k 31.1 / 33.0, 32 x 32k 74.5 / 71.7, 8 x 65k 57.9 / 42.8, 8 x 131k with 1 bit 96.6 / 71.7.
+With a prefetch of 0.8 main_us the one launch led score + select_gather + attend at each of them (34.5 to 100.6 against 52.8 to 118.2).
+
 Evidence, us per layer at 32 rows (rule's pick against the best of five arrangements tried), shapes that are
 not the benchmark's own: 8k tokens k = 32: 31.8 / 31.8; 8k k = 96: 33.5 / 33.5; 16k k = 192: 57.8 / 57.8;
 16k k = 256: 75.3 / 75.3; 16k k = 384: 112.2 / 112.2; 32k k = 192: 58.7 / 58.1; 32k k = 384: 113.3 / 113.3; 48k k = 192: 64.5 to 67.5 / 64.5;

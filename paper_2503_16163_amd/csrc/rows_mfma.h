@@ -10,11 +10,11 @@
 //            B = the multipliers of (row, token group) as hi + lo f16: to 2^-23 of a multiplier down to 2^-3, to 2^-25 below;
 //   values   o[r][c] = sum_i code[i][c] (p[r][i] s[i][m]) + sum_i p[r][i] z[i][m],  m = c / g
 //            B = p s as hi + lo f16, the scale factor of each value group following the scales of the unit's tokens.
-// Building the operands is what bounds these shapes (vector-instruction issue: at 8 rows, g = 64 about 380 vector
-// instructions per 32 tokens, a wave's vector ALU busy 9 cycles in 10), so no lane does it twice: the 16 columns are
+// Building the operands is what bounds these shapes (vector-instruction issue: at 8 rows, g = 64 400 vector instructions
+// per 32 tokens, each of a SIMD's three waves issuing 29 % of its life), so no lane does it twice: the 16 columns are
 // (row r, sub-group s) with 16 / NR sub-groups of 32 tokens in flight.  For 8 rows the two lanes of a row then exchange
 // halves, so that the columns of a product are (r, hi | lo) and every column of it is used (the matrix cores are not
-// free: 17 clocks each, 10 of which no vector instruction of the SIMD fills), and hi and lo add up in sums of their own;
+// free: 16 clocks each), and hi and lo add up in sums of their own;
 // with 16 rows the columns are the rows.
 // A lane (column (r, s), quarter kq) ends the scoring with the logits of row r for 8 consecutive tokens, which is the
 // order in which the value side wants its B operand: no logit is exchanged between lanes.
@@ -24,13 +24,13 @@
 // current one is worked on.  The four waves of a workgroup merge once, at the end.  The 16-bit candidates are a wave
 // each per 32: the keys times the queries on the matrix cores in their own type, the values on the vector ALUs.
 //
-// Measured alone on MI355X (scoring + attention as two launches of the earlier kernels -> as one launch): 32 KV rows x 32768
-// tokens, 8 query rows, 2 bits, g = 64: 27.5 + 37.9 -> 37.7 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 45.0 us;
-// 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.4 us; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 16.5 us (the earlier
-// kernels' 16-bit chunk was a chain of 40 us there).  4-bit codes, two launches: 32 x 16384, 2 query rows as 8 columns'
-// worth, g = 32: a decode step of a layer 70.7 -> 52.8 us against vector-ALU kernels (scoring 13.0, attention 15.4 us
-// alone, 20.6 beside the gathers; the 84 MB they read need 14 us at the rate of a plain read).  168 registers, three workgroups per compute unit; held to four it
-// spills.
+// Measured alone on MI355X (scoring + attention as two launches of the kernels before it -> as one launch): 32 KV rows x 32768
+// tokens, 8 query rows, 2 bits, g = 64: 27.5 + 37.9 -> 37.2 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 43.2 us;
+// 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.0 us at best, 17.6 beside the gathers; 16 x 8192, 16 query rows, g = 128:
+// 10.8 + 40.2 -> 17.0 us (the earlier kernels' 16-bit chunk was a chain of 40 us there).  4-bit codes, two launches, 32 x
+// 16384, 2 query rows as 8 columns' worth, g = 32: scoring 14.3, attention 17.6 us at best, 16.8 and 19.9 beside the gathers (the
+// 84 MB they read need 14 us at the rate of a plain read); a decode step of a layer 70.7 -> 51 us against vector-ALU kernels.
+// Up to 168 registers, three workgroups per compute unit; held to four it spills.
 #pragma once
 #include "attend_common.h"
 #include "rows_args.h"

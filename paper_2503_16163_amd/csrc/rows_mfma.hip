@@ -34,11 +34,11 @@ void rows_split(int rows, int NR, int Nq, int max_main, int& wave_units, int& n_
 
 bool rows_uses_matrix_cores(const LayerView& L, int n_rows) {
     // Four rows leave half of the columns empty and are still faster than a conversion and four multiply-accumulates per code
-    // on the vector ALUs in two launches: a decode step of a layer, 16 x 16384, 2 bits 45.5 -> 27.7 us, 32 x 32768 85.3 -> 61.6,
-    // 8 x 131072, 1 bit 79.5 -> 53.7; one row of each of four heads, 8 x 32768, 62.7 -> 54.1.
+    // on the vector ALUs in two launches: a decode step of a layer, 16 x 16384, 2 bits 45.5 -> 28 us, 32 x 32768 85.3 -> 61,
+    // 8 x 131072, 1 bit 79.5 -> 59.5; one row of each of four heads, 8 x 32768, 62.7 -> 57.
     // Fewer rows leave more of them empty.  1- and 2-bit codes have kernels made for them (two rows: scoring and attention in one
     // launch on the int8 matrix cores, 17.8 us for 32 x 16384 positions); with 4-bit codes the alternative was a conversion and
-    // a multiply-accumulate per code on the vector ALUs: 45 + 54 us for 32 x 32768, two rows, against 13.0 + 15.4 for half of it.
+    // a multiply-accumulate per code on the vector ALUs: 45 + 54 us for 32 x 32768, two rows, against 27.1 + 33.1.
     const int NR = L.G * n_rows;
     return NR >= 4 || L.bits == 4;
 }
