@@ -1,75 +1,119 @@
 // ArgTopK of the speculative row (Appendix A "Decoding": K_{t+1} = ArgTopK(A_{1,:});
-// "Pre-decoding" for the single-row case).  Softmax is monotone, so the selection
-// runs on the logits' order-preserving integer keys.
+// "Pre-decoding" for the single-row case).  Softmax is monotone, so the selection runs on the
+// logits' order-preserving integer keys.
 //
-// One workgroup of 1024 threads per (batch, KV head); rows of up to 65536 keys sit in
-// registers, longer rows are re-read from L2 in batches of independent loads.  The
-// number of barrier-separated phases, not arithmetic, bounds this kernel, so the exact
-// k-th largest key tau is found in three short steps:
-//   1. floor: every thread's largest key is a distinct element of the row, so tau is at
-//      least the k-th largest thread maximum; one 2048-bin histogram of the maxima's
-//      leading bits gives a floor F below which nothing can be selected;
-//   2. one 2048-bin histogram of (key - F) >> shift over the keys >= F, with the shift
-//      chosen from the row maximum so that the bins are as fine as 2048 bins allow,
-//      locates the bin that holds tau and the rank of tau inside it;
-//   3. the handful of keys in that bin are collected and ranked by one wave.
-// If that bin holds more than 64 keys (many equal or almost equal scores) step 2 is
-// repeated inside the bin, which narrows the range by 11 bits each time.
-// A two-pass ordered compaction then emits every position with key > tau and the first
-// `need` positions with key == tau in ascending index order (ties to the lower index).
+// One workgroup per (batch, KV head), its keys in registers (longer rows in two launches, see
+// topk_parts).  What bounds the kernel is neither arithmetic nor the 4 bytes per key but the chain of
+// barrier-separated phases and, in each of them, the instructions of a pass over the registers
+// (unrolled, and fetched once per compute unit).  So two passes see all the keys and the rest works on a few hundred:
+//   1. floor: every thread's largest key is a distinct element of the row (every four registers', where k is not
+//      small beside the number of threads), so tau, the k-th largest key, is at least the k-th largest of those maxima.  A
+//      512-bin histogram of the maxima over the four binades below the row's largest gives a floor F <= tau; every wave reads
+//      it for itself, which saves a barrier;
+//   2. the keys >= F (1.2 to 1.5 k of them where k is a quarter to a half of the maxima) are collected in LDS, and a second
+//      histogram, of those, finds the bin that holds tau and tau's rank inside it;
+//   3. the handful of keys in that bin are ranked by one wave (larger key first, then lower position), which decides for
+//      each of them at once, ties included; the selected positions are bits of a bitmap, whose order is the output's.
+// A row whose candidates do not fit, or whose boundary bin is crowded (many equal or almost equal scores), goes on
+// with histograms of 2048 bins inside the range left, which narrow it by 11 bits each time, and an ordered
+// compaction (select_crowded).
+//
+// Measured on MI355X, us, one launch alone (before: a histogram of the maxima's leading bits, one of the keys, 64
+// readlanes to rank, a counting and an emitting pass over all registers): rows x keys, k = 64 unless stated: 1 x 4096 10.6 -> 6.0,
+// 32 x 8192 13.8 -> 8.5, 32 x 16384 12.0 -> 7.0, 32 x 32768 15.2 -> 8.6 (k = 256: 16.7 -> 9.8), 32 x 16384 with k = 1024 14.0 ->
+// 9.4; in two launches 8 x 131072 with k = 256 27.2 -> 16.2, with k = 1024 32.3 -> 21.8.
 #include "kernels.h"
 #include "layout.h"
 
 namespace specache {
 namespace {
 
-constexpr int kBins = 2048;
-constexpr int kBatch = 8;    // key loads in flight per thread (streaming variant)
-constexpr int kSmall = 64;   // keys one wave ranks directly
+constexpr int kBins = 512;         // of either histogram of the short way
+constexpr int kCandidates = 2048;  // keys the short way collects
+constexpr int kCrowdedBins = 2048;
+constexpr int kSmall = 64;         // keys one wave ranks directly
+constexpr int kMapWords = 65536 / 32;
 
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+// sum over this lane and the lanes below it
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+    v += dpp_or_zero<0x111>(v);          // row_shr 1, 2, 4, 8: inside rows of 16 lanes
+    v += dpp_or_zero<0x112>(v);
+    v += dpp_or_zero<0x114>(v);
+    v += dpp_or_zero<0x118>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);     // row_bcast 15: a row's sum to the odd row behind it
+    v += dpp_or_zero<0x143, 0xc>(v);     // row_bcast 31: the first two rows' sum to the last two
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_largest(uint32_t v) {
+    auto step = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = step(v, dpp_or_zero<0xB1>(v));   // lanes 1 and 2 apart, the other half and the mirror of the row of 16
+    v = step(v, dpp_or_zero<0x4E>(v));
+    v = step(v, dpp_or_zero<0x141>(v));
+    v = step(v, dpp_or_zero<0x140>(v));
+    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    return step(step(a, b), step(c, d));
+}
 // exclusive prefix of a 64-bit ballot below this lane
 __device__ __forceinline__ int prefix_below(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// hist[] is stored skewed (bin b at b + b / 32) so that a lane walking 32 consecutive bins
+// The bin that holds the need-th largest counted key (larger bin = larger keys) and that key's rank in the bin (from
+// 1, largest first), worked out by every wave for itself; bin = kBins if fewer than `need` keys were counted.
+struct BinRank { uint32_t bin, rank; };
+__device__ __forceinline__ BinRank find_bin(const uint32_t* hist, uint32_t need) {
+    const int lane = threadIdx.x & 63;
+    const uint4 lo = reinterpret_cast<const uint4*>(hist)[2 * (63 - lane)], hi = reinterpret_cast<const uint4*>(hist)[2 * (63 - lane) + 1];
+    const uint32_t h[8] = {hi.w, hi.z, hi.y, hi.x, lo.w, lo.z, lo.y, lo.x};   // bins 8 (63 - lane) + 7 downwards
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mine += h[j];
+    const uint32_t upto = wave_prefix(mine);
+    const unsigned long long reached = __ballot(upto >= need);
+    if (reached == 0) return {(uint32_t)kBins, 0};
+    uint32_t above = upto - mine, bin = 0, rank = 0;
+    bool found = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const bool here = !found && above + h[j] >= need;
+        bin = here ? 8 * (63 - lane) + 7 - j : bin;
+        rank = here ? need - above : rank;
+        found = found || here;
+        above += h[j];
+    }
+    const int at = __builtin_ctzll(reached);
+    return {(uint32_t)__builtin_amdgcn_readlane(bin, at), (uint32_t)__builtin_amdgcn_readlane(rank, at)};
+}
+
+// Crowded rows.  hist[] is stored skewed (bin b at b + b / 32) so that a lane walking 32 consecutive bins
 // and its neighbours touch different banks.
 __device__ __forceinline__ int skew(int b) { return b + (b >> 5); }
-constexpr int kHistWords = kBins + kBins / 32;
+constexpr int kHistWords = kCrowdedBins + kCrowdedBins / 32;
 
 // Wave 0 only: find the bin holding the need-th largest counted key (bins ordered by
-// value, larger bin = larger keys).  Writes sel[0] = bin (or 0xFFFFFFFF if fewer than
-// `need` keys were counted) and sel[1] = rank of the wanted key inside that bin (1-based,
+// value, larger bin = larger keys).  Writes sel[0] = bin and sel[1] = rank of the wanted key inside that bin (1-based,
 // counted from the bin's largest key).
 __device__ __forceinline__ void select_bin_wave0(const uint32_t* hist, uint32_t* sel, uint32_t need) {
     const int lane = threadIdx.x & 63;
-    // lane l owns bins 32l .. 32l+31, held in registers
-    uint32_t h[32];
+    // lane l owns the 32 bins from 32 (63 - l) on
     uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        h[j] = hist[skew(32 * lane + j)];
-        mine += h[j];
-    }
-    // keys in bins owned by higher lanes
-    uint32_t above = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_down(above, d, 64);
-        if (lane + d < 64) above += o;
-    }
-    above -= mine;
-    if (lane == 0) sel[0] = 0xFFFFFFFFu;
-    // walk this lane's bins from the top; exactly one (lane, bin) pair brackets `need`
-    uint32_t gt = above, found_bin = 0xFFFFFFFFu, found_rank = 0;
-#pragma unroll
+#pragma unroll 1
+    for (int j = 0; j < 32; ++j) mine += hist[skew(32 * (63 - lane) + j)];
+    uint32_t above = wave_prefix(mine) - mine;
+#pragma unroll 1
     for (int j = 31; j >= 0; --j) {
-        const bool hit = gt < need && need <= gt + h[j];
-        found_bin = hit ? (uint32_t)(32 * lane + j) : found_bin;
-        found_rank = hit ? need - gt : found_rank;
-        gt += h[j];
+        const uint32_t h = hist[skew(32 * (63 - lane) + j)];
+        if (above < need && need <= above + h) {
+            sel[0] = 32 * (63 - lane) + j;
+            sel[1] = need - above;
+        }
+        above += h;
     }
-    if (found_bin != 0xFFFFFFFFu) { sel[0] = found_bin; sel[1] = found_rank; }
 }
 
 // A row may be split into `parts` ranges of part_len keys, one workgroup each, that write
@@ -88,15 +132,18 @@ struct TopkIo {
 template <int THREADS, int KPT>
 __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const uint32_t* __restrict__ keys,
                                                        size_t key_stride, int32_t* __restrict__ idx_out) {
-    constexpr int kTopkThreads = THREADS;
-    constexpr int kTopkWaves = THREADS / 64;
-    __shared__ uint32_t hist[kHistWords];
-    __shared__ uint32_t wave_red[kTopkWaves];
-    __shared__ uint32_t sel[2];
-    __shared__ uint32_t small_keys[kSmall];
-    __shared__ uint32_t small_n;
-    __shared__ uint32_t result[2];     // tau, number of keys == tau to take
-    __shared__ uint32_t wave_gt[kTopkWaves], wave_eq[kTopkWaves];
+    constexpr int kWavesHere = THREADS / 64;
+    constexpr int kMapHere = THREADS * KPT / 32;      // words of the bitmap
+    constexpr int kSub = 4;                           // registers of a finer maximum
+    static_assert(kMapHere <= kMapWords, "a row's positions");
+    __shared__ __attribute__((aligned(16))) uint32_t bins[2][kBins];
+    __shared__ uint2 cand[kCandidates];               // key, position; a crowded row's histogram
+    __shared__ uint32_t bitmap[kMapHere];
+    __shared__ uint32_t wave_red[kWavesHere], wave_eq[kWavesHere], sel[2], result[2];
+    __shared__ uint2 small_keys[kSmall];
+    __shared__ uint32_t n_cand, n_small;
+    static_assert(sizeof(cand) >= kHistWords * 4, "the histogram takes the candidates' place");
+    uint32_t* crowded_hist = reinterpret_cast<uint32_t*>(cand);
 
     const int row = blockIdx.x / io.parts, part = blockIdx.x % io.parts;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -113,192 +160,289 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
         out[pos] = map ? map[i] : base + i;
         if (kout) kout[pos] = kv;
     };
-
-    for (int j = keff + tid; j < k; j += kTopkThreads) {
+    auto none = [&](int j) {
         out[j] = -1;
         if (kout) kout[j] = 0u;     // below every key: never selected by the second launch
-    }
-    if (keff == 0) return;
-    if (keff == Nq) {   // everything is selected
-        for (int j = tid; j < Nq; j += kTopkThreads) emit(j, j, kr[j]);
-        return;
-    }
+    };
 
     // wave w owns the contiguous index range [w*seg, (w+1)*seg), seg a multiple of 64
-    const int seg = ((Nq + kTopkWaves * 64 - 1) / (kTopkWaves * 64)) * 64;
+    const int seg = ((Nq + kWavesHere * 64 - 1) / (kWavesHere * 64)) * 64;
     const int lo = wave * seg, hi = (lo + seg < Nq) ? lo + seg : Nq;
 
-    uint32_t key[KPT > 0 ? KPT : 1];
-    if constexpr (KPT > 0) {
+    auto select = [&]() {
+        // Key slots with index >= hi are padding and hold key 0 (what a load beyond the descriptor's range returns); every
+        // range tested below starts at 1 or above, so padding never matches and no pass needs an index test.  (Key 0
+        // itself is the one NaN pattern 0xFFFFFFFF; it is treated as below every other score.)
+        uint32_t key[KPT];
+        {
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(kr), 0, hi > lo ? hi * 4 : 0, 0x00027000);
 #pragma unroll
-        for (int it = 0; it < KPT; ++it) {
-            const int i = lo + it * 64 + lane;
-            key[it] = i < hi ? kr[i] : 0u;
+            for (int it = 0; it < KPT; ++it) key[it] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (lo + lane) * 4 + it * 256, 0, 0);
         }
-    }
-    // apply f(index, key) to every key slot of this thread.  Slots with index >= hi are padding
-    // and hold key 0; every range tested below starts at 1 or above, so padding never matches
-    // and no pass needs an index test.  (Key 0 itself is the one NaN pattern 0xFFFFFFFF; it is
-    // treated as below every other score.)
-    auto for_each_key = [&](auto&& f) {
-        if constexpr (KPT > 0) {
+        // while they travel
+        for (int b = tid; b < 2 * kBins; b += THREADS) bins[0][b] = 0;
+        for (int b = tid; b < kMapHere; b += THREADS) bitmap[b] = 0;
+        if (tid == 0) n_cand = n_small = 0;
+        // ---- the maxima, of the thread or of every kSub registers
+        const bool fine = 2 * keff > THREADS;     // uniform
+        uint32_t sub[KPT / kSub], tmax = 0;
 #pragma unroll
-            for (int it = 0; it < KPT; ++it) f(lo + it * 64 + lane, key[it]);
-        } else {
-            for (int i0 = lo; i0 < hi; i0 += 64 * kBatch) {
-                uint32_t kb[kBatch];
+        for (int s = 0; s < KPT / kSub; ++s) {
+            sub[s] = 0;
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
+            for (int it = s * kSub; it < (s + 1) * kSub; ++it) sub[s] = key[it] > sub[s] ? key[it] : sub[s];
+            tmax = sub[s] > tmax ? sub[s] : tmax;
+        }
+        {
+            const uint32_t wm = wave_largest(tmax);
+            if (lane == 0) wave_red[wave] = wm;
+        }
+        __syncthreads();
+        uint32_t row_max = wave_red[0];
+#pragma unroll
+        for (int w = 1; w < kWavesHere; ++w) row_max = wave_red[w] > row_max ? wave_red[w] : row_max;
+        // ---- floor: the maxima among the top four binades, else all of them by binade
+        constexpr uint32_t kTopSpan = 1u << 25;
+        static_assert(kTopSpan / kBins == 1u << 16, "a bin of the top binades");
+        const uint32_t top_lo = row_max >= kTopSpan ? row_max - (kTopSpan - 1) : 0u;
+        auto count_maxima = [&](uint32_t* hist, uint32_t from, int shift) {
+            if (fine) {
+#pragma unroll
+                for (int s = 0; s < KPT / kSub; ++s)
+                    if (sub[s] >= from && sub[s] != 0) atomicAdd(&hist[(sub[s] - from) >> shift], 1u);
+            } else if (tmax >= from && tmax != 0) {
+                atomicAdd(&hist[(tmax - from) >> shift], 1u);
+            }
+        };
+        count_maxima(bins[0], top_lo, 16);
+        __syncthreads();
+        uint32_t floor_key = 1u;                   // fewer maxima than keff: no floor
+        {
+            const BinRank br = find_bin(bins[0], (uint32_t)keff);
+            if (br.bin < kBins) {
+                floor_key = top_lo + (br.bin << 16);
+            } else {                               // uniform over the workgroup
+                __syncthreads();
+                for (int b = tid; b < kBins; b += THREADS) bins[0][b] = 0;
+                __syncthreads();
+                count_maxima(bins[0], 0u, 23);
+                __syncthreads();
+                const BinRank all = find_bin(bins[0], (uint32_t)keff);
+                if (all.bin < kBins) floor_key = all.bin << 23;
+            }
+            floor_key = floor_key < 1u ? 1u : floor_key;
+        }
+        // ---- the keys from the floor on
+#pragma unroll
+        for (int it = 0; it < KPT; ++it)
+            if (key[it] >= floor_key) {
+                const uint32_t at = atomicAdd(&n_cand, 1u);
+                if (at < kCandidates) cand[at] = make_uint2(key[it], (uint32_t)(lo + it * 64 + lane));
+            }
+        __syncthreads();
+        const uint32_t n = n_cand;
+        bool crowded = n > kCandidates;
+        uint32_t need = (uint32_t)keff;
+        if (!crowded) {
+            if (n < need) need = n;                // keys that are NaN are below everything and stay unselected
+            // ---- the bin of tau
+            const uint32_t span = row_max - floor_key;
+            const int shift = span < (uint32_t)kBins ? 0 : 32 - __builtin_clz(span) - 9;
+            for (uint32_t c = tid; c < n; c += THREADS) atomicAdd(&bins[1][(cand[c].x - floor_key) >> shift], 1u);
+            __syncthreads();
+            const BinRank br = find_bin(bins[1], need);
+            crowded = bins[1][br.bin < kBins ? br.bin : 0] > kSmall;
+            if (!crowded) {
+                for (uint32_t c = tid; c < n; c += THREADS) {
+                    const uint2 kv = cand[c];
+                    const uint32_t b = (kv.x - floor_key) >> shift;
+                    if (b > br.bin) atomicOr(&bitmap[kv.y >> 5], 1u << (kv.y & 31));
+                    if (b == br.bin) small_keys[atomicAdd(&n_small, 1u)] = kv;
+                }
+                __syncthreads();
+                // ---- the boundary bin's keys: larger first, then lower position
+                if (wave == 0) {
+                    const uint32_t m = n_small;
+                    const uint2 mine = lane < (int)m ? small_keys[lane] : make_uint2(0u, 0u);
+                    uint32_t before = 0;
+#pragma unroll 2
+                    for (uint32_t j = 0; j < m; ++j) {
+                        const uint2 o = small_keys[j];
+                        before += o.x > mine.x || (o.x == mine.x && o.y < mine.y);
+                    }
+                    if (lane < (int)m && before < br.rank) atomicOr(&bitmap[mine.y >> 5], 1u << (mine.y & 31));
+                }
+                __syncthreads();
+                // ---- the bits in order: this thread's words, behind those of the threads and waves before it
+                constexpr int kWords = (kMapHere + THREADS - 1) / THREADS;
+                uint32_t w[kWords], mine = 0;
+#pragma unroll
+                for (int u = 0; u < kWords; ++u) {
+                    w[u] = tid * kWords + u < kMapHere ? bitmap[tid * kWords + u] : 0u;
+                    mine += __popc(w[u]);
+                }
+                const uint32_t upto = wave_prefix(mine);
+                if (lane == 63) wave_red[wave] = upto;
+                __syncthreads();
+                uint32_t pos = upto - mine;
+#pragma unroll 1
+                for (int v = 0; v < wave; ++v) pos += wave_red[v];
+#pragma unroll
+                for (int u = 0; u < kWords; ++u)
+                    while (w[u]) {
+                        const int i = 32 * (tid * kWords + u) + __builtin_ctz(w[u]);
+                        w[u] &= w[u] - 1;
+                        emit(pos++, i, kout ? kr[i] : 0u);
+                    }
+                for (int j = (int)need + tid; j < k; j += THREADS) none(j);
+                return;
+            }
+        }
+        // ---- crowded: histograms inside [range_lo, range_hi], the keys read again in every pass (the registers that would
+        // hold them until here, in a way seldom taken, would be spilled in the other)
+        auto for_each_key = [&](auto&& f) {        // f(index, key); whole waves, padding has key 0
+#pragma unroll 1
+            for (int i0 = lo; i0 < hi; i0 += 256) {
+                uint32_t kb[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
                     const int i = i0 + u * 64 + lane;
                     kb[u] = i < hi ? kr[i] : 0u;
                 }
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) f(i0 + u * 64 + lane, kb[u]);
+                for (int u = 0; u < 4; ++u) f(i0 + u * 64 + lane, kb[u]);
             }
-        }
-    };
-
-    // ---- step 1: row maximum and the floor from the thread maxima ---------------------
-    uint32_t tmax = 0;
-    for_each_key([&](int, uint32_t kv) { tmax = kv > tmax ? kv : tmax; });
-    const bool any = lo + lane < hi;   // this thread holds at least one key
-    {
-        uint32_t wm = tmax;
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) { const uint32_t o = __shfl_xor(wm, m, 64); wm = o > wm ? o : wm; }
-        if (lane == 0) wave_red[wave] = wm;
-    }
-    for (int b = tid; b < kHistWords; b += kTopkThreads) hist[b] = 0;
-    __syncthreads();
-    uint32_t row_max = 0;
-#pragma unroll
-    for (int w = 0; w < kTopkWaves; ++w) row_max = wave_red[w] > row_max ? wave_red[w] : row_max;
-    if (any) atomicAdd(&hist[skew(tmax >> 21)], 1u);
-    __syncthreads();
-    if (wave == 0) select_bin_wave0(hist, sel, (uint32_t)keff);
-    __syncthreads();
-    // fewer than keff threads hold keys: no floor
-    uint32_t range_lo = sel[0] == 0xFFFFFFFFu ? 1u : (sel[0] << 21);
-    range_lo = range_lo < 1u ? 1u : range_lo;
-    uint32_t range_hi = row_max;          // inclusive
-    uint32_t need = (uint32_t)keff;       // rank of tau among the keys >= range_lo
-    __syncthreads();
-
-    // ---- step 2 (repeated while the bin is crowded): histogram inside [range_lo, range_hi] ----
-    for (int round = 0; round < 4; ++round) {
-        const uint32_t span = range_hi - range_lo;
-        const int shift = span < (uint32_t)kBins ? 0 : 32 - __builtin_clz(span) - 11;
-        for (int b = tid; b < kHistWords; b += kTopkThreads) hist[b] = 0;
-        if (tid == 0) small_n = 0;
-        __syncthreads();
-        for_each_key([&](int, uint32_t kv) {
-            const uint32_t off = kv - range_lo;
-            const bool cand = off <= span;       // one unsigned test for range_lo <= kv <= range_hi
-            if (__ballot(cand) == 0) return;     // wave-uniform: most key slots hold no candidate
-            if (cand) atomicAdd(&hist[skew(off >> shift)], 1u);
-        });
-        __syncthreads();
-        if (wave == 0) select_bin_wave0(hist, sel, need);
-        __syncthreads();
-        const uint32_t bin = sel[0], rank = sel[1];
-        const uint32_t bin_lo = range_lo + (bin << shift);
-        const uint32_t bin_hi = shift == 0 ? bin_lo : bin_lo + ((1u << shift) - 1u);
-        const uint32_t in_bin = hist[skew(bin)];
-        if (shift == 0) {                  // the bin is a single key value
-            if (tid == 0) { result[0] = bin_lo; result[1] = rank; }
+        };
+        uint32_t range_lo = floor_key, range_hi = row_max;    // inclusive
+        for (int round = 0; round < 4; ++round) {
+            const uint32_t span = range_hi - range_lo;
+            const int shift = span < (uint32_t)kCrowdedBins ? 0 : 32 - __builtin_clz(span) - 11;
             __syncthreads();
-            break;
-        }
-        if (in_bin <= (uint32_t)kSmall) {
-            // ---- step 3: one wave ranks the bin's keys ----
+            for (int b = tid; b < kHistWords; b += THREADS) crowded_hist[b] = 0;
+            if (tid == 0) {
+                n_small = 0;
+                sel[0] = 0xFFFFFFFFu;
+            }
+            __syncthreads();
             for_each_key([&](int, uint32_t kv) {
-                const bool cand = kv - bin_lo <= bin_hi - bin_lo;
-                if (__ballot(cand) == 0) return;
-                if (cand) small_keys[atomicAdd(&small_n, 1u)] = kv;
+                const uint32_t off = kv - range_lo;
+                if (off <= span) atomicAdd(&crowded_hist[skew(off >> shift)], 1u);   // one unsigned test for range_lo <= kv <= range_hi
             });
             __syncthreads();
-            if (wave == 0) {
-                const uint32_t n = small_n;
-                const uint32_t mine = lane < (int)n ? small_keys[lane] : 0u;
-                uint32_t greater = 0, equal = 0;
-#pragma unroll
-                for (int j = 0; j < kSmall; ++j) {
-                    const uint32_t kj = __builtin_amdgcn_readlane(mine, j);   // lane j's key, wave-uniform
-                    const bool live = (uint32_t)j < n;
-                    greater += live && kj > mine;
-                    equal += live && kj == mine;
-                }
-                // tau is the key with greater < rank <= greater + equal
-                if (lane < (int)n && greater < rank && rank <= greater + equal) {
-                    result[0] = mine;
-                    result[1] = rank - greater;
-                }
-            }
+            if (wave == 0) select_bin_wave0(crowded_hist, sel, need);
             __syncthreads();
-            break;
+            if (sel[0] == 0xFFFFFFFFu) {           // fewer keys than wanted (the others are NaN): all of them
+                if (tid == 0) { result[0] = range_lo; result[1] = 0xFFFFFFFFu; }
+                __syncthreads();
+                break;
+            }
+            const uint32_t bin = sel[0], rank = sel[1];
+            const uint32_t bin_lo = range_lo + (bin << shift);
+            const uint32_t bin_hi = shift == 0 ? bin_lo : bin_lo + ((1u << shift) - 1u);
+            const uint32_t in_bin = crowded_hist[skew(bin)];
+            if (shift == 0) {                      // the bin is a single key value
+                if (tid == 0) { result[0] = bin_lo; result[1] = rank; }
+                __syncthreads();
+                break;
+            }
+            if (in_bin <= (uint32_t)kSmall) {
+                for_each_key([&](int, uint32_t kv) {
+                    if (kv - bin_lo <= bin_hi - bin_lo) small_keys[atomicAdd(&n_small, 1u)].x = kv;
+                });
+                __syncthreads();
+                if (wave == 0) {
+                    const uint32_t m = n_small;
+                    const uint32_t mine = lane < (int)m ? small_keys[lane].x : 0u;
+                    uint32_t greater = 0, equal = 0;
+#pragma unroll 1
+                    for (uint32_t j = 0; j < m; ++j) {
+                        const uint32_t kj = small_keys[j].x;
+                        greater += kj > mine;
+                        equal += kj == mine;
+                    }
+                    // tau is the key with greater < rank <= greater + equal
+                    if (lane < (int)m && greater < rank && rank <= greater + equal) {
+                        result[0] = mine;
+                        result[1] = rank - greater;
+                    }
+                }
+                __syncthreads();
+                break;
+            }
+            range_lo = bin_lo;
+            range_hi = bin_hi;
+            need = rank;
         }
-        range_lo = bin_lo;
-        range_hi = bin_hi;
-        need = rank;
+        const uint32_t tau = result[0];
+        need = result[1];                          // keys == tau to take
+        // ---- ordered compaction: count per wave, then emit in index order (ties to the lower index)
+        uint32_t cnt_gt = 0, cnt_eq = 0;
+        for_each_key([&](int, uint32_t kv) {
+            cnt_gt += __popcll(__ballot(kv > tau));
+            cnt_eq += __popcll(__ballot(kv == tau));
+        });
+        if (lane == 0) { wave_red[wave] = cnt_gt; wave_eq[wave] = cnt_eq; }
         __syncthreads();
-    }
-    const uint32_t tau = result[0];
-    need = result[1];
-
-    // ---- ordered compaction: count per wave, then emit in index order ---------------
-    uint32_t cnt_gt = 0, cnt_eq = 0;
-    for_each_key([&](int, uint32_t kv) {
-        const unsigned long long mge = __ballot(kv >= tau);
-        if (mge == 0) return;              // wave-uniform skip
-        const unsigned long long me = __ballot(kv == tau);
-        cnt_gt += __popcll(mge & ~me);
-        cnt_eq += __popcll(me);
-    });
-    if (lane == 0) { wave_gt[wave] = cnt_gt; wave_eq[wave] = cnt_eq; }
-    __syncthreads();
-    uint32_t gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
-    for_each_key([&](int i, uint32_t kv) {
-        if (__ballot(kv >= tau) == 0) return;   // wave-uniform skip
-        const bool gt = kv > tau, eq = kv == tau;
-        const unsigned long long mg = __ballot(gt), me = __ballot(eq);
-        const uint32_t my_eq_rank = eq_before + prefix_below(me);
-        if (gt || (eq && my_eq_rank < need)) {
-            const uint32_t eq_taken_before = my_eq_rank < need ? my_eq_rank : need;
-            emit(gt_before + prefix_below(mg) + eq_taken_before, i, kv);
+        uint32_t gt_before = 0, eq_before = 0, total = 0, eq_total = 0;
+#pragma unroll 1
+        for (int w = 0; w < kWavesHere; ++w) {
+            gt_before += w < wave ? wave_red[w] : 0u;
+            eq_before += w < wave ? wave_eq[w] : 0u;
+            total += wave_red[w];
+            eq_total += wave_eq[w];
         }
-        gt_before += __popcll(mg);
-        eq_before += __popcll(me);
-    });
+        total += eq_total < need ? eq_total : need;
+        for_each_key([&](int i, uint32_t kv) {
+            const bool gt = kv > tau, eq = kv == tau;
+            const unsigned long long mg = __ballot(gt), me = __ballot(eq);
+            const uint32_t my_eq_rank = eq_before + prefix_below(me);
+            if (gt || (eq && my_eq_rank < need)) {
+                const uint32_t eq_taken_before = my_eq_rank < need ? my_eq_rank : need;
+                emit(gt_before + prefix_below(mg) + eq_taken_before, i, kv);
+            }
+            gt_before += __popcll(mg);
+            eq_before += __popcll(me);
+        });
+        for (int j = (int)total + tid; j < k; j += THREADS) none(j);
+    };
+
+    if (keff == Nq) {   // everything is selected
+        for (int j = tid; j < k; j += THREADS) {
+            if (j < Nq) emit(j, j, kr[j]);
+            else none(j);
+        }
+    } else {
+        select();
+    }
+
 }
 
 // one launch over `rows * io.parts` ranges of at most n keys each
 hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_t* keys, size_t key_stride,
                          int32_t* idx_out, hipStream_t stream) {
     const int per_lane_256 = (n + 255) / 256, per_lane = (n + 1023) / 1024;   // keys per lane held in registers
+    // the floor needs more maxima than k to bite: small workgroups only for small k
+    const bool small_wg = k <= 256 && per_lane_256 <= 32;
 #define SPC_TOPK(T, K) SPC_LAUNCH((topk_kernel<T, K>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out)
-    // the floor of step 1 needs more threads than k to bite: small workgroups only for small k
-    const bool small_wg = k <= 256;
     if (small_wg && per_lane_256 <= 8) SPC_TOPK(256, 8);
     else if (small_wg && per_lane_256 <= 16) SPC_TOPK(256, 16);
-    else if (small_wg && per_lane_256 <= 32) SPC_TOPK(256, 32);
+    else if (small_wg) SPC_TOPK(256, 32);
     else if (per_lane <= 16) SPC_TOPK(1024, 16);
     else if (per_lane <= 24) SPC_TOPK(1024, 24);
     else if (per_lane <= 32) SPC_TOPK(1024, 32);
     else if (per_lane <= 40) SPC_TOPK(1024, 40);
     else if (per_lane <= 48) SPC_TOPK(1024, 48);
     else if (per_lane <= 64) SPC_TOPK(1024, 64);
-    else SPC_TOPK(1024, 0);
+    else return hipErrorInvalidValue;                // launch_topk splits such a row
 #undef SPC_TOPK
     return hipGetLastError();
 }
 
 }  // namespace
 
-// One workgroup's registers hold 65536 keys, but its time grows faster than the row (32 rows, k = 256, alone:
-// 17 us for 32768 keys, 34 for 49152, 61 and more for 65536), so rows beyond kTopkSingleLaunchKeys are split
-// into ranges of about kTopkPartKeys keys, as many as keep the candidate list of the second launch within
-// one workgroup's registers: two launches of 12 to 15 us each.
+// One workgroup's registers hold 65536 keys, but its time grows faster than the row, so rows beyond kTopkSingleLaunchKeys
+// are split into ranges of about kTopkPartKeys keys, as many as keep the candidate list of the second launch within
+// one workgroup's registers.
 constexpr int kTopkRegisterKeys = 65536, kTopkPartKeys = 16384, kTopkSingleLaunchKeys = 40960;
 
 int topk_parts(int Nq, int k) {

@@ -1,0 +1,88 @@
+"""ArgTopK and the fetch behind it against the scores they were made from: the selection has to be exactly the k largest
+keys of the logits that the scoring kernel left (ties to the lower position), at the sizes where the kernel changes its
+shape, and the staged pairs those that a fetch of the same index list brings."""
+import numpy as np
+import pytest
+
+from paper_2503_16163_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def keys_of(logits):
+    u = (logits + np.float32(0.0)).view(np.uint32)
+    return np.where(u & 0x80000000, ~u, u | np.uint32(0x80000000)).astype(np.uint32)
+
+
+def expected(keys, k):
+    """Positions of the k largest keys, ascending, -1 padded; key 0 (one NaN pattern) is below everything and stays out of a real choice."""
+    keff = min(k, keys.size)
+    order = np.lexsort((np.arange(keys.size), -keys.astype(np.int64)))[:keff]
+    if keff < keys.size:
+        order = order[keys[order] != 0]
+    return np.concatenate([np.sort(order), np.full(k - order.size, -1)]).astype(np.int32)
+
+
+def prompt(pattern, S, H, q):
+    rng = np.random.default_rng(S + H)
+    K = rng.standard_normal((1, H, S, 128)).astype(np.float32)
+    if pattern == "one value":
+        K[:] = K[:, :, :1]
+    elif pattern == "few values":
+        K = K[:, :, np.arange(S) % 64]
+    elif pattern == "binades apart":
+        K *= np.exp2(-(np.arange(S) // 32 % 12)).astype(np.float32)[None, None, :, None]
+    elif pattern == "one far above":
+        K[:, :, 40:44] = 30.0 * np.sign(q)[:, :, None, :]
+    elif pattern == "negative":
+        K = -np.abs(K) * np.sign(q)[:, :, None, :]
+    elif pattern == "not numbers":
+        K[:, :, 96 % S, 5] = np.nan
+        K[:, :, 300 % S, 6] = np.inf
+    return K
+
+
+# positions at the edges of a workgroup's registers: 8, 16, 32 keys for each of 256 threads, 16 to 40 for each of 1024, two launches
+SIZES = [(64, 16), (64, 256), (320, 300), (2048, 64), (2080, 200), (4096, 256), (4128, 1), (8192, 128), (8224, 64), (8192, 257), (16384, 1024),
+         (16416, 64), (24576, 256), (32768, 64), (32800, 500), (40960, 256), (40992, 256), (70016, 64), (49152, 4096), (131072, 1024)]
+PATTERNS = ["even", "one value", "few values", "binades apart", "one far above", "negative", "not numbers"]
+
+
+@pytest.mark.parametrize("Nq,k", SIZES)
+def test_selected_positions_are_the_largest_keys(Nq, k):
+    import torch
+    H = 3 if Nq < 70000 else 1
+    S = Nq + 32
+    q = np.random.default_rng(3).standard_normal((1, H, 2, 128)).astype(np.float32)
+    qd = torch.from_numpy(q).half().cuda()
+    side = torch.cuda.Stream()
+    for pattern in PATTERNS if Nq <= 40992 else PATTERNS[:5]:
+        K = prompt(pattern, S, H, q[:, :, 1])
+        kd = torch.from_numpy(K).half().cuda()
+        vd = torch.from_numpy(np.random.default_rng(4).standard_normal((1, H, S, 128)).astype(np.float32)).half().cuda()
+        sc = binding.SpeCache(1, 1, H, H, 2, 32, (S + 63) // 64 * 64, k, synth.FP16, async_select=2)
+        try:
+            sc.quantize_append(0, kd, vd, S)
+            assert sc.counts(0) == (S, Nq)
+            idx = [torch.full((1, H, k), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+            out = [torch.empty((1, H, 2, 128), dtype=torch.float32, device="cuda") for _ in range(2)]
+            sc.score(0, qd, 2)
+            sc.select_gather(0, idx[0], -1, side)           # the selection alone
+            sc.select_gather(0, idx[1], 0, side)            # the selection and its pairs
+            sc.gather(0, idx[1], 1, side)                   # the pairs of that list again
+            sc.score_topk(0, qd, 2, idx[2])
+            for slot in (0, 1):
+                sc.attend(0, qd, 2, None, None, slot, out[slot])
+            torch.cuda.synchronize()
+            keys = keys_of(sc.debug_logits(0, 2)[0, :, 1])
+            for h in range(H):
+                want = expected(keys[h], k)
+                for i in range(3):
+                    got = idx[i][0, h].cpu().numpy()
+                    assert np.array_equal(got, want), (pattern, h, i, got[:8], want[:8])
+            assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32)), pattern
+            if pattern != "not numbers":
+                assert torch.isfinite(out[0]).all()
+        finally:
+            torch.cuda.synchronize()
+            sc.close()
