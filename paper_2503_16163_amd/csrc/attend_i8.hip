@@ -27,13 +27,14 @@
 // and row).
 //
 // A workgroup takes a chunk of 512 quantised positions (or, as in the vector-ALU kernel, 128 16-bit
-// candidates: attend_extra_chunk); its four waves are independent, each with 128 tokens and its own
+// candidates: rows_extra_wave); its four waves are independent, each with 128 tokens and its own
 // softmax maximum, and meet once, at the end, to merge their (max, sum, sum p V) into the chunk's
 // partial result.  Lane = (32-token sub-group, h, token quad): it holds the logits of four
 // consecutive tokens of row h (the layout in which the scoring wave finishes them), exchanges the
 // numerators with the lane that holds the other row (one DPP rotation), and prepares p s of both
 // rows for the value groups of channel set h.
 #include "attend_common.h"
+#include "extra_wave.h"
 #include "score_i8_wave.h"
 
 namespace specache {
@@ -437,13 +438,17 @@ __device__ __forceinline__ void chunk_bitmap(const AttendArgs& A, int topk, int 
 // Registers: the pass that also scores needs 84 to 88 (five waves per SIMD); compiled for six or eight it
 // spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).
 template <int GROUP, int BITS, bool BF16, bool FUSED>
-__global__ __launch_bounds__(kThreads) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
+__global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
                                                              size_t key_stride) {
     constexpr int NR = 2;
     constexpr int kAreaBytes = FUSED ? kWaveDwords * 4 : kWaveArea;        // per wave
-    constexpr int kRegion = (kWaves * kAreaBytes) / 4 > extra_chunk_floats(NR) ? (kWaves * kAreaBytes) / 4 : extra_chunk_floats(NR);
+    constexpr int kQStride = kD + 8;                                       // halves between the query rows of a 16-bit chunk
+    constexpr int kExtraQ = NR * kQStride / 2, kExtraOut = kWaves * NR * kRowsOStride;   // floats
+    constexpr int kRegion = FUSED || (kWaves * kAreaBytes) / 4 > extra_chunk_floats(NR) ? (kWaves * kAreaBytes) / 4 : extra_chunk_floats(NR);
+    static_assert(kRegion >= kExtraOut && kRegion >= kExtraQ + kWaves * 32 * NR && kExtraQ % 4 == 0, "a 16-bit chunk in the same region");
     __shared__ __attribute__((aligned(16))) float smem[kRegion];
-    __shared__ float red[kWaves * NR];
+    __shared__ RowsOut xout;
+    __shared__ float red[FUSED ? 1 : kWaves * NR];
     __shared__ uint32_t maskbits[kI8Chunk / 32];
     __shared__ __attribute__((aligned(8))) float2 fin[FUSED ? kWaves : 1][4][2];
     __shared__ WaveOut wout;
@@ -469,11 +474,37 @@ __global__ __launch_bounds__(kThreads) void attend_i8_kernel(LayerView L, Attend
     float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2;
 
     if (chunk >= A.n_main) {
-        float m_row[NR], l_row[NR];
-        attend_extra_chunk<NR, 2, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
-        if (tid < NR) {
-            pml[2 * tid] = tid == 0 ? m_row[0] : m_row[1];
-            pml[2 * tid + 1] = tid == 0 ? l_row[0] : l_row[1];
+        if constexpr (!FUSED) {
+            // (the wave-wise form takes 90 registers, this kernel alone 63: eight waves per SIMD)
+            float m_row[NR], l_row[NR];
+            attend_extra_chunk<NR, 2, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
+            if (tid < NR) {
+                pml[2 * tid] = tid == 0 ? m_row[0] : m_row[1];
+                pml[2 * tid + 1] = tid == 0 ? l_row[0] : l_row[1];
+            }
+            return;
+        }
+        // a wave each per 32 candidates, merged as the quantised chunks are
+        uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
+        if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
+        __syncthreads();
+        rows_extra_wave<NR, BF16, NR>(L, A, NR, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, kQStride,
+                                      smem + kExtraQ + wave * 32 * NR, smem, xout);
+        __syncthreads();
+        const int r = tid >> 7, c = tid & 127;
+        float mx = -INFINITY, o = 0.0f, sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, xout.m[w][r]);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float e = xout.m[w][r] == -INFINITY ? 0.0f : exp2_of((xout.m[w][r] - mx) * kLog2e);
+            if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
+            sum = __builtin_fmaf(e, xout.l[w][r], sum);
+        }
+        po[r * kD + c] = o;
+        if (c == 0) {
+            pml[2 * r] = mx;
+            pml[2 * r + 1] = sum;
         }
         return;
     }

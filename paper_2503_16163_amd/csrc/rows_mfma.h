@@ -33,39 +33,19 @@
 // Up to 168 registers, three workgroups per compute unit; held to four it spills.
 #pragma once
 #include "attend_common.h"
+#include "extra_wave.h"
 #include "rows_args.h"
 
 namespace specache {
 namespace {
 
-typedef __bf16 bfloat8 __attribute__((ext_vector_type(8)));
-
-constexpr int kRowsOStride = kD + 4;           // floats between the columns of a wave's merged outputs
 constexpr float kLazyMax = 4.0f;               // a column's maximum moves when a logit exceeds it by more than this
 // The f16 operands are hi + lo (23 bits of a product's multiplier as long as hi is at least 2^-3, an absolute 2^-25 below
 // that), so the scales that go into them are kept near the top of the range: times a power of two, 2^3 to 2^9 for the value
 // scales (p < 2^6), 2^4 to 2^8 for the key scales (|q'| < 2^7), moved where a unit's largest one leaves these bounds.
 constexpr float kValueScaleMost = 512.0f, kValueScaleLeast = 8.0f, kKeyScaleMost = 256.0f, kKeyScaleLeast = 16.0f;
 constexpr int kScaleSet = 7;
-constexpr float kLog2e = 1.44269504088896340736f;
 
-// lane exchange across the 16-lane rows of a wave: result pairs of lanes 16 (32) apart
-__device__ __forceinline__ float xor16_max(float v) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float xor32_max(float v) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float xor16_sum(float v) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-__device__ __forceinline__ float xor32_sum(float v) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
 // hi halves of the lanes of sub-group 0 beside lo halves of sub-group 1's lanes, or the other way round: with the two lanes of a
 // row (8 apart) holding (hi, lo) of sub-groups 0 and 1, columns (r, hi | lo) of sub-group 0 and of sub-group 1
 __device__ __forceinline__ void hi_lo_columns(const uint4v& hi, const uint4v& lo, uint4v& sub0, uint4v& sub1) {
@@ -87,8 +67,6 @@ __device__ __forceinline__ uint32_t wave_max_bits(uint32_t v) {
     return step(step(a, b), step(c, d));
 }
 __device__ __forceinline__ float times_pow2(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
-__device__ __forceinline__ float quarters_max(float v) { return xor32_max(xor16_max(v)); }
-__device__ __forceinline__ float quarters_sum(float v) { return xor32_sum(xor16_sum(v)); }
 
 // Codes as normal numbers instead of subnormals, at half a vector instruction more per code.  The matrix cores align products
 // by their operands' exponents, so that a subnormal code gives up the low end of the other products of a step by as many bits as
@@ -189,18 +167,6 @@ __device__ __forceinline__ void split8(const float x[8], uint4v& hi, uint4v& lo)
     }
 }
 
-__device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
-}
-// the product of 16-bit inputs of the cache's own type: exact products, fp32 accumulation
-template <bool BF16>
-__device__ __forceinline__ float4v mfma_native(uint4v a, uint4v b, float4v c) {
-    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfloat8, a), __builtin_bit_cast(bfloat8, b), c, 0, 0, 0);
-    else return mfma16(a, b, c);
-}
-
-__device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2f(x); }
-
 template <int BITS, int GROUP, int NR>
 struct RowsShape {
     static constexpr int SUBS = 16 / NR;                                     // sub-groups of 32 tokens in flight
@@ -224,122 +190,6 @@ struct RowsShape {
     static constexpr int kBytes = kMainBytes > kMergeBytes ? (kMainBytes > kExtraBytes ? kMainBytes : kExtraBytes)
                                                            : (kMergeBytes > kExtraBytes ? kMergeBytes : kExtraBytes);
 };
-
-// what the waves hand to the merge, per column (r, s): softmax maximum and sum; the merge turns the maximum into the weight
-struct RowsOut {
-    float m[kWaves][16], l[kWaves][16], w[kWaves][16];
-};
-
-// ---- one wave's 32 candidates in 16 bits: staged pairs, residual, the speculative pair ---------------------------
-template <int NR, bool BF16>
-__device__ __forceinline__ void rows_extra_wave(const LayerView& L, const AttendArgs& A, int n_rows, int row, int x0, int lane, int wave,
-                                                const uint16_t* qraw, int q_stride, float* weights, float* o_lds, RowsOut& out) {
-    const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
-    const int ks = A.slot_idx ? L.topk : 0, n_res = A.N - A.Nq, n_ex = ks + n_res + (A.k_spec ? 1 : 0);
-    // A rows: tile mt, row ic is candidate x0 + 2 ic + mt
-    const uint16_t* kp[2];
-    const uint16_t* vp[2];
-    bool spec[2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-        const int x = x0 + 2 * ic + mt;
-        kp[mt] = nullptr;
-        spec[mt] = false;
-        if (x < ks) {
-            const int t = A.slot_idx[(size_t)row * L.topk + x];
-            if (t >= 0 && t < A.Nq) kp[mt] = A.slot + ((size_t)row * L.topk + x) * 256;
-        } else if (x < ks + n_res) {
-            const int t = A.Nq + (x - ks);
-            kp[mt] = L.ring + ((size_t)row * L.R + (t % L.R)) * 256;
-        } else {
-            spec[mt] = x < n_ex;
-        }
-        vp[mt] = kp[mt] ? kp[mt] + kD : nullptr;
-        // a token that this very launch appends (its copy into the ring may not have landed yet) is read from the
-        // caller's buffers, and so is the speculative pair
-        if (L.tail_k != nullptr && x >= ks && x < ks + n_res && A.Nq + (x - ks) == L.tail_N0) {
-            kp[mt] = L.tail_k + (size_t)row * kD;
-            vp[mt] = L.tail_v + (size_t)row * kD;
-        }
-        if (spec[mt]) {
-            kp[mt] = A.k_spec + (size_t)row * kD;
-            vp[mt] = A.v_spec + (size_t)row * kD;
-        }
-    }
-    uint4v kb[2][4];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int kc = 0; kc < 4; ++kc)
-            kb[mt][kc] = kp[mt] ? *reinterpret_cast<const uint4v*>(kp[mt] + 32 * kc + 8 * kq) : uint4v{0u, 0u, 0u, 0u};
-    // value rows: lane = channel pair, one 256-byte row per candidate (lane 2 ic + mt / 2 of the wave knows where)
-    uint32_t vw[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        const uint64_t p = (uint64_t)(uintptr_t)vp[i & 1];
-        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)p, i >> 1), hi = __builtin_amdgcn_readlane((uint32_t)(p >> 32), i >> 1);
-        const uint16_t* v = reinterpret_cast<const uint16_t*>((uintptr_t)(((uint64_t)hi << 32) | lo));
-        vw[i] = v ? *reinterpret_cast<const uint32_t*>(v + 2 * lane) : 0u;
-    }
-    float4v acc[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-        const uint4v b = *reinterpret_cast<const uint4v*>(qraw + r * q_stride + 32 * kc + 8 * kq);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) acc[mt] = mfma_native<BF16>(kb[mt][kc], b, acc[mt]);
-    }
-    // C row 4 kq + v of tile mt is candidate x0 + 8 kq + 2 v + mt.  Which of them exist, and which is the speculative
-    // pair: one bit per candidate, from the lanes of the first quarter
-    const unsigned long long have0 = __ballot(kp[0] != nullptr) & 0xFFFFull, have1 = __ballot(kp[1] != nullptr) & 0xFFFFull;
-    const unsigned long long spec0 = __ballot(spec[0]) & 0xFFFFull, spec1 = __ballot(spec[1]) & 0xFFFFull;
-    const bool last = r % n_rows == n_rows - 1;
-    float l[8], m = -INFINITY;
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int i = 4 * kq + v;
-            const bool sees = s == 0 && (((mt ? have1 : have0) >> i) & 1) && (last || !(((mt ? spec1 : spec0) >> i) & 1));
-            l[2 * v + mt] = sees ? acc[mt][v] * A.sm_scale : -INFINITY;
-            m = fmaxf(m, l[2 * v + mt]);
-        }
-    m = quarters_max(m);
-    const float ms = m == -INFINITY ? 0.0f : m;
-    float sum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const float p = exp2_of((l[t] - ms) * kLog2e);
-        sum += p;
-        if (s == 0) weights[(8 * kq + t) * NR + r] = p;
-    }
-    sum = quarters_sum(sum);
-    if (kq == 0) {
-        out.m[wave][ic] = m;
-        out.l[wave][ic] = sum;
-    }
-    wave_sync();
-    float o[NR][2];
-#pragma unroll
-    for (int rr = 0; rr < NR; ++rr) o[rr][0] = o[rr][1] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        const float v0 = widen16<BF16>(vw[i] & 0xFFFFu), v1 = widen16<BF16>(vw[i] >> 16);
-#pragma unroll
-        for (int r4 = 0; r4 < NR / 4; ++r4) {
-            const float4 p = *reinterpret_cast<const float4*>(weights + i * NR + 4 * r4);
-            const float pv[4] = {p.x, p.y, p.z, p.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o[4 * r4 + e][0] = __builtin_fmaf(pv[e], v0, o[4 * r4 + e][0]);
-                o[4 * r4 + e][1] = __builtin_fmaf(pv[e], v1, o[4 * r4 + e][1]);
-            }
-        }
-    }
-    __syncthreads();   // every wave is done with its weights and with the query rows: the outputs take their place
-#pragma unroll
-    for (int rr = 0; rr < NR; ++rr)
-        *reinterpret_cast<float2*>(o_lds + ((size_t)wave * 16 + rr) * kRowsOStride + 2 * lane) = make_float2(o[rr][0], o[rr][1]);
-}
 
 // sum_c code[i][c] q'[c] s'[c] of the eight tokens of a lane in binary32
 template <int BITS>
