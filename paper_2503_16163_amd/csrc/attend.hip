@@ -18,6 +18,7 @@
 // p_i s[i][m] comes from LDS (computed once per token by the softmax phase).  With 4, 8 or 16 query rows per KV head the
 // matrix cores take the contraction (rows_mfma.h).
 #include "attend_common.h"
+#include "finish_row.h"
 
 namespace specache {
 namespace {
@@ -44,12 +45,14 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     // the one region, and LDS per workgroup decides how many chunks are resident per compute unit
     constexpr int kExtra = extra_chunk_floats(NR);
     constexpr int kMax1 = kExtra > kPs ? kExtra : kPs;
-    constexpr int kRegion = kMax1 > kOl ? kMax1 : kOl;
+    constexpr int kMax2 = kMax1 > kOl ? kMax1 : kOl;
+    constexpr int kRegion = kMax2 * 4 > kFinishLdsBytes ? kMax2 : kFinishLdsBytes / 4;
     __shared__ __attribute__((aligned(16))) float smem[kRegion];
     __shared__ float red[kWaves * NR * (1 + M)];
     __shared__ float red_sum[kWaves * NR];
     __shared__ float red_z[kWaves * NR * M];
     __shared__ uint32_t maskbits[CH / 32];
+    __shared__ FinishShared fin_shared;
 
     float* ps = smem;                        // [CH/16][M] cells
     float* o_lds = smem;                     // [kWaves][NR][128]
@@ -68,8 +71,8 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
         chunk = id % A.n_main;
     }
     float m_row[NR], l_row[NR];
-    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
-    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2;
+    const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4);
+    const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
 
     if (chunk < A.n_main) {
         // ------------------------------------------------------------ quantised positions
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
             float v = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) v += o_lds[((size_t)w * NR + r) * kD + c] + red_z[(w * NR + r) * M + c / GROUP];
-            po[e] = v;
+            store_partial(po, e, v, A.fin.arrived != nullptr);
         }
     } else {
         attend_extra_chunk<NR, NROWS, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
@@ -278,9 +281,9 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
 #pragma unroll
         for (int r = 0; r < NR; ++r)
             if (r == tid) { mv = m_row[r]; lv = l_row[r]; }
-        pml[2 * tid] = mv;
-        pml[2 * tid + 1] = lv;
+        store_max_sum(pml, tid, mv, lv, A.fin.arrived != nullptr);
     }
+    if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
 }
 
 // Merge the chunk partials of one (KV head, query row): o = sum_c o_c e^(m_c - m) / sum_c l_c e^(m_c - m).
@@ -396,7 +399,7 @@ hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* 
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (phases & kAttendCombine)
+    if ((phases & kAttendCombine) && !A.fin.arrived)
         SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
                    A.max_chunks, A.n_main + n_extra, NR, out, announce);
     return hipGetLastError();
@@ -410,6 +413,7 @@ hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, floa
         const int n_extra = (n_ex + kExtraChunk - 1) / kExtraChunk;             \
         A.n_chunks = A.n_main + n_extra;                                        \
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
+        if (!merges_in_launch(L.rows, A.n_chunks, L.G * n_rows)) A.fin.arrived = nullptr; \
         return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, announce, stream); \
     }
     SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1)
@@ -432,7 +436,7 @@ int attend_max_chunks() { return kCombineMaxChunks; }
 hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, int Nq, float sm_scale,
                          const float* logits, size_t logit_stride, const uint16_t* slot, const int32_t* slot_idx,
                          const void* k_spec, const void* v_spec, const AttendScratch& scratch, float* out,
-                         int phases, hipStream_t stream, Announce announce) {
+                         int phases, uint32_t* arrived, hipStream_t stream, Announce announce) {
     AttendArgs A;
     A.q = (const uint16_t*)q;
     A.logits = logits;
@@ -451,24 +455,29 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
     A.N = N;
     A.Nq = Nq;
     A.sm_scale = sm_scale;
+    A.fin.arrived = arrived;
+    A.fin.out = out;
+    A.fin.rows = L.rows;
     const int n_ex = (slot_idx ? L.topk : 0) + (N - Nq) + (k_spec ? 1 : 0);
     // 4, 8 or 16 query rows per KV head, and 4-bit codes: a partial pass of their own (rows_mfma.h), with its own chunking
     if (rows_uses_matrix_cores(L, n_rows)) {
         if (phases & kAttendPartial) {
             RowsArgs R{A, nullptr, 0, n_rows, 0};
-            hipError_t e = launch_rows(L, R, kRowsAttend, stream);
+            hipError_t e = launch_rows(L, R, kRowsAttend, nullptr, stream);
             if (e != hipSuccess) return e;
         }
-        if (phases & kAttendCombine)
+        const int n_chunks = rows_chunks(L, n_rows, Nq, n_ex, A.max_chunks);
+        if ((phases & kAttendCombine) && !(arrived && merges_in_launch(L.rows, n_chunks, L.G * n_rows)))
             SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * L.G * n_rows), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                       A.max_chunks, rows_chunks(L, n_rows, Nq, n_ex, A.max_chunks), L.G * n_rows, out, announce);
+                       A.max_chunks, n_chunks, L.G * n_rows, out, announce);
         return hipGetLastError();
     }
     // one query head per KV head, two rows, 2-bit values: the partial pass with the value side on the
     // integer matrix cores (same chunking, same partial-result format, same merge kernel)
     if ((phases & kAttendPartial) && attend_uses_int8_matrix_cores(L, n_rows) && !(kernel_choice() & kChoiceAttendValu)) {
+        bool merged = false;
         hipError_t e = launch_attend_i8_partial(L, q, N, Nq, sm_scale, logits, logit_stride, slot, slot_idx, k_spec, v_spec,
-                                                scratch, nullptr, 0, nullptr, stream);
+                                                scratch, nullptr, 0, nullptr, A.fin, &merged, stream);
         if (e != hipSuccess) return e;
         phases &= ~kAttendPartial;
         if (!phases) return hipSuccess;

@@ -100,6 +100,26 @@ __device__ __forceinline__ void chunk_softmax(float (*lg)[CH], int n, float* red
     __syncthreads();
 }
 
+// Partials that another workgroup of the same launch merges (finish_row.h) are stored past the L2.
+constexpr int kAgentScope = 16;   // cache policy bit sc1 of a buffer load or store: device scope, where the L2 caches meet
+
+__device__ __forceinline__ auto buffer_of(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
+}
+// a chunk's partials: output e of [NR][128], and the maximum and sum of row r
+template <typename Buffer>
+__device__ __forceinline__ void store_partial(Buffer po, int e, float v, bool past_l2) {
+    if (past_l2) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), po, e * 4, 0, kAgentScope);
+    else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), po, e * 4, 0, 0);
+}
+template <typename Buffer>
+__device__ __forceinline__ void store_max_sum(Buffer pml, int r, float m, float sum, bool past_l2) {
+    typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+    const uint2v v = {__float_as_uint(m), __float_as_uint(sum)};
+    if (past_l2) __builtin_amdgcn_raw_buffer_store_b64(v, pml, r * 8, 0, kAgentScope);
+    else __builtin_amdgcn_raw_buffer_store_b64(v, pml, r * 8, 0, 0);
+}
+
 // LDS floats attend_extra_chunk needs: lg[NR][128], the query rows [NR][128], two pointer tables
 // and a flag table of 128 entries; at the end the same area holds o_lds[4][NR][128].
 __host__ __device__ constexpr int extra_chunk_floats(int NR) {
@@ -108,12 +128,12 @@ __host__ __device__ constexpr int extra_chunk_floats(int NR) {
 }
 
 // One chunk of up to 128 16-bit candidates of a (batch, KV head) row: logits from the 16-bit keys,
-// softmax numerators, weighted sum of the 16-bit values.  Writes the chunk's un-normalised output
-// to po[NR][128] and its (max, sum) per query row to m_row / l_row.  Workgroup of 256 threads;
+// softmax numerators, weighted sum of the 16-bit values.  Stores the chunk's un-normalised output
+// [NR][128] in po and its (max, sum) per query row to m_row / l_row.  Workgroup of 256 threads;
 // smem: extra_chunk_floats(NR) floats, 16-byte aligned; red: 4 * NR floats.
-template <int NR, int NROWS, bool BF16>
+template <int NR, int NROWS, bool BF16, typename Buffer>
 __device__ __forceinline__ void attend_extra_chunk(const LayerView& L, const AttendArgs& A, int row, int chunk, float* smem,
-                                                   float* red, float* m_row, float* l_row, float* po) {
+                                                   float* red, float* m_row, float* l_row, Buffer po) {
     constexpr int CHX = kExtraChunk;
     float (*lg)[CHX] = reinterpret_cast<float (*)[CHX]>(smem);
     float* o_lds = smem;                     // [4][NR][128]
@@ -259,7 +279,7 @@ __device__ __forceinline__ void attend_extra_chunk(const LayerView& L, const Att
         float v = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) v += o_lds[((size_t)w * NR + r) * kD + cc];
-        po[e] = v;
+        store_partial(po, e, v, A.fin.arrived != nullptr);
     }
 }
 

@@ -35,6 +35,7 @@
 // rows for the value groups of channel set h.
 #include "attend_common.h"
 #include "extra_wave.h"
+#include "finish_row.h"
 #include "score_i8_wave.h"
 
 namespace specache {
@@ -364,9 +365,9 @@ __device__ __forceinline__ void empty_wave(int wave, int lane, WaveOut& out) {
 }
 
 // Merge of the four waves of a chunk (after a workgroup barrier): thread = (row r, channel c).
-template <int GROUP, int BITS>
-__device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_stride, const WaveOut& out, int tid, float* po,
-                                            float* pml) {
+template <int GROUP, int BITS, typename Buffer>
+__device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_stride, const WaveOut& out, int tid, Buffer po,
+                                            Buffer pml, bool past_l2) {
     constexpr int M = kD / GROUP, MPL = M >= 2 ? M / 2 : 1;
     const int r = tid >> 7, c = tid & 127;
     // where the channel's sums sit in its set's results: 2 bits [row][plane][j = c % 4][code lane (c / 4) % 16],
@@ -403,11 +404,8 @@ __device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_strid
         o = __builtin_fmaf(e, val, o);
         lsum = __builtin_fmaf(e, ls, lsum);
     }
-    po[r * kD + c] = o;
-    if (c == 0) {
-        pml[2 * r] = mmax;
-        pml[2 * r + 1] = lsum;
-    }
+    store_partial(po, r * kD + c, o, past_l2);
+    if (c == 0) store_max_sum(pml, r, mmax, lsum, past_l2);
 }
 
 // (row, chunk) of this workgroup: the 16-bit chunks are chains of dependent loads and are dispatched first
@@ -452,6 +450,8 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
     __shared__ uint32_t maskbits[kI8Chunk / 32];
     __shared__ __attribute__((aligned(8))) float2 fin[FUSED ? kWaves : 1][4][2];
     __shared__ WaveOut wout;
+    __shared__ FinishShared fin_shared;
+    static_assert(kRegion * 4 >= kFinishLdsBytes, "the merge of a row in the same region");
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n_tail = L.tail_k ? L.rows : 0;
@@ -470,42 +470,38 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
     }
     int row, chunk;
     chunk_of_block(A, L.rows, (int)blockIdx.x - n_tail, row, chunk);
-    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
-    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2;
+    float* po_chunk = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
+    const auto po = buffer_of(po_chunk, NR * kD * 4);
+    const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
 
     if (chunk >= A.n_main) {
         if constexpr (!FUSED) {
             // (the wave-wise form takes 90 registers, this kernel alone 63: eight waves per SIMD)
             float m_row[NR], l_row[NR];
             attend_extra_chunk<NR, 2, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
-            if (tid < NR) {
-                pml[2 * tid] = tid == 0 ? m_row[0] : m_row[1];
-                pml[2 * tid + 1] = tid == 0 ? l_row[0] : l_row[1];
+            if (tid < NR) store_max_sum(pml, tid, tid == 0 ? m_row[0] : m_row[1], tid == 0 ? l_row[0] : l_row[1], A.fin.arrived != nullptr);
+        } else {
+            // a wave each per 32 candidates, merged as the quantised chunks are
+            uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
+            if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
+            __syncthreads();
+            rows_extra_wave<NR, BF16, NR>(L, A, NR, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, kQStride,
+                                          smem + kExtraQ + wave * 32 * NR, smem, xout);
+            __syncthreads();
+            const int r = tid >> 7, c = tid & 127;
+            float mx = -INFINITY, o = 0.0f, sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, xout.m[w][r]);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float e = xout.m[w][r] == -INFINITY ? 0.0f : exp2_of((xout.m[w][r] - mx) * kLog2e);
+                if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
+                sum = __builtin_fmaf(e, xout.l[w][r], sum);
             }
-            return;
+            store_partial(po, r * kD + c, o, A.fin.arrived != nullptr);
+            if (c == 0) store_max_sum(pml, r, mx, sum, A.fin.arrived != nullptr);
         }
-        // a wave each per 32 candidates, merged as the quantised chunks are
-        uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
-        if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
-        __syncthreads();
-        rows_extra_wave<NR, BF16, NR>(L, A, NR, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, kQStride,
-                                      smem + kExtraQ + wave * 32 * NR, smem, xout);
-        __syncthreads();
-        const int r = tid >> 7, c = tid & 127;
-        float mx = -INFINITY, o = 0.0f, sum = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, xout.m[w][r]);
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const float e = xout.m[w][r] == -INFINITY ? 0.0f : exp2_of((xout.m[w][r] - mx) * kLog2e);
-            if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
-            sum = __builtin_fmaf(e, xout.l[w][r], sum);
-        }
-        po[r * kD + c] = o;
-        if (c == 0) {
-            pml[2 * r] = mx;
-            pml[2 * r + 1] = sum;
-        }
+        if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
         return;
     }
 
@@ -542,9 +538,13 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
                                    [&]() { if (wave_maps) wave_bitmap_apply(ti, nw, lane, maskbits + 4 * wave); },
                                    [&]() { value_loads<GROUP, BITS>(L, row, c0, w0, nw, lane, v); });
             if (live) {
-                if (h == 1)   // the speculative row ranks the positions
-                    *reinterpret_cast<uint4*>(keys + (size_t)row * key_stride + c0 + w0 + t0) =
-                        make_uint4(float_to_key(lgv[0]), float_to_key(lgv[1]), float_to_key(lgv[2]), float_to_key(lgv[3]));
+                if (h == 1) {   // the speculative row ranks the positions
+                    const uint4v k4 = {float_to_key(lgv[0]), float_to_key(lgv[1]), float_to_key(lgv[2]), float_to_key(lgv[3])};
+                    const auto keys_row = buffer_of(keys + (size_t)row * key_stride, (uint32_t)A.Nq * 4u);
+                    // past the L2 where the launch announces them before it ends (finish_row.h)
+                    if (A.fin.word) __builtin_amdgcn_raw_buffer_store_b128(k4, keys_row, (c0 + w0 + t0) * 4, 0, kAgentScope);
+                    else __builtin_amdgcn_raw_buffer_store_b128(k4, keys_row, (c0 + w0 + t0) * 4, 0, 0);
+                }
                 if (A.logits_out)   // kept only when the caller asked for them (parity hook)
                     *reinterpret_cast<float4*>(A.logits_out + ((size_t)row * NR + h) * A.logit_stride + c0 + w0 + t0) =
                         make_float4(lgv[0], lgv[1], lgv[2], lgv[3]);
@@ -561,7 +561,8 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
         empty_wave(wave, lane, wout);
     }
     __syncthreads();
-    merge_waves<GROUP, BITS>(reinterpret_cast<const uint8_t*>(smem), kAreaBytes, wout, tid, po, pml);
+    merge_waves<GROUP, BITS>(reinterpret_cast<const uint8_t*>(smem), kAreaBytes, wout, tid, po, pml, A.fin.arrived != nullptr);
+    if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
 }
 
 }  // namespace
@@ -572,7 +573,7 @@ bool attend_uses_int8_matrix_cores(const LayerView& L, int n_rows) { return L.G 
 hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, int Nq, float sm_scale, const float* logits,
                                     size_t logit_stride, const uint16_t* slot, const int32_t* slot_idx, const void* k_spec,
                                     const void* v_spec, const AttendScratch& scratch, uint32_t* keys, size_t key_stride,
-                                    float* logits_out, hipStream_t stream) {
+                                    float* logits_out, const Finish& finish, bool* merged, hipStream_t stream) {
     if (!attend_uses_int8_matrix_cores(L, 2) || Nq % kBlockTokens) return hipErrorInvalidValue;
     AttendArgs A;
     A.q = (const uint16_t*)q;
@@ -593,6 +594,9 @@ hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, in
     A.n_main = (Nq + kI8Chunk - 1) / kI8Chunk;
     A.n_chunks = A.n_main + (n_ex + kExtraChunk - 1) / kExtraChunk;
     if (A.n_chunks > A.max_chunks || A.n_chunks < 1) return hipErrorInvalidValue;
+    A.fin = finish;
+    if (!merges_in_launch(L.rows, A.n_chunks, 2)) A.fin = Finish{};
+    *merged = A.fin.arrived != nullptr;
     const dim3 grid(A.n_chunks * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
 #define SPC_AI8_B(G_, B_, F_)                                                                                              \
     do {                                                                                                                   \

@@ -107,6 +107,23 @@ struct Announce {
     uint64_t* word = nullptr;
     uint64_t value = 0;
 };
+// The merge inside the launch that makes the partials (finish_row.h).  arrived: [rows + 1] counters, zero between launches; null:
+// a launch of its own merges.
+struct Finish {
+    uint32_t* arrived = nullptr;
+    float* out = nullptr;        // [rows][NR][128]
+    uint64_t* word = nullptr;    // announced when every row's keys are stored (null: nothing to announce)
+    uint64_t value = 0;
+    int rows = 0;
+};
+// Where the launch merges: a row's partials are few enough for one workgroup's loads to be requested at once (chunks x NR <= 64), and
+// the launch is no more than one round of workgroups.  A step of 8 layers, us a pass, merge in the launch against a launch of its own: 1
+// x 4096 (chunks x NR = 20) 260 / 320, 4 x 1500 x 2 sequences, 4 bits (12) 304 / 365, 8 x 9000 (40) 165 / 169, 16 x 8000 (34) 217 / 226, 32 x
+// 4000 (20) 230 / 242, 32 x 8000 (36, 576 workgroups) 246 / 264.  Beyond: 32 x 16k (70) 349 / 336; 8 query rows, 2 x 2000 (72) 168 /
+// 163; 16 query rows, 4 x 3000 (400) 246 / 173 (partials past the L2 cost more the more there are, and one workgroup reads them).
+constexpr int kFinishMost = 64;
+inline bool merges_in_launch(int rows, int n_chunks, int NR) { return rows * n_chunks <= 1024 && n_chunks * NR <= kFinishMost; }
+
 int attend_main_chunk_tokens(int NR);   // for the limits of specache_create and specache_attend_static
 // the chunks that such a limit allows for NR query rows per KV head, Nq quantised and n_16bit 16-bit candidates
 int attend_chunks(int NR, int Nq, int n_16bit);
@@ -115,7 +132,8 @@ int attend_max_chunks();   // chunks per row the merge kernel handles
 hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, int Nq, float sm_scale,
                          const float* logits, size_t logit_stride, const uint16_t* slot,
                          const int32_t* slot_idx, const void* k_spec, const void* v_spec,
-                         const AttendScratch& scratch, float* out, int phases, hipStream_t stream, Announce announce = Announce());
+                         const AttendScratch& scratch, float* out, int phases, uint32_t* arrived, hipStream_t stream,
+                         Announce announce = Announce());
 
 // the same partial pass for one query head per KV head, two rows, 2-bit values: value side on the integer matrix cores
 bool attend_uses_int8_matrix_cores(const LayerView& L, int n_rows);
@@ -124,7 +142,7 @@ bool attend_uses_int8_matrix_cores(const LayerView& L, int n_rows);
 hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, int Nq, float sm_scale, const float* logits,
                                     size_t logit_stride, const uint16_t* slot, const int32_t* slot_idx, const void* k_spec,
                                     const void* v_spec, const AttendScratch& scratch, uint32_t* keys, size_t key_stride,
-                                    float* logits_out, hipStream_t stream);
+                                    float* logits_out, const Finish& finish, bool* merged, hipStream_t stream);
 
 // Process-wide choice of kernels, for A/B measurements of one formulation against the other
 // (specache_debug_kernel_choice): bits set here send the shapes that the matrix-core kernels

@@ -18,6 +18,7 @@ struct AttendArgs {
     float* part_ml;            // [rows][max_chunks][NR][2]
     int max_chunks, n_main, n_chunks, N, Nq;
     float sm_scale;
+    Finish fin;
 };
 
 // rows_kernel (rows_mfma.h): scoring and attention of 4, 8 or 16 query rows per KV head, and of any number on 4-bit codes
@@ -36,6 +37,7 @@ bool rows_in_one_launch(const LayerView& L, int n_rows);                       /
 int rows_max_main_chunks(int rows, int max_seq);                               // most chunks of quantised positions per row
 // chunks launch_rows splits a row into: at most max_chunks, where chunks of kRowsMaxChunk tokens allow that
 int rows_chunks(const LayerView& L, int n_rows, int Nq, int n_16bit, int max_chunks);
-hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, hipStream_t stream);
+// merged: whether the launch merges its partials itself (R.at.fin)
+hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, bool* merged, hipStream_t stream);
 
 }  // namespace specache

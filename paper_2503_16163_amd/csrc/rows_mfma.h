@@ -34,6 +34,7 @@
 #pragma once
 #include "attend_common.h"
 #include "extra_wave.h"
+#include "finish_row.h"
 #include "rows_args.h"
 
 namespace specache {
@@ -219,6 +220,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     __shared__ __attribute__((aligned(16))) uint8_t smem[S::kBytes];
     __shared__ uint32_t maskbits[MODE == kRowsScore ? 1 : kRowsMaxChunk / 32];
     __shared__ RowsOut out;
+    __shared__ FinishShared fin_shared;
+    static_assert(MODE == kRowsScore || S::kBytes >= kFinishLdsBytes, "the merge of a row in the same region");
     const AttendArgs& A = R.at;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
@@ -315,7 +318,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         // a wave's position is the same for its lanes: addresses are a scalar base plus a lane's offset
         const uint32_t km_lane = 8u * lane, kc_lane = (uint32_t)(((ic % 4) / 2) * 1024 + (ic / 4) * 16 + 8 * (ic % 2) + kq * 2048);
         const uint32_t vc_lane = (uint32_t)((kq >> 1) * (256 * BITS) + 8 * (kq & 1) + value_lane<BITS>(0, ic) * 16);
-        uint32_t* keys_row = R.keys + (size_t)row * R.key_stride;
+        // (where the launch announces its scores, the keys have to be past the L2 by then: finish_row.h)
+        const auto keys_row = buffer_of(R.keys + (size_t)row * R.key_stride, (uint32_t)A.Nq * 4u);
         const size_t row_logits = (size_t)row * nq * A.logit_stride;
         const uint32_t logit_lane = (uint32_t)(r * A.logit_stride + 32 * s + 8 * kq);
         auto load_keys = [&](int t_wave) {
@@ -584,7 +588,10 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                             for (int h = 0; h < G / 2; ++h) b = fmaxf(b, l_tab[((lane >> 5) * (G / 2) + h) * S::kKeyStride + t]);
                             b = xor32_max(b);
                         }
-                        if (t0 + t < A.Nq && (UNIT >= 64 || lane < 32)) keys_row[(uint32_t)(t0 + t)] = float_to_key(b);
+                        if (UNIT >= 64 || lane < 32) {   // (positions beyond the quantised ones lie beyond the buffer's range)
+                            if (MODE == kRowsBoth && A.fin.word) __builtin_amdgcn_raw_buffer_store_b32(float_to_key(b), keys_row, (t0 + t) * 4, 0, kAgentScope);
+                            else __builtin_amdgcn_raw_buffer_store_b32(float_to_key(b), keys_row, (t0 + t) * 4, 0, 0);
+                        }
                     }
                     wave_sync();
                 }
@@ -783,8 +790,8 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
         out.w[w][col] = mv == -INFINITY ? 0.0f : exp2_of((mv - mx) * kLog2e);
     }
     __syncthreads();
-    float* po = A.part_o + (((size_t)row * A.max_chunks + chunk) * nq) * kD;
-    float* pml = A.part_ml + (((size_t)row * A.max_chunks + chunk) * nq) * 2;
+    const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * nq) * kD, (uint32_t)(nq * kD) * 4u);
+    const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * nq) * 2, (uint32_t)nq * 8u);
     for (int e = tid; e < nq * kD; e += kThreads) {
         const int rr = e / kD, c = e % kD;
         float v = 0.0f;
@@ -795,7 +802,7 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 const float wt = out.w[w][ss * NR + rr];
                 if (wt != 0.0f) v = __builtin_fmaf(wt, o_lds[((size_t)w * 16 + ss * NR + rr) * kRowsOStride + c], v);
             }
-        po[e] = v;
+        store_partial(po, e, v, A.fin.arrived != nullptr);
     }
     if (tid < nq) {
         float mx = -INFINITY, sum = 0.0f;
@@ -805,9 +812,9 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 mx = fmaxf(mx, out.m[w][ss * NR + tid]);
                 sum = __builtin_fmaf(out.w[w][ss * NR + tid], out.l[w][ss * NR + tid], sum);
             }
-        pml[2 * tid] = mx;
-        pml[2 * tid + 1] = sum;
+        store_max_sum(pml, tid, mx, sum, A.fin.arrived != nullptr);
     }
+    if (A.fin.arrived) finish_row(A, row, nq, reinterpret_cast<float*>(smem), fin_shared);
 }
 
 // launch of one mode for codes of BITS bits; at: everything but the chunking

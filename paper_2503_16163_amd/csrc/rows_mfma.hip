@@ -59,7 +59,7 @@ int rows_chunks(const LayerView& L, int n_rows, int Nq, int n_16bit, int max_chu
     return n_main + n_extra;
 }
 
-hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, hipStream_t stream) {
+hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, bool* merged, hipStream_t stream) {
     const int NR = padded_rows(L, R.n_rows);
     if (!rows_uses_matrix_cores(L, R.n_rows) || R.at.Nq % kBlockTokens || R.at.Nq % L.group) return hipErrorInvalidValue;
     const int n_ex = mode == kRowsScore ? 0 : (R.at.slot_idx ? L.topk : 0) + (R.at.N - R.at.Nq) + (R.at.k_spec ? 1 : 0);
@@ -68,6 +68,8 @@ hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, hipStream_t str
     R.at.n_chunks = R.at.n_main + n_extra;
     if (R.at.n_chunks < 1) return hipErrorInvalidValue;
     if (mode != kRowsScore && R.at.n_chunks > R.at.max_chunks) return hipErrorInvalidValue;
+    if (!merges_in_launch(L.rows, R.at.n_chunks, L.G * R.n_rows)) R.at.fin = Finish{};
+    if (merged) *merged = mode != kRowsScore && R.at.fin.arrived != nullptr;
     return L.bits == 1   ? launch_rows_b1(L, R, NR, mode, stream)
            : L.bits == 2 ? launch_rows_b2(L, R, NR, mode, stream)
                          : launch_rows_b4(L, R, NR, mode, stream);

@@ -278,7 +278,7 @@ hipError_t launch_score(const LayerView& L, const void* q, int n_rows, int Nq, f
         R.keys = keys;
         R.key_stride = key_stride;
         R.n_rows = n_rows;
-        return launch_rows(L, R, kRowsScore, stream);
+        return launch_rows(L, R, kRowsScore, nullptr, stream);
     }
     if (L.bits == 2) return launch2<2>(L, q, n_rows, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);
     if (L.bits == 1) return launch2<1>(L, q, n_rows, Nq, sm_scale, logits, logit_stride, keys, key_stride, stream);

@@ -72,6 +72,7 @@ struct Layer {
     // Where scoring and attention are one call its merge kernel stores `scored_value` to the word `scored_word`, and the
     // selection's stream waits for that value: an event, pending as it always is when the selection is enqueued, costs
     // the issuing thread 10 us more (launch, event, wait, launch on the other stream: 19.7 us; with the word: 8.6).
+    uint32_t* arrived = nullptr;         // [rows + 1] counters of the merge inside a launch (finish_row.h), zero between launches
     uint64_t* scored_word = nullptr;     // signal memory, one word per layer (layers may be stepped on different streams)
     uint64_t scored_value = 0;
     bool scored_by_word = false;         // the layer's last scoring announced itself through the word, not idx_ready
@@ -270,6 +271,7 @@ void free_all(specache_ctx* ctx) {
         if (L.selected) (void)hipEventDestroy(L.selected);
         (void)hipFree(L.keys);
         (void)hipFree(L.scored_word);
+        (void)hipFree(L.arrived);
     }
     for (auto& ss : ctx->select_scratch) { (void)hipFree(ss.s.cand_keys); (void)hipFree(ss.s.cand_idx); }
     for (auto& sp : ctx->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
@@ -477,6 +479,8 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         SPC_ALLOC(hipMalloc((void**)&v.vc, rows * v.vc_stride));
         SPC_ALLOC(hipMalloc((void**)&v.km, rows * v.km_stride * 4));
         SPC_ALLOC(hipMalloc((void**)&v.vm, rows * v.vm_stride * 4));
+        SPC_ALLOC(hipMalloc((void**)&L.arrived, ((size_t)rows + 1) * 4));
+        SPC_ALLOC(hipMemset(L.arrived, 0, ((size_t)rows + 1) * 4));
         SPC_ALLOC(hipMalloc((void**)&v.ring, (size_t)rows * c.residual * kRowBytes));
         SPC_ALLOC(hipHostMalloc(&L.host_alloc, (size_t)rows * cap * kRowBytes, hipHostMallocDefault));
         void* dev_view = nullptr;
@@ -877,7 +881,7 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
         TimedLaunch t(ctx, st, phase == kAttendPartial ? SPECACHE_K_ATTEND : SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
                                    slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
-                                   v_spec, scratch, out, phase, st));
+                                   v_spec, scratch, out, phase, L.arrived, st));
     }
     return record_attended(ctx, L, slot, st);
 }
@@ -935,7 +939,13 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
     const bool by_word = !captured && words_may_order(ctx);
-    bool scored_carried = false;
+    bool scored_carried = false, merged = false;
+    Finish finish;
+    finish.arrived = L.arrived;
+    finish.out = out;
+    finish.word = by_word ? L.scored_word : nullptr;
+    finish.value = L.scored_value + 1;
+    finish.rows = L.view.rows;
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
         CarriedEvent scored(ctx, by_word || captured ? nullptr : L.idx_ready);
@@ -958,11 +968,12 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
             R.keys = L.keys;
             R.key_stride = ctx->logit_stride;
             R.n_rows = n_rows;
-            SPC_HIP(ctx, launch_rows(view, R, kRowsBoth, st));
+            R.at.fin = finish;
+            SPC_HIP(ctx, launch_rows(view, R, kRowsBoth, &merged, st));
         } else {
             SPC_HIP(ctx, launch_attend_i8_partial(view, q, N1, L.Nq, ctx->sm_scale, nullptr, ctx->logit_stride,
                                                   slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
-                                                  v_spec, ctx->scratch, L.keys, ctx->logit_stride, keep ? ctx->logits : nullptr, st));
+                                                  v_spec, ctx->scratch, L.keys, ctx->logit_stride, keep ? ctx->logits : nullptr, finish, &merged, st));
         }
         scored_carried = scored.landed();
     }
@@ -973,11 +984,11 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     // the side stream runs beside it
     if (!by_word)
         if (int rc = record_scored(ctx, L, layer, n_rows, st, scored_carried)) return rc;
-    {
+    if (!merged) {
         TimedLaunch t(ctx, st, SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
                                    slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec, v_spec,
-                                   ctx->scratch, out, kAttendCombine, st, by_word ? Announce{L.scored_word, L.scored_value + 1} : Announce{}));
+                                   ctx->scratch, out, kAttendCombine, nullptr, st, by_word ? Announce{L.scored_word, L.scored_value + 1} : Announce{}));
     }
     if (by_word) {
         ++L.scored_value;

@@ -1,0 +1,59 @@
+"""The merge of a row's partial results inside the launch that makes them, on both sides of the rule that chooses it (chunks x query
+rows up to 64): scoring and attention in one launch, attention alone, one and two query rows, shapes whose slices of the
+chunks differ, with steps in a row so that a counter left wrong by one launch shows in the next."""
+import pytest
+
+from paper_2503_16163_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv,S,bits,g,k,n_rows,one_pass", [
+    (2, 2, 200, 2, 32, 16, 2, True), (1, 1, 4096, 2, 32, 64, 2, True), (3, 3, 15872 + 40, 2, 64, 64, 2, True), (3, 3, 15872 + 600, 1, 32, 64, 2, True),
+    (2, 2, 3000, 2, 32, 300, 2, False), (2, 2, 3000, 1, 128, 64, 1, False), (4, 2, 1500, 2, 32, 40, 1, False),
+    (8, 2, 1700, 2, 32, 48, 2, True), (8, 2, 1990, 2, 64, 48, 2, True), (8, 2, 1700, 1, 32, 48, 2, False), (8, 1, 340, 2, 32, 48, 2, True),
+    (8, 1, 600, 2, 32, 48, 2, True), (4, 4, 1500, 4, 32, 32, 2, False), (4, 2, 900, 2, 32, 200, 2, True), (2, 2, 1500, 4, 64, 16, 1, False)])
+def test_merge_in_the_launch(Hq, Hkv, S, bits, g, k, n_rows, one_pass):
+    from tests.harness import Case
+    # the speculative flow with two query rows, the non-speculative one with one
+    c = Case(1, Hq, Hkv, S, synth.BF16 if Hq > 4 else synth.FP16, bits, g, k, R=max(64, g), seed=7300 + S + bits, n_rows=n_rows,
+             sample=[(0, h) for h in range(min(Hkv, 2))], async_select=2 if n_rows == 2 else 0, one_pass=one_pass, fused_append=one_pass)
+    try:
+        c.load()
+        for t in range(5):
+            c.append_token(t)
+            if n_rows == 2:
+                c.decode_step(check_logits=False)
+            else:
+                c.nonspec_step()
+        assert c.stats["max_out_err"] < 5e-5, c.stats
+    finally:
+        c.close()
+
+
+def test_layers_on_streams_of_their_own_keep_their_counters():
+    """Every layer counts for itself: layers stepped on different streams, one after the other, and a context opened in between."""
+    import torch
+    from paper_2503_16163_amd import binding
+    H, S, k = 4, 1000, 16
+    q = synth.make_queries_device(5, 1, 1, H, 128, synth.FP16).view(1, H, 2, 128).contiguous()
+    kd, vd = synth.make_kv_device(5, 1, H, S, 128, synth.FP16)
+    want = None
+    for rounds in range(2):
+        sc = binding.SpeCache(3, 1, H, H, 2, 32, 1024, k, synth.FP16, async_select=2)
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        try:
+            for L in range(3):
+                sc.quantize_append(L, kd, vd, S)
+            torch.cuda.synchronize()
+            for t in range(6):
+                for L in range(3):
+                    out = torch.zeros((1, H, 2, 128), dtype=torch.float32, device="cuda")
+                    torch.cuda.synchronize()
+                    sc.score_attend(L, q, 2, None, None, -1, out, streams[(L + t) % 3])
+                    torch.cuda.synchronize()
+                    want = out if want is None else want
+                    assert torch.equal(out, want), (rounds, t, L)
+        finally:
+            torch.cuda.synchronize()
+            sc.close()
