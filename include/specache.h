@@ -396,7 +396,8 @@ enum {
     SPECACHE_K_APPEND_COPY = 1, /* offload to host store + residual update   */
     SPECACHE_K_SCORE = 2,       /* fused dequantise + q.K^T                  */
     SPECACHE_K_TOPK = 3,        /* radix select + ordered compaction         */
-    SPECACHE_K_GATHER = 4,      /* host-link gather (side stream)            */
+    SPECACHE_K_GATHER = 4,      /* host-link gather (side stream); of specache_select_gather the launch
+                                   that selects and fetches (then nothing counts as K_TOPK) */
     SPECACHE_K_ATTEND = 5,      /* mixed attention: partial pass over chunks */
     SPECACHE_K_ATTEND_COMBINE = 6, /* mixed attention: merge of the chunks    */
     SPECACHE_K_SCORE_ATTEND = 7, /* scoring and partial pass of specache_score_attend in one launch */

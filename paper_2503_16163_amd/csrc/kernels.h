@@ -94,6 +94,11 @@ hipError_t launch_topk(int rows, int Nq, int k, const uint32_t* keys, size_t key
 hipError_t launch_gather(const LayerView& L, int Nq, const int32_t* idx, uint16_t* slot, int32_t* slot_idx,
                          bool link_shared, hipStream_t stream);
 
+// both in one launch: a row's pairs are fetched by the workgroup that selected them
+bool selects_and_gathers(int rows, int Nq, int k);   // where that is the better way
+hipError_t launch_select_gather(const LayerView& L, int Nq, const uint32_t* keys, size_t key_stride, int32_t* idx_out,
+                                uint16_t* slot, int32_t* slot_idx, bool link_shared, hipStream_t stream);
+
 // attend: partial pass + combine.  slot/slot_idx may be null (nothing prefetched).
 struct AttendScratch {
     float* part_o;   // [rows][max_chunks][NR][128]

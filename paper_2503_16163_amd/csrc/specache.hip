@@ -335,8 +335,9 @@ int order_gather_after_attend(specache_ctx* ctx, Layer& L, int slot, hipStream_t
     return SPECACHE_OK;
 }
 
-// Launches the gather of `idx` into `slot` on st and records its completion.
-int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int slot, hipStream_t st) {
+// Launches the gather of `idx` into `slot` on st and records its completion.  select_out: the gather's launch also ranks
+// the layer's keys, and idx (= select_out) receives the positions it fetches.
+int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int slot, hipStream_t st, int32_t* select_out = nullptr) {
     // the slot's previous gather, if it ran on another stream that this one has not waited for
     if (L.slot_filled[slot] && L.gather_stream[slot] != st && !(L.gathered_waited_set[slot] && L.gathered_waited[slot] == st))
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
@@ -346,7 +347,11 @@ int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int sl
         CarriedEvent gathered(ctx, L.gathered[slot]);
         // a caller that alternates side streams has two gathers on the link at a time
         const bool link_shared = ctx->last_gather_stream_set && ctx->last_gather_stream != st;
-        SPC_HIP(ctx, launch_gather(L.view, Nq, idx, L.slot[slot], L.slot_idx[slot], link_shared, st));
+        if (select_out)
+            SPC_HIP(ctx, launch_select_gather(L.view, Nq, L.keys, ctx->logit_stride, select_out, L.slot[slot], L.slot_idx[slot],
+                                              link_shared, st));
+        else
+            SPC_HIP(ctx, launch_gather(L.view, Nq, idx, L.slot[slot], L.slot_idx[slot], link_shared, st));
         gathered_carried = gathered.landed();
         ctx->last_gather_stream = st;
         ctx->last_gather_stream_set = true;
@@ -777,13 +782,14 @@ int specache_select_gather(specache_ctx* ctx, int32_t layer, int32_t* topk_idx_o
             if (ss->used) SPC_HIP(ctx, hipStreamWaitEvent(st, ss->done, 0));
         }
     }
-    {
+    const TopkScratch& scratch = ss ? ss->s : ctx->select_scratch[0].s;
+    const bool together = slot >= 0 && selects_and_gathers(L.view.rows, L.keys_Nq, ctx->cfg.topk);
+    if (!together) {
         TimedLaunch t(ctx, st, SPECACHE_K_TOPK, /*kernel_events=*/true);
-        SPC_HIP(ctx, launch_topk(L.view.rows, L.keys_Nq, ctx->cfg.topk, L.keys, ctx->logit_stride, topk_idx_out,
-                                 ss ? ss->s : ctx->select_scratch[0].s, st));
+        SPC_HIP(ctx, launch_topk(L.view.rows, L.keys_Nq, ctx->cfg.topk, L.keys, ctx->logit_stride, topk_idx_out, scratch, st));
     }
     if (slot >= 0) {
-        if (int rc = gather_phase(ctx, L, L.keys_Nq, topk_idx_out, slot, st)) return rc;
+        if (int rc = gather_phase(ctx, L, L.keys_Nq, topk_idx_out, slot, st, together ? topk_idx_out : nullptr)) return rc;
         L.keys_reader_slot = slot;
     } else {
         // selection only: an event of its own tells the layer's next scoring pass that the keys were read

@@ -1,6 +1,7 @@
 // ArgTopK of the speculative row (Appendix A "Decoding": K_{t+1} = ArgTopK(A_{1,:});
-// "Pre-decoding" for the single-row case).  Softmax is monotone, so the selection runs on the
-// logits' order-preserving integer keys.
+// "Pre-decoding" for the single-row case), alone or with Pre-fetch(C_K) of the selected pairs
+// behind it in the same launch.  Softmax is monotone, so the selection runs on the logits'
+// order-preserving integer keys.
 //
 // One workgroup per (batch, KV head), its keys in registers (longer rows in two launches, see
 // topk_parts).  What bounds the kernel is neither arithmetic nor the 4 bytes per key but the chain of
@@ -32,6 +33,7 @@ constexpr int kBins = 512;         // of either histogram of the short way
 constexpr int kCandidates = 2048;  // keys the short way collects
 constexpr int kCrowdedBins = 2048;
 constexpr int kSmall = 64;         // keys one wave ranks directly
+constexpr int kMaxTopk = 4096;
 constexpr int kMapWords = 65536 / 32;
 
 template <int CTRL, int ROW_MASK = 0xf>
@@ -127,11 +129,40 @@ struct TopkIo {
     uint32_t* key_out;       // [rows * parts][k] or null
 };
 
+// Pre-fetch(C_K) behind the selection (GATHER): the row's pairs from the pinned host store into the staging slot.
+struct GatherIo {
+    const uint4* host;       // [rows][max_seq][32]
+    uint4* slot;             // [rows][k][32]
+    int32_t* slot_idx;       // [rows][k]
+    int max_seq, waves, reads;   // waves of a workgroup that fetch, host reads of a lane in flight
+};
+
+template <int READS>
+__device__ __forceinline__ void fetch_pairs(const GatherIo& g, int row, int k, const int32_t* list) {
+    const int part = threadIdx.x & 31, group = threadIdx.x >> 5, groups = 2 * g.waves;
+    const uint4* host = g.host + (size_t)row * g.max_seq * 32 + part;
+    uint4* slot = g.slot + (size_t)row * k * 32 + part;
+    for (int j0 = group; j0 < k; j0 += groups * READS) {
+        int src[READS];
+        uint4 v[READS];
+#pragma unroll
+        for (int u = 0; u < READS; ++u) {
+            const int j = j0 + u * groups;
+            src[u] = j < k ? list[j] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < READS; ++u) v[u] = src[u] >= 0 ? host[(size_t)src[u] * 32] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < READS; ++u)
+            if (src[u] >= 0) slot[(size_t)(j0 + u * groups) * 32] = v[u];
+    }
+}
+
 // THREADS: 1024 for long rows; 256 for rows of up to 8192 keys, so that several rows share a
 // compute unit and hide each other's barrier latency.
-template <int THREADS, int KPT>
+template <int THREADS, int KPT, bool GATHER>
 __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const uint32_t* __restrict__ keys,
-                                                       size_t key_stride, int32_t* __restrict__ idx_out) {
+                                                       size_t key_stride, int32_t* __restrict__ idx_out, GatherIo g) {
     constexpr int kWavesHere = THREADS / 64;
     constexpr int kMapHere = THREADS * KPT / 32;      // words of the bitmap
     constexpr int kSub = 4;                           // registers of a finer maximum
@@ -142,8 +173,11 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
     __shared__ uint32_t wave_red[kWavesHere], wave_eq[kWavesHere], sel[2], result[2];
     __shared__ uint2 small_keys[kSmall];
     __shared__ uint32_t n_cand, n_small;
+
     static_assert(sizeof(cand) >= kHistWords * 4, "the histogram takes the candidates' place");
     uint32_t* crowded_hist = reinterpret_cast<uint32_t*>(cand);
+    static_assert(sizeof(cand) >= kMaxTopk * 4, "and so does the list of the selected positions, when both are done with");
+    int32_t* list = reinterpret_cast<int32_t*>(cand);
 
     const int row = blockIdx.x / io.parts, part = blockIdx.x % io.parts;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -157,11 +191,14 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
     const int keff = k < Nq ? k : Nq;
     // output slot `pos` receives local position i, whose key is kv
     auto emit = [&](uint32_t pos, int i, uint32_t kv) {
-        out[pos] = map ? map[i] : base + i;
+        const int at = map ? map[i] : base + i;
+        if constexpr (GATHER) list[pos] = at;
+        else out[pos] = at;
         if (kout) kout[pos] = kv;
     };
     auto none = [&](int j) {
-        out[j] = -1;
+        if constexpr (GATHER) list[j] = -1;
+        else out[j] = -1;
         if (kout) kout[j] = 0u;     // below every key: never selected by the second launch
     };
 
@@ -415,26 +452,58 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
         select();
     }
 
+    if constexpr (GATHER) {
+        __syncthreads();
+        for (int j = tid; j < k; j += THREADS) {
+            const int i = list[j];
+            out[j] = i;
+            g.slot_idx[(size_t)row * k + j] = i < g.max_seq ? i : -1;
+        }
+        if (wave >= g.waves) return;
+        __builtin_amdgcn_s_setprio(3);   // a wave's issue priority inside its SIMD, not a stream priority
+        switch (g.reads) {
+            case 1: fetch_pairs<1>(g, row, k, list); break;
+            case 2: fetch_pairs<2>(g, row, k, list); break;
+            case 4: fetch_pairs<4>(g, row, k, list); break;
+            default: fetch_pairs<8>(g, row, k, list); break;
+        }
+    }
 }
 
-// one launch over `rows * io.parts` ranges of at most n keys each
+// one launch over `rows * io.parts` ranges of at most n keys each; gather: and the fetch behind it (gather_kb: KB of a row's pairs
+// under way at a time)
 hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_t* keys, size_t key_stride,
-                         int32_t* idx_out, hipStream_t stream) {
+                         int32_t* idx_out, hipStream_t stream, const GatherIo* gather = nullptr, int gather_kb = 0) {
     const int per_lane_256 = (n + 255) / 256, per_lane = (n + 1023) / 1024;   // keys per lane held in registers
-    // the floor needs more maxima than k to bite: small workgroups only for small k
-    const bool small_wg = k <= 256 && per_lane_256 <= 32;
-#define SPC_TOPK(T, K) SPC_LAUNCH((topk_kernel<T, K>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out)
-    if (small_wg && per_lane_256 <= 8) SPC_TOPK(256, 8);
-    else if (small_wg && per_lane_256 <= 16) SPC_TOPK(256, 16);
-    else if (small_wg) SPC_TOPK(256, 32);
-    else if (per_lane <= 16) SPC_TOPK(1024, 16);
-    else if (per_lane <= 24) SPC_TOPK(1024, 24);
-    else if (per_lane <= 32) SPC_TOPK(1024, 32);
-    else if (per_lane <= 40) SPC_TOPK(1024, 40);
+    GatherIo g = gather ? *gather : GatherIo{};
+    // the floor needs more maxima than k to bite: small workgroups only for small k; nor can one with few waves keep the reads of a
+    // launch over few rows under way (2 rows, k = 200: 188 us a pass with 256 threads, 182 with 1024; the others level)
+    const bool small_wg = k <= 256 && per_lane_256 <= 32 && (!gather || gather_kb <= 4);
+    if (gather) {
+        const int most = (small_wg ? 256 : 1024) / 64;
+        g.waves = gather_kb < most ? gather_kb : most;   // a wave's read is 1 KB
+        const int reads = gather_kb / g.waves;
+        g.reads = reads >= 8 ? 8 : reads >= 4 ? 4 : reads >= 2 ? 2 : 1;
+    }
+#define SPC_TOPK(T, K) SPC_LAUNCH((topk_kernel<T, K, false>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out, g)
+#define SPC_TOPK_GATHER(T, K)                                                                                                    \
+    do {                                                                                                                         \
+        if (gather) SPC_LAUNCH((topk_kernel<T, K, true>), dim3(rows), dim3(T), stream, io, k, keys, key_stride, idx_out, g);     \
+        else SPC_TOPK(T, K);                                                                                                     \
+    } while (0)
+    if (small_wg && per_lane_256 <= 8) SPC_TOPK_GATHER(256, 8);
+    else if (small_wg && per_lane_256 <= 16) SPC_TOPK_GATHER(256, 16);
+    else if (small_wg) SPC_TOPK_GATHER(256, 32);
+    else if (per_lane <= 16) SPC_TOPK_GATHER(1024, 16);
+    else if (per_lane <= 24) SPC_TOPK_GATHER(1024, 24);
+    else if (per_lane <= 32) SPC_TOPK_GATHER(1024, 32);
+    else if (per_lane <= 40) SPC_TOPK_GATHER(1024, 40);
+    else if (gather) return hipErrorInvalidValue;     // selects_and_gathers: rows of one launch
     else if (per_lane <= 48) SPC_TOPK(1024, 48);
     else if (per_lane <= 64) SPC_TOPK(1024, 64);
     else return hipErrorInvalidValue;                // launch_topk splits such a row
 #undef SPC_TOPK
+#undef SPC_TOPK_GATHER
     return hipGetLastError();
 }
 
@@ -467,6 +536,29 @@ hipError_t launch_topk(int rows, int Nq, int k, const uint32_t* keys, size_t key
     }
     TopkIo io{Nq, 1, Nq, nullptr, 0, nullptr};
     return launch_ranges(rows, Nq, io, k, keys, key_stride, idx_out, stream);
+}
+
+// In one launch the selection's 4-byte list does not go through memory to a kernel of its own, which costs a boundary (2.4 us on a
+// side stream), a launch of the issuing thread (3 us) and the list's latency.  us a pass, two launches against one: 1 x 4096, 16 layers 280 /
+// 158 to 230 (bound by the issuing thread), 32 x 16k 337 / 308, 32 x 32k with k = 256 372 / 360, 1 bit 196 / 176, 24 x 5003 with 8 rows 255 / 246.
+// Not where a row takes two launches to select (8 x 131072: 387 / 394), nor with many rows: a row's workgroup keeps its place on a
+// compute unit for as long as it fetches, and more reads are under way than the link wants: 128 rows 207 / 182, but 256 rows 172 /
+// 193 and 512 rows 176 / 223.
+bool selects_and_gathers(int rows, int Nq, int k) { return rows <= 128 && topk_parts(Nq, k) == 1; }
+
+hipError_t launch_select_gather(const LayerView& L, int Nq, const uint32_t* keys, size_t key_stride, int32_t* idx_out,
+                                uint16_t* slot, int32_t* slot_idx, bool link_shared, hipStream_t stream) {
+    if (!selects_and_gathers(L.rows, Nq, L.topk)) return hipErrorInvalidValue;
+    // How much of the host store is under way at a time: as much as the link needs, and no more, since every read in flight slows the
+    // attention kernels beside the fetch.  Steps of several layers, us a pass with 32, 64, 96, 128, 256 KB (two fetches
+    // sharing the link): 32 rows x 16k, k = 64: 267, 241, 230, 241, 275; 32 x 32k, k = 256: 451, 387, 370, 367, 400; 32 x 32k, 1
+    // bit: 191, 166, 162, 166, 172; 32 x 32k, 8 query rows: 137, 119, 119, 122, 128.  A caller with one fetch at a time gets what
+    // gather_kernel (gather.hip) gives it: more the fewer keys are scored for a fetched pair.
+    const double keys_per_pair = (double)L.G * Nq / L.topk;
+    const int total_kb = link_shared ? 96 : keys_per_pair >= 384.0 ? 128 : keys_per_pair >= 192.0 ? 192 : 256;
+    const GatherIo g{(const uint4*)L.host, (uint4*)slot, slot_idx, L.max_seq, 0, 0};
+    const TopkIo io{Nq, 1, Nq, nullptr, 0, nullptr};
+    return launch_ranges(L.rows, Nq, io, L.topk, keys, key_stride, idx_out, stream, &g, total_kb > L.rows ? total_kb / L.rows : 1);
 }
 
 }  // namespace specache
