@@ -151,21 +151,22 @@ __device__ __forceinline__ void value_meta_exchange(ValueLoads<GROUP, BITS>& v, 
 
 // Bits of the wave's 128 tokens that the staged index list names (they enter through the 16-bit chunks),
 // built by the wave alone from an index list of at most 256 entries: the lane's four entries are requested
-// with wave_bitmap_loads (positions relative to the wave's first token, -1 = none) and turned into wbits[4]
-// by wave_bitmap_apply, once other loads are under way.
-__device__ __forceinline__ void wave_bitmap_loads(const int32_t* __restrict__ idx_row, int topk, int first, int lane, int t[4]) {
+// with wave_bitmap_loads and turned into wbits[4] by wave_bitmap_apply, once other loads are under way.  (Requested under a
+// condition and made relative at once, they were up to four loads one behind the other, each waited for before the wave asked for
+// its keys: a step of 32 x 16384, k = 64, 38.5 us a layer against 37.6.)
+__device__ __forceinline__ void wave_bitmap_loads(const int32_t* __restrict__ idx_row, int topk, int lane, int t[4]) {
+    const auto list = buffer_of(idx_row, idx_row ? (uint32_t)topk * 4u : 0u);   // beyond the list: 0, and no lane looks at it
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int j = 64 * u + lane;
-        t[u] = (idx_row && j < topk) ? idx_row[j] - first : -1;
-    }
+    for (int u = 0; u < 4; ++u) t[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(list, (64 * u + lane) * 4, 0, 0);
 }
-__device__ __forceinline__ void wave_bitmap_apply(const int t[4], int nw, int lane, uint32_t* wbits) {
+__device__ __forceinline__ void wave_bitmap_apply(const int t[4], int n_idx, int first, int nw, int lane, uint32_t* wbits) {
     if (lane < 4) wbits[lane] = 0u;
     wave_sync();
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (t[u] >= 0 && t[u] < nw) atomicOr(&wbits[t[u] >> 5], 1u << (t[u] & 31));
+    for (int u = 0; u < 4; ++u) {
+        const int p = t[u] - first;
+        if (64 * u + lane < n_idx && t[u] >= 0 && p >= 0 && p < nw) atomicOr(&wbits[p >> 5], 1u << (p & 31));
+    }
     wave_sync();
 }
 
@@ -523,19 +524,20 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
         float lgv[4];
         // everything this wave reads from global memory is requested before the first wait on any of it
         int ti[4];
-        if (wave_maps) wave_bitmap_loads(A.slot_idx ? A.slot_idx + (size_t)row * L.topk : nullptr, L.topk, c0 + w0, lane, ti);
+        const int n_idx = A.slot_idx ? L.topk : 0;
+        if (wave_maps) wave_bitmap_loads(n_idx ? A.slot_idx + (size_t)row * L.topk : nullptr, L.topk, lane, ti);
         if constexpr (!FUSED) {
             float4 lg4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             if (live) lg4 = *reinterpret_cast<const float4*>(A.logits + ((size_t)row * NR + h) * A.logit_stride + c0 + w0 + t0);
             value_loads<GROUP, BITS>(L, row, c0, w0, nw, lane, v);
-            if (wave_maps) wave_bitmap_apply(ti, nw, lane, maskbits + 4 * wave);
+            if (wave_maps) wave_bitmap_apply(ti, n_idx, c0 + w0, nw, lane, maskbits + 4 * wave);
             lgv[0] = lg4.x; lgv[1] = lg4.y; lgv[2] = lg4.z; lgv[3] = lg4.w;
         } else {
             // the low-bit logits of the wave's tokens (Appendix A "Decoding": A = Q K^T on C'); the value-side loads
             // are requested once the scoring operands are built and travel while the scoring contraction runs
             score_i8_wave<BITS, BF16>(L, A.q, row, chunk, wave, lane, A.Nq / kBlockTokens, sm_scale, reinterpret_cast<uint32_t*>(area),
                                    fin[wave], lgv,
-                                   [&]() { if (wave_maps) wave_bitmap_apply(ti, nw, lane, maskbits + 4 * wave); },
+                                   [&]() { if (wave_maps) wave_bitmap_apply(ti, n_idx, c0 + w0, nw, lane, maskbits + 4 * wave); },
                                    [&]() { value_loads<GROUP, BITS>(L, row, c0, w0, nw, lane, v); });
             if (live) {
                 if (h == 1) {   // the speculative row ranks the positions

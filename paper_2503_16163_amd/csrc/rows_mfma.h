@@ -256,25 +256,40 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     float* qs = reinterpret_cast<float*>(smem);                                    // [NR][kQStride]
     uint16_t* qraw = reinterpret_cast<uint16_t*>(smem + NR * S::kQStride * 4);      // [NR][kZStride]
     int* q_unscale = reinterpret_cast<int*>(smem + NR * S::kQStride * 4 + NR * S::kZStride * 2);   // [NR], exponents
-    for (int rr = wave; rr < NR; rr += kWaves) {
-        const uint32_t w = rr < nq ? reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * nq + rr) * kD)[lane] : 0u;
-        reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
-        if constexpr (MODE == kRowsBoth)
-            if (A.q_out && chunk == 0 && rr < nq) reinterpret_cast<uint32_t*>(A.q_out + ((size_t)row * nq + rr) * kD)[lane] = w;
-        if constexpr (MODE != kRowsAttend) {
-            const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
-            const float top = wave_max(fmaxf(fabsf(a), fabsf(b)));
-            int f = 253 + key_q_bits(BITS) - (int)((__float_as_uint(top) >> 23) & 0xFFu);   // top < 2^(E - 126): field of 2^(kbits - E + 126)
-            f = f > 254 ? 254 : f;
-            const float sc = __uint_as_float((uint32_t)f << 23);
-            const int c = 2 * lane;
-            *reinterpret_cast<float2*>(qs + rr * S::kQStride + c) = make_float2(a * sc * key_factor<BITS>(c), b * sc * key_factor<BITS>(c + 1));
-            if (lane == 0) q_unscale[rr] = 127 - f;
-        }
+    // requested here and worked on when the first unit's loads are under way, too.  One behind the other (the queries, then the unit, then
+    // the index list) the three round trips made a step of 16 x 8192 with 16 query rows 35.9 us a layer, now 32.0; 24 x 5003 with 8 rows 30.7
+    // and 28.1, 32 x 32768 53.9 and 50.9.
+    static_assert(NR % kWaves == 0, "every wave takes as many rows");
+    uint32_t qw[NR / kWaves];
+    {
+        const auto q_buf = buffer_of(A.q + (size_t)row * nq * kD, (uint32_t)(nq * kD) * 2u);   // rows beyond: 0
+#pragma unroll
+        for (int i = 0; i < NR / kWaves; ++i) qw[i] = __builtin_amdgcn_raw_buffer_load_b32(q_buf, ((wave + i * kWaves) * (kD / 2) + lane) * 4, 0, 0);
     }
+    auto prepare_queries = [&]() {
+#pragma unroll
+        for (int i = 0; i < NR / kWaves; ++i) {
+            const int rr = wave + i * kWaves;
+            const uint32_t w = qw[i];
+            reinterpret_cast<uint32_t*>(qraw + rr * S::kZStride)[lane] = w;
+            if constexpr (MODE == kRowsBoth)
+                if (A.q_out && chunk == 0 && rr < nq) reinterpret_cast<uint32_t*>(A.q_out + ((size_t)row * nq + rr) * kD)[lane] = w;
+            if constexpr (MODE != kRowsAttend) {
+                const float a = widen16<BF16>(w & 0xFFFFu) * A.sm_scale, b = widen16<BF16>(w >> 16) * A.sm_scale;
+                const float top = wave_max(fmaxf(fabsf(a), fabsf(b)));
+                int f = 253 + key_q_bits(BITS) - (int)((__float_as_uint(top) >> 23) & 0xFFu);   // top < 2^(E - 126): field of 2^(kbits - E + 126)
+                f = f > 254 ? 254 : f;
+                const float sc = __uint_as_float((uint32_t)f << 23);
+                const int c = 2 * lane;
+                *reinterpret_cast<float2*>(qs + rr * S::kQStride + c) = make_float2(a * sc * key_factor<BITS>(c), b * sc * key_factor<BITS>(c + 1));
+                if (lane == 0) q_unscale[rr] = 127 - f;
+            }
+        }
+    };
 
     float* o_lds = reinterpret_cast<float*>(smem);                                  // [kWaves][16][kRowsOStride], at the end
     if (MODE != kRowsScore && chunk >= A.n_main) {
+        prepare_queries();
         __syncthreads();
         float* weights = reinterpret_cast<float*>(smem + (S::kQBytes + 15) / 16 * 16) + wave * 32 * NR;
         rows_extra_wave<NR, BF16>(L, A, R.n_rows, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, S::kZStride, weights,
@@ -370,19 +385,23 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
                 }
             }
         };
+        // the first entries of the index list travel with them
+        const int n_idx = MODE != kRowsScore && A.slot_idx ? L.topk : 0;
+        const int first_idx = (int)__builtin_amdgcn_raw_buffer_load_b32(buffer_of(n_idx ? A.slot_idx + (size_t)row * L.topk : nullptr, (uint32_t)n_idx * 4u), tid * 4, 0, 0);
         load_keys(w0 < A.Nq ? w0 : 0);
         load_values(w0 < A.Nq ? w0 : 0);
+        __builtin_amdgcn_sched_barrier(0);
+        prepare_queries();
 
         // ---- bitmap of the chunk's staged positions (they enter through the 16-bit chunks)
         if constexpr (MODE != kRowsScore) {
             const int words = chunk_tokens / 32;
             for (int i = tid; i < words; i += kThreads) maskbits[i] = 0u;
             __syncthreads();
-            if (A.slot_idx)
-                for (int j = tid; j < L.topk; j += kThreads) {
-                    const int t = A.slot_idx[(size_t)row * L.topk + j] - c0;
-                    if (t >= 0 && t < chunk_tokens) atomicOr(&maskbits[t >> 5], 1u << (t & 31));
-                }
+            for (int j = tid; j < n_idx; j += kThreads) {
+                const int t = (j == tid ? first_idx : A.slot_idx[(size_t)row * L.topk + j]) - c0;
+                if (t >= 0 && t < chunk_tokens) atomicOr(&maskbits[t >> 5], 1u << (t & 31));
+            }
         }
         __syncthreads();
 
