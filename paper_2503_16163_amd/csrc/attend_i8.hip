@@ -484,9 +484,11 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
         } else {
             // a wave each per 32 candidates, merged as the quantised chunks are
             uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
+            const int x0 = ((chunk - A.n_main) * kWaves + wave) * 32;
+            const int2 staged = staged_positions(L, A, row, x0, lane);
             if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
             __syncthreads();
-            rows_extra_wave<NR, BF16, NR>(L, A, NR, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, kQStride,
+            rows_extra_wave<NR, BF16, NR>(L, A, NR, row, x0, staged, lane, wave, qraw, kQStride,
                                           smem + kExtraQ + wave * 32 * NR, smem, xout);
             __syncthreads();
             const int r = tid >> 7, c = tid & 127;

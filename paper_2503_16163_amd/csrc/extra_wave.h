@@ -54,9 +54,18 @@ struct RowsOut {
 };
 
 // ---- one wave's 32 candidates in 16 bits: staged pairs, residual, the speculative pair ---------------------------
-// weights: [32][NR] of the wave; o_lds: [kWaves][O_ROWS][kRowsOStride], may lie over the query rows and the weights.
+// The staged positions of a lane's two candidates (x0 + 2 (lane % 16), + 1), requested ahead of everything else: where they lead decides
+// what the rest of the chunk reads (behind the queries' exchange: 24 x 5003 with 8 query rows 266 us a pass, now 262).  Beyond the
+// list: 0, and the candidate is another kind.
+__device__ __forceinline__ int2 staged_positions(const LayerView& L, const AttendArgs& A, int row, int x0, int lane) {
+    const auto list = buffer_of(A.slot_idx ? A.slot_idx + (size_t)row * L.topk : nullptr, A.slot_idx ? (uint32_t)L.topk * 4u : 0u);
+    const int at = (x0 + 2 * (lane & 15)) * 4;
+    return make_int2((int)__builtin_amdgcn_raw_buffer_load_b32(list, at, 0, 0), (int)__builtin_amdgcn_raw_buffer_load_b32(list, at + 4, 0, 0));
+}
+
+// staged: staged_positions of the wave; weights: [32][NR] of the wave; o_lds: [kWaves][O_ROWS][kRowsOStride], may lie over the query rows and the weights.
 template <int NR, bool BF16, int O_ROWS = 16>
-__device__ __forceinline__ void rows_extra_wave(const LayerView& L, const AttendArgs& A, int n_rows, int row, int x0, int lane, int wave,
+__device__ __forceinline__ void rows_extra_wave(const LayerView& L, const AttendArgs& A, int n_rows, int row, int x0, int2 staged, int lane, int wave,
                                                 const uint16_t* qraw, int q_stride, float* weights, float* o_lds, RowsOut& out) {
     const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
     const int ks = A.slot_idx ? L.topk : 0, n_res = A.N - A.Nq, n_ex = ks + n_res + (A.k_spec ? 1 : 0);
@@ -70,7 +79,7 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
         kp[mt] = nullptr;
         spec[mt] = false;
         if (x < ks) {
-            const int t = A.slot_idx[(size_t)row * L.topk + x];
+            const int t = mt ? staged.y : staged.x;
             if (t >= 0 && t < A.Nq) kp[mt] = A.slot + ((size_t)row * L.topk + x) * 256;
         } else if (x < ks + n_res) {
             const int t = A.Nq + (x - ks);

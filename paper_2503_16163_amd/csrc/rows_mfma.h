@@ -289,10 +289,12 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
 
     float* o_lds = reinterpret_cast<float*>(smem);                                  // [kWaves][16][kRowsOStride], at the end
     if (MODE != kRowsScore && chunk >= A.n_main) {
+        const int x0 = ((chunk - A.n_main) * kWaves + wave) * 32;
+        const int2 staged = staged_positions(L, A, row, x0, lane);
         prepare_queries();
         __syncthreads();
         float* weights = reinterpret_cast<float*>(smem + (S::kQBytes + 15) / 16 * 16) + wave * 32 * NR;
-        rows_extra_wave<NR, BF16>(L, A, R.n_rows, row, ((chunk - A.n_main) * kWaves + wave) * 32, lane, wave, qraw, S::kZStride, weights,
+        rows_extra_wave<NR, BF16>(L, A, R.n_rows, row, x0, staged, lane, wave, qraw, S::kZStride, weights,
                                   o_lds, out);
     } else {
         const int chunk_tokens = kWaves * R.wave_units * UNIT, c0 = chunk * chunk_tokens;
