@@ -9,6 +9,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "kernels.h"
@@ -91,6 +92,7 @@ struct specache_ctx {
     int device = 0;
     float sm_scale = 0.f;
     std::vector<Layer> layers;
+    void* device_memory = nullptr;   // every buffer on the device is part of this one
     float* logits = nullptr;     // [rows*G*2][logit_stride]
     uint32_t* keys = nullptr;    // [rows][logit_stride]
     float* lse = nullptr;        // (max, sum) per slice of every head's speculative row (log-probability selection)
@@ -255,36 +257,20 @@ int check_ctx_layer(specache_ctx* ctx, int32_t layer) {
 
 void free_all(specache_ctx* ctx) {
     for (Layer& L : ctx->layers) {
-        (void)hipFree(L.view.kc);
-        (void)hipFree(L.view.km);
-        (void)hipFree(L.view.vc);
-        (void)hipFree(L.view.vm);
-        (void)hipFree(L.view.ring);
         if (L.host_alloc) (void)hipHostFree(L.host_alloc);
         for (int s = 0; s < 2; ++s) {
-            (void)hipFree(L.slot[s]);
-            (void)hipFree(L.slot_idx[s]);
             if (L.gathered[s]) (void)hipEventDestroy(L.gathered[s]);
             if (L.attended[s]) (void)hipEventDestroy(L.attended[s]);
         }
         if (L.idx_ready) (void)hipEventDestroy(L.idx_ready);
         if (L.selected) (void)hipEventDestroy(L.selected);
-        (void)hipFree(L.keys);
         (void)hipFree(L.scored_word);
-        (void)hipFree(L.arrived);
     }
-    for (auto& ss : ctx->select_scratch) { (void)hipFree(ss.s.cand_keys); (void)hipFree(ss.s.cand_idx); }
     for (auto& sp : ctx->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
-    (void)hipFree(ctx->logits);
+    (void)hipFree(ctx->device_memory);
     if (ctx->select_stream) (void)hipStreamDestroy(ctx->select_stream);
     if (ctx->scored) (void)hipEventDestroy(ctx->scored);
-    (void)hipFree(ctx->keys);
-    (void)hipFree(ctx->lse);
-    (void)hipFree(ctx->scratch.part_o);
-    (void)hipFree(ctx->scratch.part_ml);
-    (void)hipFree(ctx->topk_scratch.cand_keys);
-    (void)hipFree(ctx->topk_scratch.cand_idx);
 }
 
 // The scoring pass of one layer on stream st: low-bit logits of every query row, selection keys of
@@ -480,21 +466,11 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         v.vc_stride = cap / kBlockTokens * code_block_bytes(c.bits);
         v.km_stride = cap / c.group * kD;
         v.vm_stride = cap * (kD / c.group);
-        SPC_ALLOC(hipMalloc((void**)&v.kc, rows * v.kc_stride));
-        SPC_ALLOC(hipMalloc((void**)&v.vc, rows * v.vc_stride));
-        SPC_ALLOC(hipMalloc((void**)&v.km, rows * v.km_stride * 4));
-        SPC_ALLOC(hipMalloc((void**)&v.vm, rows * v.vm_stride * 4));
-        SPC_ALLOC(hipMalloc((void**)&L.arrived, ((size_t)rows + 1) * 4));
-        SPC_ALLOC(hipMemset(L.arrived, 0, ((size_t)rows + 1) * 4));
-        SPC_ALLOC(hipMalloc((void**)&v.ring, (size_t)rows * c.residual * kRowBytes));
         SPC_ALLOC(hipHostMalloc(&L.host_alloc, (size_t)rows * cap * kRowBytes, hipHostMallocDefault));
         void* dev_view = nullptr;
         SPC_ALLOC(hipHostGetDevicePointer(&dev_view, L.host_alloc, 0));
         v.host = (uint16_t*)dev_view;
         for (int s = 0; s < 2; ++s) {
-            SPC_ALLOC(hipMalloc((void**)&L.slot[s], (size_t)rows * c.topk * kRowBytes));
-            SPC_ALLOC(hipMalloc((void**)&L.slot_idx[s], (size_t)rows * c.topk * 4));
-            SPC_ALLOC(hipMemset(L.slot_idx[s], 0xFF, (size_t)rows * c.topk * 4));
             SPC_ALLOC(hipEventCreateWithFlags(&L.gathered[s], kOrderEventFlags));
             SPC_ALLOC(hipEventCreateWithFlags(&L.attended[s], kOrderEventFlags));
         }
@@ -509,19 +485,10 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         ctx->one_at_a_time = environment_names_a_tool();
         dl_iterate_phdr(look_at_object, ctx);
         for (Layer& L : ctx->layers) {
-            SPC_ALLOC(hipMalloc((void**)&L.keys, (size_t)rows * cap * 4));
             SPC_ALLOC(hipEventCreateWithFlags(&L.selected, kOrderEventFlags));
             if (ctx->scores_by_word) {
                 SPC_ALLOC(hipExtMallocWithFlags((void**)&L.scored_word, 8, hipMallocSignalMemory));
                 *L.scored_word = 0;
-            }
-        }
-        const int parts = topk_parts((int)cap, c.topk);
-        for (auto& ss : ctx->select_scratch) {
-            ss.s.max_parts = parts;
-            if (parts > 1) {
-                SPC_ALLOC(hipMalloc((void**)&ss.s.cand_keys, (size_t)rows * parts * c.topk * 4));
-                SPC_ALLOC(hipMalloc((void**)&ss.s.cand_idx, (size_t)rows * parts * c.topk * 4));
             }
         }
     }
@@ -529,13 +496,9 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         SPC_ALLOC(hipStreamCreateWithFlags(&ctx->select_stream, hipStreamNonBlocking));
         SPC_ALLOC(hipEventCreateWithFlags(&ctx->scored, kOrderEventFlags));
     }
+    // One allocation for the device's buffers: a context of two layers has 34 buffers, whose hipMalloc and hipFree took 75
+    // of the 135 us of its creation and as many of closing it.  The pass without a base adds the sizes up.
     ctx->logit_stride = cap;
-    SPC_ALLOC(hipMalloc((void**)&ctx->logits, (size_t)rows * G * 2 * cap * 4));
-    SPC_ALLOC(hipMalloc((void**)&ctx->keys, (size_t)rows * cap * 4));
-    {
-        const size_t floats = select_logprob_scratch_floats(rows, G, cap), queries = (size_t)rows * G * 2 * kD / 2;
-        SPC_ALLOC(hipMalloc((void**)&ctx->lse, (floats > queries ? floats : queries) * 4));
-    }
     int max_main = 0;
     for (int n = 1; n <= 2; ++n) {
         const int ch = attend_main_chunk_tokens(G * n);
@@ -547,14 +510,53 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
     ctx->scratch.max_chunks = max_main + (c.topk + c.residual + 1 + ec - 1) / ec;
     // no more than the merge kernel takes: with that many candidates rows_kernel splits a row less finely
     if (ctx->scratch.max_chunks > attend_max_chunks()) ctx->scratch.max_chunks = attend_max_chunks();
-    SPC_ALLOC(hipMalloc((void**)&ctx->scratch.part_o, (size_t)rows * ctx->scratch.max_chunks * G * 2 * kD * 4));
-    SPC_ALLOC(hipMalloc((void**)&ctx->scratch.part_ml, (size_t)rows * ctx->scratch.max_chunks * G * 2 * 2 * 4));
-    ctx->topk_scratch.max_parts = topk_parts((int)cap, c.topk);
-    if (ctx->topk_scratch.max_parts > 1) {
-        const size_t n = (size_t)rows * ctx->topk_scratch.max_parts * c.topk;
-        SPC_ALLOC(hipMalloc((void**)&ctx->topk_scratch.cand_keys, n * 4));
-        SPC_ALLOC(hipMalloc((void**)&ctx->topk_scratch.cand_idx, n * 4));
+    const int parts = topk_parts((int)cap, c.topk);
+    ctx->topk_scratch.max_parts = parts;
+    for (auto& ss : ctx->select_scratch) ss.s.max_parts = ctx->select_on_gather ? parts : 0;
+    size_t used = 0, idx_end = 0, cleared_end = 0;
+    bool refused = false;   // by specache_debug_fail_alloc, to which a buffer's place is an allocation like any other
+    for (int pass = 0; pass < 2; ++pass) {
+        uint8_t* base = (uint8_t*)ctx->device_memory;
+        used = 0;
+        auto place = [&](auto*& ptr, size_t bytes) {
+            const size_t align = bytes >= 65536 ? 4096 : 256;
+            used = (used + align - 1) / align * align;
+            if (base && ++alloc_no == fail_at) refused = true;
+            ptr = base ? reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + used) : nullptr;
+            used += bytes;
+        };
+        // what starts at a value of its own first: index lists (-1), then counters (0)
+        for (Layer& L : ctx->layers)
+            for (int s = 0; s < 2; ++s) place(L.slot_idx[s], (size_t)rows * c.topk * 4);
+        idx_end = used;
+        for (Layer& L : ctx->layers) place(L.arrived, ((size_t)rows + 1) * 4);
+        cleared_end = used;
+        for (Layer& L : ctx->layers) {
+            LayerView& v = L.view;
+            place(v.kc, rows * v.kc_stride);
+            place(v.vc, rows * v.vc_stride);
+            place(v.km, rows * v.km_stride * 4);
+            place(v.vm, rows * v.vm_stride * 4);
+            place(v.ring, (size_t)rows * c.residual * kRowBytes);
+            for (int s = 0; s < 2; ++s) place(L.slot[s], (size_t)rows * c.topk * kRowBytes);
+            if (ctx->select_on_gather) place(L.keys, (size_t)rows * cap * 4);
+        }
+        place(ctx->logits, (size_t)rows * G * 2 * cap * 4);
+        place(ctx->keys, (size_t)rows * cap * 4);
+        const size_t floats = select_logprob_scratch_floats(rows, G, cap), queries = (size_t)rows * G * 2 * kD / 2;
+        place(ctx->lse, (floats > queries ? floats : queries) * 4);
+        place(ctx->scratch.part_o, (size_t)rows * ctx->scratch.max_chunks * G * 2 * kD * 4);
+        place(ctx->scratch.part_ml, (size_t)rows * ctx->scratch.max_chunks * G * 2 * 2 * 4);
+        for (TopkScratch* s : {&ctx->topk_scratch, &ctx->select_scratch[0].s, &ctx->select_scratch[1].s})
+            if (s->max_parts > 1) {
+                place(s->cand_keys, (size_t)rows * parts * c.topk * 4);
+                place(s->cand_idx, (size_t)rows * parts * c.topk * 4);
+            }
+        if (pass == 0) SPC_ALLOC(hipMalloc(&ctx->device_memory, used));
     }
+    if (refused) return bail(hipErrorOutOfMemory, "a buffer's place");
+    SPC_ALLOC(hipMemset(ctx->device_memory, 0xFF, idx_end));
+    SPC_ALLOC(hipMemset((uint8_t*)ctx->device_memory + idx_end, 0, cleared_end - idx_end));
     SPC_ALLOC(hipDeviceSynchronize());
 #undef SPC_ALLOC
     {
