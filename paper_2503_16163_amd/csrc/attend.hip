@@ -18,6 +18,7 @@
 // p_i s[i][m] comes from LDS (computed once per token by the softmax phase).  With 4, 8 or 16 query rows per KV head the
 // matrix cores take the contraction (rows_mfma.h).
 #include "attend_common.h"
+#include "extra_wave.h"
 #include "finish_row.h"
 
 namespace specache {
@@ -25,8 +26,9 @@ namespace {
 
 constexpr int kMainChunk = 512;   // quantised positions per workgroup
 
+// 72 registers, seven waves per SIMD (50 and eight without the 16-bit chunk's loads in flight: level at 32 x 32000 and 32 x 100000)
 template <int BITS, int GROUP, int G, int NROWS, bool BF16>
-__global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, AttendArgs A) {
+__global__ __launch_bounds__(kThreads, 7) void attend_partial_kernel(LayerView L, AttendArgs A) {
     constexpr int NR = G * NROWS;
     constexpr int CH = kMainChunk;
     constexpr int M = kD / GROUP;            // value groups per token
@@ -35,13 +37,13 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     constexpr uint32_t MASK = ((1u << BITS) - 1u) * 0x01010101u;
     constexpr int TPT = (CH + kThreads - 1) / kThreads;   // chunk tokens per thread
     // One LDS region serves, in turn: for main chunks ps[M][CH][NR]; for extra chunks the areas of
-    // attend_extra_chunk; at the end o_lds[kWaves][NR][128].
+    // extra_chunk; at the end o_lds[kWaves][NR][128].
     // ps is stored in cells [16-token half block][value group m] of 16*NR floats plus one
     // 16-byte pad: the lanes of one LDS read differ only in (half block, m), i.e. in
     // consecutive cells, and the pad spreads those over distinct banks.
     constexpr int kCell = 16 * NR + 4;
     constexpr int kPs = (CH / 16) * M * kCell, kOl = kWaves * NR * kD;
-    // a workgroup is either a main or an extra chunk (16-bit candidates, attend_extra_chunk): both use
+    // a workgroup is either a main or an extra chunk (16-bit candidates, extra_chunk): both use
     // the one region, and LDS per workgroup decides how many chunks are resident per compute unit
     constexpr int kExtra = extra_chunk_floats(NR);
     constexpr int kMax1 = kExtra > kPs ? kExtra : kPs;
@@ -53,6 +55,7 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
     __shared__ float red_z[kWaves * NR * M];
     __shared__ uint32_t maskbits[CH / 32];
     __shared__ FinishShared fin_shared;
+    __shared__ RowsOut xout;
 
     float* ps = smem;                        // [CH/16][M] cells
     float* o_lds = smem;                     // [kWaves][NR][128]
@@ -274,9 +277,9 @@ __global__ __launch_bounds__(kThreads) void attend_partial_kernel(LayerView L, A
             store_partial(po, e, v, A.fin.arrived != nullptr);
         }
     } else {
-        attend_extra_chunk<NR, NROWS, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
+        extra_chunk<NR, NROWS, BF16, 16>(L, A, row, chunk, smem, xout, po, pml);
     }
-    if (tid < NR) {
+    if (chunk < A.n_main && tid < NR) {
         float mv = 0.f, lv = 0.f;
 #pragma unroll
         for (int r = 0; r < NR; ++r)

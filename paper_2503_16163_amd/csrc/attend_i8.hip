@@ -27,7 +27,7 @@
 // and row).
 //
 // A workgroup takes a chunk of 512 quantised positions (or, as in the vector-ALU kernel, 128 16-bit
-// candidates: rows_extra_wave); its four waves are independent, each with 128 tokens and its own
+// candidates: extra_chunk); its four waves are independent, each with 128 tokens and its own
 // softmax maximum, and meet once, at the end, to merge their (max, sum, sum p V) into the chunk's
 // partial result.  Lane = (32-token sub-group, h, token quad): it holds the logits of four
 // consecutive tokens of row h (the layout in which the scoring wave finishes them), exchanges the
@@ -434,20 +434,19 @@ __device__ __forceinline__ void chunk_bitmap(const AttendArgs& A, int topk, int 
     __syncthreads();
 }
 
-// Registers: the pass that also scores needs 84 to 88 (five waves per SIMD); compiled for six or eight it
-// spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).
+// Registers: the pass that also scores needs 90 to 94 (five waves per SIMD); compiled for six or eight it
+// spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
+// codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
+// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).
 template <int GROUP, int BITS, bool BF16, bool FUSED>
-__global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
+__global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
                                                              size_t key_stride) {
     constexpr int NR = 2;
     constexpr int kAreaBytes = FUSED ? kWaveDwords * 4 : kWaveArea;        // per wave
-    constexpr int kQStride = kD + 8;                                       // halves between the query rows of a 16-bit chunk
-    constexpr int kExtraQ = NR * kQStride / 2, kExtraOut = kWaves * NR * kRowsOStride;   // floats
-    constexpr int kRegion = FUSED || (kWaves * kAreaBytes) / 4 > extra_chunk_floats(NR) ? (kWaves * kAreaBytes) / 4 : extra_chunk_floats(NR);
-    static_assert(kRegion >= kExtraOut && kRegion >= kExtraQ + kWaves * 32 * NR && kExtraQ % 4 == 0, "a 16-bit chunk in the same region");
+    constexpr int kRegion = (kWaves * kAreaBytes) / 4;
+    static_assert(kRegion >= extra_chunk_floats(NR), "a 16-bit chunk in the same region");
     __shared__ __attribute__((aligned(16))) float smem[kRegion];
     __shared__ RowsOut xout;
-    __shared__ float red[FUSED ? 1 : kWaves * NR];
     __shared__ uint32_t maskbits[kI8Chunk / 32];
     __shared__ __attribute__((aligned(8))) float2 fin[FUSED ? kWaves : 1][4][2];
     __shared__ WaveOut wout;
@@ -471,39 +470,11 @@ __global__ __launch_bounds__(kThreads, FUSED ? 5 : 1) void attend_i8_kernel(Laye
     }
     int row, chunk;
     chunk_of_block(A, L.rows, (int)blockIdx.x - n_tail, row, chunk);
-    float* po_chunk = A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD;
-    const auto po = buffer_of(po_chunk, NR * kD * 4);
+    const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4);
     const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
 
     if (chunk >= A.n_main) {
-        if constexpr (!FUSED) {
-            // (the wave-wise form takes 90 registers, this kernel alone 63: eight waves per SIMD)
-            float m_row[NR], l_row[NR];
-            attend_extra_chunk<NR, 2, BF16>(L, A, row, chunk, smem, red, m_row, l_row, po);
-            if (tid < NR) store_max_sum(pml, tid, tid == 0 ? m_row[0] : m_row[1], tid == 0 ? l_row[0] : l_row[1], A.fin.arrived != nullptr);
-        } else {
-            // a wave each per 32 candidates, merged as the quantised chunks are
-            uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
-            const int x0 = ((chunk - A.n_main) * kWaves + wave) * 32;
-            const int2 staged = staged_positions(L, A, row, x0, lane);
-            if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
-            __syncthreads();
-            rows_extra_wave<NR, BF16, NR>(L, A, NR, row, x0, staged, lane, wave, qraw, kQStride,
-                                          smem + kExtraQ + wave * 32 * NR, smem, xout);
-            __syncthreads();
-            const int r = tid >> 7, c = tid & 127;
-            float mx = -INFINITY, o = 0.0f, sum = 0.0f;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, xout.m[w][r]);
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const float e = xout.m[w][r] == -INFINITY ? 0.0f : exp2_of((xout.m[w][r] - mx) * kLog2e);
-                if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
-                sum = __builtin_fmaf(e, xout.l[w][r], sum);
-            }
-            store_partial(po, r * kD + c, o, A.fin.arrived != nullptr);
-            if (c == 0) store_max_sum(pml, r, mx, sum, A.fin.arrived != nullptr);
-        }
+        extra_chunk<NR, 2, BF16, FUSED ? 32 : BITS == 1 ? 16 : 0>(L, A, row, chunk, smem, xout, po, pml);
         if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
         return;
     }

@@ -4,7 +4,8 @@
 // dependent steps, not the arithmetic, is what this chunk of a launch takes: a workgroup of 128 candidates
 // that went from barrier to barrier, its values requested in batches of 8 behind the softmax, took 10.8 us alone
 // with two query rows and was the last to end in a launch over 32 rows x 16384 positions (16.0 of 16.6 us); a wave each
-// takes 4.6 us alone (that kernel over 1 x 4096 positions: 10.8 -> 5.4 us) and 11.2 there.
+// takes 4.6 us alone (that kernel over 1 x 4096 positions: 10.8 -> 5.4 us) and 11.2 there.  In the kernels of attention alone, us a
+// pass: non-speculative 32 x 8192 444 -> 425, 4 heads on 2, 2000 positions 257 -> 211, one layer of 32 x 16000 56 -> 49.
 #pragma once
 #include "attend_common.h"
 
@@ -64,7 +65,8 @@ __device__ __forceinline__ int2 staged_positions(const LayerView& L, const Atten
 }
 
 // staged: staged_positions of the wave; weights: [32][NR] of the wave; o_lds: [kWaves][O_ROWS][kRowsOStride], may lie over the query rows and the weights.
-template <int NR, bool BF16, int O_ROWS = 16>
+// AHEAD: values requested with the keys (32: all of them), the others once the keys are used up, which takes fewer registers.
+template <int NR, bool BF16, int O_ROWS = 16, int AHEAD = 32>
 __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const AttendArgs& A, int n_rows, int row, int x0, int2 staged, int lane, int wave,
                                                 const uint16_t* qraw, int q_stride, float* weights, float* o_lds, RowsOut& out) {
     const int ic = lane & 15, kq = lane >> 4, r = ic % NR, s = ic / NR;
@@ -99,6 +101,10 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
             vp[mt] = A.v_spec + (size_t)row * kD;
         }
     }
+    // one or two rows look at the weights before the values: where there is no pair any 256 bytes do, and the loads need no branches
+    if constexpr (NR <= 2)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) vp[mt] = vp[mt] ? vp[mt] : A.q + (size_t)row * NR * kD;
     uint4v kb[2][4];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
@@ -107,13 +113,16 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
             kb[mt][kc] = kp[mt] ? *reinterpret_cast<const uint4v*>(kp[mt] + 32 * kc + 8 * kq) : uint4v{0u, 0u, 0u, 0u};
     // value rows: lane = channel pair, one 256-byte row per candidate (lane 2 ic + mt / 2 of the wave knows where)
     uint32_t vw[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
+    auto load_value = [&](int i) {
         const uint64_t p = (uint64_t)(uintptr_t)vp[i & 1];
         const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)p, i >> 1), hi = __builtin_amdgcn_readlane((uint32_t)(p >> 32), i >> 1);
         const uint16_t* v = reinterpret_cast<const uint16_t*>((uintptr_t)(((uint64_t)hi << 32) | lo));
-        vw[i] = v ? *reinterpret_cast<const uint32_t*>(v + 2 * lane) : 0u;
-    }
+        if constexpr (NR <= 2) vw[i] = *reinterpret_cast<const uint32_t*>(v + 2 * lane);
+        else vw[i] = v ? *reinterpret_cast<const uint32_t*>(v + 2 * lane) : 0u;
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_value(i);
+    if constexpr (AHEAD < 32) __builtin_amdgcn_sched_barrier(0);
     float4v acc[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
@@ -121,6 +130,9 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) acc[mt] = mfma_native<BF16>(kb[mt][kc], b, acc[mt]);
     }
+    if constexpr (AHEAD < 32) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = AHEAD; i < 32; ++i) load_value(i);
     // C row 4 kq + v of tile mt is candidate x0 + 8 kq + 2 v + mt.  Which of them exist, and which is the speculative
     // pair: one bit per candidate, from the lanes of the first quarter
     const unsigned long long have0 = __ballot(kp[0] != nullptr) & 0xFFFFull, have1 = __ballot(kp[1] != nullptr) & 0xFFFFull;
@@ -157,6 +169,12 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
 #pragma unroll
     for (int i = 0; i < 32; ++i) {
         const float v0 = widen16<BF16>(vw[i] & 0xFFFFu), v1 = widen16<BF16>(vw[i] >> 16);
+        if constexpr (NR == 1) {
+            const float p = weights[i];
+            const bool use = p != 0.0f;
+            o[0][0] = __builtin_fmaf(p, use ? v0 : 0.0f, o[0][0]);
+            o[0][1] = __builtin_fmaf(p, use ? v1 : 0.0f, o[0][1]);
+        }
         if constexpr (NR == 2) {
             const float2 p = *reinterpret_cast<const float2*>(weights + i * 2);
             const bool use = p.x != 0.0f || p.y != 0.0f;      // a value that nobody weighs may be infinite
@@ -181,6 +199,41 @@ __device__ __forceinline__ void rows_extra_wave(const LayerView& L, const Attend
 #pragma unroll
     for (int rr = 0; rr < NR; ++rr)
         *reinterpret_cast<float2*>(o_lds + ((size_t)wave * O_ROWS + rr) * kRowsOStride + 2 * lane) = make_float2(o[rr][0], o[rr][1]);
+}
+
+// A workgroup's chunk of up to 128 16-bit candidates for one or two query rows: a wave each per 32, merged into the chunk's partials.
+// smem: extra_chunk_floats(NR) floats, 16-byte aligned.
+constexpr int kExtraQStride = kD + 8;                                      // halves between the query rows
+__host__ __device__ constexpr int extra_chunk_floats(int NR) {
+    return NR * kExtraQStride / 2 + kWaves * 32 * NR > kWaves * NR * kRowsOStride ? NR * kExtraQStride / 2 + kWaves * 32 * NR : kWaves * NR * kRowsOStride;
+}
+template <int NR, int NROWS, bool BF16, int AHEAD, typename Buffer>
+__device__ __forceinline__ void extra_chunk(const LayerView& L, const AttendArgs& A, int row, int chunk, float* smem, RowsOut& out, Buffer po,
+                                            Buffer pml) {
+    static_assert(NR <= 2 && (NR * kExtraQStride / 2) % 4 == 0, "a thread per output");
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
+    const int x0 = ((chunk - A.n_main) * kWaves + wave) * 32;
+    const int2 staged = staged_positions(L, A, row, x0, lane);
+    if (wave < NR) reinterpret_cast<uint32_t*>(qraw + wave * kExtraQStride)[lane] = reinterpret_cast<const uint32_t*>(A.q + ((size_t)row * NR + wave) * kD)[lane];
+    __syncthreads();
+    rows_extra_wave<NR, BF16, NR, AHEAD>(L, A, NROWS, row, x0, staged, lane, wave, qraw, kExtraQStride, smem + NR * kExtraQStride / 2 + wave * 32 * NR,
+                                         smem, out);
+    __syncthreads();
+    const int r = tid >> 7, c = tid & 127;
+    if (r < NR) {
+        float mx = -INFINITY, o = 0.0f, sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, out.m[w][r]);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float e = out.m[w][r] == -INFINITY ? 0.0f : exp2_of((out.m[w][r] - mx) * kLog2e);
+            if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
+            sum = __builtin_fmaf(e, out.l[w][r], sum);
+        }
+        store_partial(po, r * kD + c, o, A.fin.arrived != nullptr);
+        if (c == 0) store_max_sum(pml, r, mx, sum, A.fin.arrived != nullptr);
+    }
 }
 
 }  // namespace
