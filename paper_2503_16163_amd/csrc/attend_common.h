@@ -55,11 +55,16 @@ constexpr int kAgentScope = 16;   // cache policy bit sc1 of a buffer load or st
 __device__ __forceinline__ auto buffer_of(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
 }
-// a chunk's partials: output e of [NR][128], and the maximum and sum of row r
+// a chunk's partials: output e of [NR][128], outputs 4 e to 4 e + 3, and the maximum and sum of row r
 template <typename Buffer>
 __device__ __forceinline__ void store_partial(Buffer po, int e, float v, bool past_l2) {
     if (past_l2) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), po, e * 4, 0, kAgentScope);
     else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), po, e * 4, 0, 0);
+}
+template <typename Buffer>
+__device__ __forceinline__ void store_partials(Buffer po, int e, float4v v, bool past_l2) {
+    if (past_l2) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, v), po, e * 16, 0, kAgentScope);
+    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, v), po, e * 16, 0, 0);
 }
 template <typename Buffer>
 __device__ __forceinline__ void store_max_sum(Buffer pml, int r, float m, float sum, bool past_l2) {

@@ -813,17 +813,21 @@ __global__ __launch_bounds__(kThreads, 3) void rows_kernel(LayerView L, RowsArgs
     __syncthreads();
     const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * nq) * kD, (uint32_t)(nq * kD) * 4u);
     const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * nq) * 2, (uint32_t)nq * 8u);
-    for (int e = tid; e < nq * kD; e += kThreads) {
-        const int rr = e / kD, c = e % kD;
-        float v = 0.0f;
+    // four outputs of a thread at a time, read 16 bytes at once and without a branch on the weight (one by one and behind it the waves'
+    // outputs took 2.5 to 2.8 us of a kernel of 12 to 14, now 0.8)
+    for (int e = tid; e < nq * (kD / 4); e += kThreads) {
+        const int rr = e / (kD / 4), c = 4 * (e % (kD / 4));
+        float4v v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < kWaves; ++w)
 #pragma unroll
             for (int ss = 0; ss < SUBS; ++ss) {
                 const float wt = out.w[w][ss * NR + rr];
-                if (wt != 0.0f) v = __builtin_fmaf(wt, o_lds[((size_t)w * 16 + ss * NR + rr) * kRowsOStride + c], v);
+                const float4v o = *reinterpret_cast<const float4v*>(o_lds + ((size_t)w * 16 + ss * NR + rr) * kRowsOStride + c);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = wt != 0.0f ? __builtin_fmaf(wt, o[i], v[i]) : v[i];
             }
-        store_partial(po, e, v, A.fin.arrived != nullptr);
+        store_partials(po, e, v, A.fin.arrived != nullptr);
     }
     if (tid < nq) {
         float mx = -INFINITY, sum = 0.0f;
