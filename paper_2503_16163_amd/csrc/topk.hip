@@ -498,8 +498,8 @@ hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_
     else if (per_lane <= 24) SPC_TOPK_GATHER(1024, 24);
     else if (per_lane <= 32) SPC_TOPK_GATHER(1024, 32);
     else if (per_lane <= 40) SPC_TOPK_GATHER(1024, 40);
+    else if (per_lane <= 48) SPC_TOPK_GATHER(1024, 48);
     else if (gather) return hipErrorInvalidValue;     // selects_and_gathers: rows of one launch
-    else if (per_lane <= 48) SPC_TOPK(1024, 48);
     else if (per_lane <= 64) SPC_TOPK(1024, 64);
     else return hipErrorInvalidValue;                // launch_topk splits such a row
 #undef SPC_TOPK
@@ -509,10 +509,11 @@ hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_
 
 }  // namespace
 
-// One workgroup's registers hold 65536 keys, but its time grows faster than the row, so rows beyond kTopkSingleLaunchKeys
+// One workgroup's registers hold 65536 keys, but with more than 48 a thread they are spilled, so rows beyond kTopkSingleLaunchKeys
 // are split into ranges of about kTopkPartKeys keys, as many as keep the candidate list of the second launch within
-// one workgroup's registers.
-constexpr int kTopkRegisterKeys = 65536, kTopkPartKeys = 16384, kTopkSingleLaunchKeys = 40960;
+// one workgroup's registers.  us, one launch / two: 32 x 45000, k = 64 9.8 / 16.1, 32 x 49152, k = 256 12.0 / 18.1, but 32 x 60000
+// 17.2 / 15.1 and 18.9 / 18.2.
+constexpr int kTopkRegisterKeys = 65536, kTopkPartKeys = 16384, kTopkSingleLaunchKeys = 49152;
 
 int topk_parts(int Nq, int k) {
     if (Nq <= kTopkSingleLaunchKeys || k <= 0) return 1;
