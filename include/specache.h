@@ -267,10 +267,11 @@ int specache_score_attend(specache_ctx* ctx, int32_t layer, const void* q, int32
 
 /*
  * How the selection on the side stream is ordered behind the scores of the one-launch form of specache_score_attend (and of the
- * calls built on it).  By default the merge kernel stores a word that the side stream waits for (hipStreamWaitValue64), which
- * costs the issuing thread 8 to 18 us less per layer than an event that is still pending.  That wait is a kernel which ends when
- * the merge kernel, on another queue, has started: where something makes the kernels of different queues run one at a time (a
- * profiler that collects counters or traces threads), it would block them for good.  The library therefore goes by an event
+ * calls built on it).  By default the merge of the partial results (a kernel of its own, or the end of the scoring launch
+ * where that merges them) stores a word that the side stream waits for (hipStreamWaitValue64), which costs the issuing
+ * thread 8 to 18 us less per layer than an event that is still pending.  That wait is a kernel which ends when that merge, on
+ * another queue, has begun: where something makes the kernels of different queues run one at a time (a profiler that
+ * collects counters or traces threads), it would block them for good.  The library therefore goes by an event
  *   - when the environment names a profiling tool at specache_create (ROCPROF*, ROCP_*, HSA_TOOLS_LIB), or AMD_DIRECT_DISPATCH=0,
  *   - from the call on by which a rocprofiler library has been loaded into the process,
  *   - while the scoring stream is being captured, and where the device cannot wait for a word,

@@ -106,7 +106,7 @@ struct AttendScratch {
     int max_chunks;
 };
 enum { kAttendPartial = 1, kAttendCombine = 2 };   // which of the two launches launch_attend issues
-// A 64-bit word that other streams wait on (hipStreamWaitValue64): the merge kernel stores value there as it starts, i.e.
+// A 64-bit word that other streams wait on (hipStreamWaitValue64): the merge kernel (else finish_row) stores value there as it starts, i.e.
 // when the launch in front of it on its stream has completed.  word == null: nothing to announce.
 struct Announce {
     uint64_t* word = nullptr;

@@ -70,7 +70,7 @@ struct Layer {
     int keys_reader_slot = -1;           // slot of the select_gather that read `keys` last
     bool gathered_waited_set[2] = {false, false};
     hipStream_t gathered_waited[2] = {nullptr, nullptr};   // stream that has already waited for gathered[s]
-    // Where scoring and attention are one call its merge kernel stores `scored_value` to the word `scored_word`, and the
+    // Where scoring and attention are one call the merge of its partial results stores `scored_value` to the word `scored_word`, and the
     // selection's stream waits for that value: an event, pending as it always is when the selection is enqueued, costs
     // the issuing thread 10 us more (launch, event, wait, launch on the other stream: 19.7 us; with the word: 8.6).
     uint32_t* arrived = nullptr;         // [rows + 1] counters of the merge inside a launch (finish_row.h), zero between launches
@@ -209,7 +209,7 @@ struct CarriedEvent {
     ~CarriedEvent() { if (armed) pending_launch_events() = LaunchEvents{}; }
 };
 
-// The wait for a word is a kernel without a bound, which ends only if the merge kernel on another queue runs beside it or before
+// The wait for a word is a kernel without a bound, which ends only if the merging launch on another queue runs beside it or before
 // it.  Submission order sees to that (the merge is enqueued first) unless something between the streams and the queues holds
 // kernels back: a tool that collects counters or traces threads runs the kernels of all queues one at a time, and without direct
 // dispatch a thread per stream submits them in an order of its own.  No call reports such a tool, so every sign of one
@@ -988,8 +988,8 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     L.N = N1;   // only once the launch that copies the token is enqueued
     ctx->logits_kept = keep;
     ctx->q_kept = rows_pass && !keep;
-    // the keys are complete here, in front of the merge: the event says so, or else the merge as it starts, and the selection on
-    // the side stream runs beside it
+    // the keys are complete here, in front of a merge kernel: the event says so, or else that kernel as it starts (a launch that
+    // merged says so itself), and the selection on the side stream runs beside it
     if (!by_word)
         if (int rc = record_scored(ctx, L, layer, n_rows, st, scored_carried)) return rc;
     if (!merged) {

@@ -28,7 +28,8 @@ COPY_KIB = 262144.0   # bench.py --calibrate-copy copies 256 MiB device to devic
 
 
 def short_name(full):
-    """'attend_i8_kernel+score' for the instantiation with the scoring pass in front, else the bare kernel name;
+    """'attend_i8_kernel+score' for the instantiation with the scoring pass in front, 'topk_kernel+gather' for the one that also
+    fetches what it selected, else the bare kernel name;
     None for kernels that are not this library's."""
     m = re.search(r"specache::\(anonymous namespace\)::(\w+)\s*(<([^>]*)>)?", full)
     if not m:
@@ -36,6 +37,8 @@ def short_name(full):
     name, targs = m.group(1), (m.group(3) or "")
     if name == "attend_i8_kernel" and targs.replace(" ", "").endswith("true"):
         return name + "+score"
+    if name == "topk_kernel" and targs.replace(" ", "").endswith("true"):
+        return name + "+gather"
     if name == "rows_kernel":   # the last template argument is the mode: 0 both passes, 1 scoring, 2 attention
         return name + {"0": "+score", "2": "<attention>"}.get(targs.replace(" ", "").split(",")[-1], "")
     return name
