@@ -885,11 +885,14 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
     if (rescore)
         if (int rc = score_again(ctx, L, st)) return rc;
+    // The layer's counters go with the context's scratch, which calls of one context share in any case.  A call with scratch memory of
+    // its own may overlap one of those on another stream, and both would count their workgroups together: it merges in a launch of its own.
+    uint32_t* const arrived = static_scratch ? nullptr : L.arrived;
     for (int phase : {kAttendPartial, kAttendCombine}) {
         TimedLaunch t(ctx, st, phase == kAttendPartial ? SPECACHE_K_ATTEND : SPECACHE_K_ATTEND_COMBINE, /*kernel_events=*/true);
         SPC_HIP(ctx, launch_attend(L.view, q, n_rows, L.N, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride,
                                    slot >= 0 ? L.slot[slot] : nullptr, slot >= 0 ? L.slot_idx[slot] : nullptr, k_spec,
-                                   v_spec, scratch, out, phase, L.arrived, st));
+                                   v_spec, scratch, out, phase, arrived, st));
     }
     return record_attended(ctx, L, slot, st);
 }

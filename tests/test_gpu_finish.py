@@ -57,3 +57,32 @@ def test_layers_on_streams_of_their_own_keep_their_counters():
         finally:
             torch.cuda.synchronize()
             sc.close()
+
+
+def test_attend_from_static_scratch_beside_attend():
+    """specache_attend and specache_attend_static of one layer keep their partials apart, so on two streams they may overlap: neither
+    counts the other's workgroups."""
+    import torch
+    from paper_2503_16163_amd import binding
+    H, S, k = 4, 6000, 16
+    q = synth.make_queries_device(6, 1, 1, H, 128, synth.FP16).view(1, H, 2, 128).contiguous()
+    kd, vd = synth.make_kv_device(6, 1, H, S, 128, synth.FP16)
+    sc = binding.SpeCache(1, 1, H, H, 2, 32, 6144, k, synth.FP16, async_select=2)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    try:
+        sc.quantize_append(0, kd, vd, S)
+        sc.score(0, q, 2)
+        want = [torch.zeros((1, H, 2, 128), dtype=torch.float32, device="cuda") for _ in range(2)]     # each by itself first
+        sc.attend(0, q, 2, None, None, -1, want[0])
+        sc.attend_static(0, q, 2, None, None, -1, want[1])
+        outs = [torch.zeros_like(want[0]) for _ in range(40)]
+        torch.cuda.synchronize()
+        for i in range(20):
+            sc.attend(0, q, 2, None, None, -1, outs[2 * i], streams[0])
+            sc.attend_static(0, q, 2, None, None, -1, outs[2 * i + 1], streams[1])
+        torch.cuda.synchronize()
+        for i, out in enumerate(outs):
+            assert torch.equal(out, want[i % 2]), (i, (out - want[i % 2]).abs().max().item())
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
