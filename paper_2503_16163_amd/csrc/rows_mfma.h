@@ -24,12 +24,13 @@
 // current one is worked on.  The four waves of a workgroup merge once, at the end.  The 16-bit candidates are a wave
 // each per 32: the keys times the queries on the matrix cores in their own type, the values on the vector ALUs.
 //
-// Measured alone on MI355X (scoring + attention as two launches of the kernels before it -> as one launch): 32 KV rows x 32768
-// tokens, 8 query rows, 2 bits, g = 64: 27.5 + 37.9 -> 37.2 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 43.2 us;
-// 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.0 us at best, 17.6 beside the gathers; 16 x 8192, 16 query rows, g = 128:
-// 10.8 + 40.2 -> 17.0 us (the earlier kernels' 16-bit chunk was a chain of 40 us there).  4-bit codes, two launches, 32 x
-// 16384, 2 query rows as 8 columns' worth, g = 32: scoring 14.3, attention 17.6 us at best, 16.8 and 19.9 beside the gathers (the
-// 84 MB they read need 14 us at the rate of a plain read); a decode step of a layer 70.7 -> 51 us against vector-ALU kernels.
+// Measured on MI355X (scoring + attention as two launches of the kernels before it -> as one launch; then with the first
+// loads requested together and a merge of the waves that reads 16 bytes at a time, 0.8 us instead of 2.5 to 2.8): 32 KV rows x 32768 tokens, 8 query rows, 2 bits, g = 64: 27.5 +
+// 37.9 -> 37.2 -> 33.5 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 43.2 -> 39.6 us; 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.0
+// at best -> 10.3 at best, 12.3 beside the gathers; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 17.0 -> 13.6 us.  4-bit codes,
+// two launches, 32 x 16384, 2 query rows as 8 columns' worth, g = 32: scoring 14.0, attention 17.6 us at best, 16.0 and 21.5 beside
+// the gathers (the 84 MB they read need 14 us at the rate of a plain read); a decode step of a layer 70.7 -> 51 us against
+// vector-ALU kernels.
 // Up to 168 registers, three workgroups per compute unit; held to four it spills.
 #pragma once
 #include "attend_common.h"
