@@ -15,24 +15,30 @@
 //      histogram, of those, finds the bin that holds tau and tau's rank inside it;
 //   3. the handful of keys in that bin are ranked by one wave (larger key first, then lower position), which decides for
 //      each of them at once, ties included; the selected positions are bits of a bitmap, whose order is the output's.
-// A row whose candidates do not fit, or whose boundary bin is crowded (many equal or almost equal scores), goes on
-// with histograms of 2048 bins inside the range left, which narrow it by 11 bits each time, and an ordered
-// compaction (select_crowded).
+// Larger k has room for more candidates and takes maxima of two (many_candidates); where k is a quarter of the row or more a
+// floor would leave too few keys out, and the histograms are of all keys.
+// Where the boundary bin is crowded (many equal or almost equal scores) the candidates go on by themselves, with histograms
+// inside the range left; a row with more candidates than there is room for does so with all its keys.  Both leave two
+// bitmaps, the keys above tau and those equal to it, which one ordered pass writes out.
 //
-// Measured on MI355X, us, one launch alone (before: a histogram of the maxima's leading bits, one of the keys, 64
-// readlanes to rank, a counting and an emitting pass over all registers): rows x keys, k = 64 unless stated: 1 x 4096 10.6 -> 6.0,
-// 32 x 8192 13.8 -> 8.5, 32 x 16384 12.0 -> 7.0, 32 x 32768 15.2 -> 8.6 (k = 256: 16.7 -> 9.8), 32 x 16384 with k = 1024 14.0 ->
-// 9.4; in two launches 8 x 131072 with k = 256 27.2 -> 16.2, with k = 1024 32.3 -> 21.8.
+// Measured on MI355X, us, one launch alone (first: a histogram of the maxima's leading bits, one of the keys, 64
+// readlanes to rank, a counting and an emitting pass over all registers): rows x keys, k = 64 unless stated: 1 x 4096 10.6 -> 5.2,
+// 32 x 8192 13.8 -> 6.2, 32 x 16384 12.0 -> 5.3, 32 x 32768 15.2 -> 6.7 (k = 256: 16.7 -> 8.4), 32 x 16384 with k = 1024 14.0 ->
+// 8.3, with k = 3000 16.5 -> 11.3; in two launches 8 x 131072 with k = 256 27.2 -> 15.3, with k = 1024 32.3 -> 20.3, with k = 4096
+// 54.4 -> 41.  Large k with room for 2048 candidates only, its keys read from memory again in every pass: 32 x 16384, k = 3000 19.0; 32 x
+// 8192, k = 4096 16.0, now 9.9 (first 12.1); 32 x 32768, k = 4096 30.2, now 14.7 (23.8).  64 values in a row, each many times over: 32 x
+// 32768 40.3, now 12.0 to 15.6 (19.3), k = 4096 42.7, now 17.1 (23.0); a single value 80.6, now 47 (68).
+#include <cmath>
+
 #include "kernels.h"
 #include "layout.h"
 
 namespace specache {
 namespace {
 
-constexpr int kBins = 512;         // of either histogram of the short way
-constexpr int kCandidates = 2048;  // keys the short way collects
-constexpr int kCrowdedBins = 2048;
-constexpr int kSmall = 64;         // keys one wave ranks directly
+constexpr int kCandidates = 2048;      // keys the short way has room for,
+constexpr int kCandidatesMost = 8192;  // and where k asks for more of them (many_candidates)
+constexpr int kSmall = 64;             // keys one wave ranks directly
 constexpr int kMaxTopk = 4096;
 constexpr int kMapWords = 65536 / 32;
 
@@ -60,62 +66,42 @@ __device__ __forceinline__ uint32_t wave_largest(uint32_t v) {
     const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
     return step(step(a, b), step(c, d));
 }
-// exclusive prefix of a 64-bit ballot below this lane
-__device__ __forceinline__ int prefix_below(unsigned long long mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-}
-
 // The bin that holds the need-th largest counted key (larger bin = larger keys) and that key's rank in the bin (from
-// 1, largest first), worked out by every wave for itself; bin = kBins if fewer than `need` keys were counted.
+// 1, largest first), worked out by every wave for itself; bin = BINS if fewer than `need` keys were counted.
 struct BinRank { uint32_t bin, rank; };
+template <int BINS>
 __device__ __forceinline__ BinRank find_bin(const uint32_t* hist, uint32_t need) {
+    constexpr int kChunk = BINS < 512 ? BINS : 512, kChunks = BINS / kChunk;   // bins read at a time, from the top; a lane's 8 side by side
     const int lane = threadIdx.x & 63;
-    const uint4 lo = reinterpret_cast<const uint4*>(hist)[2 * (63 - lane)], hi = reinterpret_cast<const uint4*>(hist)[2 * (63 - lane) + 1];
-    const uint32_t h[8] = {hi.w, hi.z, hi.y, hi.x, lo.w, lo.z, lo.y, lo.x};   // bins 8 (63 - lane) + 7 downwards
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mine += h[j];
-    const uint32_t upto = wave_prefix(mine);
-    const unsigned long long reached = __ballot(upto >= need);
-    if (reached == 0) return {(uint32_t)kBins, 0};
-    uint32_t above = upto - mine, bin = 0, rank = 0;
-    bool found = false;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const bool here = !found && above + h[j] >= need;
-        bin = here ? 8 * (63 - lane) + 7 - j : bin;
-        rank = here ? need - above : rank;
-        found = found || here;
-        above += h[j];
-    }
-    const int at = __builtin_ctzll(reached);
-    return {(uint32_t)__builtin_amdgcn_readlane(bin, at), (uint32_t)__builtin_amdgcn_readlane(rank, at)};
-}
-
-// Crowded rows.  hist[] is stored skewed (bin b at b + b / 32) so that a lane walking 32 consecutive bins
-// and its neighbours touch different banks.
-__device__ __forceinline__ int skew(int b) { return b + (b >> 5); }
-constexpr int kHistWords = kCrowdedBins + kCrowdedBins / 32;
-
-// Wave 0 only: find the bin holding the need-th largest counted key (bins ordered by
-// value, larger bin = larger keys).  Writes sel[0] = bin and sel[1] = rank of the wanted key inside that bin (1-based,
-// counted from the bin's largest key).
-__device__ __forceinline__ void select_bin_wave0(const uint32_t* hist, uint32_t* sel, uint32_t need) {
-    const int lane = threadIdx.x & 63;
-    // lane l owns the 32 bins from 32 (63 - l) on
-    uint32_t mine = 0;
+    uint32_t passed = 0;
 #pragma unroll 1
-    for (int j = 0; j < 32; ++j) mine += hist[skew(32 * (63 - lane) + j)];
-    uint32_t above = wave_prefix(mine) - mine;
-#pragma unroll 1
-    for (int j = 31; j >= 0; --j) {
-        const uint32_t h = hist[skew(32 * (63 - lane) + j)];
-        if (above < need && need <= above + h) {
-            sel[0] = 32 * (63 - lane) + j;
-            sel[1] = need - above;
+    for (int ch = kChunks - 1; ch >= 0; --ch) {
+        const uint4* at = reinterpret_cast<const uint4*>(hist + kChunk * ch) + 2 * (63 - lane);
+        const uint4 lo = at[0], hi = at[1];
+        const uint32_t h[8] = {hi.w, hi.z, hi.y, hi.x, lo.w, lo.z, lo.y, lo.x};   // bins 8 (63 - lane) + 7 downwards
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mine += h[j];
+        const uint32_t upto = passed + wave_prefix(mine);
+        const unsigned long long reached = __ballot(upto >= need);
+        if (reached == 0) {
+            passed = __builtin_amdgcn_readlane(upto, 63);
+            continue;
         }
-        above += h;
+        uint32_t above = upto - mine, bin = 0, rank = 0;
+        bool found = false;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool here = !found && above + h[j] >= need;
+            bin = here ? 8 * (63 - lane) + 7 - j : bin;
+            rank = here ? need - above : rank;
+            found = found || here;
+            above += h[j];
+        }
+        const int first = __builtin_ctzll(reached);
+        return {(uint32_t)(kChunk * ch) + __builtin_amdgcn_readlane(bin, first), (uint32_t)__builtin_amdgcn_readlane(rank, first)};
     }
+    return {(uint32_t)BINS, 0};
 }
 
 // A row may be split into `parts` ranges of part_len keys, one workgroup each, that write
@@ -159,28 +145,31 @@ __device__ __forceinline__ void fetch_pairs(const GatherIo& g, int row, int k, c
 }
 
 // THREADS: 1024 for long rows; 256 for rows of up to 8192 keys, so that several rows share a
-// compute unit and hide each other's barrier latency.
-template <int THREADS, int KPT, bool GATHER>
+// compute unit and hide each other's barrier latency.  CAND: candidates the short way has room for.
+template <int THREADS, int KPT, bool GATHER, int CAND>
 __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const uint32_t* __restrict__ keys,
                                                        size_t key_stride, int32_t* __restrict__ idx_out, GatherIo g) {
     constexpr int kWavesHere = THREADS / 64;
     constexpr int kMapHere = THREADS * KPT / 32;      // words of the bitmap
-    constexpr int kSub = 4;                           // registers of a finer maximum
+    constexpr int kSub = CAND > kCandidates ? 2 : 4;  // registers of a finer maximum
     static_assert(kMapHere <= kMapWords, "a row's positions");
+    // Where k is a large part of the row, tau lies among small scores of either sign, and keys there are binades apart: few bins then
+    // hold all keys, whose atomics wait for each other
+    constexpr int kBins = CAND > kCandidates ? 2048 : 512, kBinBits = CAND > kCandidates ? 11 : 9;
     __shared__ __attribute__((aligned(16))) uint32_t bins[2][kBins];
-    __shared__ uint2 cand[kCandidates];               // key, position; a crowded row's histogram
-    __shared__ uint32_t bitmap[kMapHere];
-    __shared__ uint32_t wave_red[kWavesHere], wave_eq[kWavesHere], sel[2], result[2];
+    __shared__ __attribute__((aligned(16))) uint2 cand[CAND];   // key, position
+    __shared__ __attribute__((aligned(8))) uint32_t bitmap[kMapHere];
+    __shared__ uint32_t wave_red[kWavesHere], result[2];
     __shared__ uint2 small_keys[kSmall];
     __shared__ uint32_t n_cand, n_small;
 
-    static_assert(sizeof(cand) >= kHistWords * 4, "the histogram takes the candidates' place");
-    uint32_t* crowded_hist = reinterpret_cast<uint32_t*>(cand);
+    static_assert(sizeof(cand) >= kMapHere * 4, "a crowded row's second bitmap takes the candidates' place");
+    uint32_t* eq_map = reinterpret_cast<uint32_t*>(cand);
     static_assert(sizeof(cand) >= kMaxTopk * 4, "and so does the list of the selected positions, when both are done with");
     int32_t* list = reinterpret_cast<int32_t*>(cand);
 
     const int row = blockIdx.x / io.parts, part = blockIdx.x % io.parts;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // (scalar: the loads' descriptor is)
     const int base = part * io.part_len;
     const int left = io.nq_total - base;
     const int Nq = left < 0 ? 0 : (left < io.part_len ? left : io.part_len);   // keys of this range
@@ -211,11 +200,14 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
         // range tested below starts at 1 or above, so padding never matches and no pass needs an index test.  (Key 0
         // itself is the one NaN pattern 0xFFFFFFFF; it is treated as below every other score.)
         uint32_t key[KPT];
-        {
+        auto load_keys = [&]() {
+            int at = (lo + lane) * 4;
+            asm volatile("" : "+v"(at));           // (each call's addresses are its own: kept from one to the next they would be spilled)
             const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(kr), 0, hi > lo ? hi * 4 : 0, 0x00027000);
 #pragma unroll
-            for (int it = 0; it < KPT; ++it) key[it] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (lo + lane) * 4 + it * 256, 0, 0);
-        }
+            for (int it = 0; it < KPT; ++it) key[it] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at + it * 256, 0, 0);
+        };
+        load_keys();
         // while they travel
         for (int b = tid; b < 2 * kBins; b += THREADS) bins[0][b] = 0;
         for (int b = tid; b < kMapHere; b += THREADS) bitmap[b] = 0;
@@ -240,7 +232,7 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
         for (int w = 1; w < kWavesHere; ++w) row_max = wave_red[w] > row_max ? wave_red[w] : row_max;
         // ---- floor: the maxima among the top four binades, else all of them by binade
         constexpr uint32_t kTopSpan = 1u << 25;
-        static_assert(kTopSpan / kBins == 1u << 16, "a bin of the top binades");
+        constexpr int kTopShift = 25 - kBinBits, kAllShift = 32 - kBinBits;
         const uint32_t top_lo = row_max >= kTopSpan ? row_max - (kTopSpan - 1) : 0u;
         auto count_maxima = [&](uint32_t* hist, uint32_t from, int shift) {
             if (fine) {
@@ -251,43 +243,124 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
                 atomicAdd(&hist[(tmax - from) >> shift], 1u);
             }
         };
-        count_maxima(bins[0], top_lo, 16);
-        __syncthreads();
         uint32_t floor_key = 1u;                   // fewer maxima than keff: no floor
-        {
-            const BinRank br = find_bin(bins[0], (uint32_t)keff);
+        uint32_t n = 0xFFFFFFFFu;                  // candidates; uniform, as everything that decides on the way is
+        // (us with a floor against all keys: 32 x 4096, k = 2048 16.9 / 8.6; 32 x 8192, k = 2048 9.9 / 11.8, k = 3000 13.2 / 12.0, k = 4096
+        // 20 / 9.9; 32 x 16384, k = 4096 12.4 / 13.4, but with 64 values in the row 17.5 / 14)
+        const bool all_keys = CAND > kCandidates && 4 * keff >= Nq;
+        if (!all_keys) {
+            count_maxima(bins[0], top_lo, kTopShift);
+            __syncthreads();
+            const BinRank br = find_bin<kBins>(bins[0], (uint32_t)keff);
             if (br.bin < kBins) {
-                floor_key = top_lo + (br.bin << 16);
+                floor_key = top_lo + (br.bin << kTopShift);
             } else {                               // uniform over the workgroup
                 __syncthreads();
                 for (int b = tid; b < kBins; b += THREADS) bins[0][b] = 0;
                 __syncthreads();
-                count_maxima(bins[0], 0u, 23);
+                count_maxima(bins[0], 0u, kAllShift);
                 __syncthreads();
-                const BinRank all = find_bin(bins[0], (uint32_t)keff);
-                if (all.bin < kBins) floor_key = all.bin << 23;
+                const BinRank all = find_bin<kBins>(bins[0], (uint32_t)keff);
+                if (all.bin < kBins) floor_key = all.bin << kAllShift;
             }
             floor_key = floor_key < 1u ? 1u : floor_key;
-        }
-        // ---- the keys from the floor on
+            // ---- the keys from the floor on
 #pragma unroll
-        for (int it = 0; it < KPT; ++it)
-            if (key[it] >= floor_key) {
-                const uint32_t at = atomicAdd(&n_cand, 1u);
-                if (at < kCandidates) cand[at] = make_uint2(key[it], (uint32_t)(lo + it * 64 + lane));
-            }
-        __syncthreads();
-        const uint32_t n = n_cand;
-        bool crowded = n > kCandidates;
+            for (int it = 0; it < KPT; ++it)
+                if (key[it] >= floor_key) {
+                    const uint32_t at = atomicAdd(&n_cand, 1u);
+                    if (at < CAND) cand[at] = make_uint2(key[it], (uint32_t)(lo + it * 64 + lane));
+                }
+            __syncthreads();
+            n = n_cand;
+        }
+        constexpr int kWords = (kMapHere + THREADS - 1) / THREADS;   // of the bitmap, of a thread
         uint32_t need = (uint32_t)keff;
+        if (n < need && n <= CAND) need = n;       // keys that are NaN are below everything and stay unselected
+        // a wave finds the rank-th largest of up to kSmall keys and how many keys equal to it are wanted
+        auto rank_small = [&](uint32_t rank) {
+            const uint32_t m = n_small;
+            const uint32_t mine = lane < (int)m ? small_keys[lane].x : 0u;
+            uint32_t greater = 0, equal = 0;
+#pragma unroll 2
+            for (uint32_t j = 0; j < m; ++j) {
+                const uint32_t kj = small_keys[j].x;
+                greater += kj > mine;
+                equal += kj == mine;
+            }
+            if (lane < (int)m && greater < rank && rank <= greater + equal) {
+                result[0] = mine;
+                result[1] = rank - greater;
+            }
+        };
+        // Crowded: tau, the need-th largest of the keys in [range_lo, range_hi], by histograms inside a range that becomes kBins times
+        // narrower each time, and narrower still by the least and the largest key found in it: equal scores end it there.
+        // need becomes the number of keys equal to tau that are wanted.  for_each(f): f(key) for this thread's keys.
+        auto narrow = [&](auto&& for_each, uint32_t range_lo, uint32_t range_hi) {
+            for (int round = 0; round < 4 && range_lo != range_hi; ++round) {
+                const uint32_t span = range_hi - range_lo;
+                const int shift = span < (uint32_t)kBins ? 0 : 32 - __builtin_clz(span) - kBinBits;
+                __syncthreads();
+                for (int b = tid; b < kBins; b += THREADS) bins[0][b] = 0;
+                if (tid == 0) {
+                    n_small = 0;
+                    result[0] = 0xFFFFFFFFu;
+                    result[1] = 0u;
+                }
+                __syncthreads();
+                for_each([&](uint32_t kv) {
+                    const uint32_t off = kv - range_lo;
+                    if (off <= span) atomicAdd(&bins[0][off >> shift], 1u);   // one unsigned test for range_lo <= kv <= range_hi
+                });
+                __syncthreads();
+                const BinRank br = find_bin<kBins>(bins[0], need);
+                if (br.bin >= kBins) {             // fewer keys than wanted (the others are NaN): all of them
+                    need = 0xFFFFFFFFu;
+                    break;
+                }
+                const uint32_t in_bin = bins[0][br.bin];
+                range_lo += br.bin << shift;
+                range_hi = range_lo + ((1u << shift) - 1u);
+                need = br.rank;
+                if (shift == 0) break;             // the bin is a single key value
+                if (in_bin <= (uint32_t)kSmall) {
+                    for_each([&](uint32_t kv) {
+                        if (kv - range_lo <= range_hi - range_lo) small_keys[atomicAdd(&n_small, 1u)].x = kv;
+                    });
+                    __syncthreads();
+                    if (wave == 0) rank_small(br.rank);
+                    __syncthreads();
+                    range_lo = result[0];
+                    need = result[1];
+                    break;
+                }
+                uint32_t least = 0xFFFFFFFFu, largest = 0u;
+                for_each([&](uint32_t kv) {
+                    if (kv - range_lo <= range_hi - range_lo) {
+                        least = kv < least ? kv : least;
+                        largest = kv > largest ? kv : largest;
+                    }
+                });
+                least = ~wave_largest(~least);
+                largest = wave_largest(largest);
+                if (lane == 0) {
+                    atomicMin(&result[0], least);
+                    atomicMax(&result[1], largest);
+                }
+                __syncthreads();
+                range_lo = result[0];
+                range_hi = result[1];
+            }
+            return range_lo;                       // tau
+        };
+        bool crowded = n > CAND;
         if (!crowded) {
-            if (n < need) need = n;                // keys that are NaN are below everything and stay unselected
             // ---- the bin of tau
             const uint32_t span = row_max - floor_key;
-            const int shift = span < (uint32_t)kBins ? 0 : 32 - __builtin_clz(span) - 9;
+            const int shift = span < (uint32_t)kBins ? 0 : 32 - __builtin_clz(span) - kBinBits;
             for (uint32_t c = tid; c < n; c += THREADS) atomicAdd(&bins[1][(cand[c].x - floor_key) >> shift], 1u);
             __syncthreads();
-            const BinRank br = find_bin(bins[1], need);
+            const BinRank br = find_bin<kBins>(bins[1], need);
             crowded = bins[1][br.bin < kBins ? br.bin : 0] > kSmall;
             if (!crowded) {
                 for (uint32_t c = tid; c < n; c += THREADS) {
@@ -311,7 +384,6 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
                 }
                 __syncthreads();
                 // ---- the bits in order: this thread's words, behind those of the threads and waves before it
-                constexpr int kWords = (kMapHere + THREADS - 1) / THREADS;
                 uint32_t w[kWords], mine = 0;
 #pragma unroll
                 for (int u = 0; u < kWords; ++u) {
@@ -334,113 +406,77 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
                 for (int j = (int)need + tid; j < k; j += THREADS) none(j);
                 return;
             }
-        }
-        // ---- crowded: histograms inside [range_lo, range_hi], the keys read again in every pass (the registers that would
-        // hold them until here, in a way seldom taken, would be spilled in the other)
-        auto for_each_key = [&](auto&& f) {        // f(index, key); whole waves, padding has key 0
-#pragma unroll 1
-            for (int i0 = lo; i0 < hi; i0 += 256) {
-                uint32_t kb[4];
+            // ---- crowded boundary: the candidates narrow it down among themselves, out of registers, and their place takes
+            // the bitmap of the keys equal to tau
+            constexpr int kMine = CAND / THREADS;
+            uint2 c[kMine];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = i0 + u * 64 + lane;
-                    kb[u] = i < hi ? kr[i] : 0u;
-                }
+            for (int u = 0; u < kMine; ++u) c[u] = tid + u * THREADS < (int)n ? cand[tid + u * THREADS] : make_uint2(0u, 0u);
+            const uint32_t bin_lo = floor_key + (br.bin << shift);
+            need = br.rank;
+            const uint32_t tau = narrow([&](auto&& f) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) f(i0 + u * 64 + lane, kb[u]);
-            }
-        };
-        uint32_t range_lo = floor_key, range_hi = row_max;    // inclusive
-        for (int round = 0; round < 4; ++round) {
-            const uint32_t span = range_hi - range_lo;
-            const int shift = span < (uint32_t)kCrowdedBins ? 0 : 32 - __builtin_clz(span) - 11;
+                for (int u = 0; u < kMine; ++u) f(c[u].x);
+            }, bin_lo, shift == 0 ? bin_lo : bin_lo + ((1u << shift) - 1u));
             __syncthreads();
-            for (int b = tid; b < kHistWords; b += THREADS) crowded_hist[b] = 0;
-            if (tid == 0) {
-                n_small = 0;
-                sel[0] = 0xFFFFFFFFu;
-            }
+            for (int b = tid; b < kMapHere; b += THREADS) eq_map[b] = 0;
             __syncthreads();
-            for_each_key([&](int, uint32_t kv) {
-                const uint32_t off = kv - range_lo;
-                if (off <= span) atomicAdd(&crowded_hist[skew(off >> shift)], 1u);   // one unsigned test for range_lo <= kv <= range_hi
-            });
+#pragma unroll
+            for (int u = 0; u < kMine; ++u) {
+                if (c[u].x > tau) atomicOr(&bitmap[c[u].y >> 5], 1u << (c[u].y & 31));
+                else if (c[u].x == tau) atomicOr(&eq_map[c[u].y >> 5], 1u << (c[u].y & 31));
+            }
+        } else {
+            // ---- more candidates than there is room for: all keys, loaded once more (registers that held them since the floor
+            // would be spilled).  A lane's keys are 64 apart, so a ballot is two words of a bitmap.
+            if (!all_keys) load_keys();
+            const uint32_t tau = narrow([&](auto&& f) {
+#pragma unroll
+                for (int it = 0; it < KPT; ++it) f(key[it]);
+            }, floor_key, row_max);
             __syncthreads();
-            if (wave == 0) select_bin_wave0(crowded_hist, sel, need);
+            for (int b = tid; b < kMapHere; b += THREADS) eq_map[b] = 0;
             __syncthreads();
-            if (sel[0] == 0xFFFFFFFFu) {           // fewer keys than wanted (the others are NaN): all of them
-                if (tid == 0) { result[0] = range_lo; result[1] = 0xFFFFFFFFu; }
-                __syncthreads();
-                break;
+#pragma unroll
+            for (int it = 0; it < KPT; ++it) {
+                const unsigned long long gt = __ballot(key[it] > tau), eq = __ballot(key[it] == tau);
+                if (it * 64 < seg && lane < 2)
+                    reinterpret_cast<unsigned long long*>(lane ? eq_map : bitmap)[(lo >> 6) + it] = lane ? eq : gt;
             }
-            const uint32_t bin = sel[0], rank = sel[1];
-            const uint32_t bin_lo = range_lo + (bin << shift);
-            const uint32_t bin_hi = shift == 0 ? bin_lo : bin_lo + ((1u << shift) - 1u);
-            const uint32_t in_bin = crowded_hist[skew(bin)];
-            if (shift == 0) {                      // the bin is a single key value
-                if (tid == 0) { result[0] = bin_lo; result[1] = rank; }
-                __syncthreads();
-                break;
-            }
-            if (in_bin <= (uint32_t)kSmall) {
-                for_each_key([&](int, uint32_t kv) {
-                    if (kv - bin_lo <= bin_hi - bin_lo) small_keys[atomicAdd(&n_small, 1u)].x = kv;
-                });
-                __syncthreads();
-                if (wave == 0) {
-                    const uint32_t m = n_small;
-                    const uint32_t mine = lane < (int)m ? small_keys[lane].x : 0u;
-                    uint32_t greater = 0, equal = 0;
-#pragma unroll 1
-                    for (uint32_t j = 0; j < m; ++j) {
-                        const uint32_t kj = small_keys[j].x;
-                        greater += kj > mine;
-                        equal += kj == mine;
-                    }
-                    // tau is the key with greater < rank <= greater + equal
-                    if (lane < (int)m && greater < rank && rank <= greater + equal) {
-                        result[0] = mine;
-                        result[1] = rank - greater;
-                    }
-                }
-                __syncthreads();
-                break;
-            }
-            range_lo = bin_lo;
-            range_hi = bin_hi;
-            need = rank;
         }
-        const uint32_t tau = result[0];
-        need = result[1];                          // keys == tau to take
-        // ---- ordered compaction: count per wave, then emit in index order (ties to the lower index)
-        uint32_t cnt_gt = 0, cnt_eq = 0;
-        for_each_key([&](int, uint32_t kv) {
-            cnt_gt += __popcll(__ballot(kv > tau));
-            cnt_eq += __popcll(__ballot(kv == tau));
-        });
-        if (lane == 0) { wave_red[wave] = cnt_gt; wave_eq[wave] = cnt_eq; }
         __syncthreads();
-        uint32_t gt_before = 0, eq_before = 0, total = 0, eq_total = 0;
+        // ---- both bitmaps in order, a thread as many bits as it has keys (where k is most of the row it has as many to write).  Fewer
+        // than k keys are above tau, so both counts fit one word.
+        static_assert(kMaxTopk < 1 << 13 && THREADS * KPT <= 1 << 18, "the counts of a row");
+        const int n_bits = seg >> 6, first = tid * n_bits;
+        auto bits_of = [&](const uint32_t* map_words) {
+            const int at = first >> 5, by = first & 31;
+            auto word = [&](int i) { return i < kMapHere ? (uint64_t)map_words[i] : 0ull; };
+            uint64_t v = (word(at) | word(at + 1) << 32) >> by;
+            if (by > 0) v |= word(at + 2) << (64 - by);
+            return n_bits < 64 ? v & ((1ull << n_bits) - 1) : v;
+        };
+        const uint64_t gt = bits_of(bitmap), eq = bits_of(eq_map);
+        const uint32_t mine = __popcll(gt) + (__popcll(eq) << 13);
+        const uint32_t upto = wave_prefix(mine);
+        if (lane == 63) wave_red[wave] = upto;
+        __syncthreads();
+        uint32_t before = upto - mine, total = 0;
 #pragma unroll 1
-        for (int w = 0; w < kWavesHere; ++w) {
-            gt_before += w < wave ? wave_red[w] : 0u;
-            eq_before += w < wave ? wave_eq[w] : 0u;
-            total += wave_red[w];
-            eq_total += wave_eq[w];
+        for (int v = 0; v < kWavesHere; ++v) {
+            before += v < wave ? wave_red[v] : 0u;
+            total += wave_red[v];
         }
-        total += eq_total < need ? eq_total : need;
-        for_each_key([&](int i, uint32_t kv) {
-            const bool gt = kv > tau, eq = kv == tau;
-            const unsigned long long mg = __ballot(gt), me = __ballot(eq);
-            const uint32_t my_eq_rank = eq_before + prefix_below(me);
-            if (gt || (eq && my_eq_rank < need)) {
-                const uint32_t eq_taken_before = my_eq_rank < need ? my_eq_rank : need;
-                emit(gt_before + prefix_below(mg) + eq_taken_before, i, kv);
-            }
-            gt_before += __popcll(mg);
-            eq_before += __popcll(me);
-        });
-        for (int j = (int)total + tid; j < k; j += THREADS) none(j);
+        uint32_t gt_before = before & 0x1FFFu, eq_before = before >> 13;
+        for (uint64_t either = gt | eq; either; either &= either - 1) {
+            const int bit = __builtin_ctzll(either);
+            const uint32_t pos = gt_before + (eq_before < need ? eq_before : need);
+            if (gt >> bit & 1) ++gt_before;
+            else if (eq_before++ >= need) continue;
+            emit(pos, first + bit, kout ? kr[first + bit] : 0u);
+        }
+        const uint32_t eq_all = total >> 13;
+        for (int j = (int)((total & 0x1FFFu) + (eq_all < need ? eq_all : need)) + tid; j < k; j += THREADS) none(j);
     };
 
     if (keff == Nq) {   // everything is selected
@@ -470,6 +506,16 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
     }
 }
 
+// Whether the short way of ArgTopK should have room for kCandidatesMost candidates.  It collects the keys above the k-th largest of
+// the maxima of four: of n keys in no particular order the share x with 1 - (1 - x)^4 = 4 k / n (to which the floor's bins add up
+// to a tenth).  Room for more costs a workgroup 60 KB of LDS and twice as many maxima; too little room a pass over the keys for
+// nothing and the way of the crowded rows (32 x 32768, k = 2000: 30.0 us, now 12.7).
+bool many_candidates(int n, int k) {
+    if (k <= kCandidates / 4) return false;
+    const double p = 4.0 * k / n;
+    return n * (p < 1.0 ? 1.0 - std::sqrt(std::sqrt(1.0 - p)) : 1.0) > 0.85 * kCandidates;
+}
+
 // one launch over `rows * io.parts` ranges of at most n keys each; gather: and the fetch behind it (gather_kb: KB of a row's pairs
 // under way at a time)
 hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_t* keys, size_t key_stride,
@@ -485,24 +531,31 @@ hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_
         const int reads = gather_kb / g.waves;
         g.reads = reads >= 8 ? 8 : reads >= 4 ? 4 : reads >= 2 ? 2 : 1;
     }
-#define SPC_TOPK(T, K) SPC_LAUNCH((topk_kernel<T, K, false>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out, g)
-#define SPC_TOPK_GATHER(T, K)                                                                                                    \
-    do {                                                                                                                         \
-        if (gather) SPC_LAUNCH((topk_kernel<T, K, true>), dim3(rows), dim3(T), stream, io, k, keys, key_stride, idx_out, g);     \
-        else SPC_TOPK(T, K);                                                                                                     \
+    const bool many = many_candidates(n, k);
+#define SPC_TOPK_AT(T, K, C) SPC_LAUNCH((topk_kernel<T, K, false, C>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out, g)
+#define SPC_TOPK_LONG(K)                                    \
+    do {                                                    \
+        if (many) SPC_TOPK_AT(1024, K, kCandidatesMost);    \
+        else SPC_TOPK_AT(1024, K, kCandidates);             \
     } while (0)
-    if (small_wg && per_lane_256 <= 8) SPC_TOPK_GATHER(256, 8);
-    else if (small_wg && per_lane_256 <= 16) SPC_TOPK_GATHER(256, 16);
-    else if (small_wg) SPC_TOPK_GATHER(256, 32);
-    else if (per_lane <= 16) SPC_TOPK_GATHER(1024, 16);
-    else if (per_lane <= 24) SPC_TOPK_GATHER(1024, 24);
-    else if (per_lane <= 32) SPC_TOPK_GATHER(1024, 32);
-    else if (per_lane <= 40) SPC_TOPK_GATHER(1024, 40);
-    else if (per_lane <= 48) SPC_TOPK_GATHER(1024, 48);
+#define SPC_TOPK_GATHER(T, K, SELECT)                                                                                                    \
+    do {                                                                                                                         \
+        if (gather) SPC_LAUNCH((topk_kernel<T, K, true, kCandidates>), dim3(rows), dim3(T), stream, io, k, keys, key_stride, idx_out, g);     \
+        else SELECT;                                                                                                             \
+    } while (0)
+    if (small_wg && per_lane_256 <= 8) SPC_TOPK_GATHER(256, 8, SPC_TOPK_AT(256, 8, kCandidates));
+    else if (small_wg && per_lane_256 <= 16) SPC_TOPK_GATHER(256, 16, SPC_TOPK_AT(256, 16, kCandidates));
+    else if (small_wg) SPC_TOPK_GATHER(256, 32, SPC_TOPK_AT(256, 32, kCandidates));
+    else if (per_lane <= 16) SPC_TOPK_GATHER(1024, 16, SPC_TOPK_LONG(16));
+    else if (per_lane <= 24) SPC_TOPK_GATHER(1024, 24, SPC_TOPK_LONG(24));
+    else if (per_lane <= 32) SPC_TOPK_GATHER(1024, 32, SPC_TOPK_LONG(32));
+    else if (per_lane <= 40) SPC_TOPK_GATHER(1024, 40, SPC_TOPK_LONG(40));
+    else if (per_lane <= 48) SPC_TOPK_GATHER(1024, 48, SPC_TOPK_LONG(48));
     else if (gather) return hipErrorInvalidValue;     // selects_and_gathers: rows of one launch
-    else if (per_lane <= 64) SPC_TOPK(1024, 64);
+    else if (per_lane <= 64) SPC_TOPK_LONG(64);
     else return hipErrorInvalidValue;                // launch_topk splits such a row
-#undef SPC_TOPK
+#undef SPC_TOPK_AT
+#undef SPC_TOPK_LONG
 #undef SPC_TOPK_GATHER
     return hipGetLastError();
 }
@@ -511,8 +564,8 @@ hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_
 
 // One workgroup's registers hold 65536 keys, but with more than 48 a thread they are spilled, so rows beyond kTopkSingleLaunchKeys
 // are split into ranges of about kTopkPartKeys keys, as many as keep the candidate list of the second launch within
-// one workgroup's registers.  us, one launch / two: 32 x 45000, k = 64 9.8 / 16.1, 32 x 49152, k = 256 12.0 / 18.1, but 32 x 60000
-// 17.2 / 15.1 and 18.9 / 18.2.
+// one workgroup's registers.  us, one launch / two: 32 x 45000, k = 64 7.6 / 13.7, 32 x 49152, k = 256 9.7 / 16.5, but 32 x 59008
+// 16.8 / 13.5 and 18.3 / 16.0.
 constexpr int kTopkRegisterKeys = 65536, kTopkPartKeys = 16384, kTopkSingleLaunchKeys = 49152;
 
 int topk_parts(int Nq, int k) {
@@ -542,10 +595,10 @@ hipError_t launch_topk(int rows, int Nq, int k, const uint32_t* keys, size_t key
 // In one launch the selection's 4-byte list does not go through memory to a kernel of its own, which costs a boundary (2.4 us on a
 // side stream), a launch of the issuing thread (3 us) and the list's latency.  us a pass, two launches against one: 1 x 4096, 16 layers 280 /
 // 158 to 230 (bound by the issuing thread), 32 x 16k 337 / 308, 32 x 32k with k = 256 372 / 360, 1 bit 196 / 176, 24 x 5003 with 8 rows 255 / 246.
-// Not where a row takes two launches to select (8 x 131072: 387 / 394), nor with many rows: a row's workgroup keeps its place on a
+// Not where a row takes two launches to select (8 x 131072: 387 / 394) or the larger room for candidates, nor with many rows: a row's workgroup keeps its place on a
 // compute unit for as long as it fetches, and more reads are under way than the link wants: 128 rows 207 / 182, but 256 rows 172 /
 // 193 and 512 rows 176 / 223.
-bool selects_and_gathers(int rows, int Nq, int k) { return rows <= 128 && topk_parts(Nq, k) == 1; }
+bool selects_and_gathers(int rows, int Nq, int k) { return rows <= 128 && topk_parts(Nq, k) == 1 && !many_candidates(Nq, k); }
 
 hipError_t launch_select_gather(const LayerView& L, int Nq, const uint32_t* keys, size_t key_stride, int32_t* idx_out,
                                 uint16_t* slot, int32_t* slot_idx, bool link_shared, hipStream_t stream) {

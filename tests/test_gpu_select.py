@@ -44,7 +44,9 @@ def prompt(pattern, S, H, q):
 
 # positions at the edges of a workgroup's registers: 8, 16, 32 keys for each of 256 threads, 16 to 48 for each of 1024, two launches
 SIZES = [(64, 16), (64, 256), (320, 300), (2048, 64), (2080, 200), (4096, 256), (4128, 1), (8192, 128), (8224, 64), (8192, 257), (16384, 1024),
-         (16416, 64), (24576, 256), (32768, 64), (32800, 500), (40960, 256), (40992, 256), (49152, 256), (49184, 64), (70016, 64), (49152, 4096), (131072, 1024)]
+         (16416, 64), (24576, 256), (32768, 64), (32800, 500), (40960, 256), (40992, 256), (49152, 256), (49184, 64), (70016, 64), (49152, 4096), (131072, 1024),
+         # room for 2048 candidates and for 8192
+         (4096, 900), (4096, 1024), (8192, 1200), (8192, 2048), (16384, 1600), (16384, 4095), (24576, 4096), (32768, 2048), (40960, 3000), (70016, 4096)]
 PATTERNS = ["even", "one value", "few values", "binades apart", "one far above", "negative", "not numbers"]
 
 
