@@ -596,9 +596,14 @@ hipError_t launch_topk(int rows, int Nq, int k, const uint32_t* keys, size_t key
 // side stream), a launch of the issuing thread (3 us) and the list's latency.  us a pass, two launches against one: 1 x 4096, 16 layers 280 /
 // 158 to 230 (bound by the issuing thread), 32 x 16k 337 / 308, 32 x 32k with k = 256 372 / 360, 1 bit 196 / 176, 24 x 5003 with 8 rows 255 / 246.
 // Not where a row takes two launches to select (8 x 131072: 387 / 394) or the larger room for candidates, nor with many rows: a row's workgroup keeps its place on a
-// compute unit for as long as it fetches, and more reads are under way than the link wants: 128 rows 207 / 182, but 256 rows 172 /
-// 193 and 512 rows 176 / 223.
-bool selects_and_gathers(int rows, int Nq, int k) { return rows <= 128 && topk_parts(Nq, k) == 1 && !many_candidates(Nq, k); }
+// compute unit for as long as it fetches, and more reads are under way than the link wants: 128 rows 207 / 182, 160 rows 215 / 206, 192 rows
+// 296 / 290, but 256 rows 172 / 193 and 512 rows 176 / 223.  Nor many pairs of few rows: a compute unit by itself brings 13 GB/s of the
+// link's 57.  A step of layers over 16384 positions, us a layer, two launches against one: 1 row, k = 192 18.1 / 14.7, k = 512 23.5 / 29.2, k = 1024 28.7 / 40.5; 2 rows,
+// k = 256 22.4 / 24.4, k = 512 28.2 / 33.6; 3 rows, k = 256 24.7 / 26.3, k = 768 26.3 / 31.7; 4 rows, k = 384 21.0 / 22.3, k = 768 31.8 / 34.7; 6
+// rows, k = 1024 66.0 / 64.9.  The fetch alone: 1 row, k = 128 14.0 / 12.3, k = 192 14.9 / 14.5, k = 256 15.6 / 16.9.
+bool selects_and_gathers(int rows, int Nq, int k) {
+    return rows <= 128 && (rows >= 6 || k <= 192 || k <= 64 * (rows + 1)) && topk_parts(Nq, k) == 1 && !many_candidates(Nq, k);
+}
 
 hipError_t launch_select_gather(const LayerView& L, int Nq, const uint32_t* keys, size_t key_stride, int32_t* idx_out,
                                 uint16_t* slot, int32_t* slot_idx, bool link_shared, hipStream_t stream) {

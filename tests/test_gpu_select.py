@@ -88,3 +88,45 @@ def test_selected_positions_are_the_largest_keys(Nq, k):
         finally:
             torch.cuda.synchronize()
             sc.close()
+
+
+# rows x quantised positions x k around the rules of the launch that selects and fetches: 256 threads a row (from about 24 rows on) with 8, 16
+# and 32 keys a thread, 1024 threads, up to 128 rows; few rows with as many pairs as one launch takes, and one more; two launches
+@pytest.mark.parametrize("B,H,Nq,k", [(1, 24, 2048, 64), (3, 8, 2080, 256), (8, 8, 4096, 33), (3, 8, 4128, 200), (4, 32, 8192, 17), (2, 32, 8192, 128), (2, 32, 8224, 64),
+                                      (16, 8, 1024, 100), (43, 3, 1024, 16), (1, 33, 64, 256), (1, 1, 4096, 192), (1, 1, 4096, 193), (1, 3, 4096, 256), (1, 3, 4096, 257),
+                                      (1, 5, 4096, 385), (1, 6, 8192, 900), (1, 6, 4096, 1000)])
+def test_pairs_behind_the_selection_are_those_of_a_fetch_of_its_list(B, H, Nq, k):
+    import torch
+    S = Nq + 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Nq + k)
+    rand = lambda *shape: torch.randn(shape, device="cuda", generator=g).half()
+    sc = binding.SpeCache(2, B, H, H, 2, 32, (S + 63) // 64 * 64, k, synth.FP16, async_select=2)
+    side = [torch.cuda.Stream() for _ in range(2)]
+    idx = torch.full((2, 2, B, H, k), -7, dtype=torch.int32, device="cuda")
+    out = torch.empty((2, 2, B, H, 2, 128), dtype=torch.float32, device="cuda")
+    q = rand(2, B, H, 2, 128)
+    try:
+        for L in range(2):
+            sc.quantize_append(L, rand(B, H, S, 128), rand(B, H, S, 128), S)
+            assert sc.counts(L) == (S, Nq)
+        for rounds in range(2):              # (the second fetch on the other stream finds the link shared)
+            for L in range(2):
+                sc.score(L, q[L], 2)
+                sc.select_gather(L, idx[0, L], 0, side[L])
+                sc.select_gather(L, idx[1, L], -1, side[L])
+                sc.gather(L, idx[1, L], 1, side[L])
+                for slot in range(2):
+                    sc.attend(L, q[L], 2, None, None, slot, out[L, slot])
+            torch.cuda.synchronize()
+            sc.score(1, q[1], 2)
+            keys = keys_of(sc.debug_logits(1, 2)[:, :, 1])
+            for b in range(B):
+                for h in range(H):
+                    assert np.array_equal(idx[0, 1, b, h].cpu().numpy(), expected(keys[b, h], k)), (b, h)
+            assert torch.equal(idx[0], idx[1])
+            assert torch.equal(out[:, 0].view(torch.int32), out[:, 1].view(torch.int32)) and torch.isfinite(out).all()
+            idx.fill_(-7)
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
