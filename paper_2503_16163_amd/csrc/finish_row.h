@@ -31,8 +31,8 @@ __device__ __forceinline__ void finish_row(const AttendArgs& A, int row, int nq,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's stores have arrived
     __syncthreads();
     if (tid == 0) {
-        const bool last = __hip_atomic_fetch_add(F.arrived + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n - 1);
-        if (last) __hip_atomic_store(F.arrived + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        const bool last = __hip_atomic_fetch_add(F.arrived + row * kFinishStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n - 1);
+        if (last) __hip_atomic_store(F.arrived + row * kFinishStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
         fs.last = last;
     }
     __syncthreads();
@@ -57,8 +57,8 @@ __device__ __forceinline__ void finish_row(const AttendArgs& A, int row, int nq,
     load(q0);
     if (tid == 0 && F.word) {
         // every key of the row is stored: the scores are complete when all rows are
-        if (__hip_atomic_fetch_add(F.arrived + F.rows, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(F.rows - 1)) {
-            __hip_atomic_store(F.arrived + F.rows, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_fetch_add(F.arrived + F.rows * kFinishStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(F.rows - 1)) {
+            __hip_atomic_store(F.arrived + F.rows * kFinishStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(F.word, F.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }

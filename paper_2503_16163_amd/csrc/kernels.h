@@ -112,8 +112,11 @@ struct Announce {
     uint64_t* word = nullptr;
     uint64_t value = 0;
 };
-// The merge inside the launch that makes the partials (finish_row.h).  arrived: [rows + 1] counters, zero between launches; null:
-// a launch of its own merges.
+// The merge inside the launch that makes the partials (finish_row.h).  arrived: rows + 1 counters, zero between launches, each in a
+// cache line of its own (all of a launch's workgroups count at about the same time, and the additions to one line wait for each
+// other: attention alone over 16 x 31000 with one query row 19.4 us with the counters side by side, 10.9 so; 32 x 15800
+// 17.2 / 11.3; both passes over 32 x 15500 20.5 / 16.5); null: a launch of its own merges.
+constexpr int kFinishStride = 32;
 struct Finish {
     uint32_t* arrived = nullptr;
     float* out = nullptr;        // [rows][NR][128]
@@ -122,10 +125,12 @@ struct Finish {
     int rows = 0;
 };
 // Where the launch merges: a row's partials are few enough for one workgroup's loads to be requested at once (chunks x NR <= 64), and
-// the launch is no more than one round of workgroups.  A step of 8 layers, us a pass, merge in the launch against a launch of its own: 1
-// x 4096 (chunks x NR = 20) 260 / 320, 4 x 1500 x 2 sequences, 4 bits (12) 304 / 365, 8 x 9000 (40) 165 / 169, 16 x 8000 (34) 217 / 226, 32 x
-// 4000 (20) 230 / 242, 32 x 8000 (36, 576 workgroups) 246 / 264.  Beyond: 32 x 16k (70) 349 / 336; 8 query rows, 2 x 2000 (72) 168 /
-// 163; 16 query rows, 4 x 3000 (400) 246 / 173 (partials past the L2 cost more the more there are, and one workgroup reads them).
+// the launch is no more than one round of workgroups.  us, a launch of its own against the merge in the launch: both passes over 1 x
+// 4096 9.9 / 8.3, 16 x 15500 12.2 / 10.6, 32 x 15500 17.9 / 16.5, 128 x 3500 17.2 / 16.3, 512 x 480 18.4 / 17.3, 8 query rows over
+// 8 x 1700 11.7 / 10.5, 64 x 2000 16.6 / 16.6, 256 x 1000 27.0 / 19.5; attention alone with one query row over 1 x 31000 9.5 / 7.4,
+// 32 x 15800 12.5 / 11.3, 4 bits 64 x 4000 14.3 / 13.6.  Beyond (a step of 8 layers, us a pass, the counters side by side): 32 x 16k (70
+// partials) 336 / 349; 8 query rows, 2 x 2000 (72) 163 / 168; 16 query rows, 4 x 3000 (400) 173 / 246 (partials past the L2 cost
+// more the more there are, and one workgroup reads them).
 constexpr int kFinishMost = 64;
 inline bool merges_in_launch(int rows, int n_chunks, int NR) { return rows * n_chunks <= 1024 && n_chunks * NR <= kFinishMost; }
 

@@ -73,7 +73,7 @@ struct Layer {
     // Where scoring and attention are one call the merge of its partial results stores `scored_value` to the word `scored_word`, and the
     // selection's stream waits for that value: an event, pending as it always is when the selection is enqueued, costs
     // the issuing thread 10 us more (launch, event, wait, launch on the other stream: 19.7 us; with the word: 8.6).
-    uint32_t* arrived = nullptr;         // [rows + 1] counters of the merge inside a launch (finish_row.h), zero between launches
+    uint32_t* arrived = nullptr;         // [rows + 1][kFinishStride] counters of the merge inside a launch (finish_row.h), zero between launches
     uint64_t* scored_word = nullptr;     // signal memory, one word per layer (layers may be stepped on different streams)
     uint64_t scored_value = 0;
     bool scored_by_word = false;         // the layer's last scoring announced itself through the word, not idx_ready
@@ -529,7 +529,7 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         for (Layer& L : ctx->layers)
             for (int s = 0; s < 2; ++s) place(L.slot_idx[s], (size_t)rows * c.topk * 4);
         idx_end = used;
-        for (Layer& L : ctx->layers) place(L.arrived, ((size_t)rows + 1) * 4);
+        for (Layer& L : ctx->layers) place(L.arrived, ((size_t)rows + 1) * kFinishStride * 4);
         cleared_end = used;
         for (Layer& L : ctx->layers) {
             LayerView& v = L.view;
