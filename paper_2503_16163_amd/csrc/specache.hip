@@ -774,7 +774,7 @@ int specache_select_gather(specache_ctx* ctx, int32_t layer, int32_t* topk_idx_o
         SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[L.keys_reader_slot], 0));
     if (L.selected_pending && L.selected_stream != st) SPC_HIP(ctx, hipStreamWaitEvent(st, L.selected, 0));
     specache_ctx::SelectScratch* ss = nullptr;
-    if (ctx->select_scratch[0].s.max_parts > 1) {
+    if (topk_parts(L.keys_Nq, ctx->cfg.topk) > 1) {   // (a row of one launch needs none, and waits for nobody's)
         // the candidate arrays last used on this stream, else the set whose turn it is (after its last user)
         for (auto& c : ctx->select_scratch)
             if (c.used && c.stream == st) ss = &c;

@@ -42,7 +42,8 @@ def prompt(pattern, S, H, q):
     return K
 
 
-# positions at the edges of a workgroup's registers: 8, 16, 32 keys for each of 256 threads, 16 to 48 for each of 1024, two launches
+# positions at the edges of a workgroup's registers: 8, 16, 32 keys for each of 256 threads (in the launches that do not fetch; with so few rows
+# those that do have 1024), 16 to 48 for each of 1024, two launches
 SIZES = [(64, 16), (64, 256), (320, 300), (2048, 64), (2080, 200), (4096, 256), (4128, 1), (8192, 128), (8224, 64), (8192, 257), (16384, 1024),
          (16416, 64), (24576, 256), (32768, 64), (32800, 500), (40960, 256), (40992, 256), (49152, 256), (49184, 64), (70016, 64), (49152, 4096), (131072, 1024),
          # room for 2048 candidates and for 8192
@@ -127,6 +128,68 @@ def test_pairs_behind_the_selection_are_those_of_a_fetch_of_its_list(B, H, Nq, k
             assert torch.equal(idx[0], idx[1])
             assert torch.equal(out[:, 0].view(torch.int32), out[:, 1].view(torch.int32)) and torch.isfinite(out).all()
             idx.fill_(-7)
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
+
+
+def test_rows_of_one_launch_do_not_wait_for_candidate_arrays():
+    """A context with room for rows that take two launches has two sets of candidate arrays; while its rows are shorter, a selection
+    on a third stream uses neither, and must not wait for the fetches of the streams that did the first two."""
+    import torch
+    k, S = 64, 600
+    sc = binding.SpeCache(3, 1, 1, 1, 2, 32, 65536, k, synth.FP16, async_select=2)
+    idx = torch.full((3, k), -1, dtype=torch.int32, device="cuda")
+    kv = torch.randn((2, 1, 1, S, 128), device="cuda").half()
+    q = torch.randn((1, 1, 1, 128), device="cuda").half()
+
+    def event_on(stream, timing=False):
+        e = torch.cuda.Event(enable_timing=timing)
+        e.record(stream)
+        return e
+
+    try:
+        for L in range(3):
+            sc.quantize_append(L, kv[0], kv[1], S)
+            sc.score(L, q, 1)
+        held = [torch.cuda.Stream() for _ in range(2)]
+        torch.cuda._sleep(1000)
+        torch.cuda.synchronize()
+        begin = event_on(held[0], True)
+        with torch.cuda.stream(held[0]):
+            torch.cuda._sleep(1000000)
+        end = event_on(held[0], True)
+        torch.cuda.synchronize()
+        cycles = int(1000000 * 30.0 / max(begin.elapsed_time(end), 0.1))      # 30 ms
+
+        def hold():
+            for stream in held:
+                with torch.cuda.stream(stream):
+                    torch.cuda._sleep(cycles)
+
+        # streams share a few hardware queues: one whose work runs beside that of the held ones
+        free = None
+        for stream in [torch.cuda.Stream() for _ in range(8)]:
+            hold()
+            blocked = [event_on(s) for s in held]
+            event_on(stream).synchronize()
+            if not any(e.query() for e in blocked):
+                free = stream
+            torch.cuda.synchronize()
+            if free is not None:
+                break
+        if free is None:
+            pytest.skip("every stream shares a hardware queue with the held ones")
+        hold()
+        for L, stream in enumerate(held):
+            sc.select_gather(L, idx[L], 0, stream)
+        blocked = [event_on(s) for s in held]
+        sc.select_gather(2, idx[2], 0, free)
+        event_on(free).synchronize()
+        waited = any(e.query() for e in blocked)
+        torch.cuda.synchronize()
+        assert not waited
+        assert torch.equal(idx[0], idx[1]) and torch.equal(idx[0], idx[2]) and (idx >= 0).all()
     finally:
         torch.cuda.synchronize()
         sc.close()
