@@ -7,8 +7,9 @@
 //
 // Split over the sequence: "main" workgroups take chunks of quantised positions,
 // "extra" workgroups take the 16-bit candidates (staged pairs, residual, transient
-// pair); each writes an un-normalised partial (max, sum, sum p*V) and a combine
-// kernel merges them with the usual log-sum-exp rescaling.  Prefetched positions
+// pair); each writes an un-normalised partial (max, sum, sum p*V), merged with the usual
+// log-sum-exp rescaling by the workgroup that completes the row (finish_row.h) where the
+// partials are few, else by a combine kernel.  Prefetched positions
 // are removed from the main chunks by setting their logit to -inf in LDS; the
 // staged pair then enters through the extra chunks, which is Eq. 1's "replace".
 //
@@ -26,9 +27,14 @@ namespace {
 
 constexpr int kMainChunk = 512;   // quantised positions per workgroup
 
-// 72 registers, seven waves per SIMD (50 and eight without the 16-bit chunk's loads in flight: level at 32 x 32000 and 32 x 100000)
-template <int BITS, int GROUP, int G, int NROWS, bool BF16>
-__global__ __launch_bounds__(kThreads, 7) void attend_partial_kernel(LayerView L, AttendArgs A) {
+// MERGES: rows short enough for the merge inside the launch (merges_in_launch), where few workgroups wait for the 16-bit chunk's chain of
+// loads: it asks for 14 values with the keys (with 16, one instance spills a register) and the kernel takes 72 registers.  Longer rows fill the
+// chip and are bound by vector issue: eight waves per SIMD (64 registers), no code and no arguments of the merge, the 16-bit chunks last.
+// Attention with one query row, us (the kernel before the merge was there, one kernel of 72 registers for both with scalar ones spilled, now):
+// 1 bit, g = 128, 16 x 60000 11.7, 13.1, 11.5; 16 x 65000 12.4, 13.4, 12.9; 8 x 131000 12.0, 13.8, 12.8; g = 32, 32 x 32300 14.0, 16.2, 14.6; 2
+// bits, 16 x 65000 13.5, 15.1, 13.9.
+template <int BITS, int GROUP, int G, int NROWS, bool BF16, bool MERGES>
+__global__ __launch_bounds__(kThreads, MERGES ? 7 : 8) void attend_partial_kernel(LayerView L, AttendArgs A) {
     constexpr int NR = G * NROWS;
     constexpr int CH = kMainChunk;
     constexpr int M = kD / GROUP;            // value groups per token
@@ -48,7 +54,7 @@ __global__ __launch_bounds__(kThreads, 7) void attend_partial_kernel(LayerView L
     constexpr int kExtra = extra_chunk_floats(NR);
     constexpr int kMax1 = kExtra > kPs ? kExtra : kPs;
     constexpr int kMax2 = kMax1 > kOl ? kMax1 : kOl;
-    constexpr int kRegion = kMax2 * 4 > kFinishLdsBytes ? kMax2 : kFinishLdsBytes / 4;
+    constexpr int kRegion = !MERGES || kMax2 * 4 > kFinishLdsBytes ? kMax2 : kFinishLdsBytes / 4;
     __shared__ __attribute__((aligned(16))) float smem[kRegion];
     __shared__ float red[kWaves * NR * (1 + M)];
     __shared__ float red_sum[kWaves * NR];
@@ -61,21 +67,25 @@ __global__ __launch_bounds__(kThreads, 7) void attend_partial_kernel(LayerView L
     float* o_lds = smem;                     // [kWaves][NR][128]
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    // The 16-bit chunks are chains of dependent loads: they are dispatched first (all rows), the
-    // quantised chunks after them.
+    // The 16-bit chunks are chains of dependent loads.  Where the whole launch is resident at once (MERGES) they are dispatched first (all
+    // rows).  Where it is not they go last: first, the many rows' chunks wait together while the chip has nothing else to do (one query row,
+    // 2 bits, g = 32, scoring and attention: 512 x 2000 37.1 us, last 35.6; 256 x 4000 34.9 / 33.8; 16 x 60000 31.8 / 31.2).
     const int n_extra = A.n_chunks - A.n_main, rows = L.rows;
+    const int id = blockIdx.x, n_first = rows * (MERGES ? n_extra : A.n_main);
     int row, chunk;
-    if ((int)blockIdx.x < rows * n_extra) {
-        row = blockIdx.x / n_extra;
-        chunk = A.n_main + blockIdx.x % n_extra;
+    if ((id < n_first) == MERGES) {
+        const int x = MERGES ? id : id - n_first;
+        row = x / n_extra;
+        chunk = A.n_main + x % n_extra;
     } else {
-        const int id = blockIdx.x - rows * n_extra;
-        row = id / A.n_main;
-        chunk = id % A.n_main;
+        const int m = MERGES ? id - n_first : id;
+        row = m / A.n_main;
+        chunk = m % A.n_main;
     }
     float m_row[NR], l_row[NR];
-    const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4);
-    const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
+    // (built where they are used: held from here on they took scalar registers that the main chunk's arguments were spilled for)
+    auto part_o = [&]() { return buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4); };
+    auto part_ml = [&]() { return buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8); };
 
     if (chunk < A.n_main) {
         // ------------------------------------------------------------ quantised positions
@@ -269,32 +279,32 @@ __global__ __launch_bounds__(kThreads, 7) void attend_partial_kernel(LayerView L
                 for (int r = 0; r < NR; ++r) o_lds[((size_t)wave * NR + r) * kD + Lc * CPB + j] = acc[j][r];
         }
         __syncthreads();
+        const auto po = part_o();
         for (int e = tid; e < NR * kD; e += kThreads) {
             const int r = e / kD, c = e % kD;
             float v = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) v += o_lds[((size_t)w * NR + r) * kD + c] + red_z[(w * NR + r) * M + c / GROUP];
-            store_partial(po, e, v, A.fin.arrived != nullptr);
+            store_partial(po, e, v, MERGES);
+        }
+        if (tid < NR) {
+            float mv = 0.f, lv = 0.f;
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (r == tid) { mv = m_row[r]; lv = l_row[r]; }
+            store_max_sum(part_ml(), tid, mv, lv, MERGES);
         }
     } else {
-        extra_chunk<NR, NROWS, BF16, 16>(L, A, row, chunk, smem, xout, po, pml);
+        extra_chunk<NR, NROWS, BF16, MERGES ? 14 : 0>(L, A, row, chunk, smem, xout, part_o(), part_ml(), MERGES);
     }
-    if (chunk < A.n_main && tid < NR) {
-        float mv = 0.f, lv = 0.f;
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-            if (r == tid) { mv = m_row[r]; lv = l_row[r]; }
-        store_max_sum(pml, tid, mv, lv, A.fin.arrived != nullptr);
-    }
-    if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
+    if constexpr (MERGES) finish_row(A, row, NR, smem, fin_shared);
 }
 
 // Merge the chunk partials of one (KV head, query row): o = sum_c o_c e^(m_c - m) / sum_c l_c e^(m_c - m).
 // 1024 threads = 16 slices of the chunk list x 64 channel pairs; the chunk weights are
 // computed once into LDS so that the partial-output loads are independent of each other.
-// (Folding this into the partial kernel behind a "last workgroup" counter needs a
-// device-scope fence in every workgroup, which writes back and invalidates the L2 of
-// its XCD; measured, that made the kernel eight times slower than this extra launch.)
+// Takes the rows beyond merges_in_launch (kernels.h), whose partials are more than one workgroup
+// requests at once, and the calls that bring scratch memory of their own.
 constexpr int kCombineMaxChunks = 1280;
 constexpr int kCombineThreads = 1024, kCombineSlices = kCombineThreads / 64;
 __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(const float* __restrict__ part_o,
@@ -395,10 +405,14 @@ hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* 
     if (A.n_main + n_extra > kCombineMaxChunks) return hipErrorInvalidValue;
     if (phases & kAttendPartial) {
         const dim3 grid((A.n_main + n_extra) * L.rows), block(kThreads);
-        if (L.bf16)
-            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, true>), grid, block, stream, L, A);
+        if (L.bf16 && A.fin.arrived)
+            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, true, true>), grid, block, stream, L, A);
+        else if (L.bf16)
+            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, true, false>), grid, block, stream, L, A);
+        else if (A.fin.arrived)
+            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, false, true>), grid, block, stream, L, A);
         else
-            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, false>), grid, block, stream, L, A);
+            SPC_LAUNCH((attend_partial_kernel<BITS, GROUP, G, NROWS, false, false>), grid, block, stream, L, A);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

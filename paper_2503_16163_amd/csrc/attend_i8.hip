@@ -474,7 +474,7 @@ __global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i
     const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
 
     if (chunk >= A.n_main) {
-        extra_chunk<NR, 2, BF16, FUSED ? 32 : BITS == 1 ? 16 : 0>(L, A, row, chunk, smem, xout, po, pml);
+        extra_chunk<NR, 2, BF16, FUSED ? 32 : BITS == 1 ? 16 : 0>(L, A, row, chunk, smem, xout, po, pml, A.fin.arrived != nullptr);
         if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
         return;
     }

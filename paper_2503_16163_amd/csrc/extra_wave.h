@@ -209,7 +209,7 @@ __host__ __device__ constexpr int extra_chunk_floats(int NR) {
 }
 template <int NR, int NROWS, bool BF16, int AHEAD, typename Buffer>
 __device__ __forceinline__ void extra_chunk(const LayerView& L, const AttendArgs& A, int row, int chunk, float* smem, RowsOut& out, Buffer po,
-                                            Buffer pml) {
+                                            Buffer pml, bool past_l2) {
     static_assert(NR <= 2 && (NR * kExtraQStride / 2) % 4 == 0, "a thread per output");
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     uint16_t* qraw = reinterpret_cast<uint16_t*>(smem);
@@ -231,8 +231,8 @@ __device__ __forceinline__ void extra_chunk(const LayerView& L, const AttendArgs
             if (e != 0.0f) o = __builtin_fmaf(e, smem[(w * NR + r) * kRowsOStride + c], o);
             sum = __builtin_fmaf(e, out.l[w][r], sum);
         }
-        store_partial(po, r * kD + c, o, A.fin.arrived != nullptr);
-        if (c == 0) store_max_sum(pml, r, mx, sum, A.fin.arrived != nullptr);
+        store_partial(po, r * kD + c, o, past_l2);
+        if (c == 0) store_max_sum(pml, r, mx, sum, past_l2);
     }
 }
 

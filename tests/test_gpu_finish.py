@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
     (8, 2, 1700, 2, 32, 48, 2, True), (8, 2, 1990, 2, 64, 48, 2, True), (8, 2, 1700, 1, 32, 48, 2, False), (8, 1, 340, 2, 32, 48, 2, True),
     (8, 1, 600, 2, 32, 48, 2, True), (4, 4, 1500, 4, 32, 32, 2, False), (4, 2, 900, 2, 32, 200, 2, True), (2, 2, 1500, 4, 64, 16, 1, False),
     # as many workgroups as the rule takes, 1024, and one more row of them
-    (32, 32, 15700, 2, 32, 64, 1, False), (32, 32, 15700, 2, 64, 64, 2, True), (33, 33, 15700, 2, 64, 64, 2, True), (16, 16, 31600, 1, 64, 64, 1, False)])
+    (32, 32, 15700, 2, 32, 64, 1, False), (32, 32, 15700, 2, 64, 64, 2, True), (33, 33, 15700, 2, 64, 64, 2, True), (16, 16, 31600, 1, 64, 64, 1, False),
+    # one query row beyond the rule by its workgroups and by its partials, two heads of one row likewise
+    (33, 33, 15700, 2, 32, 64, 1, False), (1, 1, 33000, 2, 64, 300, 1, False), (4, 2, 16400, 1, 128, 40, 1, False)])
 def test_merge_in_the_launch(Hq, Hkv, S, bits, g, k, n_rows, one_pass):
     from tests.harness import Case
     # the speculative flow with two query rows, the non-speculative one with one
