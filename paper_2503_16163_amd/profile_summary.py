@@ -37,7 +37,7 @@ def short_name(full):
     name, targs = m.group(1), (m.group(3) or "")
     if name == "attend_i8_kernel" and targs.replace(" ", "").endswith("true"):
         return name + "+score"
-    if name == "topk_kernel" and targs.replace(" ", "").endswith("true"):
+    if name == "topk_kernel" and targs.replace(" ", "").split(",")[2:3] == ["true"]:   # threads, keys of a thread, whether it fetches, ...
         return name + "+gather"
     if name == "rows_kernel":   # the last template argument is the mode: 0 both passes, 1 scoring, 2 attention
         return name + {"0": "+score", "2": "<attention>"}.get(targs.replace(" ", "").split(",")[-1], "")

@@ -125,5 +125,9 @@ def test_kernel_source_hash_follows_the_kernels_own_sources():
     full = "void specache::(anonymous namespace)::attend_i8_kernel<32, 2, false, true>(specache::LayerView, specache::(anonymous namespace)::AttendArgs, float, unsigned int*, unsigned long)"
     assert profile_summary.short_name(full) == "attend_i8_kernel+score"
     assert profile_summary.short_name(full.replace("false, true>", "false, false>")) == "attend_i8_kernel"
+    # topk_kernel<threads, keys of a thread, fetches, candidates>
+    full = "void specache::(anonymous namespace)::topk_kernel<1024, 16, true, 2048>(specache::TopkIo, int)"
+    assert profile_summary.short_name(full) == "topk_kernel+gather"
+    assert profile_summary.short_name(full.replace("true", "false").replace("2048", "8192")) == "topk_kernel"
     assert profile_summary.short_name("void at::native::vectorized_elementwise_kernel<4>(int)") is None
     assert profile_summary.short_name("__amd_rocclr_copyBuffer") == profile_summary.COPY_KERNEL
