@@ -437,7 +437,8 @@ __device__ __forceinline__ void chunk_bitmap(const AttendArgs& A, int topk, int 
 // Registers: the pass that also scores needs 90 to 94 (five waves per SIMD); compiled for six or eight it
 // spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
 // codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
-// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).
+// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).  In groups
+// of 64 and 128 the conditional loads of value_loads go through 32 bytes of scratch a lane.
 template <int GROUP, int BITS, bool BF16, bool FUSED>
 __global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
                                                              size_t key_stride) {

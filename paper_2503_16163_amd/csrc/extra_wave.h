@@ -1,7 +1,9 @@
 // One wave's share of the 16-bit candidates of the mixed attention of Eq. 1 (staged pairs, residual, the speculative
 // token's transient pair): 32 of them, the keys times the queries on the matrix cores in the cache's own type, the values on
-// the vector ALUs.  Every load of the wave is requested before the first wait on any of them, because the chain of
-// dependent steps, not the arithmetic, is what this chunk of a launch takes: a workgroup of 128 candidates
+// the vector ALUs.  The chain of dependent loads, not the arithmetic, is what this chunk of a launch takes: the index list, the
+// keys (the first 16 bytes of either tile are waited for by themselves, being loads behind a condition), then the values
+// (AHEAD of them with the keys).  The addresses come from several buffers, so that keys and values are flat loads, which
+// also hold back the reads of the queries from LDS.  A workgroup of 128 candidates
 // that went from barrier to barrier, its values requested in batches of 8 behind the softmax, took 10.8 us alone
 // with two query rows and was the last to end in a launch over 32 rows x 16384 positions (16.0 of 16.6 us); a wave each
 // takes 4.6 us alone (that kernel over 1 x 4096 positions: 10.8 -> 5.4 us) and 11.2 there.  In the kernels of attention alone, us a

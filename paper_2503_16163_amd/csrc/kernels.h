@@ -106,8 +106,10 @@ struct AttendScratch {
     int max_chunks;
 };
 enum { kAttendPartial = 1, kAttendCombine = 2 };   // which of the two launches launch_attend issues
-// A 64-bit word that other streams wait on (hipStreamWaitValue64): the merge kernel (else finish_row) stores value there as it starts, i.e.
-// when the launch in front of it on its stream has completed.  word == null: nothing to announce.
+// A 64-bit word that other streams wait on (hipStreamWaitValue64).  The merge kernel stores value there as it starts, i.e. when
+// the launch in front of it on its stream has completed.  finish_row stores it from inside the launch that scores: by then
+// the selection keys of every row are stored and its chunks have read all they read, but the outputs and the pair that the launch
+// appends need not have landed, and what reads those goes behind the launch by an event.  word == null: nothing to announce.
 struct Announce {
     uint64_t* word = nullptr;
     uint64_t value = 0;

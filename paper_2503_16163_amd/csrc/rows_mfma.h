@@ -28,10 +28,11 @@
 // loads requested together and a merge of the waves that reads 16 bytes at a time, 0.8 us instead of 2.5 to 2.8): 32 KV rows x 32768 tokens, 8 query rows, 2 bits, g = 64: 27.5 +
 // 37.9 -> 37.2 -> 33.5 us; 8 x 131072, 1 bit, g = 32: 33.1 + 43.9 -> 43.2 -> 39.6 us; 24 x 5003, 2 bits, g = 32: 8.5 + 24.8 -> 13.0
 // at best -> 10.3 at best, 12.3 beside the gathers; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 17.0 -> 13.6 us.  4-bit codes,
-// two launches, 32 x 16384, 2 query rows as 8 columns' worth, g = 32: scoring 14.0, attention 17.6 us at best, 16.0 and 21.5 beside
+// two launches, 32 x 16384, 2 query rows as 8 columns' worth, g = 32: scoring 13.9, attention with its merge 18.9 us at best, 16.0 and 21.4 beside
 // the gathers (the 84 MB they read need 14 us at the rate of a plain read); a decode step of a layer 70.7 -> 51 us against
 // vector-ALU kernels.
-// Up to 168 registers, three workgroups per compute unit; held to four it spills.
+// Up to 168 registers, three workgroups per compute unit; held to four it spills (as it is, both passes in groups of 32 with 8 columns' worth of
+// rows spill two registers with 2 bits, one with 1 bit where rows are missing).
 #pragma once
 #include "attend_common.h"
 #include "extra_wave.h"

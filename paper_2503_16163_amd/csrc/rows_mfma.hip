@@ -43,8 +43,8 @@ bool rows_uses_matrix_cores(const LayerView& L, int n_rows) {
     return NR >= 4 || L.bits == 4;
 }
 
-// 4-bit codes keep two launches: a step's arrangement scores and attends in two calls there, and the one launch would not
-// leave the logits for a later specache_attend.
+// 4-bit codes keep two launches because no instance of the one launch is built for them: a step's arrangement scores and
+// attends in two calls there.
 bool rows_in_one_launch(const LayerView& L, int n_rows) { return L.bits != 4 && rows_uses_matrix_cores(L, n_rows); }
 
 int rows_max_main_chunks(int rows, int max_seq) {

@@ -496,8 +496,8 @@ int specache_create(const specache_config* cfg, specache_ctx** out) {
         SPC_ALLOC(hipStreamCreateWithFlags(&ctx->select_stream, hipStreamNonBlocking));
         SPC_ALLOC(hipEventCreateWithFlags(&ctx->scored, kOrderEventFlags));
     }
-    // One allocation for the device's buffers: a context of two layers has 34 buffers, whose hipMalloc and hipFree took 75
-    // of the 135 us of its creation and as many of closing it.  The pass without a base adds the sizes up.
+    // One allocation for the device's buffers: a context of two layers has 27 (33 where a row may take two launches to select), whose
+    // hipMalloc and hipFree took 75 of the 135 us of its creation and as many of closing it.  The pass without a base adds the sizes up.
     ctx->logit_stride = cap;
     int max_main = 0;
     for (int n = 1; n <= 2; ++n) {

@@ -612,7 +612,8 @@ hipError_t launch_select_gather(const LayerView& L, int Nq, const uint32_t* keys
     // attention kernels beside the fetch.  Steps of several layers, us a pass with 32, 64, 96, 128, 256 KB (two fetches
     // sharing the link): 32 rows x 16k, k = 64: 267, 241, 230, 241, 275; 32 x 32k, k = 256: 451, 387, 370, 367, 400; 32 x 32k, 1
     // bit: 191, 166, 162, 166, 172; 32 x 32k, 8 query rows: 137, 119, 119, 122, 128.  A caller with one fetch at a time gets what
-    // gather_kernel (gather.hip) gives it: more the fewer keys are scored for a fetched pair.
+    // gather_kernel (gather.hip) gives it: more the fewer keys are scored for a fetched pair.  (launch_ranges rounds a lane's reads down to a
+    // power of two: 96 KB are 64 for 1, 2 and 4 rows.)
     const double keys_per_pair = (double)L.G * Nq / L.topk;
     const int total_kb = link_shared ? 96 : keys_per_pair >= 384.0 ? 128 : keys_per_pair >= 192.0 ? 192 : 256;
     const GatherIo g{(const uint4*)L.host, (uint4*)slot, slot_idx, L.max_seq, 0, 0};
