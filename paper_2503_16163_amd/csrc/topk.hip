@@ -16,7 +16,8 @@
 //   3. the handful of keys in that bin are ranked by one wave (larger key first, then lower position), which decides for
 //      each of them at once, ties included; the selected positions are bits of a bitmap, whose order is the output's.
 // Larger k has room for more candidates and takes maxima of two (many_candidates); where k is a quarter of the row or more a
-// floor would leave too few keys out, and the histograms are of all keys.
+// floor would leave too few keys out, and the histograms are of all keys; so they are of short rows where k asks for most of the
+// maxima (no_floor).
 // Where the boundary bin is crowded (many equal or almost equal scores) the candidates go on by themselves, with histograms
 // inside the range left; a row with more candidates than there is room for does so with all its keys.  Both leave two
 // bitmaps, the keys above tau and those equal to it, which one ordered pass writes out.
@@ -113,6 +114,7 @@ struct TopkIo {
     const int32_t* map;      // [rows][map_stride] or null
     size_t map_stride;
     uint32_t* key_out;       // [rows * parts][k] or null
+    bool all_keys = false;   // no_floor; for the launch to set
 };
 
 // Pre-fetch(C_K) behind the selection (GATHER): the row's pairs from the pinned host store into the staging slot.
@@ -246,8 +248,9 @@ __global__ __launch_bounds__(THREADS) void topk_kernel(TopkIo io, int k, const u
         uint32_t floor_key = 1u;                   // fewer maxima than keff: no floor
         uint32_t n = 0xFFFFFFFFu;                  // candidates; uniform, as everything that decides on the way is
         // (us with a floor against all keys: 32 x 4096, k = 2048 16.9 / 8.6; 32 x 8192, k = 2048 9.9 / 11.8, k = 3000 13.2 / 12.0, k = 4096
-        // 20 / 9.9; 32 x 16384, k = 4096 12.4 / 13.4, but with 64 values in the row 17.5 / 14)
-        const bool all_keys = CAND > kCandidates && 4 * keff >= Nq;
+        // 20 / 9.9; 32 x 16384, k = 4096 12.4 / 13.4, but with 64 values in the row 17.5 / 14.)
+        // (fewer candidates: no_floor)
+        const bool all_keys = CAND > kCandidates ? 4 * keff >= Nq : KPT <= 16 && io.all_keys;
         if (!all_keys) {
             count_maxima(bins[0], top_lo, kTopShift);
             __syncthreads();
@@ -516,9 +519,19 @@ bool many_candidates(int n, int k) {
     return n * (p < 1.0 ? 1.0 - std::sqrt(std::sqrt(1.0 - p)) : 1.0) > 0.85 * kCandidates;
 }
 
+// Where the short way of few candidates is no use.  A floor needs more than k maxima above zero, and one of `per` scores of either sign is with a
+// chance of 1 - 2^-per; short of that it lies among small scores, binades wide, and its pass over the keys is for nothing.  us with a floor /
+// with all keys: 32 x 256, k = 104 5.6 / 4.8, k = 156 9.6 / 4.8, k = 234 11.6 / 5.3; 32 x 640, k = 171 5.6 / 6.3, k = 198 10.8 / 6.3; 32 x 960, k = 220 6.0 / 5.8,
+// k = 249 11.3 / 5.8, k = 384 7.5 / 9.2, k = 576 13.2 / 9.2; 32 x 1440, k = 438 7.0 / 9.4, k = 584 13.6 / 9.4.
+bool no_floor(int n, int k, int threads) {
+    const int of_a_thread = (n + threads - 1) / threads, most = 2 * k > threads ? 4 : 31;
+    const int per = of_a_thread < most ? of_a_thread : most;
+    return 16.0 * per * k > 15.0 * (n - (n >> per));
+}
+
 // one launch over `rows * io.parts` ranges of at most n keys each; gather: and the fetch behind it (gather_kb: KB of a row's pairs
 // under way at a time)
-hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_t* keys, size_t key_stride,
+hipError_t launch_ranges(int rows, int n, TopkIo io, int k, const uint32_t* keys, size_t key_stride,
                          int32_t* idx_out, hipStream_t stream, const GatherIo* gather = nullptr, int gather_kb = 0) {
     const int per_lane_256 = (n + 255) / 256, per_lane = (n + 1023) / 1024;   // keys per lane held in registers
     GatherIo g = gather ? *gather : GatherIo{};
@@ -532,6 +545,7 @@ hipError_t launch_ranges(int rows, int n, const TopkIo& io, int k, const uint32_
         g.reads = reads >= 8 ? 8 : reads >= 4 ? 4 : reads >= 2 ? 2 : 1;
     }
     const bool many = many_candidates(n, k);
+    io.all_keys = no_floor(n, k, small_wg ? 256 : 1024);
 #define SPC_TOPK_AT(T, K, C) SPC_LAUNCH((topk_kernel<T, K, false, C>), dim3(rows * io.parts), dim3(T), stream, io, k, keys, key_stride, idx_out, g)
 #define SPC_TOPK_LONG(K)                                    \
     do {                                                    \

@@ -47,7 +47,9 @@ def prompt(pattern, S, H, q):
 SIZES = [(64, 16), (64, 256), (320, 300), (2048, 64), (2080, 200), (4096, 256), (4128, 1), (8192, 128), (8224, 64), (8192, 257), (16384, 1024),
          (16416, 64), (24576, 256), (32768, 64), (32800, 500), (40960, 256), (40992, 256), (49152, 256), (49184, 64), (70016, 64), (49152, 4096), (131072, 1024),
          # room for 2048 candidates and for 8192
-         (4096, 900), (4096, 1024), (8192, 1200), (8192, 2048), (16384, 1600), (16384, 4095), (24576, 4096), (32768, 2048), (40960, 3000), (70016, 4096)]
+         (4096, 900), (4096, 1024), (8192, 1200), (8192, 2048), (16384, 1600), (16384, 4095), (24576, 4096), (32768, 2048), (40960, 3000), (70016, 4096),
+         # a large share of a short row: a floor, or all keys at once
+         (256, 104), (256, 156), (256, 255), (448, 157), (448, 158), (640, 198), (960, 211), (960, 249), (960, 384), (960, 576), (1440, 584), (2048, 512)]
 PATTERNS = ["even", "one value", "few values", "binades apart", "one far above", "negative", "not numbers"]
 
 
