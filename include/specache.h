@@ -382,6 +382,14 @@ enum { SPECACHE_SCORE_ON_VECTOR_ALU = 1, SPECACHE_ATTEND_ON_VECTOR_ALU = 2,
 int specache_debug_kernel_choice(int32_t flags);
 
 /*
+ * Test hook, process-wide: how often a workgroup that merges a share of a row's partial results inside the launch
+ * that makes them looks whether they are all there before it leaves the share to the last one that makes
+ * any (same results).  0: it leaves it at once; -1: the default.  Takes effect for calls made afterwards.
+ * Errors: EINVAL (below -1).
+ */
+int specache_debug_merger_polls(int32_t polls);
+
+/*
  * Measurement hook.  While enabled, every hot call brackets each of its kernel
  * phases with a pair of HIP events on the stream the phase is launched on.
  * specache_timing synchronises the device, adds up the elapsed time of all

@@ -18,7 +18,7 @@ _NAMES = {EINVAL: "EINVAL", ECAPACITY: "ECAPACITY", ENOMEM: "ENOMEM", EHIP: "EHI
 EXPORTS = ["specache_create", "specache_destroy", "specache_last_error", "specache_counts",
            "specache_plan_append", "specache_quantize_append", "specache_score_topk", "specache_gather",
            "specache_score", "specache_select_gather", "specache_append_score",
-           "specache_attend", "specache_score_attend", "specache_append_score_attend", "specache_decode_step", "specache_attend_static", "specache_debug_poison_slot", "specache_debug_fail_alloc", "specache_debug_scored_by_word", "specache_order_by_events", "specache_debug_kernel_choice", "specache_export_quantized", "specache_export_rows", "specache_debug_logits",
+           "specache_attend", "specache_score_attend", "specache_append_score_attend", "specache_decode_step", "specache_attend_static", "specache_debug_poison_slot", "specache_debug_fail_alloc", "specache_debug_scored_by_word", "specache_order_by_events", "specache_debug_kernel_choice", "specache_debug_merger_polls", "specache_export_quantized", "specache_export_rows", "specache_debug_logits",
            "specache_timing", "specache_measure_hbm_read", "specache_measure_link"]
 
 
@@ -70,6 +70,7 @@ def lib():
         L.specache_decode_step.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, vp, vp, vp, i32, vp]
         L.specache_debug_poison_slot.argtypes = [vp, i32, i32, vp]
         L.specache_debug_kernel_choice.argtypes = [i32]
+        L.specache_debug_merger_polls.argtypes = [i32]
         L.specache_debug_fail_alloc.argtypes = [i32]
         L.specache_debug_scored_by_word.argtypes = [vp, i32, C.POINTER(i32)]
         L.specache_order_by_events.argtypes = [vp, i32]
@@ -128,6 +129,13 @@ def debug_kernel_choice(flags):
     rc = lib().specache_debug_kernel_choice(flags)
     if rc != OK:
         raise SpeCacheError(rc, "debug_kernel_choice: unknown flag")
+
+
+def debug_merger_polls(polls):
+    """Process-wide: looks of a merging workgroup before it leaves its share to the last chunk (0: at once, -1: the default)."""
+    rc = lib().specache_debug_merger_polls(polls)
+    if rc != OK:
+        raise SpeCacheError(rc, "debug_merger_polls: below -1")
 
 
 def measure_hbm_read(nbytes=1 << 30, reps=10):

@@ -27,7 +27,7 @@ namespace {
 
 constexpr int kMainChunk = 512;   // quantised positions per workgroup
 
-// MERGES: rows short enough for the merge inside the launch (merges_in_launch), where few workgroups wait for the 16-bit chunk's chain of
+// MERGES: rows short enough for the merge inside the launch (last_chunk_merges), where few workgroups wait for the 16-bit chunk's chain of
 // loads: it asks for 14 values with the keys (with 16, one instance spills a register) and the kernel takes 72 registers.  Longer rows fill the
 // chip and are bound by vector issue: eight waves per SIMD (64 registers), no code and no arguments of the merge, the 16-bit chunks last.
 // Attention with one query row, us (the kernel before the merge was there, one kernel of 72 registers for both with scalar ones spilled, now):
@@ -297,14 +297,22 @@ __global__ __launch_bounds__(kThreads, MERGES ? 7 : 8) void attend_partial_kerne
     } else {
         extra_chunk<NR, NROWS, BF16, MERGES ? 14 : 0>(L, A, row, chunk, smem, xout, part_o(), part_ml(), MERGES);
     }
-    if constexpr (MERGES) finish_row(A, row, NR, smem, fin_shared);
+    if constexpr (MERGES) merge_shares<8>(A, row, NR, row_arrival(A, row, fin_shared), smem);
+}
+
+// The merge of merge_rows (finish_row.h) in a launch of its own, a workgroup per share: for calls that bring scratch memory of their own
+// (the sums are then those of the merge inside a launch, bit by bit) and what last_chunk_merges (kernels.h) leaves.
+__global__ __launch_bounds__(kThreads) void attend_merge_kernel(AttendArgs A, int NR, Announce announce) {
+    if (announce.word && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(announce.word, announce.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __shared__ __attribute__((aligned(16))) float lds[kFinishLdsBytes / 4];
+    merge_rows<16>(A, blockIdx.x / A.fin.shares, NR, blockIdx.x % A.fin.shares, __builtin_ctz(NR / A.fin.shares), lds);
 }
 
 // Merge the chunk partials of one (KV head, query row): o = sum_c o_c e^(m_c - m) / sum_c l_c e^(m_c - m).
 // 1024 threads = 16 slices of the chunk list x 64 channel pairs; the chunk weights are
 // computed once into LDS so that the partial-output loads are independent of each other.
-// Takes the rows beyond merges_in_launch (kernels.h), whose partials are more than one workgroup
-// requests at once, and the calls that bring scratch memory of their own.
+// Takes the rows of more than kFinishChunks chunks (kernels.h).
 constexpr int kCombineMaxChunks = 1280;
 constexpr int kCombineThreads = 1024, kCombineSlices = kCombineThreads / 64;
 __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(const float* __restrict__ part_o,
@@ -399,6 +407,19 @@ __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(const f
     }
 }
 
+// the merge that no launch has done
+hipError_t launch_merge(const LayerView& L, AttendArgs A, int NR, float* out, Announce announce, hipStream_t stream) {
+    if (A.n_chunks > kFinishChunks) {
+        SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, A.part_o, A.part_ml, A.max_chunks, A.n_chunks, NR, out, announce);
+    } else {
+        A.fin = Finish{};
+        A.fin.out = out;
+        A.fin.shares = merge_shares_of(A.n_chunks, NR);
+        SPC_LAUNCH(attend_merge_kernel, dim3(L.rows * A.fin.shares), dim3(kThreads), stream, A, NR, announce);
+    }
+    return hipGetLastError();
+}
+
 template <int BITS, int GROUP, int G, int NROWS>
 hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* out, int phases, Announce announce, hipStream_t stream) {
     constexpr int NR = G * NROWS;
@@ -416,10 +437,8 @@ hipError_t launch3(const LayerView& L, const AttendArgs& A, int n_extra, float* 
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if ((phases & kAttendCombine) && !A.fin.arrived)
-        SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * NR), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                   A.max_chunks, A.n_main + n_extra, NR, out, announce);
-    return hipGetLastError();
+    if ((phases & kAttendCombine) && !A.fin.arrived) return launch_merge(L, A, NR, out, announce, stream);
+    return hipSuccess;
 }
 
 template <int BITS, int GROUP>
@@ -430,7 +449,8 @@ hipError_t launch2(const LayerView& L, AttendArgs& A, int n_rows, int n_ex, floa
         const int n_extra = (n_ex + kExtraChunk - 1) / kExtraChunk;             \
         A.n_chunks = A.n_main + n_extra;                                        \
         if (A.n_main + n_extra > A.max_chunks) return hipErrorInvalidValue;     \
-        if (!merges_in_launch(L.rows, A.n_chunks, L.G * n_rows)) A.fin.arrived = nullptr; \
+        const bool i8 = attend_uses_int8_matrix_cores(L, n_rows) && !(kernel_choice() & kChoiceAttendValu); \
+        if (!(i8 ? plan_merge(A.fin, L.rows, A.n_chunks, g_ * n_, false) : last_chunk_merges(L.rows, A.n_chunks, g_ * n_))) A.fin = Finish{}; \
         return launch3<BITS, GROUP, g_, n_>(L, A, n_extra, out, phases, announce, stream); \
     }
     SPC_CASE(1, 1) SPC_CASE(1, 2) SPC_CASE(2, 1)
@@ -478,16 +498,16 @@ hipError_t launch_attend(const LayerView& L, const void* q, int n_rows, int N, i
     const int n_ex = (slot_idx ? L.topk : 0) + (N - Nq) + (k_spec ? 1 : 0);
     // 4, 8 or 16 query rows per KV head, and 4-bit codes: a partial pass of their own (rows_mfma.h), with its own chunking
     if (rows_uses_matrix_cores(L, n_rows)) {
+        const int n_chunks = rows_chunks(L, n_rows, Nq, n_ex, A.max_chunks);
+        const bool merged = plan_merge(A.fin, L.rows, n_chunks, L.G * n_rows, true);
         if (phases & kAttendPartial) {
             RowsArgs R{A, nullptr, 0, n_rows, 0};
             hipError_t e = launch_rows(L, R, kRowsAttend, nullptr, stream);
             if (e != hipSuccess) return e;
         }
-        const int n_chunks = rows_chunks(L, n_rows, Nq, n_ex, A.max_chunks);
-        if ((phases & kAttendCombine) && !(arrived && merges_in_launch(L.rows, n_chunks, L.G * n_rows)))
-            SPC_LAUNCH(attend_combine_kernel, dim3(L.rows * L.G * n_rows), dim3(kCombineThreads), stream, A.part_o, A.part_ml,
-                       A.max_chunks, n_chunks, L.G * n_rows, out, announce);
-        return hipGetLastError();
+        A.n_chunks = n_chunks;
+        if ((phases & kAttendCombine) && !merged) return launch_merge(L, A, L.G * n_rows, out, announce, stream);
+        return hipSuccess;
     }
     // one query head per KV head, two rows, 2-bit values: the partial pass with the value side on the
     // integer matrix cores (same chunking, same partial-result format, same merge kernel)

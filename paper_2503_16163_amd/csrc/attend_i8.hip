@@ -409,19 +409,6 @@ __device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_strid
     if (c == 0) store_max_sum(pml, r, mmax, lsum, past_l2);
 }
 
-// (row, chunk) of this workgroup: the 16-bit chunks are chains of dependent loads and are dispatched first
-__device__ __forceinline__ void chunk_of_block(const AttendArgs& A, int rows, int bid, int& row, int& chunk) {
-    const int n_extra = A.n_chunks - A.n_main;
-    if (bid < rows * n_extra) {
-        row = bid / n_extra;
-        chunk = A.n_main + bid % n_extra;
-    } else {
-        const int id = bid - rows * n_extra;
-        row = id / A.n_main;
-        chunk = id % A.n_main;
-    }
-}
-
 // Workgroup-wide bitmap of the chunk's staged positions, for index lists too long for every wave to walk
 __device__ __forceinline__ void chunk_bitmap(const AttendArgs& A, int topk, int row, int c0, int n, int tid, uint32_t* maskbits) {
     if (tid < kI8Chunk / 32) maskbits[tid] = 0u;
@@ -434,53 +421,17 @@ __device__ __forceinline__ void chunk_bitmap(const AttendArgs& A, int topk, int 
     __syncthreads();
 }
 
-// Registers: the pass that also scores needs 90 to 94 (five waves per SIMD); compiled for six or eight it
-// spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
-// codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
-// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).  In groups
-// of 64 and 128 the conditional loads of value_loads go through 32 bytes of scratch a lane.
-template <int GROUP, int BITS, bool BF16, bool FUSED>
-__global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
-                                                             size_t key_stride) {
-    constexpr int NR = 2;
-    constexpr int kAreaBytes = FUSED ? kWaveDwords * 4 : kWaveArea;        // per wave
-    constexpr int kRegion = (kWaves * kAreaBytes) / 4;
-    static_assert(kRegion >= extra_chunk_floats(NR), "a 16-bit chunk in the same region");
-    __shared__ __attribute__((aligned(16))) float smem[kRegion];
-    __shared__ RowsOut xout;
-    __shared__ uint32_t maskbits[kI8Chunk / 32];
-    __shared__ __attribute__((aligned(8))) float2 fin[FUSED ? kWaves : 1][4][2];
-    __shared__ WaveOut wout;
-    __shared__ FinishShared fin_shared;
-    static_assert(kRegion * 4 >= kFinishLdsBytes, "the merge of a row in the same region");
-
+// One chunk of a row: its partial results and, FUSED, its positions' logits and selection keys.
+template <bool FUSED>
+struct I8Shape {
+    static constexpr int kAreaBytes = FUSED ? kWaveDwords * 4 : kWaveArea;        // per wave
+    static constexpr int kRegion = (kWaves * kAreaBytes) / 4;
+};
+template <int GROUP, int BITS, bool BF16, bool FUSED, typename Buffer>
+__device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const AttendArgs& A, float sm_scale, uint32_t* __restrict__ keys, size_t key_stride, int row, int chunk,
+                                                float* smem, uint32_t* maskbits, float2 (*fin)[4][2], WaveOut& wout, Buffer po, Buffer pml) {
+    constexpr int NR = 2, kAreaBytes = I8Shape<FUSED>::kAreaBytes;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int n_tail = L.tail_k ? L.rows : 0;
-    if ((int)blockIdx.x < n_tail) {
-        // a launch that also appends the step's new token (Appendix A "Decoding": Offload of the new pair to the
-        // CPU copy; it also joins the 16-bit residual): one more workgroup per row, 32 lanes x 16 bytes.  They are
-        // dispatched first: the store to host memory crosses a link the prefetch keeps busy, and the launch
-        // ends only when it has landed.
-        const int r = blockIdx.x;
-        if (tid < 32) {
-            const uint4 v = reinterpret_cast<const uint4*>(tid < 16 ? L.tail_k : L.tail_v)[(size_t)r * 16 + (tid & 15)];
-            reinterpret_cast<uint4*>(L.host)[((size_t)r * L.max_seq + L.tail_N0) * 32 + tid] = v;
-            reinterpret_cast<uint4*>(L.ring)[((size_t)r * L.R + (L.tail_N0 % L.R)) * 32 + tid] = v;
-        }
-        return;
-    }
-    int row, chunk;
-    chunk_of_block(A, L.rows, (int)blockIdx.x - n_tail, row, chunk);
-    const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4);
-    const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
-
-    if (chunk >= A.n_main) {
-        extra_chunk<NR, 2, BF16, FUSED ? 32 : BITS == 1 ? 16 : 0>(L, A, row, chunk, smem, xout, po, pml, A.fin.arrived != nullptr);
-        if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
-        return;
-    }
-
-    // ------------------------------------------------------------------ quantised positions
     const int c0 = chunk * kI8Chunk;
     const int n = (A.Nq - c0) < kI8Chunk ? (A.Nq - c0) : kI8Chunk;   // multiple of 32, >= 32
     const int w0 = kWaveTok * wave;                                    // first token of the wave inside the chunk
@@ -538,7 +489,69 @@ __global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i
     }
     __syncthreads();
     merge_waves<GROUP, BITS>(reinterpret_cast<const uint8_t*>(smem), kAreaBytes, wout, tid, po, pml, A.fin.arrived != nullptr);
-    if (A.fin.arrived) finish_row(A, row, NR, smem, fin_shared);
+}
+
+// Registers: the pass that also scores needs 90 to 94 (five waves per SIMD); compiled for six or eight it
+// spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
+// codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
+// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).  In groups
+// of 64 and 128 the conditional loads of value_loads go through 32 bytes of scratch a lane.
+template <int GROUP, int BITS, bool BF16, bool FUSED>
+__global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
+                                                             size_t key_stride) {
+    constexpr int NR = 2;
+    constexpr int kLoads = FUSED ? 12 : BITS == 2 ? 4 : 8;                // of a thread that merges: no more registers than the rest needs
+    constexpr int kRegion = I8Shape<FUSED>::kRegion;
+    static_assert(kRegion >= extra_chunk_floats(NR), "a 16-bit chunk in the same region");
+    __shared__ __attribute__((aligned(16))) float smem[kRegion];
+    __shared__ RowsOut xout;
+    __shared__ uint32_t maskbits[kI8Chunk / 32];
+    __shared__ __attribute__((aligned(8))) float2 fin[FUSED ? kWaves : 1][4][2];
+    __shared__ WaveOut wout;
+    __shared__ FinishShared fin_shared;
+    static_assert(kRegion * 4 >= kFinishLdsBytes, "the merge of a row in the same region");
+
+    // which (row, chunk): workgroups that append the step's token first, then the 16-bit chunks (chains of dependent loads), then the quantised
+    // positions, then the workgroups that only merge
+    const int tid = threadIdx.x, n_tail = L.tail_k ? L.rows : 0, bid = (int)blockIdx.x - n_tail, n_extra = A.n_chunks - A.n_main;
+    if (bid < 0) {
+        // a launch that also appends the step's new token (Appendix A "Decoding": Offload of the new pair to the
+        // CPU copy; it also joins the 16-bit residual): one more workgroup per row, 32 lanes x 16 bytes.  They are
+        // dispatched first: the store to host memory crosses a link the prefetch keeps busy, and the launch
+        // ends only when it has landed.
+        const int r = blockIdx.x;
+        if (tid < 32) {
+            const uint4 v = reinterpret_cast<const uint4*>(tid < 16 ? L.tail_k : L.tail_v)[(size_t)r * 16 + (tid & 15)];
+            reinterpret_cast<uint4*>(L.host)[((size_t)r * L.max_seq + L.tail_N0) * 32 + tid] = v;
+            reinterpret_cast<uint4*>(L.ring)[((size_t)r * L.R + (L.tail_N0 % L.R)) * 32 + tid] = v;
+        }
+        return;
+    }
+    int row, chunk = 0;
+    const int main_id = bid - L.rows * n_extra, merger = bid - L.rows * A.n_chunks;
+    if (main_id < 0) {
+        row = bid / n_extra;
+        chunk = A.n_main + bid % n_extra;
+    } else if (merger < 0) {
+        row = main_id / A.n_main;
+        chunk = main_id % A.n_main;
+    } else {
+        row = merger / A.fin.shares;
+    }
+    uint32_t shares;
+    if (merger < 0) {
+        const auto po = buffer_of(A.part_o + (((size_t)row * A.max_chunks + chunk) * NR) * kD, NR * kD * 4);
+        const auto pml = buffer_of(A.part_ml + (((size_t)row * A.max_chunks + chunk) * NR) * 2, NR * 8);
+        if (chunk >= A.n_main)
+            extra_chunk<NR, 2, BF16, FUSED ? 32 : BITS == 1 ? 16 : 0>(L, A, row, chunk, smem, xout, po, pml, A.fin.arrived != nullptr);
+        else
+            attend_i8_chunk<GROUP, BITS, BF16, FUSED>(L, A, sm_scale, keys, key_stride, row, chunk, smem, maskbits, fin, wout, po, pml);
+        if (A.fin.arrived == nullptr) return;
+        shares = row_arrival(A, row, fin_shared);
+    } else {
+        shares = row_complete(A, row, merger % A.fin.shares, fin_shared);
+    }
+    merge_shares<kLoads>(A, row, NR, shares, smem);
 }
 
 }  // namespace
@@ -571,9 +584,8 @@ hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, in
     A.n_chunks = A.n_main + (n_ex + kExtraChunk - 1) / kExtraChunk;
     if (A.n_chunks > A.max_chunks || A.n_chunks < 1) return hipErrorInvalidValue;
     A.fin = finish;
-    if (!merges_in_launch(L.rows, A.n_chunks, 2)) A.fin = Finish{};
-    *merged = A.fin.arrived != nullptr;
-    const dim3 grid(A.n_chunks * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
+    *merged = plan_merge(A.fin, L.rows, A.n_chunks, 2, false);
+    const dim3 grid((A.n_chunks + (A.fin.mergers ? A.fin.shares : 0)) * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
 #define SPC_AI8_B(G_, B_, F_)                                                                                              \
     do {                                                                                                                   \
         if (keys) SPC_LAUNCH((attend_i8_kernel<G_, B_, F_, true>), grid, block, stream, L, A, sm_scale, keys, key_stride); \

@@ -125,16 +125,42 @@ struct Finish {
     uint64_t* word = nullptr;    // announced when every row's keys are stored (null: nothing to announce)
     uint64_t value = 0;
     int rows = 0;
+    int shares = 1;              // a share is up to 8 of the row's query rows
+    bool mergers = false;        // a workgroup for each share that does nothing else; else the last of the row's chunks to arrive merges them all
+    int polls = 0;               // of such a workgroup, before it leaves its share to the last chunk
 };
-// Where the launch merges: a row's partials are few enough for one workgroup's loads to be requested at once (chunks x NR <= 64), and
-// the launch is no more than one round of workgroups.  us, a launch of its own against the merge in the launch: both passes over 1 x
-// 4096 9.9 / 8.3, 16 x 15500 12.2 / 10.6, 32 x 15500 17.9 / 16.5, 128 x 3500 17.2 / 16.3, 512 x 480 18.4 / 17.3, 8 query rows over
-// 8 x 1700 11.7 / 10.5, 64 x 2000 16.6 / 16.6, 256 x 1000 27.0 / 19.5; attention alone with one query row over 1 x 31000 9.5 / 7.4,
-// 32 x 15800 12.5 / 11.3, 4 bits 64 x 4000 14.3 / 13.6.  Beyond (a step of 8 layers, us a pass, the counters side by side): 32 x 16k (70
-// partials) 336 / 349; 8 query rows, 2 x 2000 (72) 163 / 168; 16 query rows, 4 x 3000 (400) 173 / 246 (partials past the L2 cost
-// more the more there are, and one workgroup reads them).
+// Where a launch of rows_kernel or attend_i8_kernel merges, by workgroups of its own: up to kFinishChunks chunks per row, in shares that one
+// workgroup's loads cover at once (chunks x query rows of a share <= kFinishShare) where that leaves at least one query row.  us, a launch
+// of its own (the last chunk of a row where that was better: 1) / mergers.  The launches alone: both passes over 1 x 4096 9.2 (1) / 9.0, 32 x
+// 8000, 1 bit 13.3 (1) / 12.9, 16 x 16384 13.8 / 12.3, 32 x 32768 30.4 / 29.9, 512 x 1000 24.5 / 21.3; 8 query rows over 64 x 1000 12.6 (1) / 12.1, 24 x
+// 5003 14.9 / 14.2, 32 x 8192 18.3 / 17.0, 8 x 131072, 1 bit (99 chunks) 43.4 / 42.7; 16 over 16 x 8192 17.3 / 16.3, 8 x 32768 (98) 25.6 / 26.0; but
+// 1 x 60000 (119) 10.4 / 11.0.  A pass of steps with their fetches: 8 layers of 32 x 16384 223 / 211, of 24 x 5003, 8 query rows 279 / 269, of 16 x
+// 8192, 16 rows 163 / 158, of 64 x 1000 198 (1) / 180, of 1 x 60000 151 / 134, of 8 x 32768, 16 rows 302 / 302.  The last chunk as the only one to
+// merge where the partials are many: 8 x 131072 59.8 and 16 rows over 8 x 32768 67.8 (one workgroup reads them all).
+constexpr int kFinishChunks = 128, kFinishShare = 128;
+constexpr int kMergerPolls = 2000;   // two to five milliseconds
+int& merger_polls();                 // that, unless specache_debug_merger_polls says otherwise
+inline int merge_shares_of(int n_chunks, int NR) {
+    int nr = NR > 8 ? 8 : NR;
+    while (nr > 1 && n_chunks * nr > kFinishShare) nr /= 2;
+    return NR / nr;
+}
+// attend_partial_kernel, and rows_kernel where it only attends, leave the merge to the last chunk to arrive where the launch is no more than
+// one round of workgroups and the partials are few.  us, a launch of its own / so: one query row over 1 x 31000 9.5 / 7.4, 32 x 15800 12.5 /
+// 11.3; mergers / so: 4 bits (scoring with it), 16 x 4000 15.6 / 15.4, 32 x 6000 22.2 / 21.9.
 constexpr int kFinishMost = 64;
-inline bool merges_in_launch(int rows, int n_chunks, int NR) { return rows * n_chunks <= 1024 && n_chunks * NR <= kFinishMost; }
+inline bool last_chunk_merges(int rows, int n_chunks, int NR) { return rows * n_chunks <= 1024 && n_chunks * NR <= kFinishMost; }
+// last_chunk: it may be left to that one
+inline bool plan_merge(Finish& fin, int rows, int n_chunks, int NR, bool last_chunk) {
+    if (!fin.arrived || n_chunks > kFinishChunks) {
+        fin = Finish{};
+        return false;
+    }
+    fin.shares = merge_shares_of(n_chunks, NR);
+    fin.mergers = !(last_chunk && last_chunk_merges(rows, n_chunks, NR));
+    fin.polls = merger_polls();
+    return true;
+}
 
 int attend_main_chunk_tokens(int NR);   // for the limits of specache_create and specache_attend_static
 // the chunks that such a limit allows for NR query rows per KV head, Nq quantised and n_16bit 16-bit candidates

@@ -68,8 +68,8 @@ hipError_t launch_rows(const LayerView& L, RowsArgs R, int mode, bool* merged, h
     R.at.n_chunks = R.at.n_main + n_extra;
     if (R.at.n_chunks < 1) return hipErrorInvalidValue;
     if (mode != kRowsScore && R.at.n_chunks > R.at.max_chunks) return hipErrorInvalidValue;
-    if (!merges_in_launch(L.rows, R.at.n_chunks, L.G * R.n_rows)) R.at.fin = Finish{};
-    if (merged) *merged = mode != kRowsScore && R.at.fin.arrived != nullptr;
+    const bool merges = mode != kRowsScore && plan_merge(R.at.fin, L.rows, R.at.n_chunks, L.G * R.n_rows, mode == kRowsAttend);
+    if (merged) *merged = merges;
     return L.bits == 1   ? launch_rows_b1(L, R, NR, mode, stream)
            : L.bits == 2 ? launch_rows_b2(L, R, NR, mode, stream)
                          : launch_rows_b4(L, R, NR, mode, stream);

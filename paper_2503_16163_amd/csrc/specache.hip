@@ -27,6 +27,10 @@ LaunchEvents& pending_launch_events() {
     static thread_local LaunchEvents le;
     return le;
 }
+int& merger_polls() {
+    static int polls = kMergerPolls;
+    return polls;
+}
 int& kernel_choice() {
     static int choice = 0;
     return choice;
@@ -1052,6 +1056,12 @@ int specache_debug_scored_by_word(specache_ctx* ctx, int32_t layer, int32_t* by_
 int specache_debug_fail_alloc(int32_t nth) {
     if (nth < 0) return SPECACHE_EINVAL;
     g_fail_alloc_at = nth;
+    return SPECACHE_OK;
+}
+
+int specache_debug_merger_polls(int32_t polls) {
+    if (polls < -1) return SPECACHE_EINVAL;
+    merger_polls() = polls < 0 ? kMergerPolls : polls;
     return SPECACHE_OK;
 }
 

@@ -90,3 +90,46 @@ def test_attend_from_static_scratch_beside_attend():
     finally:
         torch.cuda.synchronize()
         sc.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,S,bits,g,k", [
+    (1, 1, 600, 2, 32, 16), (3, 3, 5000, 1, 64, 64), (2, 2, 2000, 2, 128, 300),
+    # as many chunks as the rule takes, 128, and one more; beyond 96 a lane reads its partials in two batches
+    (1, 1, 512 * 127 + 40, 2, 32, 64), (1, 1, 512 * 128 + 40, 2, 32, 64), (1, 1, 512 * 96 + 40, 2, 64, 64),
+    # 4, 8 and 16 query rows: one share to sixteen, of one query row to eight
+    (2, 1, 3000, 2, 32, 48), (4, 1, 900, 2, 64, 48), (8, 1, 300, 2, 32, 16), (8, 1, 20000, 1, 32, 48), (16, 2, 9000, 2, 64, 48), (4, 1, 256 * 127 + 40, 2, 32, 64),
+    (4, 1, 256 * 128 + 40, 2, 32, 64), (1, 1, 2000, 4, 32, 32)])
+def test_mergers_and_what_they_leave_behind(Hq, Hkv, S, bits, g, k):
+    """A share of a row's query rows is merged by a workgroup of its own or, when that stops looking, by the last chunk: the same sums in the
+    same order, and counters as the next launch wants them.  attend_static merges in a launch of its own."""
+    import torch
+    from paper_2503_16163_amd import binding
+    q = synth.make_queries_device(7, 1, 1, Hq, 128, synth.FP16).view(1, Hq, 2, 128).contiguous()
+    kd, vd = synth.make_kv_device(7, 1, Hkv, S, 128, synth.FP16)
+    ks, vs = synth.make_kv_device(8, 1, Hkv, 1, 128, synth.FP16, n_outlier=0)
+    idx = torch.full((1, Hkv, k), -1, dtype=torch.int32, device="cuda")
+    sc = binding.SpeCache(1, 1, Hq, Hkv, bits, g, (S + 127) // 64 * 64, k, synth.FP16, residual=max(64, g), async_select=2)
+    outs = []
+    try:
+        sc.quantize_append(0, kd, vd, S)
+        sc.score(0, q, 2)
+        sc.select_gather(0, idx, 0)
+        own = torch.zeros((1, Hq, 2, 128), dtype=torch.float32, device="cuda")
+        sc.attend_static(0, q, 2, ks, vs, 0, own)
+        for polls in (-1, 0, -1, 1, 0, 3, -1):
+            binding.debug_merger_polls(polls)
+            for fn in (sc.score_attend, sc.attend):
+                if fn == sc.attend:
+                    sc.score(0, q, 2)
+                outs.append((polls, fn.__name__, torch.full((1, Hq, 2, 128), float("nan"), dtype=torch.float32, device="cuda")))
+                fn(0, q, 2, ks, vs, 0, outs[-1][2])
+        torch.cuda.synchronize()
+    finally:
+        binding.debug_merger_polls(-1)
+        torch.cuda.synchronize()
+        sc.close()
+    first = {name: out for _, name, out in reversed(outs)}
+    for polls, name, out in outs:
+        assert torch.equal(out, first[name]), (polls, name, (out - first[name]).abs().max().item())
+    # attention alone from other scratch memory: the same kernel, and the merge's own launch adds up in the same order (up to 128 chunks)
+    assert torch.equal(first["attend"], own), (first["attend"] - own).abs().max().item()
