@@ -46,7 +46,8 @@ constexpr int kWaveTok = kI8Chunk / kWaves;     // 128
 constexpr int kColStride = kWaveTok + 16;       // bytes between the B columns of a wave (pad: banks)
 constexpr int kSetBytes = 16 * kColStride;      // the 16 columns (row, group of the set, plane) of a channel set
 constexpr int kWaveArea = 2 * kSetBytes;        // bytes per wave; a set's results [2][4][4][16] int32 replace its columns
-static_assert(kSetBytes >= 2 * 4 * 4 * 16 * 4, "a set's results reuse the set's operand columns");
+constexpr int kResPlane = 64 + 4;               // dwords between the results of (row, plane) of a set (pad: banks)
+static_assert(kSetBytes >= 2 * 4 * kResPlane * 4, "a set's results reuse the set's operand columns");
 static_assert(kWaveDwords * 4 >= kWaveArea, "the value phase reuses the scoring wave's exchange area");
 constexpr int kWaveBitmapTopk = 256;            // up to here every wave builds the bitmap of its own tokens
 
@@ -83,20 +84,22 @@ struct ValueLoads {
 };
 
 template <int GROUP, int BITS>
-__device__ __forceinline__ void value_loads(const LayerView& L, int row, int c0, int w0, int nw, int lane, ValueLoads<GROUP, BITS>& v) {
+__device__ __forceinline__ void value_loads(const LayerView& L, int Nq, int row, int c0, int w0, int nw, int lane, ValueLoads<GROUP, BITS>& v) {
     constexpr int M = kD / GROUP;
     const int sg = lane >> 4, l16 = lane & 15;
-    const bool live = 32 * sg < nw;
     const size_t tok = (size_t)c0 + w0 + 32 * sg;                      // the sub-group's first token
     const uint32_t* vm_row = L.vm + (size_t)row * L.vm_stride;
-    const uint4 zero = make_uint4(0, 0, 0, 0);
+    // (positions beyond the quantised ones lie beyond the buffer's range: 0.  Loads behind a condition went through scratch memory in
+    // groups of 64 and 128)
+    const auto vm = buffer_of(vm_row, (uint32_t)Nq * M * 4u);
+    auto load = [&](size_t t) { return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vm, (int)(t * M * 4), 0, 0)); };
     if constexpr (M == 4) {            // 16 bytes per token: lane l16 takes tokens l16 and 16 + l16
-        v.raw[0] = live ? *reinterpret_cast<const uint4*>(vm_row + (tok + l16) * 4) : zero;
-        v.raw[1] = live ? *reinterpret_cast<const uint4*>(vm_row + (tok + 16 + l16) * 4) : zero;
+        v.raw[0] = load(tok + l16);
+        v.raw[1] = load(tok + 16 + l16);
     } else if constexpr (M == 2) {     // 8 bytes per token: tokens 2 l16 and 2 l16 + 1
-        v.raw[0] = live ? *reinterpret_cast<const uint4*>(vm_row + (tok + 2 * l16) * 2) : zero;
+        v.raw[0] = load(tok + 2 * l16);
     } else {                           // 4 bytes per token: the lane's own four tokens
-        v.raw[0] = (32 * sg + 4 * (lane & 7)) < nw ? *reinterpret_cast<const uint4*>(vm_row + tok + 4 * (lane & 7)) : zero;
+        v.raw[0] = load(tok + 4 * (lane & 7));
     }
     // codes: lane (il = lane % 16, tg = lane / 16) reads, for token step ks and channel set s, the 16 tokens
     // 64 ks + 16 tg .. + 15 of code lane 16 s + il (channels 4 (16 s + il) .. + 3); with 1-bit codes of code
@@ -157,15 +160,19 @@ __device__ __forceinline__ void value_meta_exchange(ValueLoads<GROUP, BITS>& v, 
 __device__ __forceinline__ void wave_bitmap_loads(const int32_t* __restrict__ idx_row, int topk, int lane, int t[4]) {
     const auto list = buffer_of(idx_row, idx_row ? (uint32_t)topk * 4u : 0u);   // beyond the list: 0, and no lane looks at it
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(list, (64 * u + lane) * 4, 0, 0);
+    for (int u = 0; u < 4; ++u) {
+        if (u > 0 && 64 * u >= topk) break;     // uniform
+        t[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(list, (64 * u + lane) * 4, 0, 0);
+    }
 }
 __device__ __forceinline__ void wave_bitmap_apply(const int t[4], int n_idx, int first, int nw, int lane, uint32_t* wbits) {
     if (lane < 4) wbits[lane] = 0u;
     wave_sync();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int p = t[u] - first;
-        if (64 * u + lane < n_idx && t[u] >= 0 && p >= 0 && p < nw) atomicOr(&wbits[p >> 5], 1u << (p & 31));
+        if (u > 0 && 64 * u >= n_idx) break;
+        const uint32_t p = (uint32_t)(t[u] - first);       // (an empty place of the list, -1, lies before the first position, too)
+        if (64 * u + lane < n_idx && p < (uint32_t)nw) atomicOr(&wbits[p >> 5], 1u << (p & 31));
     }
     wave_sync();
 }
@@ -182,14 +189,7 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
     const int sg = lane >> 4, h = (lane >> 3) & 1, tg = lane >> 4;
     const int t0 = 32 * sg + 4 * (lane & 7);
 
-    float mloc = fmaxf(fmaxf(lgv[0], lgv[1]), fmaxf(lgv[2], lgv[3]));
-    mloc = max8(mloc);
-    float mrow[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-        mrow[r] = fmaxf(fmaxf(lane_value(mloc, 8 * r), lane_value(mloc, 16 + 8 * r)),
-                        fmaxf(lane_value(mloc, 32 + 8 * r), lane_value(mloc, 48 + 8 * r)));
-    const float m_own = h ? mrow[1] : mrow[0];
+    const float m_own = quarters_max(max8(fmaxf(fmaxf(lgv[0], lgv[1]), fmaxf(lgv[2], lgv[3]))));   // of row h
     const float ms = m_own == -INFINITY ? 0.0f : m_own;
     float p[4], psum = 0.0f;
 #pragma unroll
@@ -197,18 +197,12 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
         p[j] = __expf(lgv[j] - ms);
         psum += p[j];
     }
-    // numerators of both rows for the lane's tokens: pr[r][j]
-    float pr[2][4];
-    if constexpr (RPL == 2) {
+    // numerators of the lane's tokens: of row h and, from the lane that holds it, of the other row
+    float pr[RPL][4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float other = dpp_move<kDppRowRor8>(p[j]);
-            pr[0][j] = h ? other : p[j];
-            pr[1][j] = h ? p[j] : other;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pr[0][j] = p[j];   // the lane's own row only
+    for (int j = 0; j < 4; ++j) {
+        pr[0][j] = p[j];
+        if constexpr (RPL == 2) pr[1][j] = dpp_move<kDppRowRor8>(p[j]);
     }
 
     // scale and zero-point of the lane's (token, group) pairs; the wave's largest scale
@@ -220,9 +214,8 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
             derive_scale_zero<BITS>(widen16<BF16>(v.mw[j][ml] & 0xFFFFu), widen16<BF16>(v.mw[j][ml] >> 16), one_bit_plain, sc[j][ml], zp[j][ml]);
             smax = fmaxf(smax, sc[j][ml]);
         }
-    const float top = wave_max(smax);
-    // top < 2^(E - 126) with E its exponent field, p <= 1: p s 2^(156 - E) stays below 2^30
-    uint32_t E = __float_as_uint(top) >> 23;
+    // s < 2^(E - 126) with E the largest one's exponent field, p <= 1: p s 2^(156 - E) stays below 2^30
+    uint32_t E = wave_max_bits(__float_as_uint(smax)) >> 23;
     E = E < 30u ? 30u : (E > 254u ? 254u : E);
     const float up = __uint_as_float((283u - E) << 23);
 #pragma unroll
@@ -234,29 +227,27 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
     // set, plane); with one value group per token each lane fills its own row's columns of both sets.
     float zacc[RPL][MPL];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r)
+    for (int r = 0; r < RPL; ++r) {
+        const int rr = r == 0 ? h : 1 - h;
+        uint8_t* column = area + (M >= 2 ? h * kSetBytes : 0) + rr * (8 * kColStride) + t0;
 #pragma unroll
         for (int ml = 0; ml < MPL; ++ml) {
             uint32_t y[4], planes[4];
             float za = 0.0f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                y[j] = ((uint32_t)(int)(pr[r][j] * sc[j][ml]) + 0x00808080u) ^ 0x00808080u;
+                y[j] = (uint32_t)(int)(pr[r][j] * sc[j][ml]);
                 za = __builtin_fmaf(pr[r][j], zp[j][ml], za);
             }
             zacc[r][ml] = za;
-            byte_planes(y[0], y[1], y[2], y[3], planes);
-            const int rr = RPL == 2 ? r : h;
+            signed_byte_planes(y, planes);
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                if constexpr (M >= 2) {
-                    *reinterpret_cast<uint32_t*>(area + (((h * 2 + rr) * 2 + ml) * 4 + pp) * kColStride + t0) = planes[pp];
-                } else {
-                    *reinterpret_cast<uint32_t*>(area + ((rr * 2) * 4 + pp) * kColStride + t0) = planes[pp];
-                    *reinterpret_cast<uint32_t*>(area + kSetBytes + ((rr * 2) * 4 + pp) * kColStride + t0) = planes[pp];
-                }
+                *reinterpret_cast<uint32_t*>(column + (ml * 4 + pp) * kColStride) = planes[pp];
+                if constexpr (M < 2) *reinterpret_cast<uint32_t*>(column + kSetBytes + pp * kColStride) = planes[pp];
             }
         }
+    }
     // partial sums of the 8 lanes that share (sub-group, h); the merge adds them up
     psum = sum8(psum);
 #pragma unroll
@@ -268,12 +259,11 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
 #pragma unroll
         for (int r = 0; r < RPL; ++r)
 #pragma unroll
-            for (int ml = 0; ml < MPL; ++ml) dst[r * MPL + ml] = zacc[r][ml];
+            for (int ml = 0; ml < MPL; ++ml) dst[(RPL == 1 ? 0 : r == 0 ? h : 1 - h) * MPL + ml] = zacc[r][ml];
         dst[4] = psum;
+        if (sg == 0) out.m[wave][h] = m_own;
     }
     if (lane == 0) {
-        out.m[wave][0] = mrow[0];
-        out.m[wave][1] = mrow[1];
         out.unscale[wave] = __uint_as_float((E - 29u) << 23);   // 2^(E - 156) = 1 / up
     }
     wave_sync();
@@ -310,7 +300,7 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
             if (keep) {
                 int* res = reinterpret_cast<int*>(set);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) *reinterpret_cast<v4i*>(res + (((brow * 4 + bpp) * 4 + j) * 16 + 4 * tg)) = acc[j];
+                for (int j = 0; j < 4; ++j) *reinterpret_cast<v4i*>(res + (brow * 4 + bpp) * kResPlane + j * 16 + 4 * tg) = acc[j];
             }
         }
     } else {
@@ -348,7 +338,7 @@ __device__ __forceinline__ void value_wave(const ValueLoads<GROUP, BITS>& v, flo
                     int* res = reinterpret_cast<int*>(set);
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        *reinterpret_cast<v4i*>(res + (((brow * 4 + bpp) * 8 + 4 * jh + j) * 8 + 4 * (tg & 1))) = acc[j];
+                        *reinterpret_cast<v4i*>(res + (brow * 4 + bpp) * kResPlane + (4 * jh + j) * 8 + 4 * (tg & 1)) = acc[j];
                 }
             }
         }
@@ -374,7 +364,7 @@ __device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_strid
     // where the channel's sums sit in its set's results: 2 bits [row][plane][j = c % 4][code lane (c / 4) % 16],
     // 1 bit [row][plane][j = c % 8][code lane (c / 8) % 8]
     const int s = c >> 6, i = BITS == 2 ? (c >> 2) & 15 : (c >> 3) & 7, j = BITS == 2 ? c & 3 : c & 7;
-    constexpr int NJ = BITS == 2 ? 4 : 8, NI = BITS == 2 ? 16 : 8;
+    constexpr int NI = BITS == 2 ? 16 : 8;
     const int m = c / GROUP;
     const int hh = M >= 2 ? m / MPL : r, zi = M >= 2 ? r * MPL + m % MPL : 0;   // where the zero-point sum of (r, m) sits
     float mmax = -INFINITY;
@@ -388,12 +378,10 @@ __device__ __forceinline__ void merge_waves(const uint8_t* areas, int area_strid
         const float mwv = out.m[w][r];
         const float e = mwv == -INFINITY ? 0.0f : __expf(mwv - mmax);
         const int* res = reinterpret_cast<const int*>(areas + w * area_stride + s * kSetBytes);
-        float f[4];
+        int f[4];
 #pragma unroll
-        for (int pp = 0; pp < 4; ++pp) f[pp] = (float)res[((r * 4 + pp) * NJ + j) * NI + i];
-        float t = __builtin_fmaf(f[1], 256.0f, f[0]);
-        t = __builtin_fmaf(f[2], 65536.0f, t);
-        t = __builtin_fmaf(f[3], 16777216.0f, t);
+        for (int pp = 0; pp < 4; ++pp) f[pp] = res[(r * 4 + pp) * kResPlane + j * NI + i];
+        const float t = of_byte_planes(f[0], f[1], f[2], f[3]);
         float zs = 0.0f, ls = 0.0f;
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
@@ -454,7 +442,7 @@ __device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const Attend
         if constexpr (!FUSED) {
             float4 lg4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             if (live) lg4 = *reinterpret_cast<const float4*>(A.logits + ((size_t)row * NR + h) * A.logit_stride + c0 + w0 + t0);
-            value_loads<GROUP, BITS>(L, row, c0, w0, nw, lane, v);
+            value_loads<GROUP, BITS>(L, A.Nq, row, c0, w0, nw, lane, v);
             if (wave_maps) wave_bitmap_apply(ti, n_idx, c0 + w0, nw, lane, maskbits + 4 * wave);
             lgv[0] = lg4.x; lgv[1] = lg4.y; lgv[2] = lg4.z; lgv[3] = lg4.w;
         } else {
@@ -463,7 +451,7 @@ __device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const Attend
             score_i8_wave<BITS, BF16>(L, A.q, row, chunk, wave, lane, A.Nq / kBlockTokens, sm_scale, reinterpret_cast<uint32_t*>(area),
                                    fin[wave], lgv,
                                    [&]() { if (wave_maps) wave_bitmap_apply(ti, n_idx, c0 + w0, nw, lane, maskbits + 4 * wave); },
-                                   [&]() { value_loads<GROUP, BITS>(L, row, c0, w0, nw, lane, v); });
+                                   [&]() { value_loads<GROUP, BITS>(L, A.Nq, row, c0, w0, nw, lane, v); });
             if (live) {
                 if (h == 1) {   // the speculative row ranks the positions
                     const uint4v k4 = {float_to_key(lgv[0]), float_to_key(lgv[1]), float_to_key(lgv[2]), float_to_key(lgv[3])};
@@ -491,11 +479,15 @@ __device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const Attend
     merge_waves<GROUP, BITS>(reinterpret_cast<const uint8_t*>(smem), kAreaBytes, wout, tid, po, pml, A.fin.arrived != nullptr);
 }
 
-// Registers: the pass that also scores needs 90 to 94 (five waves per SIMD); compiled for six or eight it
+// Registers: the pass that also scores needs 84 to 90 (five waves per SIMD); compiled for six or eight it
 // spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
 // codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
-// step of 128 rows x 30000), and up to 96 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).  In groups
-// of 64 and 128 the conditional loads of value_loads go through 32 bytes of scratch a lane.
+// step of 128 rows x 30000), and up to 91 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).
+// What the waves of a full chip wait for is issue slots, of the vector ALUs and of LDS (a wave of 128 tokens: 1139 vector instructions; with 1 bit LDS
+// was busy for 58 % of the launch, two fifths of that with bank conflicts).  So maxima are of bits, signs are set behind the transpositions, results
+// lie where neither their writers nor their readers share banks, and the metadata's loads have no conditions: a pass of 4 layers
+// of 32 x 32768, 1 bit, g = 64 121 -> 115 us, 2 bits, g = 32 132 -> 128, of 8 of 32 x 16384 208 -> 205.5 (sharing the fetch's queue 182 -> 173, 196 ->
+// 192, 321 -> 316).
 template <int GROUP, int BITS, bool BF16, bool FUSED>
 __global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i8_kernel(LayerView L, AttendArgs A, float sm_scale, uint32_t* __restrict__ keys,
                                                              size_t key_stride) {

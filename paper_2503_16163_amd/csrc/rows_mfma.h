@@ -58,17 +58,6 @@ __device__ __forceinline__ void hi_lo_columns(const uint4v& hi, const uint4v& lo
         sub1[d] = (uint32_t)__builtin_amdgcn_update_dpp((int)lo[d], (int)hi[d], kDppRowRor8, 0xf, 0x3, false);
     }
 }
-// largest value of a wave; floats that are not negative order as their bits do
-__device__ __forceinline__ uint32_t wave_max_bits(uint32_t v) {
-    auto step = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor1, 0xf, 0xf, true));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor2, 0xf, 0xf, true));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppHalfMirror, 0xf, 0xf, true));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppMirror, 0xf, 0xf, true));
-    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-    return step(step(a, b), step(c, d));
-}
 __device__ __forceinline__ float times_pow2(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 
 // Codes as normal numbers instead of subnormals, at half a vector instruction more per code.  The matrix cores align products

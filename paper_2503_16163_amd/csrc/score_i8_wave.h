@@ -12,16 +12,17 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kI8Waves = 4;
 constexpr int kPieceStride = 36;                          // dwords: 32 channel quads of one byte plane + pad
-constexpr int kSubStride = 2 * 4 * kPieceStride + 8;      // dwords: [row][byte plane] of one sub-group + pad
+constexpr int kSubStride = 2 * 4 * kPieceStride + 16;     // dwords: [row][byte plane] of one sub-group + pad: 8 lanes read 8 x 4 banks
 constexpr int kWaveDwords = 4 * kSubStride;
 constexpr int kResBlock = 64 + 4;                         // dwords between the result blocks of (sub-group, row, half)
 static_assert(kWaveDwords >= 16 * kResBlock, "the result exchange reuses the multiplier area");
 
-__device__ __forceinline__ float row16_max(float v) {
-    v = fmaxf(v, dpp_move<kDppXor1>(v));
-    v = fmaxf(v, dpp_move<kDppXor2>(v));
-    v = fmaxf(v, dpp_move<kDppHalfMirror>(v));
-    return fmaxf(v, dpp_move<kDppMirror>(v));
+// (of floats that are not negative, which order as their bits do: a float maximum of a moved value takes an instruction more, for NaNs)
+__device__ __forceinline__ uint32_t row16_max_bits(uint32_t v) {
+    v = max_u32(v, dpp_move_u32<kDppXor1>(v));
+    v = max_u32(v, dpp_move_u32<kDppXor2>(v));
+    v = max_u32(v, dpp_move_u32<kDppHalfMirror>(v));
+    return max_u32(v, dpp_move_u32<kDppMirror>(v));
 }
 __device__ __forceinline__ float row16_sum(float v) {
     v += dpp_move<kDppXor1>(v);
@@ -87,7 +88,7 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const uint32_t pair = comp_i8(qraw[r], e / 2);
-                const float qv = widen16<BF16>((e & 1) ? pair >> 16 : pair & 0xFFFFu) * sm_scale;
+                const float qv = widen16<BF16>((e & 1) ? pair >> 16 : pair & 0xFFFFu);
                 x[r][e] = qv * sc;
                 qz[r] = __builtin_fmaf(qv, z, qz[r]);
                 mx[r] = fmaxf(mx[r], fabsf(x[r][e]));
@@ -105,21 +106,19 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const float top = row16_max(mx[r]);
         qz[r] = row16_sum(qz[r]);
-        // top < 2^(E - 126) with E its exponent field: x * 2^(156 - E) stays below 2^30
-        uint32_t E = __float_as_uint(top) >> 23;
+        // |x| < 2^(E - 126) with E the largest one's exponent field: x * 2^(156 - E) stays below 2^30
+        uint32_t E = row16_max_bits(__float_as_uint(mx[r])) >> 23;
         E = E < 30u ? 30u : (E > 254u ? 254u : E);
         const float up = __uint_as_float((283u - E) << 23);
-        if (u == 0) fin_w[sgP][r] = make_float2(__uint_as_float((E - 29u) << 23), qz[r]);
+        if (u == 0) fin_w[sgP][r] = make_float2(__uint_as_float((E - 29u) << 23) * sm_scale, qz[r] * sm_scale);
         const float up_c[2] = {up * cls[0], up * cls[1]};
 #pragma unroll
         for (int mq = 0; mq < 2; ++mq) {
             uint32_t y[4], planes[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                y[b] = ((uint32_t)(int)(x[r][4 * mq + b] * up_c[mq]) + 0x00808080u) ^ 0x00808080u;
-            byte_planes(y[0], y[1], y[2], y[3], planes);
+            for (int b = 0; b < 4; ++b) y[b] = (uint32_t)(int)(x[r][4 * mq + b] * up_c[mq]);
+            signed_byte_planes(y, planes);
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) area[sgP * kSubStride + (r * 4 + pp) * kPieceStride + 2 * u + mq] = planes[pp];
         }
@@ -150,8 +149,8 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
     // Result register v of lane (column n, quarter qq) is MFMA row 4 qq + v: sub-group qq of the
     // wave, quad lane v, i.e. token 32 (sub0 + qq) + 8 v + 4 hf + j.  It is wanted where the
     // column's sub-group is qq too; those quads go to block (sub-group, row, hf) of the area as
-    // [byte p][token j][quad lane v], the blocks 4 dwords further apart than their size so that
-    // the lanes that read one position of 16 different blocks hit 16 different banks.
+    // [token j][byte p][quad lane v] (the lanes that write differ in p and the block: 16 bytes each, side by side), the
+    // blocks 4 dwords further apart than their size so that the lanes that read one position of 16 different blocks hit 16 different banks.
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
@@ -174,7 +173,7 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
             if (sgB == qd) {
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
-                    *reinterpret_cast<v4i*>(area + ((qd * 2 + r) * 2 + hf) * kResBlock + (p * 4 + j) * 4) = acc[r];
+                    *reinterpret_cast<v4i*>(area + ((qd * 2 + r) * 2 + hf) * kResBlock + (j * 4 + p) * 4) = acc[r];
             }
         }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -189,13 +188,11 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
 #pragma unroll
     for (int pp = 0; pp < 4; ++pp)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s[pp][j] = (int)blk[(pp * 4 + j) * 4];
+        for (int j = 0; j < 4; ++j) s[pp][j] = (int)blk[(j * 4 + pp) * 4];
     const float2 f = fin_w[sgO][rO];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        float t = __builtin_fmaf((float)s[1][j], 256.0f, (float)s[0][j]);
-        t = __builtin_fmaf((float)s[2][j], 65536.0f, t);
-        t = __builtin_fmaf((float)s[3][j], 16777216.0f, t);
+        const float t = of_byte_planes(s[0][j], s[1][j], s[2][j], s[3][j]);
         o[j] = __builtin_fmaf(t, f.x, f.y);
     }
 }
