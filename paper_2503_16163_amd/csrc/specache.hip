@@ -635,12 +635,18 @@ int specache_score_topk(specache_ctx* ctx, int32_t layer, const void* q, int32_t
         SPC_HIP(ctx, hipEventRecord(ctx->scored, st));
         SPC_HIP(ctx, hipStreamWaitEvent(tk, ctx->scored, 0));
     }
+    // (recorded where the call is captured: there a record is an edge of the graph)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(tk, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
+    bool ready_carried = false;
     {
         TimedLaunch t(ctx, tk, SPECACHE_K_TOPK, /*kernel_events=*/true);
+        CarriedEvent ready(ctx, captured ? nullptr : L.idx_ready);
         SPC_HIP(ctx, launch_topk(L.view.rows, L.Nq, ctx->cfg.topk, ctx->keys, ctx->logit_stride, topk_idx_out,
                                  ctx->topk_scratch, tk));
+        ready_carried = ready.landed();
     }
-    SPC_HIP(ctx, hipEventRecord(L.idx_ready, tk));
+    if (!ready_carried) SPC_HIP(ctx, hipEventRecord(L.idx_ready, tk));
     ctx->last_select = L.idx_ready;
     L.idx_ready_recorded = true;
     L.idx_ready_stream = tk;

@@ -195,3 +195,43 @@ def test_rows_of_one_launch_do_not_wait_for_candidate_arrays():
     finally:
         torch.cuda.synchronize()
         sc.close()
+
+
+def test_selection_captured_between_eager_ones():
+    """score_topk lets its launch carry the event that a gather waits for; captured, it records it: replays give the eager positions and
+    outputs, and an eager selection behind them orders a gather on another stream as before."""
+    import torch
+    from paper_2503_16163_amd import binding
+    H, S, k = 4, 3000, 40
+    q = synth.make_queries_device(9, 2, 1, H, 128, synth.FP16).view(2, 1, H, 2, 128)[:, :, :, :1].contiguous()
+    kd, vd = synth.make_kv_device(9, 1, H, S, 128, synth.FP16)
+    sc = binding.SpeCache(1, 1, H, H, 2, 32, 3072, k, synth.FP16)
+    new = lambda: (torch.full((1, H, k), -2, dtype=torch.int32, device="cuda"), torch.zeros((1, H, 1, 128), dtype=torch.float32, device="cuda"))
+    side = torch.cuda.Stream()
+    try:
+        sc.quantize_append(0, kd, vd, S)
+        want = [new() for _ in range(2)]
+        for i in range(2):
+            sc.score_topk(0, q[i], 1, want[i][0])
+            sc.attend(0, q[i], 1, None, None, -1, want[i][1])
+        torch.cuda.synchronize()
+        got, graph = new(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            st = torch.cuda.current_stream()
+            sc.score_topk(0, q[0], 1, got[0], st)
+            sc.attend(0, q[0], 1, None, None, -1, got[1], st)
+        for _ in range(3):
+            got[0].fill_(-2)
+            got[1].zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0][0]) and torch.equal(got[1], want[0][1])
+            eager = new()
+            sc.score_topk(0, q[1], 1, eager[0])
+            sc.gather(0, eager[0], 0, side)
+            sc.attend(0, q[1], 1, None, None, -1, eager[1])
+            torch.cuda.synchronize()
+            assert torch.equal(eager[0], want[1][0]) and torch.equal(eager[1], want[1][1])
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
