@@ -448,7 +448,7 @@ __device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const Attend
         } else {
             // the low-bit logits of the wave's tokens (Appendix A "Decoding": A = Q K^T on C'); the value-side loads
             // are requested once the scoring operands are built and travel while the scoring contraction runs
-            score_i8_wave<BITS, BF16>(L, A.q, row, chunk, wave, lane, A.Nq / kBlockTokens, sm_scale, reinterpret_cast<uint32_t*>(area),
+            score_i8_wave<BITS, GROUP, BF16>(L, A.q, row, chunk, wave, lane, A.Nq / kBlockTokens, sm_scale, reinterpret_cast<uint32_t*>(area),
                                    fin[wave], lgv,
                                    [&]() { if (wave_maps) wave_bitmap_apply(ti, n_idx, c0 + w0, nw, lane, maskbits + 4 * wave); },
                                    [&]() { value_loads<GROUP, BITS>(L, A.Nq, row, c0, w0, nw, lane, v); });

@@ -50,7 +50,7 @@ namespace {
 
 constexpr int kWaves = kI8Waves;
 
-template <int BITS, bool BF16>
+template <int BITS, int GROUP, bool BF16>
 // at most 64 registers: all eight waves a SIMD gets are resident at once
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) void score_i8_kernel(LayerView L, const uint16_t* __restrict__ q, int Nq,
                                                                float sm_scale, float* __restrict__ logits,
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8, 
     if (sub0 >= n_sub) return;                                 // the waves never meet at a barrier
 
     float o[4];
-    score_i8_wave<BITS, BF16>(L, q, row, tile, wave, lane, n_sub, sm_scale, xch[wave], fin[wave], o);
+    score_i8_wave<BITS, GROUP, BF16>(L, q, row, tile, wave, lane, n_sub, sm_scale, xch[wave], fin[wave], o);
     const int sgO = lane >> 4, rO = (lane >> 3) & 1, vO = (lane >> 1) & 3, hfO = lane & 1;
     if (sub0 + sgO < n_sub) {
         const size_t i4 = (size_t)(sub0 + sgO) * kBlockTokens + 8 * vO + 4 * hfO;
@@ -87,11 +87,13 @@ hipError_t launch_score_i8(const LayerView& L, const void* q, int Nq, float sm_s
     if (L.G != 1 || (L.bits != 1 && L.bits != 2) || (L.group != 32 && L.group != 64 && L.group != 128) || Nq % L.group != 0)
         return hipErrorInvalidValue;
     const dim3 grid((Nq + kTileTokens - 1) / kTileTokens + (L.tail_k ? 1 : 0), L.rows), block(64 * kWaves);
-#define SPC_I8(B_, F_)                                                                                         \
-    SPC_LAUNCH((score_i8_kernel<B_, F_>), grid, block, stream, L, (const uint16_t*)q, Nq, sm_scale, logits, \
-               logit_stride, keys, key_stride)
-    if (L.bits == 2) { if (L.bf16) SPC_I8(2, true); else SPC_I8(2, false); }
-    else             { if (L.bf16) SPC_I8(1, true); else SPC_I8(1, false); }
+#define SPC_I8(B_, G_, F_)                                                                                         \
+    if (L.bits == B_ && L.group == G_ && L.bf16 == F_)                                                              \
+        SPC_LAUNCH((score_i8_kernel<B_, G_, F_>), grid, block, stream, L, (const uint16_t*)q, Nq, sm_scale, logits, \
+                   logit_stride, keys, key_stride)
+    SPC_I8(1, 32, false);  SPC_I8(1, 32, true);  SPC_I8(2, 32, false);  SPC_I8(2, 32, true);
+    SPC_I8(1, 64, false);  SPC_I8(1, 64, true);  SPC_I8(2, 64, false);  SPC_I8(2, 64, true);
+    SPC_I8(1, 128, false); SPC_I8(1, 128, true); SPC_I8(2, 128, false); SPC_I8(2, 128, true);
 #undef SPC_I8
     return hipGetLastError();
 }

@@ -37,17 +37,22 @@ __device__ __forceinline__ uint32_t comp_i8(const uint4& v, int i) { return i ==
 // 4 wave < n_sub sub-groups of 32 quantised tokens).  area: kWaveDwords dwords of LDS private to the wave;
 // fin: [4 sub-groups][2 rows] (scale back, zero-point sum), private to the wave.  On return lane
 // (sub-group sgO = lane / 16, row rO = (lane / 8) % 2, quad = lane % 8) holds in o[0..3] the logits of row rO
-// for tokens 32 (sub0 + sgO) + 4 quad .. + 3; sub-groups at or beyond n_sub hold copies of the last one.
+// for tokens 32 (sub0 + sgO) + 4 quad .. + 3; those of sub-groups at or beyond n_sub are finite and mean nothing.
 // Two hooks for a caller with work of its own to interleave: loaded() is called once the wave's loads are
 // requested (work that waits for earlier loads of the caller fits there), between() once the multipliers are
 // built and read back, before the contraction (loads requested there travel while the matrix cores work).
+// The multipliers are folded per token group: with GROUP 32 four of them, a quarter of the wave each; with 64 two, half of the
+// wave each, and with 128 one, half of the wave for either row.  Wider groups leave room for both rows in the columns of a product.
 struct NoHook { __device__ void operator()() const {} };
-template <int BITS, bool BF16, typename Loaded = NoHook, typename Between = NoHook>
+template <int BITS, int GROUP, bool BF16, typename Loaded = NoHook, typename Between = NoHook>
 __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t* __restrict__ q, int row, int tile, int wave,
                                               int lane, int n_sub, float sm_scale, uint32_t* area, float2 (*fin_w)[2],
                                               float o[4], Loaded&& loaded = Loaded(), Between&& between = Between()) {
     constexpr int NW = 4 * BITS;               // code dwords per token
     constexpr int LD = NW / 4;                 // code dwords a lane quarter loads per token: 2 (2-bit) or 1 (1-bit)
+    constexpr bool WIDE = GROUP >= 64;
+    constexpr int QPL = WIDE ? 1 : 2;          // channel quads and
+    constexpr int RPL = GROUP == 128 ? 1 : 2;  // rows that a lane folds
     const int sub0 = tile * 16 + 4 * wave;     // this wave's first sub-group
     // ---- code dwords, requested first -----------------------------------------------------
     // lane = (MFMA row rA, channel quarter qd); row rA is layout lane 16 wave + rA of the tile.
@@ -62,32 +67,54 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
         for (int hf = 0; hf < 2; ++hf)
             cw[i][hf] = *reinterpret_cast<const uint4*>(kc_lane + (size_t)((4 * i + qd) * 2 + hf) * 1024);
 
-    // ---- multipliers: lane (sub-group sgP, u) folds channel quads 2u and 2u + 1 of that sub-group
-    const int sgP = lane >> 4, u = lane & 15;
-    const int subP = sub0 + sgP < n_sub ? sub0 + sgP : n_sub - 1;
-    const int group_of_sub = subP * kBlockTokens / L.group;     // the sub-groups of one token group share its metadata
-    const uint32_t* km_p = L.km + (size_t)row * L.km_stride + (size_t)group_of_sub * kD + 2 * u;
-    uint2 mt[4];                                               // (min, max) of channels 4 (2u + mq) + b, mq = .x/.y
+    // ---- multipliers: lane (token group gP of the wave, u) folds channel quads QPL u to QPL u + QPL - 1 of it, for rows r0 to r0 + RPL - 1
+    const int u = WIDE ? lane & 31 : lane & 15, gP = GROUP == 32 ? lane >> 4 : GROUP == 64 ? lane >> 5 : 0, r0 = RPL == 1 ? lane >> 5 : 0;
+    const int subP = sub0 + gP * (GROUP / 32) < n_sub ? sub0 + gP * (GROUP / 32) : n_sub - 1;
+    const uint32_t* km_p = L.km + (size_t)row * L.km_stride + (size_t)(subP / (GROUP / 32)) * kD + QPL * u;
+    uint32_t mt[4][QPL];                                       // (min, max) of channels 4 (QPL u + mq) + b
+    uint32_t qraw[RPL][2 * QPL];                               // channels 4 QPL u to 4 QPL u + 4 QPL - 1, two per word
+    if constexpr (WIDE) {
 #pragma unroll
-    for (int b = 0; b < 4; ++b) mt[b] = *reinterpret_cast<const uint2*>(km_p + b * 32);
-    uint4 qraw[2];                                             // channels 8u .. 8u + 7 of both rows
+        for (int b = 0; b < 4; ++b) mt[b][0] = km_p[b * 32];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) qraw[r] = *reinterpret_cast<const uint4*>(q + ((size_t)row * 2 + r) * kD + 8 * u);
+        for (int r = 0; r < RPL; ++r) {
+            const uint2 w = *reinterpret_cast<const uint2*>(q + ((size_t)row * 2 + r0 + r) * kD + 4 * u);
+            qraw[r][0] = w.x;
+            qraw[r][1] = w.y;
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint2 w = *reinterpret_cast<const uint2*>(km_p + b * 32);
+            mt[b][0] = w.x;
+            mt[b][1] = w.y;
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const uint4 w = *reinterpret_cast<const uint4*>(q + ((size_t)row * 2 + r) * kD + 8 * u);
+            qraw[r][0] = w.x;
+            qraw[r][1] = w.y;
+            qraw[r][2] = w.z;
+            qraw[r][3] = w.w;
+        }
+    }
 
     loaded();
 
-    float x[2][8], qz[2] = {0.0f, 0.0f}, mx[2] = {0.0f, 0.0f};
+    float x[RPL][4 * QPL], qz[RPL], mx[RPL];
 #pragma unroll
-    for (int mq = 0; mq < 2; ++mq)
+    for (int r = 0; r < RPL; ++r) qz[r] = mx[r] = 0.0f;
+#pragma unroll
+    for (int mq = 0; mq < QPL; ++mq)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            const uint32_t m = mq ? mt[b].y : mt[b].x;
+            const uint32_t m = mt[b][mq];
             float sc, z;
             derive_scale_zero<BITS>(widen16<BF16>(m & 0xFFFFu), widen16<BF16>(m >> 16), L.one_bit_plain, sc, z);
             const int e = 4 * mq + b;
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const uint32_t pair = comp_i8(qraw[r], e / 2);
+            for (int r = 0; r < RPL; ++r) {
+                const uint32_t pair = qraw[r][e / 2];
                 const float qv = widen16<BF16>((e & 1) ? pair >> 16 : pair & 0xFFFFu);
                 x[r][e] = qv * sc;
                 qz[r] = __builtin_fmaf(qv, z, qz[r]);
@@ -96,31 +123,37 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
         }
     // the factor by which the codes of a channel quad arrive multiplied: 4^(quad % 2) for 2-bit
     // codes, 2^(quad % 4) for 1-bit codes
-    float cls[2];
-    if constexpr (BITS == 2) {
-        cls[0] = 1.0f;
-        cls[1] = 0.25f;
-    } else {
-        cls[0] = (u & 1) ? 0.25f : 1.0f;
-        cls[1] = (u & 1) ? 0.125f : 0.5f;
+    float cls[QPL];
+#pragma unroll
+    for (int mq = 0; mq < QPL; ++mq) {
+        const uint32_t quad = QPL * u + mq;
+        cls[mq] = __uint_as_float((127u - (BITS == 2 ? 2u * (quad & 1u) : quad & 3u)) << 23);
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < RPL; ++r) {
         qz[r] = row16_sum(qz[r]);
+        uint32_t top = row16_max_bits(__float_as_uint(mx[r]));
+        if constexpr (WIDE) {
+            const auto z2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(qz[r]), __float_as_uint(qz[r]), false, false);
+            qz[r] = __uint_as_float(z2[0]) + __uint_as_float(z2[1]);
+            const auto t2 = __builtin_amdgcn_permlane16_swap(top, top, false, false);
+            top = max_u32(t2[0], t2[1]);
+        }
         // |x| < 2^(E - 126) with E the largest one's exponent field: x * 2^(156 - E) stays below 2^30
-        uint32_t E = row16_max_bits(__float_as_uint(mx[r])) >> 23;
+        uint32_t E = top >> 23;
         E = E < 30u ? 30u : (E > 254u ? 254u : E);
         const float up = __uint_as_float((283u - E) << 23);
-        if (u == 0) fin_w[sgP][r] = make_float2(__uint_as_float((E - 29u) << 23) * sm_scale, qz[r] * sm_scale);
-        const float up_c[2] = {up * cls[0], up * cls[1]};
+        if (u == 0) fin_w[gP][r0 + r] = make_float2(__uint_as_float((E - 29u) << 23) * sm_scale, qz[r] * sm_scale);
+        uint32_t* const at = area + gP * kSubStride + (r0 + r) * (4 * kPieceStride) + QPL * u;
 #pragma unroll
-        for (int mq = 0; mq < 2; ++mq) {
+        for (int mq = 0; mq < QPL; ++mq) {
+            const float up_c = up * cls[mq];
             uint32_t y[4], planes[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) y[b] = (uint32_t)(int)(x[r][4 * mq + b] * up_c[mq]);
+            for (int b = 0; b < 4; ++b) y[b] = (uint32_t)(int)(x[r][4 * mq + b] * up_c);
             signed_byte_planes(y, planes);
 #pragma unroll
-            for (int pp = 0; pp < 4; ++pp) area[sgP * kSubStride + (r * 4 + pp) * kPieceStride + 2 * u + mq] = planes[pp];
+            for (int pp = 0; pp < 4; ++pp) at[pp * kPieceStride + mq] = planes[pp];
         }
     }
     // The lanes of a wave run in lockstep and LDS serves one wave's accesses in order: a
@@ -129,16 +162,17 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-    // B operands of this lane: column (sub-group sgB, byte p), channel quarter qd; the 16 k-slots
-    // of step ks are channel quads m0 .. m0 + 3 in the order the masked code bytes have
-    const int sgB = (lane & 15) >> 2, p = lane & 3;
-    v4i bop[2][2];
+    // B operands of this lane, channel quarter qd: column (sub-group cB, byte p) for either row, or with wider groups (half cB of the
+    // wave, row, byte p); the 16 k-slots of step ks are channel quads m0 .. m0 + 3 in the order the masked code bytes have
+    constexpr int NB = WIDE ? 1 : 2;
+    const int cB = WIDE ? (lane & 15) >> 3 : (lane & 15) >> 2, rB = WIDE ? (lane >> 2) & 1 : 0, p = lane & 3;
+    v4i bop[2][NB];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         const int m0 = BITS == 2 ? 16 * ks + 4 * qd : 8 * qd + 4 * ks;
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
-            bop[ks][r] = *reinterpret_cast<const v4i*>(area + sgB * kSubStride + (r * 4 + p) * kPieceStride + m0);
+        for (int r = 0; r < NB; ++r)
+            bop[ks][r] = *reinterpret_cast<const v4i*>(area + (GROUP == 128 ? 0 : cB) * kSubStride + ((rB + r) * 4 + p) * kPieceStride + m0);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();                 // every lane has read its B operands: the area is free
@@ -148,14 +182,16 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
     // ---- the contraction: per token (half hf, j of the lane's four) two k-steps, two rows.
     // Result register v of lane (column n, quarter qq) is MFMA row 4 qq + v: sub-group qq of the
     // wave, quad lane v, i.e. token 32 (sub0 + qq) + 8 v + 4 hf + j.  It is wanted where the
-    // column's sub-group is qq too; those quads go to block (sub-group, row, hf) of the area as
+    // column's sub-group is qq too (or lies in its half); those quads go to block (sub-group, row, hf) of the area as
     // [token j][byte p][quad lane v] (the lanes that write differ in p and the block: 16 bytes each, side by side), the
     // blocks 4 dwords further apart than their size so that the lanes that read one position of 16 different blocks hit 16 different banks.
+    const bool mine = cB == (WIDE ? qd >> 1 : qd);
+    uint32_t* const res = area + (qd * 4 + rB * 2) * kResBlock + p * 4;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            v4i acc[2];
+            v4i acc[NB];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 v4i a;
@@ -167,13 +203,12 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
                     a = (v4i){(int)(t & 0x01010101u), (int)(t & 0x02020202u), (int)(t & 0x04040404u), (int)(t & 0x08080808u)};
                 }
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
+                for (int r = 0; r < NB; ++r)
                     acc[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bop[ks][r], ks == 0 ? (v4i){0, 0, 0, 0} : acc[r], 0, 0, 0);
             }
-            if (sgB == qd) {
+            if (mine) {
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    *reinterpret_cast<v4i*>(area + ((qd * 2 + r) * 2 + hf) * kResBlock + (j * 4 + p) * 4) = acc[r];
+                for (int r = 0; r < NB; ++r) *reinterpret_cast<v4i*>(res + (2 * r + hf) * kResBlock + j * 16) = acc[r];
             }
         }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -189,7 +224,7 @@ __device__ __forceinline__ void score_i8_wave(const LayerView& L, const uint16_t
     for (int pp = 0; pp < 4; ++pp)
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[pp][j] = (int)blk[(j * 4 + pp) * 4];
-    const float2 f = fin_w[sgO][rO];
+    const float2 f = fin_w[GROUP == 32 ? sgO : GROUP == 64 ? sgO >> 1 : 0][rO];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float t = of_byte_planes(s[0][j], s[1][j], s[2][j], s[3][j]);

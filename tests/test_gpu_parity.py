@@ -566,6 +566,28 @@ def test_append_carried_by_the_scoring_launch(Hq, Hkv, dtype, bits, g, R):
         c.close()
 
 
+@pytest.mark.parametrize("one_pass", [False, True])
+@pytest.mark.parametrize("bits,g,dtype", [(2, 64, synth.FP16), (1, 64, synth.BF16), (2, 128, synth.BF16), (1, 128, synth.FP16)])
+def test_integer_scoring_of_wide_token_groups(bits, g, dtype, one_pass):
+    """Token groups of 64 and 128: half a wave folds a group's multipliers, both rows share a product's columns.  A wave with one group of
+    its two, a last tile of one to four waves, one token group in all; token groups' key scales 256 apart, so that one
+    group's multipliers with another's codes show."""
+    from tests.harness import Case
+    for S in (g, g + 70, 3 * g + 64, 512 + g + 64, 1024 + 5 * 64 + 70):
+        binding.debug_kernel_choice(binding.KEEP_ONE_PASS_LOGITS)
+        c = Case(1, 2, 2, S, dtype, bits, g, 24, R=g, seed=3900 + S + bits, async_select=2, one_pass=one_pass)
+        try:
+            k = synth.from_bits(c.k_bits, dtype) * np.where((np.arange(S) // g) % 2 == 1, 16.0, 1.0 / 16.0).astype(np.float32)[None, None, :, None]
+            c.k_bits = synth.to_bits(k, dtype).reshape(c.k_bits.shape)
+            c.load()
+            for t in range(2):
+                c.append_token(t)
+                c.decode_step()                  # logits to 2e-4 of the largest, selection, outputs
+        finally:
+            c.close()
+            binding.debug_kernel_choice(0)
+
+
 @pytest.mark.parametrize("Hq,Hkv,S,dtype,bits,g,R,k", [
     (2, 2, 1700, synth.FP16, 2, 32, 64, 48),        # ragged tail: 1664 quantised positions = 3 chunks and a quarter
     (3, 3, 2100, synth.BF16, 2, 64, 64, 300),       # g = 64: one value group per channel set
