@@ -31,8 +31,10 @@ struct LayerView {
 
 // quantize_append: flush `n_flush` groups starting at token Nq0, whose sources are
 // the ring (tokens < N0) or k_new/v_new (tokens >= N0, index t - N0 of n_new).
+// copy_from >= 0: launch_append_copy (with that as ring_from) in the same launch, where the ring's tokens that are quantised and those that
+// are written do not share places
 hipError_t launch_flush(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0,
-                        int Nq0, int n_flush, hipStream_t stream);
+                        int Nq0, int n_flush, int copy_from, hipStream_t stream);
 // copy the n_new tokens to the host store (all) and to the ring (tokens >= ring_from)
 hipError_t launch_append_copy(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0,
                               int ring_from, hipStream_t stream);

@@ -63,9 +63,8 @@ __device__ __forceinline__ uint32_t quantize_near(float x, float z, float rs, bo
 // values over the G/4 lanes of a channel group (DPP).  Codes are assembled into the device
 // layout's 16-byte pieces in LDS and leave as coalesced 16-byte stores.
 template <int BITS, int G, bool BF16>
-__global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const uint16_t* __restrict__ k_new,
-                                                              const uint16_t* __restrict__ v_new, int n_new,
-                                                              int N0, int Nq0) {
+__device__ __forceinline__ void flush_group(const LayerView& L, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int n_new,
+                                            int N0, int t0, int row) {
     constexpr int M = kD / G;        // value groups per token
     constexpr int NT = G / 8;        // tokens per thread
     constexpr int NW = 4 * BITS;     // K code dwords per token
@@ -79,8 +78,6 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
 
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     const int hf = lane / 32, j = lane % 32;
-    const int row = blockIdx.y;
-    const int t0 = Nq0 + blockIdx.x * G;
 
     uint2 kraw[NT], vraw[NT];
 #pragma unroll
@@ -268,11 +265,9 @@ __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const
 // Offload: every new token goes to the pinned host copy C; tokens that stay
 // unquantised after this call also go to the VRAM residual ring.
 // 32 lanes x 16 B move one 512-byte (K,V) pair.
-__global__ __launch_bounds__(256) void append_copy_kernel(LayerView L, const uint4* __restrict__ k_new,
-                                                          const uint4* __restrict__ v_new, int n_new, int N0,
-                                                          int ring_from) {
-    const int row = blockIdx.y;
-    const int tn = blockIdx.x * 8 + threadIdx.x / 32;
+__device__ __forceinline__ void copy_tokens(const LayerView& L, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new, int n_new, int N0,
+                                            int ring_from, int first, int row) {
+    const int tn = first + threadIdx.x / 32;
     if (tn >= n_new) return;
     const int part = threadIdx.x % 32;
     const size_t src = ((size_t)row * n_new + tn) * 16 + (part % 16);
@@ -280,6 +275,34 @@ __global__ __launch_bounds__(256) void append_copy_kernel(LayerView L, const uin
     const int t = N0 + tn;
     reinterpret_cast<uint4*>(L.host)[((size_t)row * L.max_seq + t) * 32 + part] = v;
     if (t >= ring_from) reinterpret_cast<uint4*>(L.ring)[((size_t)row * L.R + (t % L.R)) * 32 + part] = v;
+}
+constexpr int kCopyTokens = kFlushThreads / 32;   // of a workgroup
+
+template <int BITS, int G, bool BF16>
+__global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
+                                                              int n_new, int N0, int Nq0) {
+    flush_group<BITS, G, BF16>(L, k_new, v_new, n_new, N0, Nq0 + (int)blockIdx.x * G, blockIdx.y);
+}
+
+__global__ __launch_bounds__(kFlushThreads) void append_copy_kernel(LayerView L, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
+                                                                    int n_new, int N0, int ring_from) {
+    copy_tokens(L, k_new, v_new, n_new, N0, ring_from, (int)blockIdx.x * kCopyTokens, blockIdx.y);
+}
+
+// Both in one launch, the workgroups that quantise spread evenly among those that copy, so that neither the host link nor the memory waits
+// for the other.  us, opening a context, loading two layers, the first token and closing it, two launches / one: 32 x 2048 tokens 1526 / 1510, 8 x
+// 8000 1485 / 1458, 4 x 600 305 / 285.  (Stores to the host that bypass the caches: 32 x 2048 1500 -> 1513, 32 x 1000 871 -> 903.)
+template <int BITS, int G, bool BF16>
+__global__ __launch_bounds__(kFlushThreads) void flush_copy_kernel(LayerView L, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
+                                                                   int n_new, int N0, int Nq0, int n_flush, int ring_from) {
+    const int id = blockIdx.x, n_copy = (n_new + kCopyTokens - 1) / kCopyTokens;
+    const int quantise = n_flush * L.rows, every = (quantise + n_copy * L.rows) / quantise, nth = id / every;
+    if (id % every == 0 && nth < quantise) {
+        flush_group<BITS, G, BF16>(L, k_new, v_new, n_new, N0, Nq0 + nth % n_flush * G, nth / n_flush);
+    } else {
+        const int c = id - (nth + 1 < quantise ? nth + 1 : quantise);
+        copy_tokens(L, (const uint4*)k_new, (const uint4*)v_new, n_new, N0, ring_from, c % n_copy * kCopyTokens, c / n_copy);
+    }
 }
 
 // Canonical view: one thread per (token, channel).
@@ -324,16 +347,19 @@ __global__ __launch_bounds__(128) void export_kernel(LayerView L, int Nq, uint8_
     }
 }
 
+// copy_from: the tokens from there on also go to the ring, and the copy is part of the launch; < 0: the quantiser alone
 template <int BITS, int G>
 hipError_t flush_dispatch(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0, int Nq0,
-                          int n_flush, hipStream_t stream) {
-    const dim3 grid(n_flush, L.rows), block(kFlushThreads);
-    if (L.bf16)
-        hipLaunchKernelGGL((flush_kernel<BITS, G, true>), grid, block, 0, stream, L, (const uint16_t*)k_new,
-                           (const uint16_t*)v_new, n_new, N0, Nq0);
-    else
-        hipLaunchKernelGGL((flush_kernel<BITS, G, false>), grid, block, 0, stream, L, (const uint16_t*)k_new,
-                           (const uint16_t*)v_new, n_new, N0, Nq0);
+                          int n_flush, int copy_from, hipStream_t stream) {
+    const dim3 grid(n_flush, L.rows), both((n_flush + (n_new + kCopyTokens - 1) / kCopyTokens) * L.rows), block(kFlushThreads);
+    const uint16_t *k = (const uint16_t*)k_new, *v = (const uint16_t*)v_new;
+    if (copy_from >= 0) {
+        if (L.bf16) hipLaunchKernelGGL((flush_copy_kernel<BITS, G, true>), both, block, 0, stream, L, k, v, n_new, N0, Nq0, n_flush, copy_from);
+        else hipLaunchKernelGGL((flush_copy_kernel<BITS, G, false>), both, block, 0, stream, L, k, v, n_new, N0, Nq0, n_flush, copy_from);
+    } else {
+        if (L.bf16) hipLaunchKernelGGL((flush_kernel<BITS, G, true>), grid, block, 0, stream, L, k, v, n_new, N0, Nq0);
+        else hipLaunchKernelGGL((flush_kernel<BITS, G, false>), grid, block, 0, stream, L, k, v, n_new, N0, Nq0);
+    }
     return hipGetLastError();
 }
 
@@ -353,24 +379,21 @@ hipError_t export_dispatch(const LayerView& L, int Nq, uint8_t* k_codes, uint16_
 }  // namespace
 
 hipError_t launch_flush(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0, int Nq0,
-                        int n_flush, hipStream_t stream) {
+                        int n_flush, int copy_from, hipStream_t stream) {
     if (n_flush <= 0) return hipSuccess;
-    if (L.bits == 2 && L.group == 32) return flush_dispatch<2, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 2 && L.group == 64) return flush_dispatch<2, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 1 && L.group == 32) return flush_dispatch<1, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 2 && L.group == 128) return flush_dispatch<2, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 1 && L.group == 128) return flush_dispatch<1, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 1 && L.group == 64) return flush_dispatch<1, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 4 && L.group == 32) return flush_dispatch<4, 32>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 4 && L.group == 64) return flush_dispatch<4, 64>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
-    if (L.bits == 4 && L.group == 128) return flush_dispatch<4, 128>(L, k_new, v_new, n_new, N0, Nq0, n_flush, stream);
+#define SPC_FLUSH(B_, G_) \
+    if (L.bits == B_ && L.group == G_) return flush_dispatch<B_, G_>(L, k_new, v_new, n_new, N0, Nq0, n_flush, copy_from, stream);
+    SPC_FLUSH(1, 32) SPC_FLUSH(1, 64) SPC_FLUSH(1, 128)
+    SPC_FLUSH(2, 32) SPC_FLUSH(2, 64) SPC_FLUSH(2, 128)
+    SPC_FLUSH(4, 32) SPC_FLUSH(4, 64) SPC_FLUSH(4, 128)
+#undef SPC_FLUSH
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_append_copy(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0,
                               int ring_from, hipStream_t stream) {
     if (n_new <= 0) return hipSuccess;
-    const dim3 grid((n_new + 7) / 8, L.rows), block(256);
+    const dim3 grid((n_new + kCopyTokens - 1) / kCopyTokens, L.rows), block(kFlushThreads);
     hipLaunchKernelGGL(append_copy_kernel, grid, block, 0, stream, L, (const uint4*)k_new, (const uint4*)v_new,
                        n_new, N0, ring_from);
     return hipGetLastError();

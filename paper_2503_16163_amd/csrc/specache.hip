@@ -658,14 +658,17 @@ int specache_quantize_append(specache_ctx* ctx, int32_t layer, const void* k_new
         return fail(ctx, SPECACHE_ESTATE, "inconsistent token counts");
     const int Nq1 = L.Nq + n_flush * ctx->cfg.group, N1 = L.N + n_new;
     hipStream_t st = (hipStream_t)stream;
-    // the flush reads residual tokens from the ring, so it precedes the ring update
+    const int ring_from = Nq1 > L.N ? Nq1 : L.N;
+    // The flush reads residual tokens from the ring, so it precedes the ring update, unless that leaves their places alone: nothing in
+    // the ring, or not more than it holds (tokens a ring's length apart share a place).  Timed, the two are launches of their own.
+    const bool together = n_flush > 0 && !ctx->timing && (L.N == L.Nq || N1 - L.Nq <= ctx->cfg.residual);
     if (n_flush > 0) {
         TimedLaunch t(ctx, st, SPECACHE_K_FLUSH);
-        SPC_HIP(ctx, launch_flush(L.view, k_new, v_new, n_new, L.N, L.Nq, n_flush, st));
+        SPC_HIP(ctx, launch_flush(L.view, k_new, v_new, n_new, L.N, L.Nq, n_flush, together ? ring_from : -1, st));
     }
-    {
+    if (!together) {
         TimedLaunch t(ctx, st, SPECACHE_K_APPEND_COPY);
-        SPC_HIP(ctx, launch_append_copy(L.view, k_new, v_new, n_new, L.N, Nq1 > L.N ? Nq1 : L.N, st));
+        SPC_HIP(ctx, launch_append_copy(L.view, k_new, v_new, n_new, L.N, ring_from, st));
     }
     L.N = N1;
     L.Nq = Nq1;

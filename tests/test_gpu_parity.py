@@ -566,6 +566,26 @@ def test_append_carried_by_the_scoring_launch(Hq, Hkv, dtype, bits, g, R):
         c.close()
 
 
+@pytest.mark.parametrize("bits,g,R", [(2, 32, 64), (1, 64, 64), (4, 32, 128), (2, 128, 256)])
+def test_appends_that_quantise_and_copy_at_once(bits, g, R):
+    """Quantiser and copy are one launch where the ring's places do not collide: nothing in the ring, or no more appended than it holds;
+    two otherwise.  Appends of every kind in a row, their codes, offloaded rows and (through the residual) outputs against the oracle."""
+    from tests.harness import Case
+    # from an empty cache: one to leave a residual, then up to the ring's length, exactly that, one more, more than twice of it, one token at a time
+    sizes = [R + 3, g - 3, R - g + 1, 7, g, 2 * R + 5, 1, g + 1] + [1] * (g + 2) + [3 * R]
+    bounds = np.cumsum(sizes)
+    c = Case(1, 2, 2, int(bounds[-1]), synth.FP16, bits, g, 16, R=R, seed=4700 + g + bits)
+    try:
+        c.load(chunks=[int(b) for b in bounds[:-1]])
+        c.check_quantized()
+        c.check_offload(first=0, count=c.S)
+        for t in range(2):
+            c.append_token(t)
+            c.decode_step()
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("one_pass", [False, True])
 @pytest.mark.parametrize("bits,g,dtype", [(2, 64, synth.FP16), (1, 64, synth.BF16), (2, 128, synth.BF16), (1, 128, synth.FP16)])
 def test_integer_scoring_of_wide_token_groups(bits, g, dtype, one_pass):
