@@ -46,10 +46,32 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ h
     }
 }
 
+// One read per lane, and the index of a group's next pair loaded behind the request for this one, so that the link need not wait for the
+// list between two of them.
+__global__ __launch_bounds__(256) void gather_ahead_kernel(const uint4* __restrict__ host, int max_seq, int k, int total,
+                                                           const int32_t* __restrict__ idx, uint4* __restrict__ slot,
+                                                           int32_t* __restrict__ slot_idx) {
+    __builtin_amdgcn_s_setprio(3);
+    const int part = threadIdx.x % 32, stride = gridDim.x * 8;
+    auto index_of = [&](int e) {
+        const int i = e < total ? idx[e] : -1;
+        return i < max_seq ? i : -1;                     // never read outside the store
+    };
+    int e = blockIdx.x * 8 + threadIdx.x / 32, src = index_of(e);
+    while (e < total) {
+        const uint4 v = src >= 0 ? host[((size_t)(e / k) * max_seq + src) * 32 + part] : make_uint4(0, 0, 0, 0);
+        const int next = index_of(e + stride);
+        if (part == 0) slot_idx[e] = src;
+        if (src >= 0) slot[(size_t)e * 32 + part] = v;
+        src = next;
+        e += stride;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_gather(const LayerView& L, int Nq, const int32_t* idx, uint16_t* slot, int32_t* slot_idx,
-                         bool link_shared, hipStream_t stream) {
+                         bool link_shared, bool alone, hipStream_t stream) {
     const int total = L.rows * L.topk;
     // 16 workgroups x 4 reads per lane = 256 KB of host reads in flight, issued at raised wave
     // priority.  Measured on MI355X at 32 heads x 256 pairs per layer: beside the other kernels
@@ -81,9 +103,22 @@ hipError_t launch_gather(const LayerView& L, int Nq, const int32_t* idx, uint16_
         in_flight = 1;
         max_grid = 32;
     }
+    // The list is read ahead where nothing of this context runs beside the fetch, and where a step is little else than fetches.  us a pass without
+    // / so: one query row with its own selection, 32 x 8192 382 / 372, 8 x 8000 228 / 223; a step's fetches on two streams, 512 x 2048, k = 128
+    // 1292 / 1267, 32 x 8192, k = 512 689 / 645, 256 x 1000, k = 32 174 / 170.  With more to score for a pair the attention kernels pay for it: 8 x
+    // 60000, k = 256 147 / 150, 8 x 131072, k = 1024 324 / 348.
+    const bool ahead = alone || (link_shared && keys_per_pair < 64.0);
+    if (ahead) {
+        in_flight = 1;
+        max_grid = 32;
+    }
     int grid = (total + 8 * in_flight - 1) / (8 * in_flight);
     if (grid > max_grid) grid = max_grid;
     if (grid < 1) return hipSuccess;
+    if (ahead) {
+        SPC_LAUNCH(gather_ahead_kernel, dim3(grid), dim3(256), stream, (const uint4*)L.host, L.max_seq, L.topk, total, idx, (uint4*)slot, slot_idx);
+        return hipGetLastError();
+    }
     const auto kernel = in_flight == 1 ? gather_kernel<1> : in_flight == 2 ? gather_kernel<2> : in_flight == 3 ? gather_kernel<3> : gather_kernel<4>;
     SPC_LAUNCH(kernel, dim3(grid), dim3(256), stream, (const uint4*)L.host, L.max_seq, L.topk, total, idx, (uint4*)slot, slot_idx);
     return hipGetLastError();

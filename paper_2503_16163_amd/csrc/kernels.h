@@ -92,9 +92,10 @@ hipError_t launch_topk(int rows, int Nq, int k, const uint32_t* keys, size_t key
                        const TopkScratch& scratch, hipStream_t stream);
 
 // gather rows idx[row][j] of the host store into slot [rows][k][256] and slot_idx [rows][k];
-// Nq (quantised positions of the layer) and link_shared (another gather runs beside this one) only pace the transfer
+// Nq (quantised positions of the layer), link_shared (another gather runs beside this one) and alone (on the stream that scored: nothing of this
+// context runs beside it) only pace the transfer
 hipError_t launch_gather(const LayerView& L, int Nq, const int32_t* idx, uint16_t* slot, int32_t* slot_idx,
-                         bool link_shared, hipStream_t stream);
+                         bool link_shared, bool alone, hipStream_t stream);
 
 // both in one launch: a row's pairs are fetched by the workgroup that selected them
 bool selects_and_gathers(int rows, int Nq, int k);   // where that is the better way

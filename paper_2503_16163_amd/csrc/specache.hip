@@ -396,7 +396,8 @@ int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int sl
             SPC_HIP(ctx, launch_select_gather(L.view, Nq, L.keys, ctx->logit_stride, select_out, L.slot[slot], L.slot_idx[slot],
                                               link_shared, st));
         else
-            SPC_HIP(ctx, launch_gather(L.view, Nq, idx, L.slot[slot], L.slot_idx[slot], link_shared, st));
+            SPC_HIP(ctx, launch_gather(L.view, Nq, idx, L.slot[slot], L.slot_idx[slot], link_shared,
+                                       L.idx_ready_recorded && L.idx_ready_stream == st, st));
         gathered_carried = gathered.landed();
         ctx->last_gather_stream = st;
         ctx->last_gather_stream_set = true;

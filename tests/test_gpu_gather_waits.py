@@ -54,3 +54,38 @@ def test_steps_read_what_their_layer_fetched(layers, sides, change):
     for _ in range(2):
         got = run(True)
         assert torch.equal(got, want), (got - want).abs().nan_to_num(nan=1e9).amax(dim=(1, 2, 3, 4, 5))
+
+
+@pytest.mark.parametrize("B,H,S,k", [(1, 1, 300, 5), (1, 3, 900, 33), (3, 5, 700, 200), (5, 30, 400, 31), (1, 1, 1000, 4000)])
+def test_fetches_that_read_the_list_ahead_stage_the_same_pairs(B, H, S, k):
+    """A fetch on the stream that scored, or between fetches on two streams where little is scored for a pair, reads its list ahead; one on a side
+    stream does not.  Fewer pairs than a launch takes at a time, more, none a multiple of it; empty and impossible places in the list."""
+    import torch
+    from paper_2503_16163_amd import binding
+    gen = torch.Generator(device="cpu").manual_seed(S + k)
+    q = synth.make_queries_device(14, 1, B, H, 128, synth.FP16).view(B, H, 2, 128)[:, :, :1].contiguous()
+    kd, vd = synth.make_kv_device(14, B, H, S, 128, synth.FP16)
+    idx = torch.randint(0, S, (B, H, k), generator=gen, dtype=torch.int32)
+    idx[torch.rand((B, H, k), generator=gen) < 0.1] = -1
+    idx[0, 0, 0] = 1 << 20                                   # beyond the store: nothing is fetched
+    idx = idx.cuda()
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    sc = binding.SpeCache(1, B, H, H, 2, 32, (S + 63) // 64 * 64, k, synth.FP16)
+    try:
+        sc.quantize_append(0, kd, vd, S)
+        own = torch.zeros((B, H, k), dtype=torch.int32, device="cuda")
+        outs = []
+        for where in (sides[0], None, sides[0], sides[1], sides[0]):     # None: the stream that scores; the last two alternate
+            sc.debug_poison_slot(0, 1, None)
+            sc.score_topk(0, q, 1, own)
+            torch.cuda.synchronize()
+            sc.gather(0, idx, 1, where)
+            outs.append(torch.zeros((B, H, 1, 128), dtype=torch.float32, device="cuda"))
+            sc.attend(0, q, 1, None, None, 1, outs[-1])
+            torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all()
+        for out in outs[1:]:
+            assert torch.equal(out, outs[0])
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
