@@ -576,7 +576,7 @@ hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, in
     A.n_chunks = A.n_main + (n_ex + kExtraChunk - 1) / kExtraChunk;
     if (A.n_chunks > A.max_chunks || A.n_chunks < 1) return hipErrorInvalidValue;
     A.fin = finish;
-    *merged = plan_merge(A.fin, L.rows, A.n_chunks, 2, false);
+    *merged = plan_merge(A.fin, L.rows, A.n_chunks, 2, !keys || L.rows <= kFinishFewRows);
     const dim3 grid((A.n_chunks + (A.fin.mergers ? A.fin.shares : 0)) * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
 #define SPC_AI8_B(G_, B_, F_)                                                                                              \
     do {                                                                                                                   \

@@ -150,8 +150,11 @@ inline int merge_shares_of(int n_chunks, int NR) {
 }
 // attend_partial_kernel, and rows_kernel where it only attends, leave the merge to the last chunk to arrive where the launch is no more than
 // one round of workgroups and the partials are few.  us, a launch of its own / so: one query row over 1 x 31000 9.5 / 7.4, 32 x 15800 12.5 /
-// 11.3; mergers / so: 4 bits (scoring with it), 16 x 4000 15.6 / 15.4, 32 x 6000 22.2 / 21.9.
-constexpr int kFinishMost = 64;
+// 11.3; mergers / so: 4 bits (scoring with it), 16 x 4000 15.6 / 15.4, 32 x 6000 22.2 / 21.9.  So does attend_i8_kernel where it only attends (1 x 2000
+// 8.5 / 7.6, 1 x 9000 8.7 / 7.8, 8 x 3000 8.3 / 7.7, 32 x 7000 10.1 / 9.5, 16 x 14000 10.5 / 9.7), and, scoring as well, for up to kFinishFewRows rows: a pass
+// of 16 layers with their fetches on the queue of the main stream, 1 x 1000 238 / 233, 1 x 2000 242 / 233, 1 x 9000 245 / 242, of 8 layers, 2 x 6000 129 / 126, but 8 x
+// 3000 154 / 155, 32 x 2000 251 / 254 (on queues of their own within 1 % up to 8 x 3000, 32 x 2000 168 / 171).
+constexpr int kFinishMost = 64, kFinishFewRows = 4;
 inline bool last_chunk_merges(int rows, int n_chunks, int NR) { return rows * n_chunks <= 1024 && n_chunks * NR <= kFinishMost; }
 // last_chunk: it may be left to that one
 inline bool plan_merge(Finish& fin, int rows, int n_chunks, int NR, bool last_chunk) {

@@ -94,6 +94,8 @@ def test_attend_from_static_scratch_beside_attend():
 
 @pytest.mark.parametrize("Hq,Hkv,S,bits,g,k", [
     (1, 1, 600, 2, 32, 16), (3, 3, 5000, 1, 64, 64), (2, 2, 2000, 2, 128, 300),
+    # as many rows as leave the merge to the last chunk, and one more
+    (4, 4, 600, 2, 32, 16), (5, 5, 600, 2, 32, 16), (6, 6, 3000, 1, 128, 64),
     # as many chunks as the rule takes, 128, and one more; beyond 96 a lane reads its partials in two batches
     (1, 1, 512 * 127 + 40, 2, 32, 64), (1, 1, 512 * 128 + 40, 2, 32, 64), (1, 1, 512 * 96 + 40, 2, 64, 64),
     # 4, 8 and 16 query rows: one share to sixteen, of one query row to eight
