@@ -554,6 +554,9 @@ def main():
     # and its time by itself is that of the pass without fetches
     topk_us = per_kernel_us.get("topk") or (per_kernel_ng or {}).get("topk")
     fetch_name = "gather_kernel" if per_kernel_us.get("topk") else "topk_kernel<fetch behind it>"
+    # the merge where no launch that makes the partials does it itself: up to 128 chunks of a row by one kernel, more by another
+    # (with several query rows the chunks are as long as it takes to fill the chip, and few)
+    merge_name = "attend_combine_kernel" if n_q_rows <= 2 and (Nq + 511) // 512 + (k + N - Nq + 128) // 128 > 128 else "attend_merge_kernel"
     kern = [
         entry(one_pass_name, "score + attend partial pass in one launch: packed K and V once, 16-bit pairs",
               per_kernel_us.get("score_attend"), 2 * packed + pairs, HBM_PEAK_GBS, stream_peak),
@@ -561,9 +564,9 @@ def main():
               HBM_PEAK_GBS, stream_peak),
         entry(attend_name, "mixed attention, partial pass: packed V once, 16-bit pairs (the fp32 logits it reads back are this "
                            "design's overhead, not counted)", per_kernel_us.get("attend"), packed + pairs, HBM_PEAK_GBS, stream_peak),
-        entry("attend_combine_kernel", "merge of the chunk partials (overhead of the split over the sequence: bytes = partials read)",
+        entry(merge_name, "merge of the chunk partials (overhead of the split over the sequence: bytes = partials read)",
               per_kernel_us.get("attend_combine"), rows * n_q_rows * ((Nq + 511) // 512 + 3) * 130 * 4, HBM_PEAK_GBS, stream_peak,
-              "latency-bound: one workgroup per (row, query row)"),
+              "latency-bound"),
         entry("topk_kernel", "ArgTopK: 4-byte selection keys of the speculative row (L2-resident)", topk_us,
               rows * Nq * 4, HBM_PEAK_GBS, stream_peak, "latency-bound: one workgroup per row, a chain of barrier-separated steps" +
               ("" if per_kernel_us.get("topk") else "; timed in the pass without fetches")),
@@ -579,7 +582,7 @@ def main():
     dom = max(cands, key=lambda e: e["avg_us"])
     dom_base = one_pass_key if dom["kernel"] == one_pass_name else dom["kernel"]
     workload_key = f"{args.workload}:k{k}:g{g}:b{bits}" + (f":S{S}" if args.seq else "")
-    prof = profile_figures(workload_key, [dom_base, score_name, attend_name, "topk_kernel", "topk_kernel+gather", "gather_kernel", "attend_combine_kernel"])
+    prof = profile_figures(workload_key, [dom_base, score_name, attend_name, "topk_kernel", "topk_kernel+gather", "gather_kernel", merge_name])
     traffic_tbl, traffic_src = prof["traffic"]
     for e in kern:   # measured HBM bytes per launch beside the algorithmic ones, where the profile covers the kernel
         base = {one_pass_name: one_pass_key, "topk_kernel<fetch behind it>": "topk_kernel+gather"}.get(e["kernel"], e["kernel"])

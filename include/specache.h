@@ -402,14 +402,15 @@ int specache_debug_merger_polls(int32_t polls);
  */
 enum {
     SPECACHE_K_FLUSH = 0,       /* quantise + pack of full groups            */
-    SPECACHE_K_APPEND_COPY = 1, /* offload to host store + residual update   */
+    SPECACHE_K_APPEND_COPY = 1, /* offload to host store + residual update (while this is off, a launch that
+                                   does both takes the place of the two where a call has both to do) */
     SPECACHE_K_SCORE = 2,       /* fused dequantise + q.K^T                  */
     SPECACHE_K_TOPK = 3,        /* radix select + ordered compaction         */
     SPECACHE_K_GATHER = 4,      /* host-link gather (side stream); of specache_select_gather the launch
                                    that selects and fetches (then nothing counts as K_TOPK) */
     SPECACHE_K_ATTEND = 5,      /* mixed attention: partial pass over chunks, and their merge where the
-                                   launch does that itself (rows of few chunks; then nothing counts
-                                   as K_ATTEND_COMBINE) */
+                                   launch does that itself (rows of up to 128 chunks; then nothing
+                                   counts as K_ATTEND_COMBINE) */
     SPECACHE_K_ATTEND_COMBINE = 6, /* mixed attention: merge of the chunks in a launch of its own */
     SPECACHE_K_SCORE_ATTEND = 7, /* scoring and partial pass of specache_score_attend in one launch,
                                    and the merge under the same condition   */

@@ -8,8 +8,8 @@
 // Split over the sequence: "main" workgroups take chunks of quantised positions,
 // "extra" workgroups take the 16-bit candidates (staged pairs, residual, transient
 // pair); each writes an un-normalised partial (max, sum, sum p*V), merged with the usual
-// log-sum-exp rescaling by the workgroup that completes the row (finish_row.h) where the
-// partials are few, else by a combine kernel.  Prefetched positions
+// log-sum-exp rescaling inside the launch (finish_row.h) or by a kernel of its own
+// (attend_merge_kernel; attend_combine_kernel for rows of very many chunks).  Prefetched positions
 // are removed from the main chunks by setting their logit to -inf in LDS; the
 // staged pair then enters through the extra chunks, which is Eq. 1's "replace".
 //

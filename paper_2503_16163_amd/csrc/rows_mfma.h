@@ -30,7 +30,8 @@
 // at best -> 10.3 at best, 12.3 beside the gathers; 16 x 8192, 16 query rows, g = 128: 10.8 + 40.2 -> 17.0 -> 13.6 us.  4-bit codes,
 // two launches, 32 x 16384, 2 query rows as 8 columns' worth, g = 32: scoring 13.9, attention with its merge 18.9 us at best, 16.0 and 21.4 beside
 // the gathers (the 84 MB they read need 14 us at the rate of a plain read); a decode step of a layer 70.7 -> 51 us against
-// vector-ALU kernels.
+// vector-ALU kernels.  (The figures are the kernel's without the merge of a row's chunks, which the launch does as well where they are at most
+// 128: 4.4 us of a launch of its own before, 3.6 of this one's 37.1 and 4.6 of 44.5 now, beside the fetches and a profiler.)
 // Up to 168 registers, three workgroups per compute unit; held to four it spills (as it is, both passes in groups of 32 with 8 columns' worth of
 // rows spill two registers with 2 bits, one with 1 bit where rows are missing).
 #pragma once

@@ -41,8 +41,10 @@
 // a time, so that a wave fits 64 registers and all eight waves a SIMD gets are resident at
 // once (14.8 us with four resident waves, 14.0 with six, 13.4 with eight).  What did not:
 // waves that walk several tiles with the next tile's loads in flight (15.4 - 18.3 us: fewer
-// waves, more registers), padding against LDS bank conflicts, and leaving out the key array
-// (ArgTopK ranking the logits costs it more than the store saves here).
+// waves, more registers), and leaving out the key array (ArgTopK ranking the logits costs it
+// more than the store saves here).  LDS areas without bank conflicts and a shorter
+// recombination (score_i8_wave.h), made for the launch that attends as well: 12.6 us at best
+// before, 12.0 since.
 #include "score_i8_wave.h"
 
 namespace specache {
