@@ -4,14 +4,12 @@
 // All arithmetic of the method lives in the kernels.
 #include "../../include/specache.h"
 
-#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <new>
 #include <string>
 #include <type_traits>
-#include <utility>
 #include <vector>
 
 #include "kernels.h"
@@ -74,7 +72,6 @@ struct Layer {
     bool keys_valid = false;
     int keys_Nq = 0;
     int keys_reader_slot = -1;           // slot of the select_gather that read `keys` last
-    uint64_t gather_no[2] = {0, 0};      // which of the context's gathers filled the slot last (specache_ctx::gathers)
     bool gathered_waited_set[2] = {false, false};
     hipStream_t gathered_waited[2] = {nullptr, nullptr};   // stream that has already waited for gathered[s]
     // Where scoring and attention are one call the merge of its partial results stores `scored_value` to the word `scored_word`, and the
@@ -112,12 +109,6 @@ struct specache_ctx {
     uint64_t seq = 0;            // counts the calls that order streams (see Layer)
     hipStream_t last_gather_stream = nullptr;   // stream of the previous specache_gather, of any layer
     bool last_gather_stream_set = false;
-    uint64_t gathers = 0;                       // how many there have been
-    // Which gathers of a side stream another stream has waited for: all up to a number (wait_for_gather)
-    struct Waited { hipStream_t side = nullptr, waiter = nullptr; uint64_t upto = 0; };
-    Waited waited[8];
-    int waited_next = 0;
-    std::vector<std::pair<uint64_t, hipEvent_t>> later;   // its scratch memory
     // ArgTopK on a stream of the library's own (async_select): the scoring pass stays on the caller's
     // stream, which goes on to the attention kernels while the selection runs beside them
     bool async_select = false;
@@ -334,52 +325,6 @@ int order_gather_after_attend(specache_ctx* ctx, Layer& L, int slot, hipStream_t
     return SPECACHE_OK;
 }
 
-// Stream st waits for the gather that filled `slot` of the layer last, unless it has.  A wait is a packet in the stream's queue, 2 to 3 us where the
-// queue is the side stream's, too, although its gather is long done.  So, where `ahead` allows it, a wait for a later gather of the
-// same side stream takes its place, which covers those in between: the middle one of those enqueued since, so that half of the
-// side stream's fetches need not have landed.  us a pass with a wait per layer / so, queues of their own | shared: 8 layers of 32 x 16384 203 / 204 |
-// 313 / 303, of 24 x 5003 with 8 query rows 164 / 164 | 265 / 254, of 16 x 8192 with 16 156 / 156 | 248 / 235; 32 layers of 8 x 8192 404 / 405 | 664 / 606; bound
-// by the link, 4 of 32 x 32768, k = 256 360 / 360 | 365 / 364, 12 of 8 x 30000 with 8 rows, k = 160 303 / 286 | 440 / 415.
-int wait_for_gather(specache_ctx* ctx, Layer& L, int slot, hipStream_t st, bool ahead) {
-    const hipStream_t side = L.gather_stream[slot];
-    if (side == st || (L.gathered_waited_set[slot] && L.gathered_waited[slot] == st)) return SPECACHE_OK;
-    if (!ahead) {
-        SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
-        L.gathered_waited[slot] = st;
-        L.gathered_waited_set[slot] = true;
-        return SPECACHE_OK;
-    }
-    specache_ctx::Waited* known = nullptr;
-    for (auto& w : ctx->waited)
-        if (w.upto && w.side == side && w.waiter == st) known = &w;
-    if (!known || known->upto < L.gather_no[slot]) {
-        uint64_t no = L.gather_no[slot];
-        hipEvent_t event = L.gathered[slot];
-        auto& later = ctx->later;
-        later.clear();
-        for (Layer& o : ctx->layers)
-            for (int s = 0; s < 2; ++s)
-                if (o.slot_filled[s] && o.gather_stream[s] == side && o.gather_no[s] > no) later.emplace_back(o.gather_no[s], o.gathered[s]);
-        if (later.size() >= 2) {
-            const auto mid = later.begin() + (later.size() / 2 - 1);
-            std::nth_element(later.begin(), mid, later.end());
-            no = mid->first;
-            event = mid->second;
-        }
-        SPC_HIP(ctx, hipStreamWaitEvent(st, event, 0));
-        if (!known) {
-            known = &ctx->waited[ctx->waited_next];
-            ctx->waited_next = (ctx->waited_next + 1) % 8;
-            known->side = side;
-            known->waiter = st;
-        }
-        known->upto = no;
-    }
-    L.gathered_waited[slot] = st;
-    L.gathered_waited_set[slot] = true;
-    return SPECACHE_OK;
-}
-
 // Launches the gather of `idx` into `slot` on st and records its completion.  select_out: the gather's launch also ranks
 // the layer's keys, and idx (= select_out) receives the positions it fetches.
 int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int slot, hipStream_t st, int32_t* select_out = nullptr) {
@@ -404,7 +349,6 @@ int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int sl
     }
     if (!gathered_carried) SPC_HIP(ctx, hipEventRecord(L.gathered[slot], st));
     L.gather_stream[slot] = st;
-    L.gather_no[slot] = ++ctx->gathers;
     L.gathered_waited_set[slot] = false;
     L.slot_filled[slot] = true;
     L.last_gather_idx = idx;
@@ -721,10 +665,15 @@ int specache_score_topk(specache_ctx* ctx, int32_t layer, const void* q, int32_t
 }
 
 // The layer's key array is about to be rewritten on st: the selections that read it come first.
-static int wait_for_keys_readers(specache_ctx* ctx, Layer& L, hipStream_t st, bool ahead = false) {
+static int wait_for_keys_readers(specache_ctx* ctx, Layer& L, hipStream_t st) {
     // the layer's previous selection read L.keys on the stream of the gather that followed it
     if (L.keys_reader_slot >= 0) {
-        if (int rc = wait_for_gather(ctx, L, L.keys_reader_slot, st, ahead)) return rc;
+        const int sl = L.keys_reader_slot;
+        if (L.gather_stream[sl] != st && !(L.gathered_waited_set[sl] && L.gathered_waited[sl] == st)) {
+            SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[sl], 0));
+            L.gathered_waited[sl] = st;
+            L.gathered_waited_set[sl] = true;
+        }
         L.keys_reader_slot = -1;
     }
     if (L.selected_pending) {
@@ -946,8 +895,8 @@ static int attend_impl(specache_ctx* ctx, int32_t layer, const void* q, int32_t 
         scratch.max_chunks = chunks;
     }
     hipStream_t st = (hipStream_t)stream;
-    if (slot >= 0)
-        if (int rc = wait_for_gather(ctx, L, slot, st, false)) return rc;
+    if (slot >= 0 && L.gather_stream[slot] != st && !(L.gathered_waited_set[slot] && L.gathered_waited[slot] == st))
+        SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
     if (rescore)
         if (int rc = score_again(ctx, L, st)) return rc;
     // The layer's counters go with the context's scratch, which calls of one context share in any case.  A call with scratch memory of
@@ -999,14 +948,9 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     if (slot < -1 || slot > 1) return fail(ctx, SPECACHE_EINVAL, "slot must be -1, 0 or 1");
     if (slot >= 0 && !L.slot_filled[slot]) return fail(ctx, SPECACHE_ESTATE, "slot was never gathered");
     hipStream_t st = (hipStream_t)stream;
-    // Under capture the word is no order: a replayed merge stores the value of its capture again, and the selection's
-    // stream, if it is not part of the capture, would wait at once for a value that only a replay stores.  An event it is, and of
-    // the events only those that have to be waited for, since others may lie outside the capture.
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
-    if (int rc = wait_for_keys_readers(ctx, L, st, !captured)) return rc;
-    if (slot >= 0)
-        if (int rc = wait_for_gather(ctx, L, slot, st, !captured)) return rc;
+    if (int rc = wait_for_keys_readers(ctx, L, st)) return rc;
+    if (slot >= 0 && L.gather_stream[slot] != st && !(L.gathered_waited_set[slot] && L.gathered_waited[slot] == st))
+        SPC_HIP(ctx, hipStreamWaitEvent(st, L.gathered[slot], 0));
     const bool keep = (kernel_choice() & kChoiceKeepLogits) != 0;
     LayerView view = L.view;
     if (carry) {
@@ -1015,6 +959,10 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
         view.tail_N0 = L.N;
     }
     const int N1 = L.N + (carry ? 1 : 0);
+    // Under capture the word is no order: a replayed merge stores the value of its capture again, and the selection's
+    // stream, if it is not part of the capture, would wait at once for a value that only a replay stores.  An event it is.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
     const bool by_word = !captured && words_may_order(ctx);
     bool scored_carried = false, merged = false;
     Finish finish;

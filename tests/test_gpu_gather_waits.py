@@ -1,5 +1,6 @@
-"""Waits of the caller's stream for the fetches of its side streams: a wait may cover several layers' fetches, and every step still reads
-the pairs that its own layer fetched, whichever streams the layers use and however they change."""
+"""Waits of the caller's stream for the fetches of its side streams: every step reads the pairs that its own layer fetched, whichever streams
+the layers use and however they change, and waits for no other layer's fetch."""
+import ctypes
 import random
 
 import pytest
@@ -54,6 +55,111 @@ def test_steps_read_what_their_layer_fetched(layers, sides, change):
     for _ in range(2):
         got = run(True)
         assert torch.equal(got, want), (got - want).abs().nan_to_num(nan=1e9).amax(dim=(1, 2, 3, 4, 5))
+
+
+class ThreeLayers:
+    """Three layers with a prompt and a list each; a side stream whose kernels run beside those of the caller's stream; sleeps of about 100 ms."""
+
+    def __init__(self):
+        import torch
+        from paper_2503_16163_amd import binding
+        self.torch = torch
+        B, H, S, k = 1, 4, 700, 16
+        self.sc = binding.SpeCache(3, B, H, H, 2, 32, 768, k, synth.FP16, async_select=2)
+        kd, vd = synth.make_kv_device(21, B, H, S, 128, synth.FP16)
+        self.q = synth.make_queries_device(21, 1, B, H, 128, synth.FP16).view(B, H, 2, 128).contiguous()
+        self.idx = torch.arange(k, dtype=torch.int32, device="cuda").mul(7).expand(B, H, k).contiguous()
+        self.out = torch.zeros((B, H, 2, 128), dtype=torch.float32, device="cuda")
+        for L in range(3):
+            self.sc.quantize_append(L, kd, vd, S)
+        self.main = torch.cuda.current_stream()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        torch.cuda._sleep(1000000)
+        b.record()
+        torch.cuda.synchronize()
+        self.cycles = int(1000000 * 100.0 / a.elapsed_time(b))
+        self.side = next((s for s in (torch.cuda.Stream() for _ in range(8)) if self.beside(s)), None)
+        if self.side is None:
+            pytest.skip("every stream shares the caller's hardware queue")
+
+    def sleep(self, stream):
+        with self.torch.cuda.stream(stream):
+            self.torch.cuda._sleep(self.cycles)
+        end = self.torch.cuda.Event(enable_timing=True)
+        end.record(stream)
+        return end
+
+    def beside(self, stream):
+        end = self.sleep(stream)
+        self.out.zero_()
+        done = self.torch.cuda.Event(enable_timing=True)
+        done.record(self.main)
+        self.torch.cuda.synchronize()
+        return done.elapsed_time(end) > 10.0
+
+    def attend(self):
+        self.sc.score_attend(0, self.q, 2, None, None, 0, self.out)
+
+    def want(self):
+        """The output with layer 0's pairs staged, everything in turn; then its slot is spoilt."""
+        self.sc.gather(0, self.idx, 0, self.side)
+        self.torch.cuda.synchronize()
+        self.attend()
+        self.torch.cuda.synchronize()
+        want = self.out.clone()
+        self.sc.debug_poison_slot(0, 0, None)
+        self.out.zero_()
+        self.torch.cuda.synchronize()
+        return want
+
+
+@pytest.fixture
+def three_layers():
+    t = ThreeLayers()
+    yield t
+    t.torch.cuda.synchronize()
+    t.sc.close()
+
+
+def test_a_step_does_not_wait_for_later_fetches_of_other_layers(three_layers):
+    """A caller may hold its side stream back between two layers' fetches until the first layer's step is through."""
+    t = three_layers
+    want = t.want()
+    t.sc.gather(0, t.idx, 0, t.side)
+    held = t.sleep(t.side)
+    t.sc.gather(1, t.idx, 0, t.side)
+    t.sc.gather(2, t.idx, 0, t.side)
+    t.attend()
+    done = t.torch.cuda.Event(enable_timing=True)
+    done.record(t.main)
+    t.torch.cuda.synchronize()
+    assert t.torch.equal(t.out, want)
+    assert done.elapsed_time(held) > 10.0                  # through long before the side stream goes on
+
+
+def test_a_step_waits_for_its_fetch_although_others_are_captured_behind_it(three_layers):
+    """Fetches of two other layers recorded into a graph on the same side stream, while the layer's own is still to run: no event of the graph
+    stands for it."""
+    t = three_layers
+    want = t.want()
+    hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    side, graph = ctypes.c_void_p(t.side.cuda_stream), ctypes.c_void_p()
+    t.sleep(t.side)
+    t.sc.gather(0, t.idx, 0, t.side)
+    assert hip.hipStreamBeginCapture(side, 2) == 0         # relaxed
+    try:
+        t.sc.gather(1, t.idx, 0, t.side)
+        t.sc.gather(2, t.idx, 0, t.side)
+    finally:
+        assert hip.hipStreamEndCapture(side, ctypes.byref(graph)) == 0
+    try:
+        t.attend()
+        t.torch.cuda.synchronize()
+        assert t.torch.equal(t.out, want)
+    finally:
+        t.torch.cuda.synchronize()
+        hip.hipGraphDestroy(graph)
 
 
 @pytest.mark.parametrize("B,H,S,k", [(1, 1, 300, 5), (1, 3, 900, 33), (3, 5, 700, 200), (5, 30, 400, 31), (1, 1, 1000, 4000)])
