@@ -548,6 +548,15 @@ __global__ __launch_bounds__(kThreads, FUSED || BITS == 1 ? 5 : 7) void attend_i
 
 }  // namespace
 
+// Both passes in one launch leave the merge to a launch of its own, where they are more workgroups than the chip holds at a time and the step
+// fetches more than a pair for so many keys.  The selections on the side streams, each a workgroup that needs most of a compute unit, find one between the
+// launches; behind launches of several rounds that follow each other at once they come late, the fetches of the side streams fall into step, and the
+// link idles meanwhile.  us a layer, merged inside / so (32 layers, free running): 32 x 32768, k = 256 74.3 to 79.4, up to 70 % of the steps
+// slow / 74.0, k = 128 45.2 / 41.3, k = 112 40.1 / 39.5, 1 bit, k = 96 35.5 / 33.0, k = 128 42.4 / 38.4, 32 x 49152, k = 160 59.8 / 59.1 (where link and kernels
+// are far from even it is 1 % the other way: k = 192 55.7 / 56.0).  Fewer pairs: k = 96 36.6 / 37.4, k = 80 33.7 / 34.3, k = 64 31.4 / 32.0, 1 bit
+// 27.7 / 28.0, 32 x 24576, k = 48 26.5 / 27.2.  One round: 32 x 16384, k = 128 38.2 / 39.5, k = 64 25.3 / 26.5.
+constexpr int kRoundChunks = 5 * 256, kMergeKeysPerPair = 384;
+
 bool attend_uses_int8_matrix_cores(const LayerView& L, int n_rows) { return L.G == 1 && n_rows == 2 && (L.bits == 2 || L.bits == 1); }
 
 // keys != null: the scoring pass runs inside the launch (logits are not read; they are written to logits_out if set)
@@ -576,6 +585,7 @@ hipError_t launch_attend_i8_partial(const LayerView& L, const void* q, int N, in
     A.n_chunks = A.n_main + (n_ex + kExtraChunk - 1) / kExtraChunk;
     if (A.n_chunks > A.max_chunks || A.n_chunks < 1) return hipErrorInvalidValue;
     A.fin = finish;
+    if (keys && slot_idx && L.rows * A.n_chunks > kRoundChunks && Nq < kMergeKeysPerPair * L.topk) A.fin.arrived = nullptr;
     *merged = plan_merge(A.fin, L.rows, A.n_chunks, 2, !keys || L.rows <= kFinishFewRows);
     const dim3 grid((A.n_chunks + (A.fin.mergers ? A.fin.shares : 0)) * L.rows + (L.tail_k ? L.rows : 0)), block(kThreads);
 #define SPC_AI8_B(G_, B_, F_)                                                                                              \

@@ -35,6 +35,31 @@ def test_merge_in_the_launch(Hq, Hkv, S, bits, g, k, n_rows, one_pass):
         c.close()
 
 
+# 20 chunks on 64 rows are the 1280 workgroups of one round; beside them 374 and 405 quantised positions for a pair
+@pytest.mark.parametrize("S,k,fetched,bits,g,in_launch", [
+    (512 * 19 + 40, 26, True, 2, 32, True), (512 * 20 + 40, 27, True, 2, 32, False), (512 * 20 + 40, 26, True, 1, 64, True),
+    (512 * 20 + 40, 27, False, 2, 32, True), (512 * 20 + 40, 27, True, 1, 128, False)])
+def test_launches_of_several_rounds_leave_the_merge_where_much_is_fetched(S, k, fetched, bits, g, in_launch):
+    """On both sides of the rule: where the merge runs, and the oracle's outputs either way."""
+    import torch
+    from tests.harness import Case
+    c = Case(2, 32, 32, S, synth.FP16, bits, g, k, R=max(64, g), seed=7900 + k, sample=[(0, 0), (1, 31)], async_select=2, one_pass=True, fused_append=True)
+    try:
+        c.load()
+        for t in range(2):
+            c.append_token(t)
+            c.decode_step(check_logits=False, do_gather=fetched)
+        assert c.stats["max_out_err"] < 5e-5, c.stats
+        q = synth.make_queries_device(7, 1, 2, 32, 128, synth.FP16).view(2, 32, 2, 128).contiguous()
+        out = torch.empty((2, 32, 2, 128), dtype=torch.float32, device="cuda")
+        c.sc.timing(True)
+        c.sc.score_attend(0, q, 2, None, None, 0 if fetched else -1, out)
+        spans = c.sc.timing(False)
+        assert spans["score_attend"][1] == 1 and spans["attend_combine"][1] == (0 if in_launch else 1), spans
+    finally:
+        c.close()
+
+
 def test_layers_on_streams_of_their_own_keep_their_counters():
     """Every layer counts for itself: layers stepped on different streams, one after the other, and a context opened in between."""
     import torch
