@@ -1,6 +1,7 @@
 // Quant and Offload of new KV pairs (Appendix A "Decoding"; quantiser of Eq. 2 / Eq. 3,
 // Section 3.4; KIVI's axes and residual, Section 2.1 / 4.1), plus the export hook that
 // unpacks the device layout into the canonical one-code-per-byte view.
+#include "append_shape.h"
 #include "kernels.h"
 #include "layout.h"
 
@@ -276,7 +277,7 @@ __device__ __forceinline__ void copy_tokens(const LayerView& L, const uint4* __r
     reinterpret_cast<uint4*>(L.host)[((size_t)row * L.max_seq + t) * 32 + part] = v;
     if (t >= ring_from) reinterpret_cast<uint4*>(L.ring)[((size_t)row * L.R + (t % L.R)) * 32 + part] = v;
 }
-constexpr int kCopyTokens = kFlushThreads / 32;   // of a workgroup
+static_assert(kFlushThreads == kAppendThreads, "kCopyTokens of a workgroup");
 
 template <int BITS, int G, bool BF16>
 __global__ __launch_bounds__(kFlushThreads) void flush_kernel(LayerView L, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
@@ -295,14 +296,9 @@ __global__ __launch_bounds__(kFlushThreads) void append_copy_kernel(LayerView L,
 template <int BITS, int G, bool BF16>
 __global__ __launch_bounds__(kFlushThreads) void flush_copy_kernel(LayerView L, const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
                                                                    int n_new, int N0, int Nq0, int n_flush, int ring_from) {
-    const int id = blockIdx.x, n_copy = (n_new + kCopyTokens - 1) / kCopyTokens;
-    const int quantise = n_flush * L.rows, every = (quantise + n_copy * L.rows) / quantise, nth = id / every;
-    if (id % every == 0 && nth < quantise) {
-        flush_group<BITS, G, BF16>(L, k_new, v_new, n_new, N0, Nq0 + nth % n_flush * G, nth / n_flush);
-    } else {
-        const int c = id - (nth + 1 < quantise ? nth + 1 : quantise);
-        copy_tokens(L, (const uint4*)k_new, (const uint4*)v_new, n_new, N0, ring_from, c % n_copy * kCopyTokens, c / n_copy);
-    }
+    const AppendJob job = append_job(blockIdx.x, n_flush, append_copy_blocks(n_new));
+    if (job.quantise) flush_group<BITS, G, BF16>(L, k_new, v_new, n_new, N0, Nq0 + job.nth * G, blockIdx.y);
+    else copy_tokens(L, (const uint4*)k_new, (const uint4*)v_new, n_new, N0, ring_from, job.nth * kCopyTokens, blockIdx.y);
 }
 
 // Canonical view: one thread per (token, channel).
@@ -351,7 +347,7 @@ __global__ __launch_bounds__(128) void export_kernel(LayerView L, int Nq, uint8_
 template <int BITS, int G>
 hipError_t flush_dispatch(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0, int Nq0,
                           int n_flush, int copy_from, hipStream_t stream) {
-    const dim3 grid(n_flush, L.rows), both((n_flush + (n_new + kCopyTokens - 1) / kCopyTokens) * L.rows), block(kFlushThreads);
+    const dim3 grid(n_flush, L.rows), both = append_grid(n_flush, n_new, L.rows), block(kFlushThreads);
     const uint16_t *k = (const uint16_t*)k_new, *v = (const uint16_t*)v_new;
     if (copy_from >= 0) {
         if (L.bf16) hipLaunchKernelGGL((flush_copy_kernel<BITS, G, true>), both, block, 0, stream, L, k, v, n_new, N0, Nq0, n_flush, copy_from);
@@ -393,7 +389,7 @@ hipError_t launch_flush(const LayerView& L, const void* k_new, const void* v_new
 hipError_t launch_append_copy(const LayerView& L, const void* k_new, const void* v_new, int n_new, int N0,
                               int ring_from, hipStream_t stream) {
     if (n_new <= 0) return hipSuccess;
-    const dim3 grid((n_new + kCopyTokens - 1) / kCopyTokens, L.rows), block(kFlushThreads);
+    const dim3 grid(append_copy_blocks(n_new), L.rows), block(kFlushThreads);
     hipLaunchKernelGGL(append_copy_kernel, grid, block, 0, stream, L, (const uint4*)k_new, (const uint4*)v_new,
                        n_new, N0, ring_from);
     return hipGetLastError();
