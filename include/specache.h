@@ -409,11 +409,11 @@ enum {
     SPECACHE_K_GATHER = 4,      /* host-link gather (side stream); of specache_select_gather the launch
                                    that selects and fetches (then nothing counts as K_TOPK) */
     SPECACHE_K_ATTEND = 5,      /* mixed attention: partial pass over chunks, and their merge where the
-                                   launch does that itself (rows of up to 128 chunks; then nothing
-                                   counts as K_ATTEND_COMBINE) */
+                                   launch does that itself (then nothing counts as K_ATTEND_COMBINE);
+                                   which ones do follows from the shape and the kernel that takes it */
     SPECACHE_K_ATTEND_COMBINE = 6, /* mixed attention: merge of the chunks in a launch of its own */
     SPECACHE_K_SCORE_ATTEND = 7, /* scoring and partial pass of specache_score_attend in one launch,
-                                   and the merge under the same condition   */
+                                   and the merge where it does that as well */
     SPECACHE_K_COUNT = 8
 };
 int specache_timing(specache_ctx* ctx, int32_t enable, double* total_us, int64_t* launches);

@@ -106,7 +106,8 @@ hipError_t launch_gather(const LayerView& L, int Nq, const int32_t* idx, uint16_
     // The list is read ahead where nothing of this context runs beside the fetch, and where a step is little else than fetches.  us a pass without
     // / so: one query row with its own selection, 32 x 8192 382 / 372, 8 x 8000 228 / 223; a step's fetches on two streams, 512 x 2048, k = 128
     // 1292 / 1267, 32 x 8192, k = 512 689 / 645, 256 x 1000, k = 32 174 / 170.  With more to score for a pair the attention kernels pay for it: 8 x
-    // 60000, k = 256 147 / 150, 8 x 131072, k = 1024 324 / 348.
+    // 60000, k = 256 147 / 150, 8 x 131072, k = 1024 324 / 348.  About the line, us a layer of 8 x (32 x 16384): k = 192 (85 keys a pair) 59.7 / 61.9, 224
+    // 67.8 / 67.8, 256 76.2 / 76.4, 288 86.1 / 85.6, 384 111.7 / 111.3, 640 182.7 / 184.3; 512 x 2048, k = 32 (64) 153.9 / 149.4, k = 64 294.0 / 295.8.
     const bool ahead = alone || (link_shared && keys_per_pair < 64.0);
     if (ahead) {
         in_flight = 1;

@@ -139,7 +139,8 @@ struct Finish {
 // 5003 14.9 / 14.2, 32 x 8192 18.3 / 17.0, 8 x 131072, 1 bit (99 chunks) 43.4 / 42.7; 16 over 16 x 8192 17.3 / 16.3, 8 x 32768 (98) 25.6 / 26.0; but
 // 1 x 60000 (119) 10.4 / 11.0.  A pass of steps with their fetches: 8 layers of 32 x 16384 223 / 211, of 24 x 5003, 8 query rows 279 / 269, of 16 x
 // 8192, 16 rows 163 / 158, of 64 x 1000 198 (1) / 180, of 1 x 60000 151 / 134, of 8 x 32768, 16 rows 302 / 302.  The last chunk as the only one to
-// merge where the partials are many: 8 x 131072 59.8 and 16 rows over 8 x 32768 67.8 (one workgroup reads them all).
+// merge where the partials are many: 8 x 131072 59.8 and 16 rows over 8 x 32768 67.8 (one workgroup reads them all).  (Launches of attend_i8_kernel that
+// take several rounds of workgroups: kRoundChunks, attend_i8.hip.  rows_kernel splits its rows so that they are one.)
 constexpr int kFinishChunks = 128, kFinishShare = 128;
 constexpr int kMergerPolls = 2000;   // two to five milliseconds
 int& merger_polls();                 // that, unless specache_debug_merger_polls says otherwise
