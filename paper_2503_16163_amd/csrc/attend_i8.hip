@@ -483,7 +483,7 @@ __device__ __forceinline__ void attend_i8_chunk(const LayerView& L, const Attend
 // spills and runs slower (measured at the 7B shape: 28.6 us, 32 with two registers spilled, 58 with 34).  Attention alone takes 64 with 2-bit
 // codes (eight waves; its 16-bit chunk asks for the values when the keys are used up: with 16 of them ahead it takes 72, 1 % of a
 // step of 128 rows x 30000), and up to 91 with 1-bit codes (held to 80 it spills: 64 -> 82 us for 32 x 32000, one layer).
-// What the waves of a full chip wait for is issue slots, of the vector ALUs and of LDS (a wave of 128 tokens: 1136 vector instructions, about 970 since;
+// What the waves of a full chip wait for is issue slots, of the vector ALUs and of LDS (a wave of 128 tokens: 1136 vector instructions, 1012 since;
 // with 1 bit LDS was busy for 58 % of the launch, two fifths of that with bank conflicts).  So maxima are of bits, signs are set behind the transpositions, results
 // lie where neither their writers nor their readers share banks, and the metadata's loads have no conditions: a pass of 4 layers
 // of 32 x 32768, 1 bit, g = 64 121 -> 115 us, 2 bits, g = 32 132 -> 128, of 8 of 32 x 16384 208 -> 205.5 (sharing the fetch's queue 182 -> 173, 196 ->
