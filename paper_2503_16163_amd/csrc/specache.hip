@@ -191,14 +191,20 @@ struct TimedLaunch {
     }
 };
 
+bool being_captured(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 // An ordering event completed by a kernel's own dispatch packet instead of a record behind it: one call
 // into the runtime less per event, and the issuing thread's calls are what bounds a step with little to
 // fetch.  Between arm() and landed() exactly one launcher runs; landed() is false when that launcher
-// launched nothing or when the launch carries timing events (the caller then records the event itself).
+// launched nothing, when the launch carries timing events, or when st is being captured: there a record is an edge of the
+// graph, and an event that a launch carries is none (the caller then records the event itself).
 struct CarriedEvent {
     bool armed = false;
-    CarriedEvent(specache_ctx* c, hipEvent_t ev) {
-        if (c->timing || !ev) return;
+    CarriedEvent(specache_ctx* c, hipStream_t st, hipEvent_t ev) {
+        if (c->timing || !ev || being_captured(st)) return;
         pending_launch_events() = LaunchEvents{nullptr, ev};
         armed = true;
     }
@@ -287,7 +293,7 @@ int score_phase(specache_ctx* ctx, Layer& L, const void* q, int n_rows, uint32_t
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE, /*kernel_events=*/true);
         const bool rewrites = (ctx->cfg.select_cache == SPECACHE_SELECT_MIXED && L.last_gather_slot >= 0) ||
                               (ctx->cfg.select_form == SPECACHE_SELECT_MAX_LOGPROB && L.view.G > 1);
-        CarriedEvent carried(ctx, rewrites ? nullptr : done);
+        CarriedEvent carried(ctx, st, rewrites ? nullptr : done);
         SPC_HIP(ctx, launch_score(fused_view ? *fused_view : L.view, q, n_rows, L.Nq, ctx->sm_scale, ctx->logits, ctx->logit_stride, keys,
                                   ctx->logit_stride, st));
         if (done_carried) *done_carried = carried.landed();
@@ -334,7 +340,7 @@ int gather_phase(specache_ctx* ctx, Layer& L, int Nq, const int32_t* idx, int sl
     bool gathered_carried = false;
     {
         TimedLaunch t(ctx, st, SPECACHE_K_GATHER);
-        CarriedEvent gathered(ctx, L.gathered[slot]);
+        CarriedEvent gathered(ctx, st, L.gathered[slot]);
         // a caller that alternates side streams has two gathers on the link at a time
         const bool link_shared = ctx->last_gather_stream_set && ctx->last_gather_stream != st;
         if (select_out)
@@ -639,13 +645,10 @@ int specache_score_topk(specache_ctx* ctx, int32_t layer, const void* q, int32_t
         SPC_HIP(ctx, hipEventRecord(ctx->scored, st));
         SPC_HIP(ctx, hipStreamWaitEvent(tk, ctx->scored, 0));
     }
-    // (recorded where the call is captured: there a record is an edge of the graph)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool captured = hipStreamIsCapturing(tk, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
     bool ready_carried = false;
     {
         TimedLaunch t(ctx, tk, SPECACHE_K_TOPK, /*kernel_events=*/true);
-        CarriedEvent ready(ctx, captured ? nullptr : L.idx_ready);
+        CarriedEvent ready(ctx, tk, L.idx_ready);
         SPC_HIP(ctx, launch_topk(L.view.rows, L.Nq, ctx->cfg.topk, ctx->keys, ctx->logit_stride, topk_idx_out,
                                  ctx->topk_scratch, tk));
         ready_carried = ready.landed();
@@ -961,9 +964,7 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     const int N1 = L.N + (carry ? 1 : 0);
     // Under capture the word is no order: a replayed merge stores the value of its capture again, and the selection's
     // stream, if it is not part of the capture, would wait at once for a value that only a replay stores.  An event it is.
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool captured = hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
-    const bool by_word = !captured && words_may_order(ctx);
+    const bool by_word = !being_captured(st) && words_may_order(ctx);
     bool scored_carried = false, merged = false;
     Finish finish;
     finish.arrived = L.arrived;
@@ -973,7 +974,7 @@ static int score_attend_impl(specache_ctx* ctx, int32_t layer, const void* k_new
     finish.rows = L.view.rows;
     {
         TimedLaunch t(ctx, st, SPECACHE_K_SCORE_ATTEND, /*kernel_events=*/true);
-        CarriedEvent scored(ctx, by_word || captured ? nullptr : L.idx_ready);
+        CarriedEvent scored(ctx, st, by_word ? nullptr : L.idx_ready);
         if (rows_pass) {
             RowsArgs R{};
             R.at.q = (const uint16_t*)q;

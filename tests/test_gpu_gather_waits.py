@@ -162,6 +162,62 @@ def test_a_step_waits_for_its_fetch_although_others_are_captured_behind_it(three
         hip.hipGraphDestroy(graph)
 
 
+@pytest.mark.parametrize("calls,k", [("score_topk, gather", 40), ("score, select_gather", 40), ("score, select_gather", 600)])
+def test_a_captured_step_with_its_fetch_on_a_side_stream(calls, k):
+    """Selection, fetch on a side stream and attention recorded into one graph: the launches' order is the graph's, so that it is whole without
+    waits of the caller's, every replay reads the pairs that it fetched, and eager steps between them are as ever."""
+    import torch
+    from paper_2503_16163_amd import binding
+    H, S = 4, 3000                                          # 40 pairs: selected and fetched in one launch; 600: in two
+    q = synth.make_queries_device(9, 2, 1, H, 128, synth.FP16).view(2, 1, H, 2, 128)[:, :, :, :1].contiguous()
+    kd, vd = synth.make_kv_device(9, 1, H, S, 128, synth.FP16)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    aside = calls == "score, select_gather"
+    sc, reference = (binding.SpeCache(1, 1, H, H, 2, 32, 3072, k, synth.FP16, async_select=2 if aside else 0) for _ in range(2))
+    new = lambda: (torch.full((1, H, k), -2, dtype=torch.int32, device="cuda"), torch.zeros((1, H, 1, 128), dtype=torch.float32, device="cuda"))
+
+    def step(c, query, idx, out, stream):
+        if aside:
+            c.score(0, query, 1, stream)
+            c.select_gather(0, idx, 0, side)
+        else:
+            c.score_topk(0, query, 1, idx, stream)
+            c.gather(0, idx, 0, side)
+        c.attend(0, query, 1, None, None, 0, out, stream)
+
+    main = torch.cuda.current_stream()
+    try:
+        for c in (sc, reference):
+            c.quantize_append(0, kd, vd, S, main)
+        want = [new() for _ in range(2)]
+        for i in range(2):
+            step(reference, q[i], *want[i], main)
+        torch.cuda.synchronize()
+        got, graph = new(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            step(sc, q[0], *got, torch.cuda.current_stream())
+        for _ in range(3):
+            got[0].fill_(-2)
+            got[1].zero_()
+            sc.debug_poison_slot(0, 0, None)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0][0]) and torch.equal(got[1], want[0][1])
+            out = new()[1]
+            sc.attend(0, q[0], 1, None, None, 0, out, other)        # the replay's pairs are still there
+            torch.cuda.synchronize()
+            assert torch.equal(out, want[0][1])
+            eager = new()
+            step(sc, q[1], *eager, main)
+            torch.cuda.synchronize()
+            assert torch.equal(eager[0], want[1][0]) and torch.equal(eager[1], want[1][1])
+    finally:
+        torch.cuda.synchronize()
+        sc.close()
+        reference.close()
+
+
 @pytest.mark.parametrize("B,H,S,k", [(1, 1, 300, 5), (1, 3, 900, 33), (3, 5, 700, 200), (5, 30, 400, 31), (1, 1, 1000, 4000)])
 def test_fetches_that_read_the_list_ahead_stage_the_same_pairs(B, H, S, k):
     """A fetch on the stream that scored, or between fetches on two streams where little is scored for a pair, reads its list ahead; one on a side
